@@ -234,7 +234,7 @@ def few_query_table(wl, device, steps, single_us):
         table[f"q_len_{q_len}"] = {"us_per_call": round(us, 2), "us_per_token": round(us / q_len, 2),
                                    "tokens_per_s": round(cfg.batch * q_len / us * 1e6, 0),
                                    "speedup_per_token_vs_one_query": round(single_us * q_len / us, 3),
-                                   "passes_over_span": -(-q_len // span.span_plan_query(calls[0].desc)["queries_per_pass"])}
+                                   "passes_over_span": 1}
     return table
 
 

@@ -150,11 +150,11 @@ int span_decode_attn_static(const span_attn_desc_t* desc, const void* q, const v
  * through the sequence's one span (a span is chosen once per group of tokens, Sec. 3.2, so the tokens
  * of a group share it).  Among themselves the tokens keep the causal mask of Sec. 2.2: query token j
  * of sequence b attends the span positions p <= q_pos[b] + j and no later one; eqs. (4)-(6) apply to
- * each query row.  Every K / V row of the span is fetched once per pass over the span and serves all
- * query tokens of the pass: up to 16 for fp16 / bf16 rows of head_dim 128 (from three tokens on the pass
- * runs on the matrix cores), up to 4 otherwise; q_len tokens take ceil(q_len / tokens per pass) passes
- * (span_plan_query reports the tokens per pass).  The weights of the matrix-core pass enter the p.V product
- * as two 16-bit terms (about 16 mantissa bits for bf16, 22 for fp16); sums and outputs are fp32.
+ * each query row.  From three tokens on the call runs on the matrix cores: one launch, in which a workgroup
+ * serves up to 64 tokens with one pass over its share of the span's rows (calls with num_splits > 0 whose
+ * slices the workspace holds fewer token states for take one launch per queries_per_pass tokens).  Weights meet
+ * fp32 rows as they are, fp16 rows as two fp16 terms (22 mantissa bits) and bf16 rows as three bf16 terms (24);
+ * sums and outputs are fp32.
  *   q      : device, desc->dtype, [batch, q_len, heads, head_dim]
  *   q_pos  : device int32 [batch], cache position of query token 0 (its K / V row, like those of the
  *            other new tokens, is already in the cache and inside the span if it is to be attended);
@@ -200,9 +200,7 @@ int dense_decode_attn_append(const span_attn_desc_t* desc, const void* q, const 
  * the span positions p <= append_pos[b] + j, as in span_decode_attn_multi with q_pos = append_pos.
  *   q, k_new, v_new : device, desc->dtype, [batch, q_len, heads, head_dim]
  *   out             : device fp32 [batch, q_len, heads, head_dim]
- * Within a launch the rows of that launch's tokens are taken from k_new / v_new, never re-read from the
- * cache; more tokens than one pass serves (16 or 4, see span_decode_attn_multi) take several launches on
- * the stream, each appending its own tokens' rows, which the later ones then read from the cache.
+ * The new tokens' rows are taken from k_new / v_new, never re-read from the cache.
  */
 int span_decode_attn_multi_append(const span_attn_desc_t* desc, const void* q, const void* k_new, const void* v_new,
                                   void* k_cache, void* v_cache, const int32_t* append_pos,
@@ -252,6 +250,10 @@ int span_validate(int32_t batch, int32_t num_intervals, const int32_t* span_offs
  * states go through the workspace and the workgroup that finishes last for the pair merges them by
  * log-sum-exp (still one launch).  Pure host arithmetic.
  */
+/* For few-query calls (q_len of three and more) this is the partition the workspace is sized for: slots of
+ * queries_per_pass token states each.  The launch regroups them, all tokens of the call at once, into as many
+ * slices as they hold.
+ */
 typedef struct span_plan_info {
   int32_t exact;           /* 1: slices sized from tokens_per_seq (no idle workgroup); 0: every
                               sequence gets max_splits slices of slice_tokens positions            */
@@ -262,8 +264,7 @@ typedef struct span_plan_info {
   int64_t workspace_bytes; /* same value as span_workspace_bytes()                                */
   int32_t runs_in_arguments; /* 1: host_span_* were given and the plan fits: the slices' position runs
                               travel in the kernel arguments (span form)                          */
-  int32_t queries_per_pass;  /* query tokens one launch serves (1, 2, 4 or 16): a call with q_len tokens
-                              launches ceil(q_len / queries_per_pass) passes over the span        */
+  int32_t queries_per_pass;  /* query tokens whose partial states a slot of the workspace holds (1, 2, 4 or 16) */
 } span_plan_info_t;
 int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* info);
 

@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspanattn.so")
-SOURCES = [os.path.join(CSRC, "span_kernels.hip"), os.path.join(CSRC, "span_host.cpp")]
+SOURCES = [os.path.join(CSRC, "span_kernels.hip"), os.path.join(CSRC, "span_matrix.hip"), os.path.join(CSRC, "span_host.cpp")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
          # keep the compiler from forming packed-fp32 instructions
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

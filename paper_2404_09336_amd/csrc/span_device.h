@@ -1,0 +1,448 @@
+// Shared between the kernel translation units: kernel arguments, storage types, cross-lane helpers, loads of the
+// caches and the walk over a sequence's interval list.
+#ifndef SPAN_DEVICE_H_
+#define SPAN_DEVICE_H_
+
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "span_attn.h"
+#include "span_internal.h"
+
+namespace spanattn {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kThreads = kWavesPerBlock * 64;
+constexpr int kWin = 256;  // rows of a wave whose positions are tabulated at a time (one LDS window)
+
+struct LaunchArgs {
+  const void* q;
+  const void* k;
+  const void* v;
+  float* out;
+  const int32_t* offsets;
+  const int32_t* starts;
+  const int32_t* ends;
+  const int32_t* ctx_lens;
+  const void* k_new;           // append variant: the new token's K / V rows [batch, heads, D], else null
+  const void* v_new;
+  const int32_t* append_pos;   // append variant: [batch] cache row that receives them
+  const int32_t* q_pos;        // few-query variant: [batch] cache position of query token 0 (causal limit), or null
+  int32_t* counters;  // [batch*heads] arrival tickets of the slices; zero between calls
+  // one slot per workgroup, slot = (first slice row of the sequence + slice) * heads + head:
+  float* part_ml;   // [slots, NQ, 2]  (m in log2 units, l)
+  float* part_acc;  // [slots, NQ, D]  un-normalised
+  int32_t heads, max_len, num_intervals, slice_tokens, num_splits, max_tokens;
+  int32_t q_len;                    // query tokens per sequence in q and out ([batch, q_len, heads, D])
+  int32_t q_first;                  // few-query variant: first query token this launch handles
+  float scale_log2e;
+  int32_t total_slices;             // table mode: entries of `table` in use
+  int32_t even;                     // 1: a sequence's slices share its own token count evenly; 0: slice_tokens each
+  int32_t interleave;               // 1: rows dealt to the waves round-robin (large slices); 0: contiguous quarters
+#ifdef SPAN_PHASE_TRACE
+  unsigned long long* trace;        // diagnostic build only: [trace_workgroups, kTraceStamps] times of the phases, or null
+  size_t trace_workgroups;
+#endif
+};
+// Table mode: blockIdx.y indexes `table` (sequences have different numbers of slices).  The table makes
+// the kernel arguments 3 KB larger, which costs about 0.35 us per launch, so calls that do not need it
+// (every sequence has the same number of slices) use the plain arguments and a (heads, slices, batch) grid.
+struct LaunchArgsTable : LaunchArgs {
+  static constexpr bool kHasTable = true;
+  static constexpr bool kHasRuns = false;
+  uint32_t table[kMaxPlanSlices];   // pack_slice(batch, slice, slices of the sequence)
+};
+struct LaunchArgsPlain : LaunchArgs {
+  static constexpr bool kHasTable = false;
+  static constexpr bool kHasRuns = false;
+};
+// Run mode: blockIdx.y indexes the slices of all sequences, each resolved on the host to its runs of consecutive
+// cache positions; the kernel reads no span metadata from device memory.
+struct LaunchArgsRuns : LaunchArgs {
+  static constexpr bool kHasTable = true;
+  static constexpr bool kHasRuns = true;
+  RunTables r;
+};
+
+// Diagnostic build (-DSPAN_PHASE_TRACE): every workgroup reads the constant-rate (100 MHz) clock at the phase
+// boundaries named below into registers and thread 0 writes them out when the workgroup ends, so that taking a stamp
+// puts no memory operation into the path it measures.  Each stamp names a value that must have been computed before
+// the clock is read (the compiler may not move the read ahead of it).  The regular build compiles the stamps away.
+// stamps: 0 kernel entry, 10 the sequence's interval range read (device lists), 1 span metadata read and slice known,
+// 2 first position table built, 3 first K / V rows consumed, 4 all rows consumed, 5 waves merged in LDS, 6 output row
+// stored and acknowledged (one slice per pair), 7 partial state published and acknowledged, 8 ticket returned,
+// 9 slices merged, output row stored and acknowledged (last arrival only)
+constexpr int kTraceStamps = 16;
+#ifdef SPAN_PHASE_TRACE
+#define SPAN_TRACE_DECL unsigned long long trace_t[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}
+#define SPAN_STAMP_AFTER(i, constraint, value)        \
+  do {                                                \
+    asm volatile("" ::constraint(value) : "memory");  \
+    trace_t[i] = wall_clock64();                      \
+    asm volatile("" ::: "memory");                    \
+  } while (0)
+#define SPAN_STAMP_ACKED(i)                                  \
+  do {                                                       \
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); \
+    trace_t[i] = wall_clock64();                             \
+    asm volatile("" ::: "memory");                           \
+  } while (0)
+#define SPAN_TRACE_FLUSH()                                                                                     \
+  do {                                                                                                         \
+    const size_t wg_ = (size_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;                 \
+    if (threadIdx.x == 0 && a.trace && wg_ < a.trace_workgroups) {                                             \
+      for (int i_ = 0; i_ < 11; ++i_) a.trace[wg_ * kTraceStamps + i_] = trace_t[i_];                          \
+    }                                                                                                          \
+  } while (0)
+#else
+#define SPAN_TRACE_DECL \
+  do {                  \
+  } while (0)
+#define SPAN_STAMP_AFTER(i, constraint, value) \
+  do {                                         \
+  } while (0)
+#define SPAN_STAMP_ACKED(i) \
+  do {                      \
+  } while (0)
+#define SPAN_TRACE_FLUSH() \
+  do {                     \
+  } while (0)
+#endif
+
+// ---- storage types ---------------------------------------------------------------------------------
+// unpack: 16 bytes of a row -> fp32 (for the V accumulation).
+// The q.k partial product of a lane's 16 bytes never unpacks the 16-bit types: q stays in its stored
+// form and v_dot2 multiplies two pairs per instruction into an fp32 sum (products of 16-bit floats are
+// exact in fp32); the score scale is applied to the finished dot product (kPostScale).  fp32 rows use
+// plain FMAs against a q that was scaled once up front.
+struct F32 {
+  static constexpr int kBytes = 4, kPerVec = 4;
+  static constexpr bool kPostScale = false;
+  static constexpr int kTerms = 1;  // matrix pass: terms of a weight in the storage type
+  static constexpr float kWeightScale = 1.f;
+  struct Q {
+    float f[4];
+  };
+  static __device__ __forceinline__ void unpack(const u32x4& r, float* f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = r[i];  // (bit_cast straight from a vector element reads element 0 every time)
+      f[i] = __builtin_bit_cast(float, w);
+    }
+  }
+  static __device__ __forceinline__ void unpack4(const void* p, float* f) {  // four consecutive values in memory
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+    for (int i = 0; i < 4; ++i) f[i] = v[i];
+  }
+  static __device__ __forceinline__ Q make_q(const u32x4& r, float scale) {
+    Q q;
+    unpack(r, q.f);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q.f[i] *= scale;
+    return q;
+  }
+  static __device__ __forceinline__ float dot(const u32x4& k, const Q& q) {
+    float kf[4];
+    unpack(k, kf);
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) d = fmaf(kf[i], q.f[i], d);
+    return d;
+  }
+};
+struct F16 {
+  static constexpr int kBytes = 2, kPerVec = 8;
+  static constexpr bool kPostScale = true;
+  static constexpr int kTerms = 2;
+  // weights enter the product times 2^8, which keeps those below 2^-14 of the largest out of fp16's subnormal range
+  static constexpr float kWeightScale = 256.f;
+  typedef u32x4 Q;
+  // C (16x16, fp32) += A (16 x k) * B (k x 16), k = 16 or 32: four / eight 16-bit elements of A and of B per lane
+  static __device__ __forceinline__ f32x4 mfma(u32x2 a, u32x2 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+  }
+  // two weights as kTerms pairs in the storage type: each term is what the ones before it left, rounded (two fp16
+  // terms hold 22 bits)
+  static __device__ __forceinline__ void split(float p0, float p1, uint32_t* terms) {
+    float r0 = p0, r1 = p1;
+#pragma unroll
+    for (int i = 0; i < kTerms; ++i) {
+      const f16x2 h = {(_Float16)r0, (_Float16)r1};
+      terms[i] = __builtin_bit_cast(uint32_t, h);
+      r0 -= (float)h.x;
+      r1 -= (float)h.y;
+    }
+  }
+  static __device__ __forceinline__ void unpack(const u32x4& r, float* f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = r[i];
+      const f16x2 h = __builtin_bit_cast(f16x2, w);
+      f[2 * i] = (float)h.x;
+      f[2 * i + 1] = (float)h.y;
+    }
+  }
+  static __device__ __forceinline__ void unpack4(const void* p, float* f) {
+    const f16x4 v = *reinterpret_cast<const f16x4*>(p);
+    for (int i = 0; i < 4; ++i) f[i] = (float)v[i];
+  }
+  static __device__ __forceinline__ Q make_q(const u32x4& r, float) { return r; }
+  static __device__ __forceinline__ float dot(const u32x4& k, const Q& q) {
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t kw = k[i], qw = q[i];
+      d = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, kw), __builtin_bit_cast(f16x2, qw), d, false);
+    }
+    return d;
+  }
+};
+struct BF16 {
+  static constexpr int kBytes = 2, kPerVec = 8;
+  static constexpr bool kPostScale = true;
+  static constexpr int kTerms = 3;  // 24 bits, as many as an fp32 weight has
+  static constexpr float kWeightScale = 1.f;
+  typedef u32x4 Q;
+  static __device__ __forceinline__ f32x4 mfma(u32x2 a, u32x2 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(i16x4, a), __builtin_bit_cast(i16x4, b), c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ void split(float p0, float p1, uint32_t* terms) {
+    float r0 = p0, r1 = p1;
+#pragma unroll
+    for (int i = 0; i < kTerms; ++i) {
+      const bf16x2 h = {(__bf16)r0, (__bf16)r1};
+      const uint32_t w = __builtin_bit_cast(uint32_t, h);
+      terms[i] = w;
+      r0 -= __builtin_bit_cast(float, w << 16);
+      r1 -= __builtin_bit_cast(float, w & 0xffff0000u);
+    }
+  }
+  static __device__ __forceinline__ void unpack(const u32x4& r, float* f) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = r[i];
+      f[2 * i] = __builtin_bit_cast(float, w << 16);
+      f[2 * i + 1] = __builtin_bit_cast(float, w & 0xffff0000u);
+    }
+  }
+  static __device__ __forceinline__ void unpack4(const void* p, float* f) {
+    const u32x2 v = *reinterpret_cast<const u32x2*>(p);
+    const uint32_t v0 = v[0], v1 = v[1];
+    f[0] = __builtin_bit_cast(float, v0 << 16);
+    f[1] = __builtin_bit_cast(float, v0 & 0xffff0000u);
+    f[2] = __builtin_bit_cast(float, v1 << 16);
+    f[3] = __builtin_bit_cast(float, v1 & 0xffff0000u);
+  }
+  static __device__ __forceinline__ Q make_q(const u32x4& r, float) { return r; }
+  static __device__ __forceinline__ float dot(const u32x4& k, const Q& q) {
+    float d = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t kw = k[i], qw = q[i];
+      d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kw), __builtin_bit_cast(bf16x2, qw), d, false);
+    }
+    return d;
+  }
+};
+
+// ---- cross-lane helpers (wave64) ---------------------------------------------------------------
+template <int kCtrl>
+__device__ __forceinline__ float dpp_f(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kCtrl, 0xf, 0xf, true));
+}
+template <int kCtrl>
+__device__ __forceinline__ int dpp_i(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, kCtrl, 0xf, 0xf, true);
+}
+
+// Sum over each aligned group of kLanes lanes (8, 16 or 32); every lane of the group gets the sum.
+template <int kLanes>
+__device__ __forceinline__ float group_allreduce_sum(float x) {
+  x += dpp_f<0xB1>(x);                          // quad_perm [1,0,3,2]
+  x += dpp_f<0x4E>(x);                          // quad_perm [2,3,0,1]
+  if (kLanes >= 8) x += dpp_f<0x141>(x);        // row_half_mirror
+  if (kLanes >= 16) x += dpp_f<0x140>(x);       // row_mirror
+  if (kLanes >= 32) x += __shfl_xor(x, 16, 64);
+  return x;
+}
+
+// Inclusive prefix sum over the 64 lanes.
+__device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
+  x += dpp_i<0x111>(x);  // row_shr:1   (lanes without a source inside their row of 16 add 0)
+  x += dpp_i<0x112>(x);  // row_shr:2
+  x += dpp_i<0x114>(x);  // row_shr:4
+  x += dpp_i<0x118>(x);  // row_shr:8
+  const int t0 = __builtin_amdgcn_readlane(x, 15);
+  const int t1 = __builtin_amdgcn_readlane(x, 31);
+  const int t2 = __builtin_amdgcn_readlane(x, 47);
+  const int row = lane >> 4;
+  x += (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
+  return x;
+}
+
+__device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
+
+// K / V rows are fetched with raw buffer loads: the descriptor covers exactly one (batch, head) slab,
+// so the hardware itself returns zeros for any offset outside it, and the cache policy is explicit.
+// Non-temporal (streaming) loads: every row is used once; measured 17 % faster than default-policy loads.
+// A wave sends its first batch of row loads, and consumes it, at raised instruction priority and drops back to the
+// default for the rest of its rows.  Among waves of equal priority a SIMD issues the oldest first, so without this the
+// waves of the workgroups that arrived last on a CU get their first rows only when the earlier ones are nearly done
+// (per-workgroup stamps: first rows after 4 us for the first quarter of a launch, after 15-18 us for the last) and
+// the launch ends on a thin tail of late starters.  Measured on batch 64 x ~155 positions: 27.67 -> 27.11 us; raising
+// the priority for the start-up chain as well, or by progress through the rows, gains less or loses.  One-token
+// kernels for 16-bit rows of 128 only, and only launches whose slices hold up to four batches of rows per wave (kBoost
+// instances, chosen by the launcher): the passes that serve several tokens lose by it (3 tokens: 31.9 -> 33.6 us), fp32
+// rows at the same shape (5 batches) lose 1 %, 16-bit rows of 64 lose 6 %, 9 batches (batch 8 x 300..2000) lose 0.5 %,
+// 16 and more gain nothing;
+// even the untaken branch in the loop costs the longer streams 0.5 %, hence instances of their own.
+#ifndef SPAN_FIRST_BATCH_PRIORITY
+#define SPAN_FIRST_BATCH_PRIORITY 3  // (a measurement build sets 0 to time the default arbitration)
+#endif
+constexpr int kBoostUpToBatches = 4;  // per wave
+__device__ __forceinline__ void first_batch_priority(bool first_batch) {
+#if SPAN_FIRST_BATCH_PRIORITY > 0
+  if (first_batch) __builtin_amdgcn_s_setprio(SPAN_FIRST_BATCH_PRIORITY);
+  else __builtin_amdgcn_s_setprio(0);
+#else
+  (void)first_batch;
+#endif
+}
+#ifndef SPAN_ROW_LOAD_POLICY
+#define SPAN_ROW_LOAD_POLICY 2  // (a measurement build overrides it to time the other policies)
+#endif
+constexpr int kRowLoadPolicy = SPAN_ROW_LOAD_POLICY;  // bit 0 = sc0, bit 1 = nt, bit 4 = sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_resource(const void* slab, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(slab), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 load_row_piece(__amdgpu_buffer_rsrc_t slab, uint32_t byte_off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(slab, byte_off, 0, kRowLoadPolicy);
+}
+
+// Device-coherent store / load of one float that another workgroup reads / wrote in the same kernel.
+__device__ __forceinline__ void publish(float* p, float v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float observe(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Merge two un-normalised softmax states held in log2 units.
+__device__ __forceinline__ void merge_state(float& m, float& l, float* acc, int n, float m2, float l2,
+                                            const float* acc2) {
+  const float mn = fmaxf(m, m2);
+  const float ms = (mn == -INFINITY) ? 0.f : mn;
+  const float a = __builtin_amdgcn_exp2f(m - ms), b = __builtin_amdgcn_exp2f(m2 - ms);
+  // one rounding order, written out: the compiler may contract x*a + y*b either way round, and every instance of
+  // the kernel has to give the same bits
+  l = fmaf(l, a, l2 * b);
+  for (int i = 0; i < n; ++i) acc[i] = fmaf(acc[i], a, acc2[i] * b);
+  m = mn;
+}
+
+// ---- the interval list of a sequence -----------------------------------------------------------------
+struct Intervals {
+  int count, first;     // intervals first .. first + count - 1 of the lists (scalar)
+  int st0, len0, incl0; // this lane's interval of the first 64: start, length, inclusive prefix sum of the lengths
+};
+struct IntervalChunk {  // one wave's LDS copy of up to 64 intervals: exclusive prefix sums and starts
+  int pref[64], start[64];
+};
+
+__device__ __forceinline__ Intervals interval_range(const LaunchArgs& a, int b) {
+  const int lo = clampi(a.offsets[b], 0, a.num_intervals);
+  const int hi = clampi(a.offsets[b + 1], lo, a.num_intervals);
+  return Intervals{__builtin_amdgcn_readfirstlane(hi - lo), __builtin_amdgcn_readfirstlane(lo), 0, 0, 0};
+}
+
+// Positions of the sequence's list (counting may stop once `stop` is reached); fills the first chunk's lane values.
+__device__ __forceinline__ int count_positions(const LaunchArgs& a, Intervals& iv, int lane, int stop) {
+  if (lane < iv.count) {
+    iv.st0 = a.starts[iv.first + lane];
+    iv.len0 = clampi(a.ends[iv.first + lane] - iv.st0, 0, a.max_len);
+  }
+  iv.incl0 = wave_inclusive_scan(iv.len0, lane);
+  int n = __builtin_amdgcn_readlane(iv.incl0, 63);
+  for (int c0 = 64; c0 < iv.count && n < stop; c0 += 64) {
+    int len = 0;
+    if (c0 + lane < iv.count)
+      len = clampi(a.ends[iv.first + c0 + lane] - a.starts[iv.first + c0 + lane], 0, a.max_len);
+    n += __builtin_amdgcn_readlane(wave_inclusive_scan(len, lane), 63);
+  }
+  return n;
+}
+
+// Cache positions of the wave's rows w0 .. w0 + wn - 1 into `pos`; row r is virtual token vrow(r) of the sequence.
+// kFirst: the first 64 intervals are still in registers from count_positions; later windows re-read them, so that
+// nothing stays live across the streaming loop.
+template <bool kFirst, class RowMap>
+__device__ __forceinline__ void tabulate_positions(const LaunchArgs& a, const Intervals& iv, const RowMap& vrow, int w0,
+                                                   int wn, int lane, IntervalChunk& chunk, int* pos) {
+  const int vbeg = vrow(w0), vend = vrow(w0 + wn - 1) + 1;
+  int carry = 0;
+  for (int c0 = 0; c0 < iv.count; c0 += 64) {
+    int st = 0, len = 0, incl = 0;
+    if (kFirst && c0 == 0) {
+      st = iv.st0;
+      len = iv.len0;
+      incl = iv.incl0;
+    } else {
+      if (c0 + lane < iv.count) {
+        st = a.starts[iv.first + c0 + lane];
+        len = clampi(a.ends[iv.first + c0 + lane] - st, 0, a.max_len);
+      }
+      incl = wave_inclusive_scan(len, lane);
+    }
+    const int chunk_total = __builtin_amdgcn_readlane(incl, 63);
+    if (carry + chunk_total > vbeg) {
+      // the chunk's exclusive prefixes and starts go to this wave's private LDS rows; the wave
+      // reads them back itself (LDS executes a wave's requests in order), so no block barrier
+      chunk.pref[lane] = carry + incl - len;
+      chunk.start[lane] = st;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const int n_here = min(64, iv.count - c0);
+      for (int r = lane; r < wn; r += 64) {
+        const int v = vrow(w0 + r);
+        if (v >= carry && v < carry + chunk_total) {
+          int idx = 0;  // last interval of the chunk whose exclusive prefix is <= v
+#pragma unroll
+          for (int step = 32; step > 0; step >>= 1) {
+            const int j = idx + step;
+            if (j < n_here && chunk.pref[j] <= v) idx = j;
+          }
+          const int p = chunk.start[idx] + (v - chunk.pref[idx]);
+          pos[r] = clampi(p, 0, a.max_len - 1);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    carry += chunk_total;
+    if (carry >= vend) break;
+  }
+}
+
+}  // namespace spanattn
+#endif

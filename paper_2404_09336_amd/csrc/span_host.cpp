@@ -62,27 +62,26 @@ int check_desc(const span_attn_desc_t* d) {
 
 int32_t query_tokens(const span_attn_desc_t* d) { return d->q_len > 1 ? d->q_len : 1; }
 
-// Query tokens one launch serves: 1, 2 or 4 on the vector units (their register budget stops there), 16 on the
-// matrix cores (16-bit types with head_dim 128).  The matrix pass takes over from three tokens: measured on
-// batch 64 x ~155 attended positions, 32 heads, fp16: 3 tokens 31.9 us against 37.7 us for the four-token vector
-// pass, 2 tokens 31.5 against 29.7; batch 8 x 300..2000 positions: 27.5 against 29.4 and 27.4 against 25.0.
-#ifndef SPAN_MATRIX_PASS_FROM
-#define SPAN_MATRIX_PASS_FROM 3
-#endif
+// Query tokens a slot of the workspace holds (one partial state each): 1, 2, 4, or 16 for 16-bit types with head_dim
+// 128 from three tokens on.  One- and two-token calls run as planned with it; from three tokens on plan_matrix regroups
+// the slots.
 static int32_t queries_per_pass(const span_attn_desc_t* d) {
   const int32_t n = query_tokens(d);
-  if (n >= SPAN_MATRIX_PASS_FROM && d->dtype != SPAN_F32 && d->head_dim == 128) return 16;
+  if (n >= 3 && d->dtype != SPAN_F32 && d->head_dim == 128) return 16;
   return n >= 3 ? 4 : n;
 }
 
-// Workgroups of one resident round: the kernel for one query token runs 8 workgroups per CU, the one for
-// two tokens 6, the ones for four and for sixteen tokens 4 (their register budgets).
+// Workgroups of one resident round: the kernel for one query token runs 8 workgroups per CU, the one for two tokens 6
+// (their register budgets); the workspace of longer calls is sized for 4.
 static int64_t target_workgroups(const span_attn_desc_t* d) {
   const int32_t nq = queries_per_pass(d);
   return nq == 1 ? kTargetWorkgroups : kTargetWorkgroups * (nq == 2 ? 6 : 4) / 8;
 }
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// (a few-query call's slots are regrouped into slices of at least kMinSlice positions, see plan_matrix)
+static int64_t min_slice(const span_attn_desc_t* d) { return queries_per_pass(d) > 2 ? kSliceGranule : kMinSlice; }
 
 // Slices (per head, over all sequences) a call aims at.  The upper end is one resident round of workgroups.  But
 // few, large slices beat many small ones as long as the memory system stays busy and a ragged batch can still be
@@ -94,6 +93,13 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static int64_t slice_room(const span_attn_desc_t* d) {
   const int64_t round = target_workgroups(d);
   const int64_t most = round / d->heads, least = ceil_div(round / 4, d->heads);
+  if (queries_per_pass(d) > 2) {
+    // Few-query calls: room for the partial states of a whole round, and where the (batch, head) pairs alone do not
+    // fill the chip, for those of kUnsplitFromPairs workgroups with all tokens of the call.
+    const int64_t few_pairs = (int64_t)d->batch * d->heads < kUnsplitFromPairs
+                                  ? ceil_div(ceil_div(kUnsplitFromPairs, d->heads) * query_tokens(d), queries_per_pass(d)) : 0;
+    return std::min<int64_t>(std::max<int64_t>(std::max<int64_t>(1, most), few_pairs), kMaxPlanSlices);
+  }
   const int64_t room = std::max<int64_t>(least, 2 * (int64_t)d->batch);
   return std::max<int64_t>(1, std::min(room, most));
 }
@@ -128,7 +134,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   int64_t room = slice_room(d);  // slices (per head) the call aims at, at most one resident round
   if (room > kMaxPlanSlices) room = kMaxPlanSlices;
   int64_t T = ceil_div(sum, room);
-  if (T < kMinSlice) T = kMinSlice;
+  if (T < min_slice(d)) T = min_slice(d);
   int64_t total = count(T);
   // A quarter of the chip's wavefront slots (512 workgroups) already keeps the memory system busy, and a
   // pair that is one workgroup needs no partial states and no tickets.  So a batch of at least 512 (batch,
@@ -146,7 +152,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
       total = count(T);
     }
     // fits: give back what the proportional step overshot
-    for (int i = 0; i < 8 && T - kSliceGranule >= kMinSlice && count(T - kSliceGranule) <= room; ++i)
+    for (int i = 0; i < 8 && T - kSliceGranule >= min_slice(d) && count(T - kSliceGranule) <= room; ++i)
       T -= kSliceGranule;
     total = count(T);
   }
@@ -290,7 +296,7 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
   }
   const int64_t pairs = (int64_t)d->batch * d->heads;
   int64_t splits = d->num_splits > 0 ? d->num_splits : slice_room(d) / d->batch;  // stay within one round
-  const int64_t most = ceil_div(max_tok, kMinSlice);
+  const int64_t most = ceil_div(max_tok, min_slice(d));
   if (d->num_splits == 0 && splits > most) splits = most;
   if (splits > max_tok) splits = max_tok;
   if (splits < 1) splits = 1;
@@ -308,6 +314,138 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
   p.granule = (int32_t)slice;
   p.runs = false;
   return p;
+}
+
+// Few-query calls on the matrix cores: all tokens of the call in one launch, a workgroup serving up to 64 of them with
+// one pass over its rows.
+//
+// From three tokens on, for every type and head_dim.  Measured against the passes it replaces (four tokens on the vector
+// units, sixteen on the matrix cores, one launch per pass): batch 16 x ~380 positions, 16 heads x 64, fp16, 9 tokens
+// 63.9 -> 14.7 us; batch 8 x ~600, 32 heads x 128, fp32, 8 tokens 83.6 -> 39.7 us; 3 tokens, batch 16 x ~370, fp32 49.9 ->
+// 45.3 us; batch 16 x ~700, bf16, 32 tokens 96.4 -> 50.1 us; batch 32 x 1000, bf16, 64 tokens 313 -> 130 us.
+//
+// Slices.  512 workgroups a call (two per CU), but one slice per sequence at least and one resident round at most: of
+// 256, 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 shapes; more only pays for itself in
+// partial states, which grow with the tokens (batch 16 x ~700, 32 tokens, 16 slices per head against 32: 50.4 and 59.3 us).
+// The slices have to fit the workspace (total_slices * queries_per_pass token states per head), so sequences that stay
+// in one slice, which need no state, come after the others in the table.
+//
+// Groups.  A workgroup that serves all tokens reads every row once; where the batch has too few (batch, head) pairs to
+// fill the chip that way (fewer than 128 workgroups before slicing), several workgroups share a slice's rows through the
+// L2, each for its own tokens: 12 heads x 8, 60 tokens 36.1 us with 64 tokens a workgroup, 29.2 us with 32; 32 pairs x 1500
+// fp32 positions, 30 tokens 38.9 -> 31.1 us; 256 pairs, 24 tokens 22.2 us in two workgroups, 18.9 us in one.
+constexpr int32_t kMatrixFromTokens = 3;
+constexpr int64_t kMatrixWorkgroups = 512;
+constexpr int64_t kMatrixPairs = 128;
+constexpr int32_t kMatrixMaxFieldSlices = 255;  // slices of a pair when several query blocks share its ticket counter
+
+bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table) {
+  int32_t n = query_tokens(d);
+  if (n < kMatrixFromTokens) return false;
+  const bool sliced = p.num_splits > 1;
+  const int64_t states = sliced ? (int64_t)p.total_slices * p.queries_per_pass : 0;  // the workspace's, per head
+  m->tokens = n;
+  m->table = false;
+  m->even = p.even;
+  m->num_splits = p.num_splits;
+  m->slice_tokens = p.slice_tokens;
+  m->total_slices = p.total_slices;
+  const int32_t max_groups = kMatrixMaxGroups(d->dtype == SPAN_F32 ? 4 : 2, d->head_dim);
+  auto groups_for = [&](int64_t tokens) { return std::min<int32_t>(max_groups, tokens <= 16 ? 1 : (tokens <= 32 ? 2 : 4)); };
+  if (d->num_splits > 0) {  // the caller's number of slices stands: as many tokens a launch as their states fit
+    if (sliced && n > p.queries_per_pass) m->tokens = p.queries_per_pass;
+    m->groups = groups_for(m->tokens);
+    while ((int64_t)d->batch * ceil_div(m->tokens, 16 * m->groups) > 65535) m->tokens = 16 * m->groups;  // (grid.z limit)
+    return true;
+  }
+  m->groups = groups_for(n);
+  const int64_t pairs = (int64_t)d->batch * d->heads;
+  auto blocks_for = [&](int32_t groups) { return ceil_div(n, 16 * groups); };
+  while (m->groups > 1 && pairs * blocks_for(m->groups) < kMatrixPairs) m->groups /= 2;
+  if (d->batch * blocks_for(m->groups) > 65535) m->tokens = n = 16 * m->groups;  // (grid.z limit)
+  const int64_t blocks = blocks_for(m->groups);
+  const int64_t per_cu = m->groups == 1 ? 4 : (m->groups == 2 ? 3 : 2);  // resident workgroups
+  const int64_t most = 256 * per_cu / (d->heads * blocks), wanted = ceil_div(kMatrixWorkgroups, d->heads * blocks);
+  const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
+  if (!p.even) {  // the counts are not known: every sequence gets the same number of slices
+    if (!sliced) return true;
+    int64_t splits = std::min<int64_t>(room / d->batch, states / ((int64_t)d->batch * n));
+    splits = std::min<int64_t>(std::min<int64_t>(splits, blocks > 1 ? kMatrixMaxFieldSlices : 65535), ceil_div(p.max_tokens, kMinSlice));
+    if (splits < 1) splits = 1;
+    int64_t slice = std::min<int64_t>(ceil_div(ceil_div(p.max_tokens, splits), kSliceGranule) * kSliceGranule, kMaxSlice);
+    m->num_splits = (int32_t)ceil_div(p.max_tokens, slice);
+    m->slice_tokens = (int32_t)slice;
+    m->total_slices = m->num_splits * d->batch;
+    return true;
+  }
+  std::vector<int64_t> from_lists;
+  const int64_t* counts = d->tokens_per_seq;
+  if (has_host_lists(d) && d->batch <= kMaxPlanBatch) {
+    tokens_from_host_lists(d, &from_lists);
+    counts = from_lists.data();
+  }
+  auto tokens = [&](int32_t b) { return std::min<int64_t>(std::max<int64_t>(counts[b], 0), p.max_tokens); };
+  int64_t sum = 0;
+  for (int32_t b = 0; b < d->batch; ++b) sum += tokens(b);
+  // `cap` slices at most, and those of the sequences with several fit the slots
+  auto fits = [&](int64_t t, int64_t cap) {
+    int64_t total = 0, in_slots = 0;
+    for (int32_t b = 0; b < d->batch; ++b) {
+      const int64_t s = slices_for(tokens(b), t);
+      if (s > (blocks > 1 ? kMatrixMaxFieldSlices : kMaxPlanSplits)) return false;
+      total += s;
+      if (s > 1) in_slots += s;
+    }
+    return total <= cap && in_slots * n <= states;
+  };
+  int64_t T = std::max<int64_t>(p.max_tokens, 1);
+  // smallest slice size from `from` on that fits (the counts fall as it grows); T where none below it does
+  auto smallest_fit = [&](int64_t from, int64_t cap) {
+    int64_t lo = 0, hi = T > from ? ceil_div(T - from, kSliceGranule) : 0;  // in granules above `from`; hi always fits
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (fits(from + mid * kSliceGranule, cap)) hi = mid;
+      else lo = mid + 1;
+    }
+    return std::min(T, from + hi * kSliceGranule);
+  };
+  if (sliced) {
+    if (room >= d->batch) {
+      const int64_t cap = std::min<int64_t>(room, kMaxPlanSlices);
+      T = smallest_fit(std::max<int64_t>(kMinSlice, ceil_div(sum, cap)), cap);
+    }
+    // as in plan_exact: slices well above the average and large in themselves run in several rounds of smaller ones
+    int64_t total = 0, largest = 1;
+    for (int32_t b = 0; b < d->batch; ++b) {
+      const int64_t s = slices_for(tokens(b), T);
+      total += s;
+      largest = std::max(largest, ceil_div(tokens(b), s));
+    }
+    if (largest > kLargeSlice && 2 * largest * total > 3 * sum) T = smallest_fit(kLargeSlice, kMaxPlanSlices);
+  }
+  int64_t total = 0, longest = 1, most_s = 1, least_s = kMaxPlanSplits + 1;
+  for (int32_t b = 0; b < d->batch; ++b) {
+    const int64_t s = slices_for(tokens(b), T);
+    total += s;
+    most_s = std::max(most_s, s);
+    least_s = std::min(least_s, s);
+    longest = std::max(longest, ceil_div(tokens(b), s));
+  }
+  m->num_splits = (int32_t)most_s;
+  m->slice_tokens = (int32_t)longest;
+  m->total_slices = (int32_t)total;
+  if (most_s != least_s) {
+    m->table = true;
+    int32_t y = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int32_t b = 0; b < d->batch; ++b) {
+        const int64_t s = slices_for(tokens(b), T);
+        if ((s > 1) != (pass == 0)) continue;
+        for (int64_t i = 0; i < s; ++i) table[y++] = pack_slice((uint32_t)b, (uint32_t)i, (uint32_t)s);
+      }
+    }
+  }
+  return true;
 }
 
 size_t workspace_counter_bytes(const span_attn_desc_t* d) {

@@ -1,0 +1,778 @@
+// Span-restricted attention for several query tokens of a sequence (the few-query calls, three tokens and more) on
+// gfx950's matrix cores: the one place of the decode path that is a dense contraction.
+//
+// A workgroup of 4 wavefronts takes one slice of a (batch, head) pair's span, as decode_kernel does, and up to 16 G
+// query tokens; a call is one launch.  A wave takes its rows in tiles of 16 S rows.  Lane (qi, c4) = (lane % 16,
+// lane / 16) plays row / column qi and contraction share c4 of the 16x16 MFMAs:
+//   * scores S^T = K Q^T.  Lane (i, c) holds the 16-byte pieces 4 mm + c of K row i and of query row i; both use the
+//     same assignment of the head dimension to (MFMA, lane group, element), so K pieces go from the load straight into
+//     the operand.  Lane (qi, c4) ends up with the scores of query qi against rows 4 c4 + t of each 16 rows -
+//   * outputs O^T = V^T P^T - which is the B operand of the second product (contraction over the tile's rows).  For
+//     A = V^T lane (i, c) loads its D / 16 values of rows 4 c + t (whole rows per quarter wave, coalesced) and MFMA e
+//     takes element e of each, so lane (qi, c4) accumulates NE = D / 16 x 4 output columns of query qi, and the
+//     online-softmax rescaling factor is a per-lane scalar.
+//   * 16-bit weights: the fp32 weight enters the second product as kTerms terms of the storage type, each rounding what
+//     the ones before left.  fp32 rows use the fp32 MFMA throughout.
+// Bound by memory except for few pairs, where the start-up chain (1 us of list metadata, 2 us to the first rows) and the
+// merge count.  Its rounding is that of the vector kernels or less (measured against 64 bits, relative 2-norm: fp32 1.6e-7
+// for 1.8e-7, 16-bit rows of 64 1.5e-7 for 1.6e-7, fp16 rows of 128 1.8e-7, bf16 2.1e-7 for the 1.8e-6 of two-term weights).
+// K and V are streamed through registers: the next tile's K loads go out as soon as the scores of this one are taken,
+// its V loads as soon as the outputs are, so a wave always has loads in flight.
+#include "span_device.h"
+#include "span_matrix.h"
+
+namespace spanattn {
+namespace {
+
+constexpr int kMWin = 512;  // rows of a wave whose positions are tabulated at a time
+constexpr uint32_t kNoRow = 0xfffffc00u;  // an offset past every slab (and still so with a piece offset added)
+
+struct MatrixArgs : LaunchArgs {
+  int32_t tokens;        // query tokens of this launch: q_first .. q_first + tokens - 1
+  int32_t slot_tokens;   // query tokens a slot of the workspace holds
+  int32_t batch;
+  int32_t query_blocks;  // workgroups per slice, each serving its own 16 G of the tokens
+};
+struct MatrixArgsPlain : MatrixArgs {
+  static constexpr bool kHasTable = false;
+};
+struct MatrixArgsTable : MatrixArgs {
+  static constexpr bool kHasTable = true;
+  uint32_t table[kMaxPlanSlices];  // entries of sequences with several slices come first: their index is the slot
+};
+
+// Shape of one instance.
+template <class Elt, int D, int G>
+struct MatrixShape {
+  static constexpr int kRowBytes = D * Elt::kBytes;
+  static constexpr int NK = kRowBytes / 64;   // 16-byte pieces of a K row per lane
+  static constexpr int NE = D / 16;           // values of a V row per lane
+  static constexpr int VW = NE * Elt::kBytes / 4;  // dwords they fill: 2 (16-bit, D = 64), 4, or 8 (fp32, D = 128: two pieces)
+  // Groups of 16 rows in a tile.  Two feed the 16x16x32 MFMA of the second product; one keeps 64 tokens inside the
+  // register file, and 16 tokens of 16-bit rows of 128 at four waves per SIMD (batch 64 x ~155 positions, 16 tokens: 40.4
+  // us against 44.2 with two and three waves).
+  static constexpr int S = Elt::kBytes == 4 || G == 4 || (G == 1 && D == 128) ? 1 : 2;
+  // Waves per SIMD: the most whose registers hold the state (4 NE per group), a tile and its weights without spills.
+  static constexpr int kWaves = D == 128 ? (G == 1 && Elt::kBytes == 2 ? 4 : 2) : (G == 1 ? 4 : (G == 2 ? 3 : 2));
+};
+
+__device__ __forceinline__ float exchange_max(float x) {  // maximum over the four lanes qi + 16 c
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t a0 = a[0], a1 = a[1];
+  const float y = fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1));
+  const uint32_t w = __builtin_bit_cast(uint32_t, y);
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  const uint32_t b0 = b[0], b1 = b[1];
+  return fmaxf(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
+}
+
+// The value is computed here and not later: the compiler would otherwise sink the additions below the next tile's loads,
+// and keep all their operands in registers across them.
+__device__ __forceinline__ void pin(f32x4& v) { asm volatile("" : "+v"(v)); }
+
+// 16 bytes to / from memory that all XCDs share (sc1: written through, never served from a stale L2 line).
+constexpr int kShared = 16;
+__device__ __forceinline__ void publish4(__amdgpu_buffer_rsrc_t slot, uint32_t byte_off, f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), slot, byte_off, 0, kShared);
+}
+__device__ __forceinline__ f32x4 observe4(__amdgpu_buffer_rsrc_t slot, uint32_t byte_off) {
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slot, byte_off, 0, kShared));
+}
+
+template <class Elt, int D, int G, class Args>
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<Elt, D, G>::kWaves))) void matrix_kernel(const Args a) {
+  using Shape = MatrixShape<Elt, D, G>;
+  constexpr int NK = Shape::NK, NE = Shape::NE, VW = Shape::VW, S = Shape::S;
+  constexpr int TR = 16 * S;                 // rows of a tile
+  constexpr uint32_t ROWB = Shape::kRowBytes;
+  constexpr int NQ = 16 * G;
+  constexpr int kPieces = ROWB / 16;
+  constexpr int kQRow = ROWB + 16;           // LDS rows of q, padded: operand reads spread over the banks
+  constexpr int kAccRow = D + 4;
+  constexpr bool kSplitPieces = VW == 8;     // the lane's V values are two pieces half a row apart
+  static_assert(kMWin % TR == 0, "tiles do not straddle a window");
+
+  SPAN_TRACE_DECL;
+  SPAN_STAMP_AFTER(0, "s", 0);
+  const int h = blockIdx.x;
+  int b, split, nsl, y0, qb;
+  if constexpr (Args::kHasTable) {
+    const uint32_t e = a.table[blockIdx.y];
+    b = e & 1023u;
+    split = (e >> 10) & 2047u;
+    nsl = e >> 21;
+    y0 = blockIdx.y - split;
+    qb = blockIdx.z;
+  } else {
+    qb = 0;  // grid.z = sequences of block 0, then of block 1, ...
+    b = blockIdx.z;
+    while (b >= a.batch) {
+      b -= a.batch;
+      ++qb;
+    }
+    split = blockIdx.y;
+    nsl = a.num_splits;
+    y0 = b * nsl;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qi = lane & 15, c4 = lane >> 4;
+  const size_t bh = (size_t)b * a.heads + h;
+
+  struct StreamTables {
+    int pos[kWavesPerBlock][kMWin];
+    IntervalChunk chunk[kWavesPerBlock];
+    unsigned char q[NQ * kQRow] __attribute__((aligned(16)));
+  };
+  struct WaveStates {  // of one group of 16 tokens at a time
+    float acc[kWavesPerBlock][16][kAccRow];
+  };
+  union Overlaid {
+    StreamTables st;
+    WaveStates ws;
+  };
+  __shared__ __attribute__((aligned(16))) Overlaid s_u;
+  __shared__ float s_ml[kWavesPerBlock][NQ][2];
+  __shared__ uint32_t s_ticket;
+  auto& s_pos = s_u.st.pos;
+  auto& s_q = s_u.st.q;
+
+  // Query token j of this workgroup is row (b, q0 + j, h) of q and out; tokens past the launch's last one are
+  // computed from the last real one and never written.
+  const int q0 = a.q_first + qb * NQ;
+  const int nq_here = min(NQ, a.q_first + a.tokens - q0);
+  auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(q0 + min(j, nq_here - 1))) * a.heads + h; };
+
+  // q goes to LDS (the same for the four waves).  It is fetched here, as are the append form's new rows for the cache
+  // (written by the first slice's workgroup, whatever the span holds); both have arrived when the rows' positions are known.
+  constexpr int kQLoads = (NQ * kPieces + kThreads - 1) / kThreads;
+  const bool append = a.append_pos != nullptr;
+  const bool writes_new = append && split == 0;
+  u32x4 q_piece[kQLoads], k_piece[kQLoads], v_piece[kQLoads];
+#pragma unroll
+  for (int i = 0; i < kQLoads; ++i) {
+    const int idx = min(tid + i * kThreads, NQ * kPieces - 1);
+    const size_t src = qrow(idx / kPieces) * ROWB + 16u * (uint32_t)(idx % kPieces);
+    q_piece[i] = *reinterpret_cast<const u32x4*>((const char*)a.q + src);
+    if (writes_new) {
+      k_piece[i] = *reinterpret_cast<const u32x4*>((const char*)a.k_new + src);
+      v_piece[i] = *reinterpret_cast<const u32x4*>((const char*)a.v_new + src);
+    }
+  }
+  const float post = Elt::kPostScale ? a.scale_log2e : 1.f;
+
+  // Causal limit: query token j sees no position after lim0 + j.  In the append form the call's tokens sit at
+  // positions new0 .. new0 + q_len - 1; those rows come from k_new / v_new, never from the cache.
+  // (clamped: any q_pos at or beyond the cache length means "no limit", without overflow)
+  const bool limited = a.q_pos != nullptr;
+  const int pos0 = limited ? min(a.q_pos[b], kMaxLen) : 0;
+  const int lim0 = limited ? pos0 + q0 : 0x7fffffff;
+  const int last_any = limited ? lim0 + nq_here - 1 : 0x7fffffff;
+  const int new0 = append ? min(a.append_pos[b], kMaxLen) : 0x7fffffff;
+
+  const int scan_stop = a.even ? 0x7fffffff : (split + 1) * a.slice_tokens;
+  Intervals intervals = interval_range(a, b);
+  SPAN_STAMP_AFTER(10, "s", intervals.count);
+  int n_total = count_positions(a, intervals, lane, scan_stop);
+  n_total = n_total < a.max_tokens ? n_total : a.max_tokens;
+  const int T = a.even ? (n_total + nsl - 1) / nsl : a.slice_tokens;
+  const int slice_begin = split * T;
+  const int cnt = __builtin_amdgcn_readfirstlane(clampi(n_total - slice_begin, 0, T));
+  SPAN_STAMP_AFTER(1, "s", cnt);
+
+  // How the slice's rows are dealt to the waves (see decode_kernel): contiguous quarters of small slices, tiles
+  // round-robin for large ones.
+  int nrows, r_first = 0;
+  if (a.interleave) {
+    const int units_all = (cnt + TR - 1) / TR;
+    const int units = units_all > wave ? (units_all - wave + kWavesPerBlock - 1) / kWavesPerBlock : 0;
+    const bool own_last = units > 0 && (wave + (units - 1) * kWavesPerBlock) == units_all - 1;
+    nrows = units * TR - (own_last ? units_all * TR - cnt : 0);
+  } else {
+    const int rpw = (((cnt + kWavesPerBlock - 1) / kWavesPerBlock) + 3) / 4 * 4;
+    r_first = min(wave * rpw, cnt);
+    nrows = min(r_first + rpw, cnt) - r_first;
+  }
+  auto vrow = [&](int r) {
+    return slice_begin + (a.interleave ? ((r / TR) * kWavesPerBlock + wave) * TR + (r % TR) : r_first + r);
+  };
+  if (nrows > 0) tabulate_positions<true>(a, intervals, vrow, 0, min(kMWin, nrows), lane, s_u.st.chunk[wave], s_pos[wave]);
+  SPAN_STAMP_AFTER(2, "s", cnt);
+
+  const uint32_t slab_bytes = (uint32_t)a.max_len * ROWB;
+  const __amdgpu_buffer_rsrc_t kslab = slab_resource((const char*)a.k + bh * (size_t)slab_bytes, slab_bytes);
+  const __amdgpu_buffer_rsrc_t vslab = slab_resource((const char*)a.v + bh * (size_t)slab_bytes, slab_bytes);
+  // new row i of the call (only addressed for positions that the append form brings)
+  auto new_row = [&](const void* rows, int i) {
+    return (const char*)rows + (((size_t)b * a.q_len + (size_t)i) * a.heads + h) * ROWB;
+  };
+
+  // State of query 16 g + qi in lane (qi, c4).  ref: reference exponent of the weights, their running maximum (the same
+  // in the four lanes of a query); lsum: this lane's share of their sum; O[g][e][r]: un-normalised output column
+  // column(4 c4 + r) + e, times Elt::kWeightScale.
+  float ref[G], lsum[G];
+  f32x4 O[G][NE];
+  // first column of quad u of the values that lane group row i of V^T stands for
+  auto column = [&](int i, int u) { return kSplitPieces ? 64 * u + 4 * i : NE * i + 4 * u; };
+
+  u32x4 kr[S][NK];
+  uint32_t vr[S][4][VW];
+
+  struct TileRows {         // wave-uniform
+    uint32_t ok[S];         // bit i: row 16 s + i takes part
+    bool plain;             // every row takes part and every query of the workgroup sees all of them
+  };
+  auto load_k = [&](int base, int wn) {
+    TileRows tr;
+    tr.plain = true;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int r = base + 16 * s + qi;
+      const int p = s_pos[wave][r];
+      const bool ok = r < wn && p <= last_any;
+      tr.ok[s] = (uint32_t)__builtin_amdgcn_ballot_w64(ok) & 0xffffu;
+      tr.plain = tr.plain && tr.ok[s] == 0xffffu && __builtin_amdgcn_ballot_w64(p > lim0) == 0;
+      const uint32_t off = ok ? (uint32_t)p * ROWB + 16u * (uint32_t)c4 : kNoRow;
+      const bool fresh = ok && p >= new0;
+#pragma unroll
+      for (int mm = 0; mm < NK; ++mm) kr[s][mm] = load_row_piece(kslab, (fresh ? kNoRow : off) + 64u * mm);
+      if (__builtin_amdgcn_ballot_w64(fresh) != 0) {  // (rare: the tiles of the call's own tokens)
+        if (fresh) {
+          const u32x4* src = reinterpret_cast<const u32x4*>(new_row(a.k_new, p - new0)) + c4;
+#pragma unroll
+          for (int mm = 0; mm < NK; ++mm) kr[s][mm] = src[4 * mm];
+        }
+      }
+    }
+    return tr;
+  };
+  auto load_v = [&](int base, const TileRows& tr) {
+    const uint32_t in_row = (kSplitPieces ? 16u : (uint32_t)(VW * 4)) * (uint32_t)qi;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const i32x4 p4 = *reinterpret_cast<const i32x4*>(&s_pos[wave][base + 16 * s + 4 * c4]);
+      bool ok[4], any_fresh = false;
+      uint32_t off[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        ok[t] = (tr.ok[s] >> (4 * c4 + t)) & 1u;
+        any_fresh = any_fresh || (ok[t] && p4[t] >= new0);
+        off[t] = ok[t] && p4[t] < new0 ? (uint32_t)p4[t] * ROWB + in_row : kNoRow;
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        if constexpr (VW == 2) {
+          const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(vslab, off[t], 0, kRowLoadPolicy);
+          vr[s][t][0] = w[0];
+          vr[s][t][1] = w[1];
+        } else {
+#pragma unroll
+          for (int u = 0; u < VW / 4; ++u) {
+            const u32x4 w = load_row_piece(vslab, off[t] + 256u * u);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) vr[s][t][4 * u + k] = w[k];
+          }
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(any_fresh) != 0) {  // (rare: the tiles of the call's own tokens)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          if (ok[t] && p4[t] >= new0) {
+            const char* src = new_row(a.v_new, p4[t] - new0) + in_row;
+#pragma unroll
+            for (int k = 0; k < VW; ++k) vr[s][t][k] = *reinterpret_cast<const uint32_t*>(src + 256 * (k / 4) + 4 * (k % 4));
+          }
+        }
+      }
+    }
+  };
+
+  // Scores of the tile in kr: sc[g][s][t] = query 16 g + qi against row 16 s + 4 c4 + t.  A score is summed in pieces (8
+  // products of fp32 values, or 32 of 16-bit values of head_dim 64, from zero; the pieces pairwise), not in one long
+  // accumulator chain: its rounding goes straight into the weight.
+  auto take_scores = [&](f32x4 (&sc)[G][S]) {
+    constexpr f32x4 kZero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const unsigned char* qrow_lds = &s_q[(16 * g + qi) * kQRow + 16 * c4];
+      if constexpr (Elt::kBytes == 2) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) sc[g][s] = kZero;
+#pragma unroll
+        for (int mm = 0; mm < NK; ++mm) {
+          const u32x4 qm = *reinterpret_cast<const u32x4*>(qrow_lds + 64 * mm);
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            if constexpr (D == 64) sc[g][s] += Elt::mfma(kr[s][mm], qm, kZero);
+            else sc[g][s] = Elt::mfma(kr[s][mm], qm, sc[g][s]);
+          }
+        }
+      } else {
+        f32x4 sum[4] = {kZero, kZero, kZero, kZero}, prev[2];
+#pragma unroll
+        for (int mm = 0; mm < NK; ++mm) {
+          const u32x4 qm = *reinterpret_cast<const u32x4*>(qrow_lds + 64 * mm);
+          f32x4 piece[2] = {kZero, kZero};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t kw = kr[0][mm][k], qw = qm[k];
+            piece[k & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, kw), __builtin_bit_cast(float, qw), piece[k & 1], 0, 0, 0);
+          }
+          if (mm > 0) sum[(mm - 1) & 3] += prev[0] + prev[1];  // (one piece late: the MFMAs of this one run meanwhile)
+          prev[0] = piece[0];
+          prev[1] = piece[1];
+        }
+        sum[(NK - 1) & 3] += prev[0] + prev[1];
+        sc[g][0] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        pin(sc[g][0]);
+      }
+    }
+  };
+  // Scores -> weights, and the states' reference and sum; rescales O when the reference moved.
+  auto softmax_step = [&](f32x4 (&sc)[G][S], int base, const TileRows& tr) {
+    if (!tr.plain) {
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const i32x4 p4 = *reinterpret_cast<const i32x4*>(&s_pos[wave][base + 16 * s + 4 * c4]);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const bool ok = (tr.ok[s] >> (4 * c4 + t)) & 1u;
+          const int beyond = (ok ? p4[t] : 0x7fffffff) - lim0;  // (no limit: lim0 is the largest int)
+#pragma unroll
+          for (int g = 0; g < G; ++g) sc[g][s][t] = ok && beyond <= 16 * g + qi ? sc[g][s][t] * post : -INFINITY;
+        }
+      }
+    } else if (Elt::kPostScale) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) sc[g][s][t] *= post;
+        }
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mx = fmaxf(mx, sc[g][s][t]);
+      }
+      if (__builtin_amdgcn_ballot_w64(mx > ref[g]) != 0) {  // (the maximum settles after the first tiles)
+        mx = exchange_max(mx);
+        const float ref_new = fmaxf(ref[g], mx);
+        const float ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
+        const float alpha = __builtin_amdgcn_exp2f(ref[g] - ref_safe);
+        ref[g] = ref_new;
+        lsum[g] *= alpha;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) O[g][e] *= alpha;
+      }
+      const float ref_safe = ref[g] == -INFINITY ? 0.f : ref[g];
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sc[g][s][t] = __builtin_amdgcn_exp2f(sc[g][s][t] - ref_safe);
+        lsum[g] += (sc[g][s][0] + sc[g][s][1]) + (sc[g][s][2] + sc[g][s][3]);
+      }
+    }
+  };
+  // O += V^T P^T with the tile in vr and the weights w.
+  auto add_outputs = [&](const f32x4 (&w)[G][S]) {
+    if constexpr (Elt::kBytes == 2) {
+      uint32_t terms[G][Elt::kTerms][2 * S];  // dword 2 s + k: rows 4 c4 + 2 k, + 1 of group s
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            uint32_t tt[Elt::kTerms];
+            Elt::split(w[g][s][2 * k] * Elt::kWeightScale, w[g][s][2 * k + 1] * Elt::kWeightScale, tt);
+#pragma unroll
+            for (int i = 0; i < Elt::kTerms; ++i) terms[g][i][2 * s + k] = tt[i];
+          }
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        // element e of the V values, as the pairs (rows 4 c4, + 1), (+ 2, + 3) of each group the MFMA wants
+        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+        uint32_t va[2 * S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          va[2 * s] = __builtin_amdgcn_perm(vr[s][1][e >> 1], vr[s][0][e >> 1], sel);
+          va[2 * s + 1] = __builtin_amdgcn_perm(vr[s][3][e >> 1], vr[s][2][e >> 1], sel);
+        }
+        // (head_dim 64: the tile's own sum first, the running one is rounded once per tile; the smallest terms lead)
+        f32x4 part[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) part[g] = D == 64 ? f32x4{0.f, 0.f, 0.f, 0.f} : O[g][e];
+#pragma unroll
+        for (int i = Elt::kTerms - 1; i >= 0; --i) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const uint32_t* tg = terms[g][i];
+            if constexpr (S == 2) part[g] = Elt::mfma(u32x4{va[0], va[1], va[2], va[3]}, u32x4{tg[0], tg[1], tg[2], tg[3]}, part[g]);
+            else part[g] = Elt::mfma(u32x2{va[0], va[1]}, u32x2{tg[0], tg[1]}, part[g]);
+          }
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          O[g][e] = D == 64 ? O[g][e] + part[g] : part[g];
+          if (D == 64) pin(O[g][e]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        f32x4 part[G][2];  // the tile's own sums first: the running one is rounded once per tile
+#pragma unroll
+        for (int g = 0; g < G; ++g) part[g][0] = part[g][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const uint32_t vw = vr[0][t][e];
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            part[g][t & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, vw), w[g][0][t], part[g][t & 1], 0, 0, 0);
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          O[g][e] += part[g][0] + part[g][1];
+          pin(O[g][e]);
+        }
+      }
+    }
+  };
+  // The whole pass again, one row at a time on the vector units, for a cache with non-finite V rows: a row never meets
+  // the sums of a query that does not see it, not even with weight zero (0 * Inf), and the fp32 weight meets the V
+  // value whole (the terms of a 16-bit weight would turn Inf into Inf + 0 * Inf).
+  auto stream_by_row = [&]() {
+    for (int w0 = 0; w0 < nrows; w0 += kMWin) {
+      const int wn = min(kMWin, nrows - w0);
+      tabulate_positions<false>(a, intervals, vrow, w0, wn, lane, s_u.st.chunk[wave], s_pos[wave]);
+#pragma unroll 1
+      for (int i = 0; i < wn; ++i) {
+        const int p = __builtin_amdgcn_readfirstlane(s_pos[wave][i]);
+        if (p > last_any) continue;
+        const size_t cached = (bh * (size_t)a.max_len + (size_t)p) * ROWB;
+        const char* krow = p >= new0 ? new_row(a.k_new, p - new0) : (const char*)a.k + cached;
+        const char* vrow_p = p >= new0 ? new_row(a.v_new, p - new0) : (const char*)a.v + cached;
+        float w[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          float d = 0.f;
+#pragma unroll 1
+          for (int mm = 0; mm < NK; ++mm) {
+            const u32x4 kp = *reinterpret_cast<const u32x4*>(krow + 16 * (4 * mm + c4));
+            const u32x4 qp = *reinterpret_cast<const u32x4*>(&s_q[(16 * g + qi) * kQRow + 16 * (4 * mm + c4)]);
+            d += Elt::dot(kp, Elt::make_q(qp, 1.f));
+          }
+          d += __shfl_xor(d, 16, 64);
+          d += __shfl_xor(d, 32, 64);
+          d = p - lim0 <= 16 * g + qi ? d * post : -INFINITY;
+          const float ref_new = fmaxf(ref[g], d), ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
+          const float alpha = ref[g] == ref_new ? 1.f : __builtin_amdgcn_exp2f(ref[g] - ref_safe);
+          ref[g] = ref_new;
+          w[g] = __builtin_amdgcn_exp2f(d - ref_safe);
+          lsum[g] = lsum[g] * alpha + (c4 == 0 ? w[g] : 0.f);
+          w[g] *= Elt::kWeightScale;
+#pragma unroll
+          for (int e = 0; e < NE; ++e) O[g][e] *= alpha;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+          for (int u = 0; u < NE / 4; ++u) {
+            float vf[4];
+            Elt::unpack4(vrow_p + column(4 * c4 + r, u) * Elt::kBytes, vf);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+              if (p - lim0 <= 16 * g + qi) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) O[g][4 * u + k][r] = fmaf(w[g], vf[k], O[g][4 * u + k][r]);
+              }
+            }
+          }
+        }
+      }
+    }
+  };
+  auto clear_state = [&]() {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      ref[g] = -INFINITY;
+      lsum[g] = 0.f;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) O[g][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+
+#pragma unroll
+  for (int i = 0; i < kQLoads; ++i) {
+    const int idx = tid + i * kThreads, j = idx / kPieces;
+    const uint32_t piece = 16u * (uint32_t)(idx % kPieces);
+    if (NQ * kPieces % kThreads != 0 && idx >= NQ * kPieces) continue;
+    if constexpr (!Elt::kPostScale) {  // fp32: the score scale goes into q
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t w = q_piece[i][k];
+        q_piece[i][k] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, w) * a.scale_log2e);
+      }
+    }
+    *reinterpret_cast<u32x4*>(&s_q[j * kQRow + piece]) = q_piece[i];
+    if (writes_new && j < nq_here) {
+      const int p = new0 + q0 + j;
+      if (p >= 0 && p < a.max_len) {
+        const size_t row = (bh * (size_t)a.max_len + (size_t)p) * ROWB + piece;
+        *reinterpret_cast<u32x4*>((char*)a.k + row) = k_piece[i];
+        *reinterpret_cast<u32x4*>((char*)a.v + row) = v_piece[i];
+      }
+    }
+  }
+  TileRows cur = {};
+  if (nrows > 0) {
+    cur = load_k(0, min(kMWin, nrows));
+    load_v(0, cur);
+  }
+  __syncthreads();  // q is in LDS
+  clear_state();
+  for (int w0 = 0; w0 < nrows; w0 += kMWin) {
+    const int wn = min(kMWin, nrows - w0);
+    if (w0 > 0) {
+      tabulate_positions<false>(a, intervals, vrow, w0, wn, lane, s_u.st.chunk[wave], s_pos[wave]);
+      cur = load_k(0, wn);
+      load_v(0, cur);
+    }
+    for (int base = 0; base < wn; base += TR) {
+      f32x4 sc[G][S];
+      take_scores(sc);
+      const bool more = base + TR < wn;
+      TileRows next = cur;
+      if (more) next = load_k(base + TR, wn);
+      softmax_step(sc, base, cur);
+      add_outputs(sc);
+      if (more) load_v(base + TR, next);
+      cur = next;
+#ifdef SPAN_PHASE_TRACE
+      if (w0 == 0 && base == 0) SPAN_STAMP_AFTER(3, "v", lsum[0]);
+#endif
+      // (the scheduler must not pull the next iteration's work up into this one: the registers would not suffice)
+      asm volatile("" ::"v"(lsum[0]) : "memory");
+    }
+  }
+  {
+    float z = 0.f;  // stays 0 unless some output is Inf or NaN
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z = fmaf(O[g][e][r], 0.f, z);
+      }
+    }
+    if (__builtin_amdgcn_ballot_w64(z != 0.f) != 0) {
+      clear_state();
+      stream_by_row();
+    }
+  }
+  SPAN_STAMP_AFTER(4, "v", O[0][0][0] + lsum[0]);
+
+  // ---- the waves' states are merged in LDS, 16 tokens at a time ------------------------------------------
+#pragma unroll
+  for (int g = 0; g < G; ++g) {  // the four lanes of a query hold the weights of disjoint rows
+    lsum[g] += __shfl_xor(lsum[g], 16, 64);
+    lsum[g] += __shfl_xor(lsum[g], 32, 64);
+    lsum[g] *= Elt::kWeightScale;
+    if (c4 == 0) {
+      s_ml[wave][16 * g + qi][0] = ref[g];
+      s_ml[wave][16 * g + qi][1] = lsum[g];
+    }
+  }
+  // A thread finishes quads of four columns: quad i of a group is columns 4 (i % (D / 4)) .. + 3 of token i / (D / 4).
+  constexpr int kQuadsPerToken = D / 4, kQuads = 16 * kQuadsPerToken / kThreads;
+  static_assert(16 * kQuadsPerToken % kThreads == 0, "whole quads per thread");
+  const bool direct = nsl == 1;
+  const size_t slot_floats = (size_t)a.slot_tokens * D;
+  const size_t slot0 = (size_t)y0 * a.heads + h, my_slot = slot0 + (size_t)split * a.heads;
+  const uint32_t q_in_slot = (uint32_t)(q0 - a.q_first);
+  auto acc_slot = [&](size_t slot) { return slab_resource(a.part_acc + slot * slot_floats, (uint32_t)(slot_floats * 4)); };
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    if (16 * g >= nq_here) break;  // (workgroup-uniform: groups without a real token)
+    __syncthreads();  // the streaming tables, or the states of the group before, are no longer read
+    if (16 * g + qi < nq_here) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int u = 0; u < NE / 4; ++u)
+          *reinterpret_cast<f32x4*>(&s_u.ws.acc[wave][qi][column(4 * c4 + r, u)]) =
+              f32x4{O[g][4 * u][r], O[g][4 * u + 1][r], O[g][4 * u + 2][r], O[g][4 * u + 3][r]};
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kQuads; ++i) {
+      const int j = (tid + i * kThreads) / kQuadsPerToken, col = 4 * ((tid + i * kThreads) % kQuadsPerToken);
+      const int token = 16 * g + j;
+      if (token >= nq_here) continue;
+      float m[kWavesPerBlock], l[kWavesPerBlock], M = -INFINITY, L = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) {
+        m[w] = s_ml[w][token][0];
+        l[w] = s_ml[w][token][1];
+        if (l[w] != 0.f) M = fmaxf(M, m[w]);  // (a NaN sum counts: it has to reach the output)
+      }
+      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) {
+        const float wgt = l[w] != 0.f ? __builtin_amdgcn_exp2f(m[w] - M) : 0.f;
+        const f32x4 ow = *reinterpret_cast<const f32x4*>(&s_u.ws.acc[w][j][col]);
+        L = fmaf(wgt, l[w], L);
+        if (l[w] != 0.f) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) o[k] = fmaf(wgt, ow[k], o[k]);
+        }
+      }
+      if (direct) {
+        const float sum = L != 0.f ? L : 1.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] /= sum;
+        *reinterpret_cast<f32x4*>(a.out + qrow(token) * D + col) = o;
+      } else {
+        publish4(acc_slot(my_slot), ((q_in_slot + (uint32_t)token) * D + (uint32_t)col) * 4u, o);
+        if (col == 0) {
+          float* ml = a.part_ml + (my_slot * (size_t)a.slot_tokens + q_in_slot + (size_t)token) * 2;
+          publish(ml, M);
+          publish(ml + 1, L);
+        }
+      }
+    }
+  }
+  SPAN_STAMP_ACKED(6);
+  if (direct) {
+    SPAN_TRACE_FLUSH();
+    return;
+  }
+
+  // ---- several slices: the workgroup that arrives last for (b, h) and these tokens merges them all ------------
+  // (the hand-over of decode_kernel, step 5).  With several query blocks each has 8 bits of the pair's counter.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // my published stores are acknowledged
+  __syncthreads();
+  SPAN_STAMP_AFTER(7, "s", 0);
+  const int field = a.query_blocks > 1 ? 8 * qb : 0;
+  const uint32_t field_mask = a.query_blocks > 1 ? 0xffu : 0xffffffffu;
+  if (tid == 0)
+    s_ticket = (uint32_t)__hip_atomic_fetch_add(&a.counters[bh], (int)(1u << field), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  SPAN_STAMP_AFTER(8, "v", s_ticket);
+  if (((s_ticket >> field) & field_mask) != (uint32_t)(nsl - 1)) {
+    SPAN_TRACE_FLUSH();
+    return;
+  }
+  for (int i = tid; i < nq_here * kQuadsPerToken; i += kThreads) {
+    const int token = i / kQuadsPerToken, col = 4 * (i % kQuadsPerToken);
+    const uint32_t off = ((q_in_slot + (uint32_t)token) * D + (uint32_t)col) * 4u;
+    float M = -INFINITY, L = 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    constexpr int kBatch = 4;  // slices fetched together
+    for (int s0 = 0; s0 < nsl; s0 += kBatch) {
+      float m[kBatch], l[kBatch];
+      f32x4 os[kBatch];
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const size_t slot = slot0 + (size_t)min(s0 + k, nsl - 1) * a.heads;  // (past the end: a slot that exists, unused)
+        const float* ml = a.part_ml + (slot * (size_t)a.slot_tokens + q_in_slot + (size_t)token) * 2;
+        m[k] = observe(ml);
+        l[k] = observe(ml + 1);
+        os[k] = observe4(acc_slot(slot), off);
+      }
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        if (s0 + k < nsl && l[k] != 0.f) {
+          const float mn = fmaxf(M, m[k]);
+          const float ms = mn == -INFINITY ? 0.f : mn;
+          const float wa = __builtin_amdgcn_exp2f(M - ms), wb = __builtin_amdgcn_exp2f(m[k] - ms);
+          L = fmaf(L, wa, l[k] * wb);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) o[c] = fmaf(o[c], wa, os[k][c] * wb);
+          M = mn;
+        }
+      }
+    }
+    const float sum = L != 0.f ? L : 1.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) o[k] /= sum;
+    *reinterpret_cast<f32x4*>(a.out + qrow(token) * D + col) = o;
+  }
+  // leave this block's part of the ticket counter ready for the next call
+  if (tid == 0) __hip_atomic_fetch_add(&a.counters[bh], (int)(0u - ((uint32_t)nsl << field)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  SPAN_STAMP_ACKED(9);
+  SPAN_TRACE_FLUSH();
+}
+
+template <class Elt, int D, int G>
+void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* table, int batch, int q_first, int tokens, hipStream_t stream) {
+  const int blocks = (tokens + 16 * G - 1) / (16 * G);
+  auto fill = [&](MatrixArgs& m) {
+    static_cast<LaunchArgs&>(m) = base;
+    m.q_first = q_first;
+    m.tokens = tokens;
+    m.slot_tokens = p.tokens;
+    m.batch = batch;
+    m.query_blocks = blocks;
+    m.num_splits = p.num_splits;
+    m.slice_tokens = p.slice_tokens;
+    m.total_slices = p.total_slices;
+    m.even = p.even ? 1 : 0;
+    m.interleave = p.slice_tokens >= kInterleaveFrom ? 1 : 0;
+  };
+  if (p.table) {
+    MatrixArgsTable m;
+    fill(m);
+    for (int i = 0; i < p.total_slices; ++i) m.table[i] = table[i];
+    hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsTable>), dim3((unsigned)base.heads, (unsigned)p.total_slices, (unsigned)blocks),
+                       dim3(kThreads), 0, stream, m);
+  } else {
+    MatrixArgsPlain m;
+    fill(m);
+    hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsPlain>),
+                       dim3((unsigned)base.heads, (unsigned)p.num_splits, (unsigned)(batch * blocks)), dim3(kThreads), 0, stream, m);
+  }
+}
+
+template <class Elt, int D>
+void launch_groups(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* table, int batch, int q_first, int tokens, hipStream_t stream) {
+  if (p.groups == 1) launch_shape<Elt, D, 1>(base, p, table, batch, q_first, tokens, stream);
+  else if (p.groups == 2 || kMatrixMaxGroups(Elt::kBytes, D) == 2) launch_shape<Elt, D, 2>(base, p, table, batch, q_first, tokens, stream);
+  else if constexpr (kMatrixMaxGroups(Elt::kBytes, D) == 4) launch_shape<Elt, D, 4>(base, p, table, batch, q_first, tokens, stream);
+}
+
+}  // namespace
+
+hipError_t launch_matrix(const LaunchArgs& base, int dtype, int head_dim, const MatrixPlan& p, const uint32_t* table,
+                         int batch, hipStream_t stream) {
+  for (int first = 0; first < base.q_len; first += p.tokens) {
+    const int tokens = base.q_len - first < p.tokens ? base.q_len - first : p.tokens;
+    const bool d128 = head_dim == 128;
+    if (dtype == SPAN_F32) {
+      if (d128) launch_groups<F32, 128>(base, p, table, batch, first, tokens, stream);
+      else launch_groups<F32, 64>(base, p, table, batch, first, tokens, stream);
+    } else if (dtype == SPAN_F16) {
+      if (d128) launch_groups<F16, 128>(base, p, table, batch, first, tokens, stream);
+      else launch_groups<F16, 64>(base, p, table, batch, first, tokens, stream);
+    } else {
+      if (d128) launch_groups<BF16, 128>(base, p, table, batch, first, tokens, stream);
+      else launch_groups<BF16, 64>(base, p, table, batch, first, tokens, stream);
+    }
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
+}
+
+}  // namespace spanattn

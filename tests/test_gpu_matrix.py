@@ -1,0 +1,102 @@
+"""The matrix-core kernel of the few-query calls at the sizes where its tiling can go wrong, against the fp64 oracle.
+
+Tolerance: with fp32 outputs of unit-variance V rows the error of the sums is about 2^-23 times a few units, and of the
+weights 2^-23 (fp32 rows, fp16 as two terms, bf16 as three); 1e-5 is some ten times what that adds up to over the rows
+attended here, and a thousand times less than one wrong row of the largest span would show."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2404_09336_amd as span
+from workloads import DecodeConfig, SpanBatch, draw_qkv, draw_queries, to_host_raw
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+
+
+def _dev(a, device):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(device)
+
+
+def _run(cfg, per_seq, q_len, device, q_pos="end", poison=None, **kw):
+    ctx = np.full(cfg.batch, cfg.max_len, np.int32)
+    sp = SpanBatch.from_lists(per_seq, ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=device, seed=7 + q_len)
+    q = draw_queries(cfg, q_len, device=device)
+    pos = (ctx - q_len).astype(np.int32) if isinstance(q_pos, str) else q_pos
+    if poison is not None:
+        poison(K, V)
+    code, _, _, tok = span.span_validate(sp.offsets, sp.starts, sp.ends, sp.ctx_lens)
+    assert code == 0
+    kw.setdefault("tokens_per_seq", tok)
+    out = span.span_decode_attn_multi(q, K, V, _dev(sp.offsets, device), _dev(sp.starts, device), _dev(sp.ends, device),
+                                      None if pos is None else _dev(pos, device), np.float32(cfg.scale),
+                                      max_tokens=int(tok.max()), **kw)
+    torch.cuda.synchronize()
+    ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos,
+                                 np.float32(cfg.scale), dtype=cfg.dtype)
+    return out.cpu().numpy().astype(np.float64), ref
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len", [3, 16, 17, 32, 33, 64])
+def test_tile_and_group_edges(dtype, D, q_len, gpu_device):
+    """Token counts around the groups of 16; rows per wave around the tiles of 16 and 32 rows, and a slice that takes
+    more than one position window of a wave (2048 rows a workgroup).  Many pairs: a workgroup serves all tokens."""
+    cfg = DecodeConfig(96, "matrix-edges", 10, 13, D, 2500, 2500, dtype, TOL)
+    L = cfg.max_len
+    spans = [1, 15, 16, 17, 61, 64, 65, 129, 700, 2347]
+    per_seq = [[(5, 5 + n - q_len // 2), (L - q_len, L - q_len + q_len // 2)] if n > q_len else [(L - n, L)] for n in spans]
+    got, ref = _run(cfg, per_seq, q_len, gpu_device)
+    err = float(np.abs(got - ref).max())
+    print(f"[parity] matrix edges {dtype} D={D} q_len={q_len}: {err:.3e}", flush=True)
+    assert np.isfinite(got).all() and err <= TOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len", [20, 48, 64])
+def test_query_blocks_share_a_slice(dtype, D, q_len, gpu_device):
+    """Few pairs: several workgroups per slice, each for its own tokens, with one ticket counter per pair; repeated on
+    one workspace (the counters must come back to zero), with and without the token counts."""
+    cfg = DecodeConfig(97, "matrix-blocks", 2, 3, D, 1500, 1500, dtype, TOL)
+    per_seq = [[(0, 700), (800, 1500)], [(3, 40), (100, 411), (1490, 1500)]]
+    for kw in (dict(), dict(tokens_per_seq=None)):
+        got, ref = _run(cfg, per_seq, q_len, gpu_device, **kw)
+        assert np.isfinite(got).all() and float(np.abs(got - ref).max()) <= TOL
+    ctx = np.full(2, 1500, np.int32)
+    sp = SpanBatch.from_lists(per_seq, ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=gpu_device)
+    q = draw_queries(cfg, q_len, device=gpu_device)
+    lists = [_dev(a, gpu_device) for a in (sp.offsets, sp.starts, sp.ends)]
+    call = span.prepare_span_decode_attn_multi(q, K, V, *lists, None, np.float32(cfg.scale), max_tokens=1400,
+                                               tokens_per_seq=sp.tokens_per_seq())
+    first = call().clone()
+    for _ in range(20):
+        call.out.fill_(float("nan"))
+        assert torch.equal(call(), first)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_non_finite_rows_reach_only_the_tokens_that_see_them(dtype, D, gpu_device):
+    """V rows of +-Inf and NaN that tokens from the 20th on see: earlier tokens equal the oracle, later ones get exactly
+    the oracle's infinities and NaNs (no 0 * Inf, and no Inf turned NaN by the terms of a 16-bit weight)."""
+    cfg = DecodeConfig(98, "matrix-inf", 2, 4, D, 600, 600, dtype, TOL)
+    q_pos = np.array([500, 520], np.int32)
+
+    def poison(K, V):
+        for b in range(2):
+            p = int(q_pos[b])
+            V[b, :, p + 20, ::2] = float("inf")
+            V[b, :, p + 25, 1::4] = float("-inf")
+            V[b, :, p + 25, 3::4] = float("nan")
+            V[b, :, p + 30, ::4] = float("-inf")      # meets +inf: NaN
+
+    got, ref = _run(cfg, [[(0, 100), (400, 600)], [(450, 600)]], 40, gpu_device, q_pos=q_pos, poison=poison)
+    assert np.isfinite(ref[:, :20]).all() and np.isinf(ref).any() and np.isnan(ref).any()
+    ok = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), ok) and float(np.abs(got[ok] - ref[ok]).max()) <= TOL
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
