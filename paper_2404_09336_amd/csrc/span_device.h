@@ -359,13 +359,30 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float* acc, int 
   m = mn;
 }
 
+// The kernel arguments are wanted in registers together: left to itself the compiler fetches some of them only after the
+// first have arrived, and each such trip costs some tenths of a microsecond at the head of every call (measured: batch 1 x
+// ~560 positions 7.9 -> 7.7 us, 4 workgroups x 80 positions 4.4 -> 4.2 us).
+// Returns a.heads, which everything else is computed from, tied to the other arguments of the start-up.  (Not volatile: a
+// statement with side effects in front of them would turn the scalar loads of the lists into vector loads.)
+__device__ __forceinline__ int heads_with_arguments(const LaunchArgs& a) {
+  int heads = a.heads;
+  asm("" : "+s"(heads) : "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.offsets), "s"(a.starts), "s"(a.ends), "s"(a.append_pos), "s"(a.q_pos),
+      "s"(a.max_len), "s"(a.num_intervals), "s"(a.q_len), "s"(a.even), "s"(a.interleave));
+  return heads;
+}
+
 // ---- the interval list of a sequence -----------------------------------------------------------------
 struct Intervals {
   int count, first;     // intervals first .. first + count - 1 of the lists (scalar)
   int st0, len0, incl0; // this lane's interval of the first 64: start, length, inclusive prefix sum of the lengths
 };
-struct IntervalChunk {  // one wave's LDS copy of up to 64 intervals: exclusive prefix sums and starts
-  int pref[64], start[64];
+constexpr int kChunkTotals = 256;  // chunks of 64 intervals whose position counts are kept (16384 intervals)
+struct IntervalTables {  // LDS of a workgroup
+  struct Chunk {         // one wave's copy of up to 64 intervals: exclusive prefix sums and starts
+    int pref[64], start[64];
+  } chunk[kWavesPerBlock];
+  int total[kChunkTotals];    // lists of more than 64 intervals: positions of each chunk
+  int wave_sum[kWavesPerBlock];
 };
 
 __device__ __forceinline__ Intervals interval_range(const LaunchArgs& a, int b) {
@@ -374,72 +391,123 @@ __device__ __forceinline__ Intervals interval_range(const LaunchArgs& a, int b) 
   return Intervals{__builtin_amdgcn_readfirstlane(hi - lo), __builtin_amdgcn_readfirstlane(lo), 0, 0, 0};
 }
 
-// Positions of the sequence's list (counting may stop once `stop` is reached); fills the first chunk's lane values.
-__device__ __forceinline__ int count_positions(const LaunchArgs& a, Intervals& iv, int lane, int stop) {
+__device__ __forceinline__ int interval_length(const LaunchArgs& a, int i) { return clampi(a.ends[i] - a.starts[i], 0, a.max_len); }
+
+// Positions of the sequence's list; fills the first chunk's lane values.  Called by all waves of the workgroup.
+// Up to 64 intervals every wave counts for itself and no barrier is met.  Longer lists (a mask in which every token
+// decides for itself has an interval per four positions) are a chain of dependent trips to memory if walked chunk by
+// chunk, and nothing hides them when few workgroups run: the waves share the chunks, four in flight each, and leave the
+// chunks' counts in LDS, where tabulate_positions finds a wave's first chunk.  2 sequences x 14000 positions in 3500
+// intervals, 16 heads x 128, bf16: 49.0 -> 30.8 us; one x 4000 in 1000, 32 heads, fp16: 17.1 -> 14.1 us; 32 x 900 (bound by
+// the rows): no change.  The long walk is kept out of the straight path: code that is jumped over costs a call of few
+// workgroups 0.2 - 0.4 us of instruction fetch.
+__device__ __forceinline__ int count_positions(const LaunchArgs& a, Intervals& iv, int wave, int lane, IntervalTables& tab) {
   if (lane < iv.count) {
     iv.st0 = a.starts[iv.first + lane];
     iv.len0 = clampi(a.ends[iv.first + lane] - iv.st0, 0, a.max_len);
   }
   iv.incl0 = wave_inclusive_scan(iv.len0, lane);
   int n = __builtin_amdgcn_readlane(iv.incl0, 63);
-  for (int c0 = 64; c0 < iv.count && n < stop; c0 += 64) {
-    int len = 0;
-    if (c0 + lane < iv.count)
-      len = clampi(a.ends[iv.first + c0 + lane] - a.starts[iv.first + c0 + lane], 0, a.max_len);
-    n += __builtin_amdgcn_readlane(wave_inclusive_scan(len, lane), 63);
+  if (__builtin_expect(iv.count > 64, 0)) {
+    const int chunks = (iv.count + 63) / 64;
+    if (wave == 0 && lane == 0) tab.total[0] = n;
+    int mine = 0;
+    constexpr int kInFlight = 4;
+    for (int c = 1 + wave; c < chunks; c += kWavesPerBlock * kInFlight) {
+      int len[kInFlight];
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k) {
+        const int i = (c + k * kWavesPerBlock) * 64 + lane;
+        len[k] = i < iv.count ? interval_length(a, iv.first + i) : 0;
+      }
+#pragma unroll
+      for (int k = 0; k < kInFlight; ++k) {
+        const int total = __builtin_amdgcn_readlane(wave_inclusive_scan(len[k], lane), 63);
+        mine += total;
+        if (lane == 0 && c + k * kWavesPerBlock < min(chunks, kChunkTotals)) tab.total[c + k * kWavesPerBlock] = total;
+      }
+    }
+    if (lane == 0) tab.wave_sum[wave] = mine;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) n += __builtin_amdgcn_readfirstlane(tab.wave_sum[w]);
   }
   return n;
 }
 
-// Cache positions of the wave's rows w0 .. w0 + wn - 1 into `pos`; row r is virtual token vrow(r) of the sequence.
-// kFirst: the first 64 intervals are still in registers from count_positions; later windows re-read them, so that
-// nothing stays live across the streaming loop.
-template <bool kFirst, class RowMap>
-__device__ __forceinline__ void tabulate_positions(const LaunchArgs& a, const Intervals& iv, const RowMap& vrow, int w0,
-                                                   int wn, int lane, IntervalChunk& chunk, int* pos) {
-  const int vbeg = vrow(w0), vend = vrow(w0 + wn - 1) + 1;
-  int carry = 0;
-  for (int c0 = 0; c0 < iv.count; c0 += 64) {
-    int st = 0, len = 0, incl = 0;
-    if (kFirst && c0 == 0) {
-      st = iv.st0;
-      len = iv.len0;
-      incl = iv.incl0;
-    } else {
-      if (c0 + lane < iv.count) {
-        st = a.starts[iv.first + c0 + lane];
-        len = clampi(a.ends[iv.first + c0 + lane] - st, 0, a.max_len);
-      }
-      incl = wave_inclusive_scan(len, lane);
-    }
-    const int chunk_total = __builtin_amdgcn_readlane(incl, 63);
-    if (carry + chunk_total > vbeg) {
-      // the chunk's exclusive prefixes and starts go to this wave's private LDS rows; the wave
-      // reads them back itself (LDS executes a wave's requests in order), so no block barrier
-      chunk.pref[lane] = carry + incl - len;
-      chunk.start[lane] = st;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const int n_here = min(64, iv.count - c0);
-      for (int r = lane; r < wn; r += 64) {
-        const int v = vrow(w0 + r);
-        if (v >= carry && v < carry + chunk_total) {
-          int idx = 0;  // last interval of the chunk whose exclusive prefix is <= v
+// The chunk's exclusive prefixes and starts go to the wave's own LDS rows and every lane finds the intervals of its rows:
+// virtual token v lies in the last interval whose exclusive prefix is <= v (lanes past the list's end hold the chunk's end
+// as prefix and are never chosen).  The wave reads back what it wrote itself (LDS executes a wave's requests in order), so
+// there is no block barrier.
+template <class RowMap>
+__device__ __forceinline__ void place_chunk(const RowMap& vrow, int w0, int wn, int lane, int n_here, int carry, int st, int len,
+                                            int incl, int max_len, IntervalTables::Chunk& chunk, int* pos) {
+  const int chunk_total = __builtin_amdgcn_readlane(incl, 63);
+  chunk.pref[lane] = carry + incl - len;
+  chunk.start[lane] = st;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int r = lane; r < wn; r += 64) {
+    const int v = vrow(w0 + r);
+    if (v >= carry && v < carry + chunk_total) {
+      int idx = 0;
 #pragma unroll
-          for (int step = 32; step > 0; step >>= 1) {
-            const int j = idx + step;
-            if (j < n_here && chunk.pref[j] <= v) idx = j;
-          }
-          const int p = chunk.start[idx] + (v - chunk.pref[idx]);
-          pos[r] = clampi(p, 0, a.max_len - 1);
-        }
+      for (int step = 32; step > 0; step >>= 1) {
+        const int j = idx + step;
+        if (j < n_here && chunk.pref[j] <= v) idx = j;
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const int p = chunk.start[idx] + (v - chunk.pref[idx]);
+      pos[r] = clampi(p, 0, max_len - 1);
     }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Cache positions of the wave's first rows 0 .. wn - 1 into `pos` for a list of up to 64 intervals, which are still in
+// registers from count_positions; row r is virtual token vrow(r) of the sequence.
+template <class RowMap>
+__device__ __forceinline__ void tabulate_short(const LaunchArgs& a, const Intervals& iv, const RowMap& vrow, int wn, int wave,
+                                               int lane, IntervalTables& tab, int* pos) {
+  place_chunk(vrow, 0, wn, lane, iv.count, 0, iv.st0, iv.len0, iv.incl0, a.max_len, tab.chunk[wave], pos);
+}
+
+// The same for rows w0 .. w0 + wn - 1 and any list: re-reads the intervals, so that nothing stays live across the
+// streaming loop.
+template <class RowMap>
+__device__ __forceinline__ void tabulate_positions(const LaunchArgs& a, const Intervals& iv, const RowMap& vrow, int w0,
+                                                   int wn, int wave, int lane, IntervalTables& tab, int* pos) {
+  const int vbeg = vrow(w0), vend = vrow(w0 + wn - 1) + 1;
+  int c0 = 0, carry = 0;  // first interval of the chunk the walk stands in, positions before it
+  if (iv.count > 64) {    // skip the chunks before the window
+    const int known = min((iv.count + 63) / 64, kChunkTotals);
+    for (int t0 = 0; t0 < known; t0 += 64) {
+      const int incl = wave_inclusive_scan(t0 + lane < known ? tab.total[t0 + lane] : 0, lane);
+      const int skip = __popcll(__builtin_amdgcn_ballot_w64(t0 + lane < known && carry + incl <= vbeg));
+      if (skip > 0) carry += __builtin_amdgcn_readlane(incl, skip - 1);
+      c0 = (t0 + skip) * 64;
+      if (skip < 64) break;
+    }
+  }
+  int st = 0, len = 0;
+  auto load_chunk = [&](int c) {
+    st = len = 0;
+    if (c + lane < iv.count) {
+      st = a.starts[iv.first + c + lane];
+      len = clampi(a.ends[iv.first + c + lane] - st, 0, a.max_len);
+    }
+  };
+  load_chunk(c0);
+  while (c0 < iv.count) {
+    const int incl = wave_inclusive_scan(len, lane), chunk_total = __builtin_amdgcn_readlane(incl, 63);
+    const int here = c0, here_carry = carry, here_st = st, here_len = len;
+    c0 += 64;
     carry += chunk_total;
+    if (carry < vend) load_chunk(c0);  // the next chunk is on its way while this one is searched
+    if (carry > vbeg)
+      place_chunk(vrow, w0, wn, lane, min(64, iv.count - here), here_carry, here_st, here_len, incl, a.max_len, tab.chunk[wave], pos);
     if (carry >= vend) break;
   }
 }

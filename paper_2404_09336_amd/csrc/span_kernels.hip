@@ -57,6 +57,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   // answer is the same for all heads of a (batch, slice), so full and empty slices spread evenly
   SPAN_TRACE_DECL;
   SPAN_STAMP_AFTER(0, "s", 0);
+  const int heads = heads_with_arguments(a);
   const int h = blockIdx.x;
   int b, split, nsl, y0;  // sequence, slice within it, slices of the sequence, first slice row of the sequence
   if constexpr (Args::kHasTable) {
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // in a scalar register: what derives from it stays scalar
   const int grp = lane / LPR, lir = lane % LPR;
-  const size_t bh = (size_t)b * a.heads + h;
+  const size_t bh = (size_t)b * heads + h;
 
   // Append variant.  Every lane fetches its piece of the new token's K / V row right away (the latency
   // hides behind the metadata chain).  The row is written into the cache by the first slice's workgroup
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   }
 
   __shared__ int s_pos[kWavesPerBlock][kWin];
-  __shared__ IntervalChunk s_chunk[kWavesPerBlock];
+  __shared__ IntervalTables s_tab;
   __shared__ __attribute__((aligned(16))) float s_acc[kWavesPerBlock][NQ][D];
   __shared__ u32x4 s_new[NQ == 1 ? kWavesPerBlock : 1][2][LPR];  // append variant: the new K / V row, parked until its owner needs it
   __shared__ float s_ml[kWavesPerBlock][NQ][2];
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   // Query token j of this launch is row (b, q_first + j, h) of q and out; a launch whose last tokens do
   // not exist (q_len not a multiple of NQ) computes them from the last real one and never writes them.
   const int nq_here = NQ == 1 ? 1 : min(NQ, a.q_len - a.q_first);  // (the one-token kernel serves one token, whatever q_len says)
-  auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(a.q_first + min(j, nq_here - 1))) * a.heads + h; };
+  auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(a.q_first + min(j, nq_here - 1))) * heads + h; };
   // q pieces of this lane.  Scores carry the factor scale*log2(e), so that exp() becomes exp2(): fp32 q is
   // multiplied by it here, 16-bit q stays as stored and the finished dot product is multiplied instead.
   typename Elt::Q qv[NQ];
@@ -124,8 +125,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     lim[j] = a.q_pos ? min(a.q_pos[b], kMaxLen) + a.q_first + j : 0x7fffffff;
 
   // ---- step 1: how many attended positions does the sequence have, which are mine ----------------
-  // with fixed-size slices the count may stop at the slice's end; even slices need the sequence's total
-  const int scan_stop = a.even ? 0x7fffffff : (split + 1) * a.slice_tokens;
   int n_total;
   Intervals intervals = {0, 0, 0, 0, 0};
   if constexpr (Args::kHasRuns) {
@@ -135,7 +134,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   } else {
     intervals = interval_range(a, b);
     SPAN_STAMP_AFTER(10, "s", intervals.count);
-    n_total = count_positions(a, intervals, lane, scan_stop);
+    n_total = count_positions(a, intervals, wave, lane, s_tab);
   }
   n_total = n_total < a.max_tokens ? n_total : a.max_tokens;
   int slice_begin, cnt;
@@ -188,20 +187,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   //    streams (and those of the neighbouring heads, a power-of-two slab stride away) pile onto the same
   //    channels: measured 6.1 -> 6.8 TB/s on batch 64 x 1024 cached tokens when dealing round-robin,
   //    while slices of 100-170 rows are 2-4 % faster with quarters.
-  int nrows, q_first = 0;
+  int nrows, vbase, vgap;  // row r is virtual token vbase + r + (r / RPL) * vgap: one formula, no branch where rows are named
   if (a.interleave) {
     const int units_all = (cnt + RPL - 1) / RPL;
     const int units = units_all > wave ? (units_all - wave + kWavesPerBlock - 1) / kWavesPerBlock : 0;
     const bool own_last = units > 0 && (wave + (units - 1) * kWavesPerBlock) == units_all - 1;
     nrows = units * RPL - (own_last ? units_all * RPL - cnt : 0);
+    vbase = slice_begin + wave * RPL;
+    vgap = (kWavesPerBlock - 1) * RPL;
   } else {
     const int rpw = (((cnt + kWavesPerBlock - 1) / kWavesPerBlock) + RPL - 1) / RPL * RPL;
-    q_first = min(wave * rpw, cnt);
-    nrows = min(q_first + rpw, cnt) - q_first;
+    const int first = min(wave * rpw, cnt);
+    nrows = min(first + rpw, cnt) - first;
+    vbase = slice_begin + first;
+    vgap = 0;
   }
-  auto vrow = [&](int r) {
-    return slice_begin + (a.interleave ? ((r / RPL) * kWavesPerBlock + wave) * RPL + (r % RPL) : q_first + r);
-  };
+  auto vrow = [&](int r) { return vbase + r + (r / RPL) * vgap; };
 
   // ---- steps 2 and 3, one window of kWin rows at a time -----------------------------------------
   const uint32_t slab_bytes = (uint32_t)a.max_len * ROWB;
@@ -223,10 +224,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     s_new[wave][1][lane] = vn_raw;
   }
 
-  // ---- step 2: virtual token -> KV position for a window's rows (span path only) -----------------
-  auto tabulate = [&](auto first_tag, int w0, int wn) {
-    tabulate_positions<decltype(first_tag)::value>(a, intervals, vrow, w0, wn, lane, s_chunk[wave], s_pos[wave]);
-  };
+  // ---- step 2: virtual token -> KV position (span path only) -----------------------------------------
   if constexpr (Args::kHasRuns) {
     // Run mode: the slice is a short list of runs [start, start + len) in the kernel arguments.  Row number v of
     // the slice lies in the last run whose rows-before count is <= v; a wave has at most kWin rows (the host
@@ -265,14 +263,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   } else {
-    if (!kDense && nrows > 0) tabulate(std::true_type{}, 0, min(kWin, nrows));
+    if (!kDense && nrows > 0 && __builtin_expect(intervals.count <= 64, 1)) tabulate_short(a, intervals, vrow, min(kWin, nrows), wave, lane, s_tab, s_pos[wave]);
   }
   SPAN_STAMP_AFTER(2, "v", lane_off);
 
   for (int w0 = 0; w0 < nrows; w0 += kWin) {
   const int wn = min(kWin, nrows - w0);  // rows w0 .. w0+wn-1 of mine
   if constexpr (!Args::kHasRuns) {
-    if (!kDense && w0 > 0) tabulate(std::false_type{}, w0, wn);
+    if (!kDense && __builtin_expect(w0 > 0 || intervals.count > 64, 0)) tabulate_positions(a, intervals, vrow, w0, wn, wave, lane, s_tab, s_pos[wave]);
   }
 
   if (NQ == 1 && a.append_pos) {  // is the appended row one of the window's rows?  Then row group 0 takes it in now.
@@ -476,7 +474,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   // only starts after its own ticket came back.  A device-scope fence would write back and
   // invalidate the whole L2 of the XCD for every workgroup, which costs far more than the merge.
   // state of slice s of (b, h) lives in slot (y0 + s) * heads + h
-  const size_t H = (size_t)a.heads;
+  const size_t H = (size_t)heads;
   const size_t my_slot = (size_t)(y0 + split) * H + h;
   if (owns) {
 #pragma unroll

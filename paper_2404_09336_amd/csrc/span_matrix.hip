@@ -96,6 +96,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 
   SPAN_TRACE_DECL;
   SPAN_STAMP_AFTER(0, "s", 0);
+  const int heads = heads_with_arguments(a);
   const int h = blockIdx.x;
   int b, split, nsl, y0, qb;
   if constexpr (Args::kHasTable) {
@@ -119,11 +120,11 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qi = lane & 15, c4 = lane >> 4;
-  const size_t bh = (size_t)b * a.heads + h;
+  const size_t bh = (size_t)b * heads + h;
 
   struct StreamTables {
     int pos[kWavesPerBlock][kMWin];
-    IntervalChunk chunk[kWavesPerBlock];
+    IntervalTables tab;
     unsigned char q[NQ * kQRow] __attribute__((aligned(16)));
   };
   struct WaveStates {  // of one group of 16 tokens at a time
@@ -143,7 +144,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   // computed from the last real one and never written.
   const int q0 = a.q_first + qb * NQ;
   const int nq_here = min(NQ, a.q_first + a.tokens - q0);
-  auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(q0 + min(j, nq_here - 1))) * a.heads + h; };
+  auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(q0 + min(j, nq_here - 1))) * heads + h; };
 
   // q goes to LDS (the same for the four waves).  It is fetched here, as are the append form's new rows for the cache
   // (written by the first slice's workgroup, whatever the span holds); both have arrived when the rows' positions are known.
@@ -172,10 +173,9 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   const int last_any = limited ? lim0 + nq_here - 1 : 0x7fffffff;
   const int new0 = append ? min(a.append_pos[b], kMaxLen) : 0x7fffffff;
 
-  const int scan_stop = a.even ? 0x7fffffff : (split + 1) * a.slice_tokens;
   Intervals intervals = interval_range(a, b);
   SPAN_STAMP_AFTER(10, "s", intervals.count);
-  int n_total = count_positions(a, intervals, lane, scan_stop);
+  int n_total = count_positions(a, intervals, wave, lane, s_u.st.tab);
   n_total = n_total < a.max_tokens ? n_total : a.max_tokens;
   const int T = a.even ? (n_total + nsl - 1) / nsl : a.slice_tokens;
   const int slice_begin = split * T;
@@ -184,21 +184,26 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 
   // How the slice's rows are dealt to the waves (see decode_kernel): contiguous quarters of small slices, tiles
   // round-robin for large ones.
-  int nrows, r_first = 0;
+  int nrows, vbase, vgap;
   if (a.interleave) {
     const int units_all = (cnt + TR - 1) / TR;
     const int units = units_all > wave ? (units_all - wave + kWavesPerBlock - 1) / kWavesPerBlock : 0;
     const bool own_last = units > 0 && (wave + (units - 1) * kWavesPerBlock) == units_all - 1;
     nrows = units * TR - (own_last ? units_all * TR - cnt : 0);
+    vbase = slice_begin + wave * TR;
+    vgap = (kWavesPerBlock - 1) * TR;
   } else {
     const int rpw = (((cnt + kWavesPerBlock - 1) / kWavesPerBlock) + 3) / 4 * 4;
-    r_first = min(wave * rpw, cnt);
-    nrows = min(r_first + rpw, cnt) - r_first;
+    const int first = min(wave * rpw, cnt);
+    nrows = min(first + rpw, cnt) - first;
+    vbase = slice_begin + first;
+    vgap = 0;
   }
-  auto vrow = [&](int r) {
-    return slice_begin + (a.interleave ? ((r / TR) * kWavesPerBlock + wave) * TR + (r % TR) : r_first + r);
-  };
-  if (nrows > 0) tabulate_positions<true>(a, intervals, vrow, 0, min(kMWin, nrows), lane, s_u.st.chunk[wave], s_pos[wave]);
+  auto vrow = [&](int r) { return vbase + r + (r / TR) * vgap; };
+  if (nrows > 0) {
+    if (__builtin_expect(intervals.count <= 64, 1)) tabulate_short(a, intervals, vrow, min(kMWin, nrows), wave, lane, s_u.st.tab, s_pos[wave]);
+    else tabulate_positions(a, intervals, vrow, 0, min(kMWin, nrows), wave, lane, s_u.st.tab, s_pos[wave]);
+  }
   SPAN_STAMP_AFTER(2, "s", cnt);
 
   const uint32_t slab_bytes = (uint32_t)a.max_len * ROWB;
@@ -206,7 +211,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   const __amdgpu_buffer_rsrc_t vslab = slab_resource((const char*)a.v + bh * (size_t)slab_bytes, slab_bytes);
   // new row i of the call (only addressed for positions that the append form brings)
   auto new_row = [&](const void* rows, int i) {
-    return (const char*)rows + (((size_t)b * a.q_len + (size_t)i) * a.heads + h) * ROWB;
+    return (const char*)rows + (((size_t)b * a.q_len + (size_t)i) * heads + h) * ROWB;
   };
 
   // State of query 16 g + qi in lane (qi, c4).  ref: reference exponent of the weights, their running maximum (the same
@@ -454,10 +459,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   auto stream_by_row = [&]() {
     for (int w0 = 0; w0 < nrows; w0 += kMWin) {
       const int wn = min(kMWin, nrows - w0);
-      tabulate_positions<false>(a, intervals, vrow, w0, wn, lane, s_u.st.chunk[wave], s_pos[wave]);
+      tabulate_positions(a, intervals, vrow, w0, wn, wave, lane, s_u.st.tab, s_pos[wave]);
 #pragma unroll 1
       for (int i = 0; i < wn; ++i) {
-        const int p = __builtin_amdgcn_readfirstlane(s_pos[wave][i]);
+        const int p = clampi(__builtin_amdgcn_readfirstlane(s_pos[wave][i]), 0, a.max_len - 1);  // (plain pointers here)
         if (p > last_any) continue;
         const size_t cached = (bh * (size_t)a.max_len + (size_t)p) * ROWB;
         const char* krow = p >= new0 ? new_row(a.k_new, p - new0) : (const char*)a.k + cached;
@@ -543,8 +548,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   clear_state();
   for (int w0 = 0; w0 < nrows; w0 += kMWin) {
     const int wn = min(kMWin, nrows - w0);
-    if (w0 > 0) {
-      tabulate_positions<false>(a, intervals, vrow, w0, wn, lane, s_u.st.chunk[wave], s_pos[wave]);
+    if (__builtin_expect(w0 > 0, 0)) {
+      tabulate_positions(a, intervals, vrow, w0, wn, wave, lane, s_u.st.tab, s_pos[wave]);
       cur = load_k(0, wn);
       load_v(0, cur);
     }
@@ -598,7 +603,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   static_assert(16 * kQuadsPerToken % kThreads == 0, "whole quads per thread");
   const bool direct = nsl == 1;
   const size_t slot_floats = (size_t)a.slot_tokens * D;
-  const size_t slot0 = (size_t)y0 * a.heads + h, my_slot = slot0 + (size_t)split * a.heads;
+  const size_t slot0 = (size_t)y0 * heads + h, my_slot = slot0 + (size_t)split * heads;
   const uint32_t q_in_slot = (uint32_t)(q0 - a.q_first);
   auto acc_slot = [&](size_t slot) { return slab_resource(a.part_acc + slot * slot_floats, (uint32_t)(slot_floats * 4)); };
 #pragma unroll
@@ -685,7 +690,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       f32x4 os[kBatch];
 #pragma unroll
       for (int k = 0; k < kBatch; ++k) {
-        const size_t slot = slot0 + (size_t)min(s0 + k, nsl - 1) * a.heads;  // (past the end: a slot that exists, unused)
+        const size_t slot = slot0 + (size_t)min(s0 + k, nsl - 1) * heads;  // (past the end: a slot that exists, unused)
         const float* ml = a.part_ml + (slot * (size_t)a.slot_tokens + q_in_slot + (size_t)token) * 2;
         m[k] = observe(ml);
         l[k] = observe(ml + 1);
