@@ -579,26 +579,31 @@ __global__ __launch_bounds__(256) void zero_words_kernel(uint32_t* p, size_t n) 
   if (i < n) p[i] = 0u;
 }
 
-// One thread per sequence: the span gains the positions after the ones just appended (see span_advance).
-__global__ __launch_bounds__(256) void advance_kernel(int batch, int max_len, int num_intervals, int count,
-                                                      const int32_t* offsets, const int32_t* starts, int32_t* ends,
-                                                      int32_t* append_pos, int32_t* ctx_lens) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= batch) return;
+// One wave per sequence: the span gains the positions after the ones just appended (see span_advance).  Bound by its chain
+// of trips to memory (arguments, list range, list): the lanes read 64 intervals at a time, where one thread per sequence
+// walked them one after the other (a group of 8 steps: 8 sequences of 6 - 14 intervals 183.9 -> 175.6 us, 4 of ~700 intervals 766 -> 151 us).
+__global__ __launch_bounds__(64) void advance_kernel(int max_len, int num_intervals, int count, const int32_t* offsets,
+                                                     const int32_t* starts, int32_t* ends, int32_t* append_pos, int32_t* ctx_lens) {
+  const int b = blockIdx.x, lane = threadIdx.x;
   const int p = append_pos[b];
+  const int lo = clampi(offsets[b], 0, num_intervals), hi = clampi(offsets[b + 1], lo, num_intervals);
+  const int ctx = ctx_lens ? ctx_lens[b] : 0;
   if (p < 0 || (long long)p + 2 * (long long)count > (long long)max_len) return;
   const int next = p + count;  // first position of the next step's tokens; they take next .. next + count - 1
-  const int lo = clampi(offsets[b], 0, num_intervals), hi = clampi(offsets[b + 1], lo, num_intervals);
-  int grow = -1;        // interval that ends right after the appended tokens
+  int grow = -1;        // interval that ends right after the appended tokens (the last one that does)
   bool taken = false;   // some of the next positions are already inside an interval
-  for (int i = lo; i < hi; ++i) {
-    const int st = starts[i], en = ends[i];
-    if (st < en && en == next) grow = i;
-    if (st < en && st < next + count && next < en) taken = true;
+  for (int i0 = lo; i0 < hi; i0 += 64) {
+    const bool here = i0 + lane < hi;
+    const int st = here ? starts[i0 + lane] : 0, en = here ? ends[i0 + lane] : 0;
+    const uint64_t closes = __builtin_amdgcn_ballot_w64(st < en && en == next);
+    if (closes != 0) grow = i0 + 63 - __builtin_clzll(closes);
+    taken = taken || __builtin_amdgcn_ballot_w64(st < en && st < next + count && next < en) != 0;
   }
-  if (grow >= 0 && !taken) ends[grow] = next + count;
-  append_pos[b] = next;
-  if (ctx_lens) ctx_lens[b] += count;
+  if (lane == 0) {
+    if (grow >= 0 && !taken) ends[grow] = next + count;
+    append_pos[b] = next;
+    if (ctx_lens) ctx_lens[b] = ctx + count;
+  }
 }
 
 thread_local int g_last_hip_error = 0;
@@ -873,9 +878,9 @@ extern "C" int span_advance(const span_attn_desc_t* desc, const int32_t* span_of
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
   if (!span_offsets || !append_pos || (desc->num_intervals > 0 && (!span_starts || !span_ends))) return SPAN_ERR_NULL;
-  hipLaunchKernelGGL(spanattn::advance_kernel, dim3((unsigned)((desc->batch + 255) / 256)), dim3(256), 0,
-                     (hipStream_t)desc->stream, desc->batch, desc->max_len, desc->num_intervals,
-                     spanattn::query_tokens(desc), span_offsets, span_starts, span_ends, append_pos, ctx_lens);
+  hipLaunchKernelGGL(spanattn::advance_kernel, dim3((unsigned)desc->batch), dim3(64), 0, (hipStream_t)desc->stream,
+                     desc->max_len, desc->num_intervals, spanattn::query_tokens(desc), span_offsets, span_starts, span_ends,
+                     append_pos, ctx_lens);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) {
     spanattn::g_last_hip_error = (int)err;
