@@ -150,7 +150,8 @@ int span_decode_attn_static(const span_attn_desc_t* desc, const void* q, const v
  * through the sequence's one span (a span is chosen once per group of tokens, Sec. 3.2, so the tokens
  * of a group share it).  Among themselves the tokens keep the causal mask of Sec. 2.2: query token j
  * of sequence b attends the span positions p <= q_pos[b] + j and no later one; eqs. (4)-(6) apply to
- * each query row.  From three tokens on the call runs on the matrix cores: one launch, in which a workgroup
+ * each query row.  From three tokens on (two, for 16-bit rows and few (batch, head) pairs) the call runs on
+ * the matrix cores: one launch, in which a workgroup
  * serves up to 64 tokens with one pass over its share of the span's rows (calls with num_splits > 0 whose
  * slices the workspace holds fewer token states for take one launch per queries_per_pass tokens).  Weights meet
  * fp32 rows as they are, fp16 rows as two fp16 terms (22 mantissa bits) and bf16 rows as three bf16 terms (24);

@@ -319,7 +319,7 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
 // Few-query calls on the matrix cores: all tokens of the call in one launch, a workgroup serving up to 64 of them with
 // one pass over its rows.
 //
-// From three tokens on, for every type and head_dim.  Measured against the passes it replaces (four tokens on the vector
+// From three tokens on for every type and head_dim, two tokens see below.  Measured against the passes it replaces (four tokens on the vector
 // units, sixteen on the matrix cores, one launch per pass): batch 16 x ~380 positions, 16 heads x 64, fp16, 9 tokens
 // 63.9 -> 14.7 us; batch 8 x ~600, 32 heads x 128, fp32, 8 tokens 83.6 -> 39.7 us; 3 tokens, batch 16 x ~370, fp32 49.9 ->
 // 45.3 us; batch 16 x ~700, bf16, 32 tokens 96.4 -> 50.1 us; batch 32 x 1000, bf16, 64 tokens 313 -> 130 us.
@@ -335,13 +335,24 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
 // L2, each for its own tokens: 12 heads x 8, 60 tokens 36.1 us with 64 tokens a workgroup, 29.2 us with 32; 32 pairs x 1500
 // fp32 positions, 30 tokens 38.9 -> 31.1 us; 256 pairs, 24 tokens 22.2 us in two workgroups, 18.9 us in one.
 constexpr int32_t kMatrixFromTokens = 3;
+// Two tokens: 16-bit rows and few (batch, head) pairs, where the start-up and the hand-over count and the matrix kernel's
+// are shorter; many pairs stream better through the vector kernel's 24 waves per CU.  us, vector -> matrix: 64 pairs of 128
+// 10.4 -> 9.4 (32 pairs), 20.3 -> 18.0 (192), 23.6 -> 22.4 (256), 28.4 -> 29.2 (384), 33.8 -> 35.7 (512); of 64 20.9 -> 16.3
+// (288), 23.8 -> 23.4 (512), 33.7 -> 36.8 (1536); fp32 rows 25.9 -> 26.8 (128), 49.9 -> 54.7 (1024).
+constexpr int64_t kMatrixTwoTokenColumns = 32768;  // pairs x head_dim
 constexpr int64_t kMatrixWorkgroups = 512;
 constexpr int64_t kMatrixPairs = 128;
 constexpr int32_t kMatrixMaxFieldSlices = 255;  // slices of a pair when several query blocks share its ticket counter
 
+bool runs_on_matrix_cores(const span_attn_desc_t* d) {
+  const int32_t n = query_tokens(d);
+  if (n >= kMatrixFromTokens) return true;
+  return n == 2 && d->dtype != SPAN_F32 && (int64_t)d->batch * d->heads * d->head_dim <= kMatrixTwoTokenColumns;
+}
+
 bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table) {
   int32_t n = query_tokens(d);
-  if (n < kMatrixFromTokens) return false;
+  if (!runs_on_matrix_cores(d)) return false;
   const bool sliced = p.num_splits > 1;
   const int64_t states = sliced ? (int64_t)p.total_slices * p.queries_per_pass : 0;  // the workspace's, per head
   m->tokens = n;

@@ -85,6 +85,7 @@ struct MatrixPlan {
 };
 // Most groups a workgroup serves: the state of 64 tokens of fp32 rows of 128 does not fit the registers next to a tile.
 constexpr int kMatrixMaxGroups(int elt_bytes, int head_dim) { return elt_bytes == 4 && head_dim == 128 ? 2 : 4; }
+bool runs_on_matrix_cores(const span_attn_desc_t* d);
 // False if the call does not run on the matrix cores.  `p` is the call's partition, `table` has kMaxPlanSlices entries.
 bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table);
 

@@ -28,7 +28,7 @@
 //     so the whole call is a single launch.
 //   * the append entry points also write the new token's K / V row into the cache; within that launch
 //     the row is taken from the arguments, never read back from the cache.
-//   * two query tokens of a sequence are served with one pass over the span's rows (template argument NQ):
+//   * two query tokens of a sequence are (for many pairs or fp32 rows) served with one pass over the span's rows (template argument NQ):
 //     per-token softmax states in registers, each token under its own causal limit.  Three and more run on the
 //     matrix cores (span_matrix.hip).
 #include <mutex>
@@ -719,7 +719,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
     own.host_span_offsets = own.host_span_starts = own.host_span_ends = nullptr;
     d = &own;
   }
-  const Partition p = plan_partition(d, a.table, kDense || query_tokens(d) > 2 ? nullptr : &runs);  // (two tokens at most use them)
+  const Partition p = plan_partition(d, a.table, kDense || runs_on_matrix_cores(d) ? nullptr : &runs);
   const GridMode mode = p.runs ? GridMode::kRuns : (p.exact ? GridMode::kTable : GridMode::kPlain);
   const size_t need = workspace_bytes(d, p);
   if (need > 0 && (!d->workspace || ((uintptr_t)d->workspace & 255u) || d->workspace_bytes < need))

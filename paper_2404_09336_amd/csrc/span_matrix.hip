@@ -15,7 +15,7 @@
 //     the ones before left.  fp32 rows use the fp32 MFMA throughout.
 // Bound by memory except for few pairs, where the start-up chain (1 us of list metadata, 2 us to the first rows) and the
 // merge count.  Its rounding is that of the vector kernels or less (measured against 64 bits, relative 2-norm: fp32 1.6e-7
-// for 1.8e-7, 16-bit rows of 64 1.5e-7 for 1.6e-7, fp16 rows of 128 1.8e-7, bf16 2.1e-7 for the 1.8e-6 of two-term weights).
+// for 1.8e-7, 16-bit rows of 64 1.45e-7 for 1.6e-7, 16-bit rows of 128 1.65e-7 for 1.75e-7).
 // K and V are streamed through registers: the next tile's K loads go out as soon as the scores of this one are taken,
 // its V loads as soon as the outputs are, so a wave always has loads in flight.
 #include "span_device.h"
@@ -162,7 +162,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       v_piece[i] = *reinterpret_cast<const u32x4*>((const char*)a.v_new + src);
     }
   }
-  const float post = Elt::kPostScale ? a.scale_log2e : 1.f;
+  // A weight is exp2(fma(score, post, -reference)): the scaled score is never rounded by itself.  post is positive (a hidden
+  // row's -Inf stays -Inf); a negative scale goes into the sign of q.
+  const float post = a.scale_log2e == 0.f ? 1e-37f : fabsf(a.scale_log2e);
+  const uint32_t q_sign = a.scale_log2e < 0.f ? (Elt::kBytes == 2 ? 0x80008000u : 0x80000000u) : 0u;
 
   // Causal limit: query token j sees no position after lim0 + j.  In the append form the call's tokens sit at
   // positions new0 .. new0 + q_len - 1; those rows come from k_new / v_new, never from the cache.
@@ -295,7 +298,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   };
 
   // Scores of the tile in kr: sc[g][s][t] = query 16 g + qi against row 16 s + 4 c4 + t.  A score is summed in pieces (8
-  // products of fp32 values, or 32 of 16-bit values of head_dim 64, from zero; the pieces pairwise), not in one long
+  // products of fp32 values or 32 of 16-bit values, each from zero), not in one long
   // accumulator chain: its rounding goes straight into the weight.
   auto take_scores = [&](f32x4 (&sc)[G][S]) {
     constexpr f32x4 kZero = {0.f, 0.f, 0.f, 0.f};
@@ -310,8 +313,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
           const u32x4 qm = *reinterpret_cast<const u32x4*>(qrow_lds + 64 * mm);
 #pragma unroll
           for (int s = 0; s < S; ++s) {
-            if constexpr (D == 64) sc[g][s] += Elt::mfma(kr[s][mm], qm, kZero);
-            else sc[g][s] = Elt::mfma(kr[s][mm], qm, sc[g][s]);
+            if constexpr (D == 64 || G < 4) sc[g][s] += Elt::mfma(kr[s][mm], qm, kZero);
+            else sc[g][s] = Elt::mfma(kr[s][mm], qm, sc[g][s]);  // (no registers for it)
           }
         }
       } else {
@@ -346,16 +349,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
           const bool ok = (tr.ok[s] >> (4 * c4 + t)) & 1u;
           const int beyond = (ok ? p4[t] : 0x7fffffff) - lim0;  // (no limit: lim0 is the largest int)
 #pragma unroll
-          for (int g = 0; g < G; ++g) sc[g][s][t] = ok && beyond <= 16 * g + qi ? sc[g][s][t] * post : -INFINITY;
-        }
-      }
-    } else if (Elt::kPostScale) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-#pragma unroll
-        for (int s = 0; s < S; ++s) {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) sc[g][s][t] *= post;
+          for (int g = 0; g < G; ++g) sc[g][s][t] = ok && beyond <= 16 * g + qi ? sc[g][s][t] : -INFINITY;
         }
       }
     }
@@ -367,6 +361,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #pragma unroll
         for (int t = 0; t < 4; ++t) mx = fmaxf(mx, sc[g][s][t]);
       }
+      mx *= post;
       if (__builtin_amdgcn_ballot_w64(mx > ref[g]) != 0) {  // (the maximum settles after the first tiles)
         mx = exchange_max(mx);
         const float ref_new = fmaxf(ref[g], mx);
@@ -381,7 +376,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #pragma unroll
       for (int s = 0; s < S; ++s) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) sc[g][s][t] = __builtin_amdgcn_exp2f(sc[g][s][t] - ref_safe);
+        for (int t = 0; t < 4; ++t) sc[g][s][t] = __builtin_amdgcn_exp2f(fmaf(sc[g][s][t], post, -ref_safe));
         lsum[g] += (sc[g][s][0] + sc[g][s][1]) + (sc[g][s][2] + sc[g][s][3]);
       }
     }
@@ -479,11 +474,11 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
           }
           d += __shfl_xor(d, 16, 64);
           d += __shfl_xor(d, 32, 64);
-          d = p - lim0 <= 16 * g + qi ? d * post : -INFINITY;
-          const float ref_new = fmaxf(ref[g], d), ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
+          d = p - lim0 <= 16 * g + qi ? d : -INFINITY;
+          const float ref_new = fmaxf(ref[g], d * post), ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
           const float alpha = ref[g] == ref_new ? 1.f : __builtin_amdgcn_exp2f(ref[g] - ref_safe);
           ref[g] = ref_new;
-          w[g] = __builtin_amdgcn_exp2f(d - ref_safe);
+          w[g] = __builtin_amdgcn_exp2f(fmaf(d, post, -ref_safe));
           lsum[g] = lsum[g] * alpha + (c4 == 0 ? w[g] : 0.f);
           w[g] *= Elt::kWeightScale;
 #pragma unroll
@@ -522,13 +517,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     const int idx = tid + i * kThreads, j = idx / kPieces;
     const uint32_t piece = 16u * (uint32_t)(idx % kPieces);
     if (NQ * kPieces % kThreads != 0 && idx >= NQ * kPieces) continue;
-    if constexpr (!Elt::kPostScale) {  // fp32: the score scale goes into q
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t w = q_piece[i][k];
-        q_piece[i][k] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, w) * a.scale_log2e);
-      }
-    }
+    for (int k = 0; k < 4; ++k) q_piece[i][k] ^= q_sign;
     *reinterpret_cast<u32x4*>(&s_q[j * kQRow + piece]) = q_piece[i];
     if (writes_new && j < nq_here) {
       const int p = new0 + q0 + j;

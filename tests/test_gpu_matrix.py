@@ -100,3 +100,20 @@ def test_non_finite_rows_reach_only_the_tokens_that_see_them(dtype, D, gpu_devic
     ok = np.isfinite(ref)
     assert np.array_equal(np.isfinite(got), ok) and float(np.abs(got[ok] - ref[ok]).max()) <= TOL
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("scale", [-0.2, 0.0])
+def test_negative_and_zero_scales(dtype, scale, gpu_device):
+    """The scale's sign goes into q and its size into the weight's exponent: both ends of that, with hidden rows."""
+    cfg = DecodeConfig(99, "matrix-scale", 3, 4, 128, 400, 400, dtype, TOL)
+    ctx = np.full(3, 400, np.int32)
+    sp = SpanBatch.from_lists([[(0, 50), (300, 400)], [(390, 400)], [(7, 200)]], ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=gpu_device)
+    q = draw_queries(cfg, 6, device=gpu_device)
+    pos = np.array([394, 393, 150], np.int32)
+    got = span.span_decode_attn_multi(q, K, V, *(_dev(a, gpu_device) for a in (sp.offsets, sp.starts, sp.ends, pos)), np.float32(scale),
+                                      max_tokens=193, tokens_per_seq=sp.tokens_per_seq())
+    ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos,
+                                 np.float32(scale), dtype=dtype)
+    assert float(np.abs(got.cpu().numpy().astype(np.float64) - ref).max()) <= TOL
