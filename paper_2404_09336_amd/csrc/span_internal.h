@@ -77,7 +77,8 @@ inline Partition plan_partition(const span_attn_desc_t* d) { return plan_partiti
 struct MatrixPlan {
   int32_t tokens;        // query tokens of one launch (all of the call's unless the caller fixed the number of slices)
   int32_t groups;        // groups of 16 tokens a workgroup serves with one pass over its rows: 1, 2 or 4
-  bool table;            // slices from the table: sequences with several slices first, so an entry's index is its slot
+  bool table;            // slices from the table: sequences with several slices first, so an entry's index is its slot;
+                         // whole sequences in the order that levels the CUs
   bool even;             // as in Partition
   int32_t num_splits;    // as in Partition
   int32_t slice_tokens;  // as in Partition
