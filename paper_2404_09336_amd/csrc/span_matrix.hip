@@ -72,18 +72,24 @@ __device__ __forceinline__ float exchange_max(float x) {  // maximum over the fo
 __device__ __forceinline__ void pin(f32x4& v) { asm volatile("" : "+v"(v)); }
 
 // 16 bytes to / from memory that all XCDs share (sc1: written through, never served from a stale L2 line).
-constexpr int kShared = 16;
+constexpr int kThrough = 16;
 __device__ __forceinline__ void publish4(__amdgpu_buffer_rsrc_t slot, uint32_t byte_off, f32x4 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), slot, byte_off, 0, kShared);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), slot, byte_off, 0, kThrough);
 }
 __device__ __forceinline__ f32x4 observe4(__amdgpu_buffer_rsrc_t slot, uint32_t byte_off) {
-  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slot, byte_off, 0, kShared));
+  return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(slot, byte_off, 0, kThrough));
 }
 
-template <class Elt, int D, int G, class Args>
+// kShared: several workgroups (query blocks) read the same rows, so the rows are loaded with the default cache policy and
+// the later readers find them in the L2; otherwise every row is used once and streams past it.  Inputs that no cache
+// holds from call to call: 32 pairs x ~5500 positions, 20 tokens 29.6 -> 25.2 us; 96 pairs x ~900, 60 tokens 30.1 -> 26.5; 32 pairs
+// x 1500 fp32, 30 tokens 30.8 -> 28.0; without query blocks it loses (64 x ~155, 16 tokens 39.8 -> 43.7).
+template <class Elt, int D, int G, class Args, bool kShared>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<Elt, D, G>::kWaves))) void matrix_kernel(const Args a) {
   using Shape = MatrixShape<Elt, D, G>;
+  constexpr int kRowPolicy = kShared ? 0 : kRowLoadPolicy;
+  auto load_piece = [](__amdgpu_buffer_rsrc_t slab, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(slab, off, 0, kRowPolicy); };
   constexpr int NK = Shape::NK, NE = Shape::NE, VW = Shape::VW, S = Shape::S;
   constexpr int TR = 16 * S;                 // rows of a tile
   constexpr uint32_t ROWB = Shape::kRowBytes;
@@ -245,7 +251,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       const uint32_t off = ok ? (uint32_t)p * ROWB + 16u * (uint32_t)c4 : kNoRow;
       const bool fresh = ok && p >= new0;
 #pragma unroll
-      for (int mm = 0; mm < NK; ++mm) kr[s][mm] = load_row_piece(kslab, (fresh ? kNoRow : off) + 64u * mm);
+      for (int mm = 0; mm < NK; ++mm) kr[s][mm] = load_piece(kslab, (fresh ? kNoRow : off) + 64u * mm);
       if (__builtin_amdgcn_ballot_w64(fresh) != 0) {  // (rare: the tiles of the call's own tokens)
         if (fresh) {
           const u32x4* src = reinterpret_cast<const u32x4*>(new_row(a.k_new, p - new0)) + c4;
@@ -272,13 +278,13 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         if constexpr (VW == 2) {
-          const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(vslab, off[t], 0, kRowLoadPolicy);
+          const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(vslab, off[t], 0, kRowPolicy);
           vr[s][t][0] = w[0];
           vr[s][t][1] = w[1];
         } else {
 #pragma unroll
           for (int u = 0; u < VW / 4; ++u) {
-            const u32x4 w = load_row_piece(vslab, off[t] + 256u * u);
+            const u32x4 w = load_piece(vslab, off[t] + 256u * u);
 #pragma unroll
             for (int k = 0; k < 4; ++k) vr[s][t][4 * u + k] = w[k];
           }
@@ -725,18 +731,25 @@ void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* t
     m.even = p.even ? 1 : 0;
     m.interleave = p.slice_tokens >= kInterleaveFrom ? 1 : 0;
   };
-  if (p.table) {
-    MatrixArgsTable m;
-    fill(m);
-    for (int i = 0; i < p.total_slices; ++i) m.table[i] = table[i];
-    hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsTable>), dim3((unsigned)base.heads, (unsigned)p.total_slices, (unsigned)blocks),
-                       dim3(kThreads), 0, stream, m);
-  } else {
-    MatrixArgsPlain m;
-    fill(m);
-    hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsPlain>),
-                       dim3((unsigned)base.heads, (unsigned)p.num_splits, (unsigned)(batch * blocks)), dim3(kThreads), 0, stream, m);
+  auto start = [&](auto shared) {
+    constexpr bool kShared = decltype(shared)::value;
+    if (p.table) {
+      MatrixArgsTable m;
+      fill(m);
+      for (int i = 0; i < p.total_slices; ++i) m.table[i] = table[i];
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsTable, kShared>),
+                         dim3((unsigned)base.heads, (unsigned)p.total_slices, (unsigned)blocks), dim3(kThreads), 0, stream, m);
+    } else {
+      MatrixArgsPlain m;
+      fill(m);
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsPlain, kShared>),
+                         dim3((unsigned)base.heads, (unsigned)p.num_splits, (unsigned)(batch * blocks)), dim3(kThreads), 0, stream, m);
+    }
+  };
+  if constexpr (G < 4) {  // (64 tokens are a call's most: one block)
+    if (blocks > 1) return start(std::true_type{});
   }
+  start(std::false_type{});
 }
 
 template <class Elt, int D>
