@@ -6,13 +6,15 @@ re-measured, and are loaded only when SPAN_ATTN_VARIANT names one (bench.py --va
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspanattn.so")
 SOURCES = [os.path.join(CSRC, "span_kernels.hip"), os.path.join(CSRC, "span_matrix.hip"), os.path.join(CSRC, "span_host.cpp")]
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # keep the compiler from forming packed-fp32 instructions
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
@@ -35,12 +37,18 @@ def build_library(verbose: bool = False, variant: str = None) -> str:
     lib = LIB if variant is None else variant_path(variant)
     extra = [] if variant is None else VARIANTS[variant]
     tmp = lib + f".tmp{os.getpid()}"
-    cmd = [hipcc] + FLAGS + extra + ["-o", tmp] + SOURCES
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + res.stdout)
+
+    with tempfile.TemporaryDirectory() as objects, ThreadPoolExecutor(len(SOURCES)) as pool:  # one compiler per source
+        outs = [os.path.join(objects, os.path.basename(src) + ".o") for src in SOURCES]
+        list(pool.map(run, [[hipcc] + FLAGS + extra + ["-c", "-o", out, src] for src, out in zip(SOURCES, outs)]))
+        run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + outs)
     os.replace(tmp, lib)
     return lib
 
