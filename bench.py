@@ -445,7 +445,8 @@ def phase_trace(args, device):
             calls[i % len(calls)]()
         torch.cuda.synchronize()
         last = calls[49 % len(calls)]                   # every workgroup of the last call has overwritten its row
-        samples.append(buf.cpu().numpy()[:span.span_plan_query(last.desc)["workgroups"]].copy())
+        stamps = buf.cpu().numpy()[:span.span_plan_query(last.desc)["workgroups"]]
+        samples.append(stamps[stamps[:, 0] > 0].copy())     # (a few-query call launches fewer workgroups than its workspace has slots)
     lib.span_debug_set_trace(None, 0)
     rows = {}
     spans_us = []
