@@ -168,8 +168,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       v_piece[i] = *reinterpret_cast<const u32x4*>((const char*)a.v_new + src);
     }
   }
-  // A weight is exp2(fma(score, post, -reference)): the scaled score is never rounded by itself.  post is positive (a hidden
-  // row's -Inf stays -Inf); a negative scale goes into the sign of q.
+  // A weight is exp2((score - reference) * post) with the largest unscaled score as reference: the heaviest row's weight is
+  // exactly 1 and what is rounded is the distance from it, never the scaled score.  (A rounded scaled reference inside an fma
+  // leaves the heaviest row 2^r, r the rounding of the product: for scaled scores from 2^29 on r is no longer small.)
+  // post is positive (a hidden row's -Inf stays -Inf); a negative scale goes into the sign of q.
   const float post = a.scale_log2e == 0.f ? 1e-37f : fabsf(a.scale_log2e);
   const uint32_t q_sign = a.scale_log2e < 0.f ? (Elt::kBytes == 2 ? 0x80008000u : 0x80000000u) : 0u;
 
@@ -223,8 +225,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     return (const char*)rows + (((size_t)b * a.q_len + (size_t)i) * heads + h) * ROWB;
   };
 
-  // State of query 16 g + qi in lane (qi, c4).  ref: reference exponent of the weights, their running maximum (the same
-  // in the four lanes of a query); lsum: this lane's share of their sum; O[g][e][r]: un-normalised output column
+  // State of query 16 g + qi in lane (qi, c4).  ref: reference of the weights, the running maximum of the unscaled scores
+  // (the same in the four lanes of a query); lsum: this lane's share of their sum; O[g][e][r]: un-normalised output column
   // column(4 c4 + r) + e, times Elt::kWeightScale.
   float ref[G], lsum[G];
   f32x4 O[G][NE];
@@ -367,12 +369,11 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #pragma unroll
         for (int t = 0; t < 4; ++t) mx = fmaxf(mx, sc[g][s][t]);
       }
-      mx *= post;
       if (__builtin_amdgcn_ballot_w64(mx > ref[g]) != 0) {  // (the maximum settles after the first tiles)
         mx = exchange_max(mx);
         const float ref_new = fmaxf(ref[g], mx);
         const float ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
-        const float alpha = __builtin_amdgcn_exp2f(ref[g] - ref_safe);
+        const float alpha = __builtin_amdgcn_exp2f((ref[g] - ref_safe) * post);
         ref[g] = ref_new;
         lsum[g] *= alpha;
 #pragma unroll
@@ -382,7 +383,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #pragma unroll
       for (int s = 0; s < S; ++s) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) sc[g][s][t] = __builtin_amdgcn_exp2f(fmaf(sc[g][s][t], post, -ref_safe));
+        for (int t = 0; t < 4; ++t) sc[g][s][t] = __builtin_amdgcn_exp2f((sc[g][s][t] - ref_safe) * post);
         lsum[g] += (sc[g][s][0] + sc[g][s][1]) + (sc[g][s][2] + sc[g][s][3]);
       }
     }
@@ -481,10 +482,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
           d += __shfl_xor(d, 16, 64);
           d += __shfl_xor(d, 32, 64);
           d = p - lim0 <= 16 * g + qi ? d : -INFINITY;
-          const float ref_new = fmaxf(ref[g], d * post), ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
-          const float alpha = ref[g] == ref_new ? 1.f : __builtin_amdgcn_exp2f(ref[g] - ref_safe);
+          const float ref_new = fmaxf(ref[g], d), ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
+          const float alpha = ref[g] == ref_new ? 1.f : __builtin_amdgcn_exp2f((ref[g] - ref_safe) * post);
           ref[g] = ref_new;
-          w[g] = __builtin_amdgcn_exp2f(fmaf(d, post, -ref_safe));
+          w[g] = __builtin_amdgcn_exp2f((d - ref_safe) * post);
           lsum[g] = lsum[g] * alpha + (c4 == 0 ? w[g] : 0.f);
           w[g] *= Elt::kWeightScale;
 #pragma unroll
@@ -630,7 +631,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < kWavesPerBlock; ++w) {
-        const float wgt = l[w] != 0.f ? __builtin_amdgcn_exp2f(m[w] - M) : 0.f;
+        const float wgt = l[w] != 0.f ? __builtin_amdgcn_exp2f((m[w] - M) * post) : 0.f;
         const f32x4 ow = *reinterpret_cast<const f32x4*>(&s_u.ws.acc[w][j][col]);
         L = fmaf(wgt, l[w], L);
         if (l[w] != 0.f) {
@@ -696,7 +697,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
         if (s0 + k < nsl && l[k] != 0.f) {
           const float mn = fmaxf(M, m[k]);
           const float ms = mn == -INFINITY ? 0.f : mn;
-          const float wa = __builtin_amdgcn_exp2f(M - ms), wb = __builtin_amdgcn_exp2f(m[k] - ms);
+          const float wa = __builtin_amdgcn_exp2f((M - ms) * post), wb = __builtin_amdgcn_exp2f((m[k] - ms) * post);
           L = fmaf(L, wa, l[k] * wb);
 #pragma unroll
           for (int c = 0; c < 4; ++c) o[c] = fmaf(o[c], wa, os[k][c] * wb);
