@@ -346,6 +346,13 @@ __device__ __forceinline__ float observe(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The product x, rounded: the compiler must not contract it into the subtraction of the reference that follows.  There the
+// product's own rounding would stay behind as an exponent, where for scores of 2^24 and more it is no longer small.
+__device__ __forceinline__ float rounded(float x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
 // Merge two un-normalised softmax states held in log2 units.
 __device__ __forceinline__ void merge_state(float& m, float& l, float* acc, int n, float m2, float l2,
                                             const float* acc2) {

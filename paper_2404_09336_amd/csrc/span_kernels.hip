@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     if (__builtin_amdgcn_ballot_w64(mine) != 0) {  // wave-uniform
       float vf[EPL];
       Elt::unpack(s_new[wave][1][lir], vf);
-      const float d = group_allreduce_sum<LPR>(Elt::dot(s_new[wave][0][lir], qv[0])) * post;
+      const float d = rounded(group_allreduce_sum<LPR>(Elt::dot(s_new[wave][0][lir], qv[0])) * post);
       if (grp == 0) {
         const float l_one = 1.f;
         merge_state(m[0], l[0], acc[0], EPL, d, l_one, vf);
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
           Elt::unpack(vb, vf);
 #pragma unroll
           for (int j = 0; j < NQ; ++j) {
-            const float d = group_allreduce_sum<LPR>(Elt::dot(kb, qv[j])) * post;
+            const float d = rounded(group_allreduce_sum<LPR>(Elt::dot(kb, qv[j])) * post);
             if (pb <= lim[j] && grp == 0) {
               const float l_one = 1.f;
               merge_state(m[j], l[j], acc[j], EPL, d, l_one, vf);
