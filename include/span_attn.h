@@ -154,8 +154,9 @@ int span_decode_attn_static(const span_attn_desc_t* desc, const void* q, const v
  * the matrix cores: one launch, in which a workgroup
  * serves up to 64 tokens with one pass over its share of the span's rows (calls with num_splits > 0 whose
  * slices the workspace holds fewer token states for take one launch per queries_per_pass tokens).  Weights meet
- * fp32 rows as they are, fp16 rows as two fp16 terms (22 mantissa bits) and bf16 rows as three bf16 terms (24);
- * sums and outputs are fp32.
+ * fp32 rows as they are, bf16 rows as three bf16 terms (24 mantissa bits), fp16 rows of 64 and of two tokens as three
+ * fp16 terms (24) and fp16 rows of 128 of more tokens as two (22), with a smallest step of 2^-39 of the heaviest
+ * weight for fp16 rows; sums and outputs are fp32.
  *   q      : device, desc->dtype, [batch, q_len, heads, head_dim]
  *   q_pos  : device int32 [batch], cache position of query token 0 (its K / V row, like those of the
  *            other new tokens, is already in the cache and inside the span if it is to be attended);

@@ -131,7 +131,6 @@ constexpr int kTraceStamps = 16;
 struct F32 {
   static constexpr int kBytes = 4, kPerVec = 4;
   static constexpr bool kPostScale = false;
-  static constexpr int kTerms = 1;  // matrix pass: terms of a weight in the storage type
   static constexpr float kWeightScale = 1.f;
   struct Q {
     float f[4];
@@ -166,9 +165,9 @@ struct F32 {
 struct F16 {
   static constexpr int kBytes = 2, kPerVec = 8;
   static constexpr bool kPostScale = true;
-  static constexpr int kTerms = 2;
-  // weights enter the product times 2^8, which keeps those below 2^-14 of the largest out of fp16's subnormal range
-  static constexpr float kWeightScale = 256.f;
+  // weights (at most 1) enter the second product of the matrix kernel times 2^15, fp16's largest power of two: the step of
+  // a split weight is then 2^-39 of the heaviest row's
+  static constexpr float kWeightScale = 32768.f;
   typedef u32x4 Q;
   // C (16x16, fp32) += A (16 x k) * B (k x 16), k = 16 or 32: four / eight 16-bit elements of A and of B per lane
   static __device__ __forceinline__ f32x4 mfma(u32x2 a, u32x2 b, f32x4 c) {
@@ -178,7 +177,8 @@ struct F16 {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
   }
   // two weights as kTerms pairs in the storage type: each term is what the ones before it left, rounded (two fp16
-  // terms hold 22 bits)
+  // terms hold 22 bits, three all 24 of an fp32 value, as far as fp16's smallest step allows)
+  template <int kTerms>
   static __device__ __forceinline__ void split(float p0, float p1, uint32_t* terms) {
     float r0 = p0, r1 = p1;
 #pragma unroll
@@ -216,7 +216,6 @@ struct F16 {
 struct BF16 {
   static constexpr int kBytes = 2, kPerVec = 8;
   static constexpr bool kPostScale = true;
-  static constexpr int kTerms = 3;  // 24 bits, as many as an fp32 weight has
   static constexpr float kWeightScale = 1.f;
   typedef u32x4 Q;
   static __device__ __forceinline__ f32x4 mfma(u32x2 a, u32x2 b, f32x4 c) {
@@ -225,6 +224,7 @@ struct BF16 {
   static __device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   }
+  template <int kTerms>  // (three: 24 bits, as many as an fp32 weight has)
   static __device__ __forceinline__ void split(float p0, float p1, uint32_t* terms) {
     float r0 = p0, r1 = p1;
 #pragma unroll

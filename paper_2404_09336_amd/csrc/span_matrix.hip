@@ -12,7 +12,7 @@
 //     takes element e of each, so lane (qi, c4) accumulates NE = D / 16 x 4 output columns of query qi, and the
 //     online-softmax rescaling factor is a per-lane scalar.
 //   * 16-bit weights: the fp32 weight enters the second product as kTerms terms of the storage type, each rounding what
-//     the ones before left.  fp32 rows use the fp32 MFMA throughout.
+//     the ones before left (see weight_terms).  fp32 rows use the fp32 MFMA throughout.
 // Bound by memory except for few pairs, where the start-up chain (1 us of list metadata, 2 us to the first rows) and the
 // merge count.  Its rounding is that of the vector kernels or less (measured against 64 bits, relative 2-norm: fp32 1.6e-7
 // for 1.8e-7, 16-bit rows of 64 1.45e-7 for 1.6e-7, 16-bit rows of 128 1.65e-7 for 1.75e-7).
@@ -56,6 +56,17 @@ struct MatrixShape {
   static constexpr int kWaves = D == 128 ? (G == 1 && Elt::kBytes == 2 ? 4 : 2) : (G == 1 ? 4 : (G == 2 ? 3 : 2));
 };
 
+// Terms of a weight in the storage type.  Three hold all 24 bits of the fp32 weight; bf16 rows need them.  Of fp16 rows the
+// calls whose weights met the rows whole before they came to the matrix cores take three (head_dim 64, and two tokens), the
+// others the two that their sixteen-token pass had.  The third costs, us with two -> three: 16 x 16 pairs x ~380 positions of
+// 64, 9 tokens 14.5 -> 14.7; 16 x 32 x ~560 of 64, 20 tokens 25.8 -> 27.1, 60 tokens 39.3 -> 42.8; 8 x 32 x ~560 of 128, 2
+// tokens 22.4 -> 22.6.  For more tokens of 128 it would: 64 x 32 x ~155, 16 tokens 39.9 -> 40.7; 32 x 32 x ~560, 64 tokens
+// 115 -> 124.  Weights kept whole on the fp32 MFMA: 16.9, 35.9, 59.2, 25.7, 44.5 and 213.
+template <class Elt, int D>
+constexpr int weight_terms(bool two_tokens) {
+  return std::is_same<Elt, F16>::value && D == 128 && !two_tokens ? 2 : 3;
+}
+
 __device__ __forceinline__ float exchange_max(float x) {  // maximum over the four lanes qi + 16 c
   const uint32_t u = __builtin_bit_cast(uint32_t, x);
   const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
@@ -84,7 +95,7 @@ __device__ __forceinline__ f32x4 observe4(__amdgpu_buffer_rsrc_t slot, uint32_t 
 // the later readers find them in the L2; otherwise every row is used once and streams past it.  Inputs that no cache
 // holds from call to call: 32 pairs x ~5500 positions, 20 tokens 29.6 -> 25.2 us; 96 pairs x ~900, 60 tokens 30.1 -> 26.5; 32 pairs
 // x 1500 fp32, 30 tokens 30.8 -> 28.0; without query blocks it loses (64 x ~155, 16 tokens 39.8 -> 43.7).
-template <class Elt, int D, int G, class Args, bool kShared>
+template <class Elt, int D, int G, class Args, bool kShared, int kTerms>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<Elt, D, G>::kWaves))) void matrix_kernel(const Args a) {
   using Shape = MatrixShape<Elt, D, G>;
@@ -391,17 +402,17 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   // O += V^T P^T with the tile in vr and the weights w.
   auto add_outputs = [&](const f32x4 (&w)[G][S]) {
     if constexpr (Elt::kBytes == 2) {
-      uint32_t terms[G][Elt::kTerms][2 * S];  // dword 2 s + k: rows 4 c4 + 2 k, + 1 of group s
+      uint32_t terms[G][kTerms][2 * S];  // dword 2 s + k: rows 4 c4 + 2 k, + 1 of group s
 #pragma unroll
       for (int g = 0; g < G; ++g) {
 #pragma unroll
         for (int s = 0; s < S; ++s) {
 #pragma unroll
           for (int k = 0; k < 2; ++k) {
-            uint32_t tt[Elt::kTerms];
-            Elt::split(w[g][s][2 * k] * Elt::kWeightScale, w[g][s][2 * k + 1] * Elt::kWeightScale, tt);
+            uint32_t tt[kTerms];
+            Elt::template split<kTerms>(w[g][s][2 * k] * Elt::kWeightScale, w[g][s][2 * k + 1] * Elt::kWeightScale, tt);
 #pragma unroll
-            for (int i = 0; i < Elt::kTerms; ++i) terms[g][i][2 * s + k] = tt[i];
+            for (int i = 0; i < kTerms; ++i) terms[g][i][2 * s + k] = tt[i];
           }
         }
       }
@@ -420,7 +431,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #pragma unroll
         for (int g = 0; g < G; ++g) part[g] = D == 64 ? f32x4{0.f, 0.f, 0.f, 0.f} : O[g][e];
 #pragma unroll
-        for (int i = Elt::kTerms - 1; i >= 0; --i) {
+        for (int i = kTerms - 1; i >= 0; --i) {
 #pragma unroll
           for (int g = 0; g < G; ++g) {
             const uint32_t* tg = terms[g][i];
@@ -732,25 +743,29 @@ void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* t
     m.even = p.even ? 1 : 0;
     m.interleave = p.slice_tokens >= kInterleaveFrom ? 1 : 0;
   };
-  auto start = [&](auto shared) {
+  auto start = [&](auto shared, auto two_tokens) {
     constexpr bool kShared = decltype(shared)::value;
+    constexpr int kTerms = weight_terms<Elt, D>(decltype(two_tokens)::value);
     if (p.table) {
       MatrixArgsTable m;
       fill(m);
       for (int i = 0; i < p.total_slices; ++i) m.table[i] = table[i];
-      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsTable, kShared>),
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsTable, kShared, kTerms>),
                          dim3((unsigned)base.heads, (unsigned)p.total_slices, (unsigned)blocks), dim3(kThreads), 0, stream, m);
     } else {
       MatrixArgsPlain m;
       fill(m);
-      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsPlain, kShared>),
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsPlain, kShared, kTerms>),
                          dim3((unsigned)base.heads, (unsigned)p.num_splits, (unsigned)(batch * blocks)), dim3(kThreads), 0, stream, m);
     }
   };
   if constexpr (G < 4) {  // (64 tokens are a call's most: one block)
-    if (blocks > 1) return start(std::true_type{});
+    if (blocks > 1) return start(std::true_type{}, std::false_type{});
   }
-  start(std::false_type{});
+  if constexpr (G == 1) {
+    if (base.q_len == 2) return start(std::false_type{}, std::true_type{});
+  }
+  start(std::false_type{}, std::false_type{});
 }
 
 template <class Elt, int D>

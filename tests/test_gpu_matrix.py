@@ -117,3 +117,34 @@ def test_negative_and_zero_scales(dtype, scale, gpu_device):
     ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos,
                                  np.float32(scale), dtype=dtype)
     assert float(np.abs(got.cpu().numpy().astype(np.float64) - ref).max()) <= TOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len", [2, 3, 16, 20, 40])
+def test_light_rows_behind_heavy_rows_of_zeros(dtype, D, q_len, gpu_device):
+    """Every 50th row outweighs the others by 2^19 .. 2^21 and holds zeros in V, so the output is the light rows' sum alone
+    and shows the accuracy of their weights.  Bound on the relative 2-norm: an exponent of up to 21 carries two fp32
+    roundings (of the score's scale and of the product), 21 ln 2 * 2 * 2^-24 = 1.7e-6; the step of an fp16 weight is 2^-39
+    of the heaviest, half of it over 2^-20 is 1e-6 a row and independent from row to row; sums and exp2 a few 1e-7."""
+    L = 1500
+    cfg = DecodeConfig(105, "matrix-light-rows", 2, 3, D, L, L, dtype, TOL)
+    ctx = np.full(cfg.batch, L, np.int32)
+    sp = SpanBatch.from_lists([[(0, L)], [(0, 400), (410, L)]], ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=gpu_device)
+    q = torch.zeros_like(draw_queries(cfg, q_len, device=gpu_device))
+    q[..., 0] = 16.0
+    per_unit = 16.0 * cfg.scale / np.log(2.0)                    # powers of two per unit of K[..., 0]
+    light = np.random.default_rng(D + q_len).uniform(-21, -19, size=K.shape[:3]) / per_unit
+    K[..., 0] = _dev(light.astype(np.float32), gpu_device).to(K.dtype)
+    K[:, :, 7::50, 0] = 0
+    V[:, :, 7::50] = 0
+    pos = (ctx - q_len).astype(np.int32)
+    ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos,
+                                 np.float32(cfg.scale), dtype=dtype)
+    lists = [_dev(a, gpu_device) for a in (sp.offsets, sp.starts, sp.ends, pos)]
+    for kw in (dict(tokens_per_seq=sp.tokens_per_seq()), dict(num_splits=1)):
+        got = span.span_decode_attn_multi(q, K, V, *lists, np.float32(cfg.scale), max_tokens=L, **kw).cpu().numpy().astype(np.float64)
+        rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+        print(f"[parity] light rows {dtype} D={D} q_len={q_len} {sorted(kw)}: relative 2-norm {rel:.2e}", flush=True)
+        assert rel <= 4e-6
