@@ -80,7 +80,10 @@ typedef struct span_attn_desc {
                               when that is 0.  Its leading ticket counters must be zero before the
                               first call that uses it (span_workspace_init, or zero the buffer);
                               every call leaves them zero again.  Two calls that may overlap in
-                              time must not share a workspace.                                  */
+                              time must not share a workspace.  Few-query calls of three and more
+                              tokens also take what span_workspace_bytes() gives for any other
+                              such q_len of the shape, and then cut the spans into fewer slices
+                              if it is less than their own.                                     */
   size_t workspace_bytes;
   void* stream;            /* hipStream_t; NULL = the default stream                             */
   int32_t q_len;           /* query tokens per sequence: 0 or 1 for every entry point but
@@ -270,7 +273,8 @@ typedef struct span_plan_info {
 } span_plan_info_t;
 int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* info);
 
-/* Bytes of device workspace the call described by desc needs (0 when one slice is used). */
+/* Bytes of device workspace the call described by desc wants (0 when one slice is used); desc->workspace and
+ * desc->workspace_bytes are not looked at. */
 size_t span_workspace_bytes(const span_attn_desc_t* desc);
 
 /*

@@ -80,9 +80,6 @@ static int64_t target_workgroups(const span_attn_desc_t* d) {
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// (a few-query call's slots are regrouped into slices of at least kMinSlice positions, see plan_matrix)
-static int64_t min_slice(const span_attn_desc_t* d) { return queries_per_pass(d) > 2 ? kSliceGranule : kMinSlice; }
-
 // Slices (per head, over all sequences) a call aims at.  The upper end is one resident round of workgroups.  But
 // few, large slices beat many small ones as long as the memory system stays busy and a ragged batch can still be
 // levelled: a quarter of the wavefront slots saturates HBM, every slice costs its own start-up, and every extra
@@ -93,13 +90,6 @@ static int64_t min_slice(const span_attn_desc_t* d) { return queries_per_pass(d)
 static int64_t slice_room(const span_attn_desc_t* d) {
   const int64_t round = target_workgroups(d);
   const int64_t most = round / d->heads, least = ceil_div(round / 4, d->heads);
-  if (queries_per_pass(d) > 2) {
-    // Few-query calls: room for the partial states of a whole round, and where the (batch, head) pairs alone do not
-    // fill the chip, for those of kUnsplitFromPairs workgroups with all tokens of the call.
-    const int64_t few_pairs = (int64_t)d->batch * d->heads < kUnsplitFromPairs
-                                  ? ceil_div(ceil_div(kUnsplitFromPairs, d->heads) * query_tokens(d), queries_per_pass(d)) : 0;
-    return std::min<int64_t>(std::max<int64_t>(std::max<int64_t>(1, most), few_pairs), kMaxPlanSlices);
-  }
   const int64_t room = std::max<int64_t>(least, 2 * (int64_t)d->batch);
   return std::max<int64_t>(1, std::min(room, most));
 }
@@ -134,7 +124,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   int64_t room = slice_room(d);  // slices (per head) the call aims at, at most one resident round
   if (room > kMaxPlanSlices) room = kMaxPlanSlices;
   int64_t T = ceil_div(sum, room);
-  if (T < min_slice(d)) T = min_slice(d);
+  if (T < kMinSlice) T = kMinSlice;
   int64_t total = count(T);
   // A quarter of the chip's wavefront slots (512 workgroups) already keeps the memory system busy, and a
   // pair that is one workgroup needs no partial states and no tickets.  So a batch of at least 512 (batch,
@@ -152,7 +142,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
       total = count(T);
     }
     // fits: give back what the proportional step overshot
-    for (int i = 0; i < 8 && T - kSliceGranule >= min_slice(d) && count(T - kSliceGranule) <= room; ++i)
+    for (int i = 0; i < 8 && T - kSliceGranule >= kMinSlice && count(T - kSliceGranule) <= room; ++i)
       T -= kSliceGranule;
     total = count(T);
   }
@@ -296,7 +286,7 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
   }
   const int64_t pairs = (int64_t)d->batch * d->heads;
   int64_t splits = d->num_splits > 0 ? d->num_splits : slice_room(d) / d->batch;  // stay within one round
-  const int64_t most = ceil_div(max_tok, min_slice(d));
+  const int64_t most = ceil_div(max_tok, kMinSlice);
   if (d->num_splits == 0 && splits > most) splits = most;
   if (splits > max_tok) splits = max_tok;
   if (splits < 1) splits = 1;
@@ -327,8 +317,8 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
 // Slices.  512 workgroups a call (two per CU), but one slice per sequence at least and one resident round at most: of
 // 256, 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 shapes; more only pays for itself in
 // partial states, which grow with the tokens (batch 16 x ~700, 32 tokens, 16 slices per head against 32: 50.4 and 59.3 us).
-// The slices have to fit the workspace (total_slices * queries_per_pass token states per head), so sequences that stay
-// in one slice, which need no state, come after the others in the table.
+// The slices have to fit the workspace's token states, so sequences that stay in one slice, which need no state, come after
+// the others in the table.
 //
 // Groups.  A workgroup that serves all tokens reads every row once; where the batch has too few (batch, head) pairs to
 // fill the chip that way (fewer than 128 workgroups before slicing), several workgroups share a slice's rows through the
@@ -350,11 +340,26 @@ bool runs_on_matrix_cores(const span_attn_desc_t* d) {
   return n == 2 && d->dtype != SPAN_F32 && (int64_t)d->batch * d->heads * d->head_dim <= kMatrixTwoTokenColumns;
 }
 
-bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table) {
+// Token states per head.  Every sliced call brings those of its Partition (from three tokens on that does not depend on how
+// many they are); a few-query call can use more where that pool holds few slices for all its tokens at once (8 sequences x 32
+// heads x ~600 positions, 8 tokens, fp32 rows of 128: 44.5 us with the Partition's pool, 39.7 with twice that; 16 x 16 x ~380,
+// 9 tokens, fp16 rows of 64: 14.9 and 14.3), up to a whole round of 1024 workgroups and, where the (batch, head) pairs alone
+// do not fill the chip, kUnsplitFromPairs workgroups with all tokens of the call.
+int64_t least_states(const Partition& p) { return p.num_splits > 1 ? (int64_t)p.total_slices * p.queries_per_pass : 0; }
+
+int64_t most_states(const span_attn_desc_t* d, const Partition& p) {
+  const int64_t least = least_states(p);
+  if (least == 0 || p.queries_per_pass <= 2 || d->num_splits > 0) return least;
+  int64_t slices = target_workgroups(d) / d->heads * p.queries_per_pass;
+  if ((int64_t)d->batch * d->heads < kUnsplitFromPairs) slices = std::max(slices, ceil_div(kUnsplitFromPairs, d->heads) * query_tokens(d));
+  return std::max(least, std::min<int64_t>(slices, (int64_t)kMaxPlanSlices * p.queries_per_pass));
+}
+
+bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
   int32_t n = query_tokens(d);
   if (!runs_on_matrix_cores(d)) return false;
   const bool sliced = p.num_splits > 1;
-  const int64_t states = sliced ? (int64_t)p.total_slices * p.queries_per_pass : 0;  // the workspace's, per head
+  m->states = 0;
   m->tokens = n;
   m->table = false;
   m->even = p.even;
@@ -365,6 +370,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, u
   auto groups_for = [&](int64_t tokens) { return std::min<int32_t>(max_groups, tokens <= 16 ? 1 : (tokens <= 32 ? 2 : 4)); };
   if (d->num_splits > 0) {  // the caller's number of slices stands: as many tokens a launch as their states fit
     if (sliced && n > p.queries_per_pass) m->tokens = p.queries_per_pass;
+    if (sliced) m->states = (int64_t)m->total_slices * m->tokens;
     m->groups = groups_for(m->tokens);
     while ((int64_t)d->batch * ceil_div(m->tokens, 16 * m->groups) > 65535) m->tokens = 16 * m->groups;  // (grid.z limit)
     return true;
@@ -387,6 +393,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, u
     m->num_splits = (int32_t)ceil_div(p.max_tokens, slice);
     m->slice_tokens = (int32_t)slice;
     m->total_slices = m->num_splits * d->batch;
+    if (m->num_splits > 1) m->states = (int64_t)m->total_slices * n;
     return true;
   }
   std::vector<int64_t> from_lists;
@@ -438,6 +445,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, u
   for (int32_t b = 0; b < d->batch; ++b) {
     const int64_t s = slices_for(tokens(b), T);
     total += s;
+    if (s > 1) m->states += s * n;
     most_s = std::max(most_s, s);
     least_s = std::min(least_s, s);
     longest = std::max(longest, ceil_div(tokens(b), s));
@@ -478,15 +486,35 @@ size_t workspace_counter_bytes(const span_attn_desc_t* d) {
   return (n + 255) & ~(size_t)255;
 }
 
-size_t workspace_ml_bytes(const span_attn_desc_t* d, const Partition& p) {
-  const size_t n = (size_t)p.total_slices * d->heads * p.queries_per_pass * 2 * sizeof(float);
+size_t workspace_ml_bytes(const span_attn_desc_t* d, int64_t states) {
+  const size_t n = (size_t)states * d->heads * 2 * sizeof(float);
   return (n + 255) & ~(size_t)255;
 }
 
+size_t workspace_bytes_for(const span_attn_desc_t* d, int64_t states) {
+  if (states == 0) return 0;
+  return workspace_counter_bytes(d) + workspace_ml_bytes(d, states) + (size_t)states * d->heads * d->head_dim * sizeof(float);
+}
+
+size_t workspace_least_bytes(const span_attn_desc_t* d, const Partition& p) { return workspace_bytes_for(d, least_states(p)); }
+
 size_t workspace_bytes(const span_attn_desc_t* d, const Partition& p) {
-  if (p.num_splits <= 1) return 0;
-  return workspace_counter_bytes(d) + workspace_ml_bytes(d, p) +
-         (size_t)p.total_slices * d->heads * p.queries_per_pass * d->head_dim * sizeof(float);
+  int64_t states = least_states(p);
+  const int64_t most = most_states(d, p);
+  if (most > states) {  // (a few-query call whose pool may be larger: as much as its plan uses)
+    MatrixPlan m;
+    std::vector<uint32_t> table((size_t)kMaxPlanSlices);
+    if (plan_matrix(d, p, most, &m, table.data())) states = std::max(states, m.states);
+  }
+  return workspace_bytes_for(d, states);
+}
+
+int64_t states_that_fit(const span_attn_desc_t* d, const Partition& p) {
+  const size_t counters = workspace_counter_bytes(d), per_state = (size_t)d->heads * (2 + d->head_dim) * sizeof(float);
+  const size_t room = d->workspace_bytes > counters ? d->workspace_bytes - counters : 0;
+  int64_t fit = std::min<int64_t>(most_states(d, p), (int64_t)(room / per_state));
+  if (fit > 0 && workspace_bytes_for(d, fit) > d->workspace_bytes) --fit;  // (the (m, l) pairs' part is rounded up)
+  return std::max(least_states(p), fit);
 }
 
 }  // namespace spanattn

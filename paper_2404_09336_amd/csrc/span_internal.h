@@ -71,9 +71,9 @@ struct Partition {
 Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* runs = nullptr);
 inline Partition plan_partition(const span_attn_desc_t* d) { return plan_partition(d, nullptr, nullptr); }
 
-// How a few-query call runs on the matrix cores (span_matrix.hip).  The workspace holds the partial states of the
-// Partition above, total_slices * queries_per_pass query tokens per head; the launches cut the spans into as many
-// slices as that room allows for all the tokens they serve.
+// How a few-query call runs on the matrix cores (span_matrix.hip).  The workspace holds partial states of query tokens: at
+// least those of the Partition above, total_slices * queries_per_pass per head, and more where the caller brings them; the
+// launches cut the spans into as many slices as that room allows for all the tokens they serve.
 struct MatrixPlan {
   int32_t tokens;        // query tokens of one launch (all of the call's unless the caller fixed the number of slices)
   int32_t groups;        // groups of 16 tokens a workgroup serves with one pass over its rows: 1, 2 or 4
@@ -83,18 +83,28 @@ struct MatrixPlan {
   int32_t num_splits;    // as in Partition
   int32_t slice_tokens;  // as in Partition
   int32_t total_slices;  // table entries, or batch * num_splits
+  int64_t states;        // token states per head that the slices use
 };
 // Most groups a workgroup serves: the state of 64 tokens of fp32 rows of 128 does not fit the registers next to a tile.
 constexpr int kMatrixMaxGroups(int elt_bytes, int head_dim) { return elt_bytes == 4 && head_dim == 128 ? 2 : 4; }
 bool runs_on_matrix_cores(const span_attn_desc_t* d);
-// False if the call does not run on the matrix cores.  `p` is the call's partition, `table` has kMaxPlanSlices entries.
-bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table);
+int64_t least_states(const Partition& p);                             // token states per head a call must bring
+int64_t most_states(const span_attn_desc_t* d, const Partition& p);   // ... it can use
+// False if the call does not run on the matrix cores.  `p` is the call's partition, `states` what the workspace holds per
+// head (least_states at least), `table` has kMaxPlanSlices entries.
+bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table);
+inline bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table) {
+  return plan_matrix(d, p, least_states(p), m, table);
+}
 
 int check_desc(const span_attn_desc_t* d);
 int32_t query_tokens(const span_attn_desc_t* d);  // q_len of the descriptor, at least 1
 size_t workspace_counter_bytes(const span_attn_desc_t* d);
-size_t workspace_ml_bytes(const span_attn_desc_t* d, const Partition& p);
-size_t workspace_bytes(const span_attn_desc_t* d, const Partition& p);
+size_t workspace_ml_bytes(const span_attn_desc_t* d, int64_t states);
+size_t workspace_bytes_for(const span_attn_desc_t* d, int64_t states);
+size_t workspace_least_bytes(const span_attn_desc_t* d, const Partition& p);  // with less the call is refused
+size_t workspace_bytes(const span_attn_desc_t* d, const Partition& p);        // what span_workspace_bytes asks for
+int64_t states_that_fit(const span_attn_desc_t* d, const Partition& p);       // in desc->workspace_bytes (not less than the least)
 
 }  // namespace spanattn
 #endif

@@ -721,9 +721,10 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
   }
   const Partition p = plan_partition(d, a.table, kDense || runs_on_matrix_cores(d) ? nullptr : &runs);
   const GridMode mode = p.runs ? GridMode::kRuns : (p.exact ? GridMode::kTable : GridMode::kPlain);
-  const size_t need = workspace_bytes(d, p);
+  const size_t need = workspace_least_bytes(d, p);
   if (need > 0 && (!d->workspace || ((uintptr_t)d->workspace & 255u) || d->workspace_bytes < need))
     return SPAN_ERR_WORKSPACE;
+  const int64_t states = need ? states_that_fit(d, p) : 0;
 
   a.q = q;
   a.k = k;
@@ -740,7 +741,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
   a.q_len = query_tokens(d);
   a.counters = need ? (int32_t*)d->workspace : nullptr;
   a.part_ml = need ? (float*)((char*)d->workspace + workspace_counter_bytes(d)) : nullptr;
-  a.part_acc = need ? (float*)((char*)d->workspace + workspace_counter_bytes(d) + workspace_ml_bytes(d, p)) : nullptr;
+  a.part_acc = need ? (float*)((char*)d->workspace + workspace_counter_bytes(d) + workspace_ml_bytes(d, states)) : nullptr;
   a.heads = d->heads;
   a.max_len = d->max_len;
   a.num_intervals = d->num_intervals;
@@ -758,7 +759,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
   hipStream_t stream = (hipStream_t)d->stream;
 
   MatrixPlan mp;
-  if (!kDense && plan_matrix(d, p, &mp, a.table)) {
+  if (!kDense && plan_matrix(d, p, states, &mp, a.table)) {
     const hipError_t err = launch_matrix(a, d->dtype, d->head_dim, mp, a.table, d->batch, stream);
     if (err != hipSuccess) {
       g_last_hip_error = (int)err;
@@ -893,7 +894,7 @@ extern "C" int span_workspace_init(const span_attn_desc_t* desc) {
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
   const spanattn::Partition p = spanattn::plan_partition(desc);
-  const size_t need = spanattn::workspace_bytes(desc, p);
+  const size_t need = spanattn::workspace_least_bytes(desc, p);
   if (need == 0) return SPAN_OK;
   if (!desc->workspace || ((uintptr_t)desc->workspace & 255u) || desc->workspace_bytes < need) return SPAN_ERR_WORKSPACE;
   const size_t words = spanattn::workspace_counter_bytes(desc) / sizeof(uint32_t);

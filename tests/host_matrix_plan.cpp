@@ -18,8 +18,59 @@
 static std::mt19937 rng(20240409);
 static int rnd(int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); }
 
+// A workspace of any size from the least that is accepted: the plan's states fit what the launch lays out in it, the size
+// asked for gives the plan of an unlimited one, and the least does not depend on the number of tokens from three on.
+static void workspaces_of_all_sizes() {
+  using namespace spanattn;
+  std::vector<uint32_t> base_table(kMaxPlanSlices), table(kMaxPlanSlices);
+  int more = 0, fewer_slices = 0;
+  for (int it = 0; it < 20000; ++it) {
+    span_attn_desc_t d = {};
+    d.batch = rnd(1, rnd(0, 2) ? 12 : 60);
+    const int heads[] = {1, 3, 8, 16, 32};
+    d.heads = heads[rnd(0, 4)];
+    d.head_dim = rnd(0, 1) ? 128 : 64;
+    d.max_len = rnd(1, 20000);
+    d.dtype = rnd(0, 2);
+    d.num_intervals = 10;
+    d.num_splits = rnd(0, 9) ? 0 : rnd(1, 300);
+    d.q_len = rnd(2, 64);
+    std::vector<int64_t> tok(d.batch);
+    for (auto& t : tok) t = rnd(0, rnd(0, 1) ? d.max_len : (d.max_len + 9) / 10);
+    d.tokens_per_seq = rnd(0, 3) ? tok.data() : nullptr;
+    const Partition p = plan_partition(&d, base_table.data());
+    const size_t least = workspace_least_bytes(&d, p), asked = workspace_bytes(&d, p);
+    REQUIRE(least <= asked && (least == 0) == (asked == 0) && (least == 0) == (p.num_splits == 1));
+    MatrixPlan full, m;
+    if (!plan_matrix(&d, p, most_states(&d, p), &full, table.data())) {
+      REQUIRE(least == asked);
+      continue;
+    }
+    if (d.q_len >= 3) {
+      span_attn_desc_t other = d;
+      other.q_len = rnd(3, 64);
+      REQUIRE(workspace_least_bytes(&other, plan_partition(&other, base_table.data())) == least);
+    }
+    if (least == 0) {
+      REQUIRE(full.states == 0 && full.num_splits == 1);
+      continue;
+    }
+    d.workspace_bytes = rnd(0, 3) ? least + (size_t)(rng() % (uint32_t)(asked - least + 1000)) : asked;
+    const int64_t states = states_that_fit(&d, p);
+    REQUIRE(states >= least_states(p) && workspace_bytes_for(&d, states) <= d.workspace_bytes);
+    REQUIRE(plan_matrix(&d, p, states, &m, table.data()) && m.states <= states);
+    if (m.num_splits == 1) REQUIRE(m.states == 0);
+    if (d.workspace_bytes >= asked) REQUIRE(m.total_slices == full.total_slices && m.num_splits == full.num_splits && m.slice_tokens == full.slice_tokens);
+    more += asked > least;
+    fewer_slices += m.total_slices < full.total_slices;
+  }
+  const int it = -2;
+  REQUIRE(more > 500 && fewer_slices > 300);
+}
+
 int main() {
   using namespace spanattn;
+  workspaces_of_all_sizes();
   std::vector<uint32_t> base_table(kMaxPlanSlices);
   int tables = 0, sliced = 0, shared_rows = 0, forced = 0;
   for (int it = 0; it < 40000; ++it) {

@@ -148,3 +148,36 @@ def test_light_rows_behind_heavy_rows_of_zeros(dtype, D, q_len, gpu_device):
         rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
         print(f"[parity] light rows {dtype} D={D} q_len={q_len} {sorted(kw)}: relative 2-norm {rel:.2e}", flush=True)
         assert rel <= 4e-6
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 128), ("f16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("q_len", [3, 16, 64])
+@pytest.mark.parametrize("counts", [True, False])
+def test_any_workspace_from_the_least_on(dtype, D, q_len, counts, gpu_device):
+    """The least that any burst of the shape needs (slots of queries_per_pass token states for the partition that
+    span_plan_query reports) is enough for all of them; nothing past the given size is written."""
+    cfg = DecodeConfig(106, "matrix-workspace", 4, 6, D, 1800, 1800, dtype, TOL)
+    ctx = np.full(cfg.batch, cfg.max_len, np.int32)
+    sp = SpanBatch.from_lists([[(0, 900), (1000, 1800)], [(3, 400)], [(100, 1411), (1490, 1800)], [(0, 130)]], ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=gpu_device)
+    q = draw_queries(cfg, q_len, device=gpu_device)
+    pos = (ctx - q_len).astype(np.int32)
+    lists = [_dev(a, gpu_device) for a in (sp.offsets, sp.starts, sp.ends, pos)]
+    kw = dict(max_tokens=1700, tokens_per_seq=sp.tokens_per_seq() if counts else None)
+    plan = span.span_plan_query(span.prepare_span_decode_attn_multi(q, K, V, *lists, np.float32(cfg.scale), **kw).desc)
+    states = plan["workgroups"] * plan["queries_per_pass"]
+    least = 256 + (states * 8 + 255) // 256 * 256 + states * D * 4
+    assert plan["max_splits"] > 1 and least <= plan["workspace_bytes"]
+    ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos,
+                                 np.float32(cfg.scale), dtype=dtype)
+    for size in sorted({least, (least + plan["workspace_bytes"]) // 2, plan["workspace_bytes"]}):
+        buffer = torch.full((plan["workspace_bytes"] + 4096,), 0x5a, dtype=torch.uint8, device=gpu_device)
+        buffer[:256] = 0                                                   # the ticket counters
+        call = span.prepare_span_decode_attn_multi(q, K, V, *lists, np.float32(cfg.scale), workspace=buffer[:size], **kw)
+        for _ in range(3):
+            call.out.fill_(float("nan"))
+            assert float(np.abs(call().cpu().numpy().astype(np.float64) - ref).max()) <= TOL
+        assert bool((buffer[size:] == 0x5a).all()) and not bool(buffer[:256].any())
+    call.desc.workspace_bytes = least - 1
+    with pytest.raises(span.SpanAttnError):
+        call()
