@@ -177,16 +177,18 @@ struct F16 {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
   }
   // two weights as kTerms pairs in the storage type: each term is what the ones before it left, rounded (two fp16
-  // terms hold 22 bits, three all 24 of an fp32 value, as far as fp16's smallest step allows)
+  // terms hold 22 bits, three all 24 of an fp32 value, as far as fp16's smallest step allows).  Ahead of two more terms the
+  // rounding is towards zero: 11 + 11 bits leave 2 either way, and it is one instruction for the pair.
   template <int kTerms>
   static __device__ __forceinline__ void split(float p0, float p1, uint32_t* terms) {
     float r0 = p0, r1 = p1;
 #pragma unroll
     for (int i = 0; i < kTerms; ++i) {
-      const f16x2 h = {(_Float16)r0, (_Float16)r1};
+      f16x2 h = {(_Float16)r0, (_Float16)r1};
+      if (kTerms == 3 && i < 2) h = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(r0, r1));
       terms[i] = __builtin_bit_cast(uint32_t, h);
-      r0 -= (float)h.x;
-      r1 -= (float)h.y;
+      r0 = fmaf((float)h.x, -1.f, r0);
+      r1 = fmaf((float)h.y, -1.f, r1);
     }
   }
   static __device__ __forceinline__ void unpack(const u32x4& r, float* f) {

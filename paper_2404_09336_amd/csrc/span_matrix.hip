@@ -59,8 +59,8 @@ struct MatrixShape {
 // Terms of a weight in the storage type.  Three hold all 24 bits of the fp32 weight; bf16 rows need them.  Of fp16 rows the
 // calls whose weights met the rows whole before they came to the matrix cores take three (head_dim 64, and two tokens), the
 // others the two that their sixteen-token pass had.  The third costs, us with two -> three: 16 x 16 pairs x ~380 positions of
-// 64, 9 tokens 14.5 -> 14.7; 16 x 32 x ~560 of 64, 20 tokens 25.8 -> 27.1, 60 tokens 39.3 -> 42.8; 8 x 32 x ~560 of 128, 2
-// tokens 22.4 -> 22.6.  For more tokens of 128 it would: 64 x 32 x ~155, 16 tokens 39.9 -> 40.7; 32 x 32 x ~560, 64 tokens
+// 64, 9 tokens 14.5 -> 14.8; 16 x 32 x ~560 of 64, 20 tokens 25.8 -> 26.9, 60 tokens 39.8 -> 41.7; 8 x 32 x ~560 of 128, 2
+// tokens 22.4 -> 22.4.  For more tokens of 128 it would: 64 x 32 x ~155, 16 tokens 39.9 -> 40.7; 32 x 32 x ~560, 64 tokens
 // 115 -> 124.  Weights kept whole on the fp32 MFMA: 16.9, 35.9, 59.2, 25.7, 44.5 and 213.
 template <class Elt, int D>
 constexpr int weight_terms(bool two_tokens) {
