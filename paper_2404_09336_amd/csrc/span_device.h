@@ -142,10 +142,8 @@ struct F32 {
       f[i] = __builtin_bit_cast(float, w);
     }
   }
-  static __device__ __forceinline__ void unpack4(const void* p, float* f) {  // four consecutive values in memory
-    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
-    for (int i = 0; i < 4; ++i) f[i] = v[i];
-  }
+  static __device__ __forceinline__ bool not_finite(uint32_t w) { return (w & 0x7f800000u) == 0x7f800000u; }  // any value of a dword
+  static __device__ __forceinline__ void unpack4(u32x4 r, float* f) { unpack(r, f); }  // four consecutive values
   static __device__ __forceinline__ Q make_q(const u32x4& r, float scale) {
     Q q;
     unpack(r, q.f);
@@ -200,8 +198,9 @@ struct F16 {
       f[2 * i + 1] = (float)h.y;
     }
   }
-  static __device__ __forceinline__ void unpack4(const void* p, float* f) {
-    const f16x4 v = *reinterpret_cast<const f16x4*>(p);
+  static __device__ __forceinline__ bool not_finite(uint32_t w) { return (w & 0x7c00u) == 0x7c00u || (w & 0x7c000000u) == 0x7c000000u; }
+  static __device__ __forceinline__ void unpack4(u32x2 r, float* f) {
+    const f16x4 v = __builtin_bit_cast(f16x4, r);
     for (int i = 0; i < 4; ++i) f[i] = (float)v[i];
   }
   static __device__ __forceinline__ Q make_q(const u32x4& r, float) { return r; }
@@ -246,9 +245,9 @@ struct BF16 {
       f[2 * i + 1] = __builtin_bit_cast(float, w & 0xffff0000u);
     }
   }
-  static __device__ __forceinline__ void unpack4(const void* p, float* f) {
-    const u32x2 v = *reinterpret_cast<const u32x2*>(p);
-    const uint32_t v0 = v[0], v1 = v[1];
+  static __device__ __forceinline__ bool not_finite(uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; }
+  static __device__ __forceinline__ void unpack4(u32x2 r, float* f) {
+    const uint32_t v0 = r[0], v1 = r[1];
     f[0] = __builtin_bit_cast(float, v0 << 16);
     f[1] = __builtin_bit_cast(float, v0 & 0xffff0000u);
     f[2] = __builtin_bit_cast(float, v1 << 16);

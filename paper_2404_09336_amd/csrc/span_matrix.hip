@@ -466,53 +466,71 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       }
     }
   };
-  // The whole pass again, one row at a time on the vector units, for a cache with non-finite V rows: a row never meets
-  // the sums of a query that does not see it, not even with weight zero (0 * Inf), and the fp32 weight meets the V
-  // value whole (the terms of a 16-bit weight would turn Inf into Inf + 0 * Inf).
-  auto stream_by_row = [&]() {
+  // The whole pass again, for a cache with V rows that are not finite: those rows are taken out of their tiles and added one
+  // at a time on the vector units.  There a row never meets the sums of a query that does not see it, not even with weight
+  // zero (0 * Inf), and the fp32 weight meets the V value whole (the terms of a 16-bit weight would turn Inf into
+  // Inf + 0 * Inf).  us of the clean call -> with one such row per sequence (with every row taken singly, as it was before):
+  // 64 x 32 pairs x 155 positions, 16 tokens, fp16 36 -> 51 (171); 16 x 32 x 700, 32 tokens, bf16 37 -> 60 (623); 8 x 32 x 8192,
+  // 16 tokens, bf16 176 -> 291 (2159); 16 x 16 x 380 of 64, 9 tokens, fp16 10 -> 15 (65).
+  auto stream_checked = [&]() {
     for (int w0 = 0; w0 < nrows; w0 += kMWin) {
       const int wn = min(kMWin, nrows - w0);
       tabulate_positions(a, intervals, vrow, w0, wn, wave, lane, s_u.st.tab, s_pos[wave]);
 #pragma unroll 1
-      for (int i = 0; i < wn; ++i) {
-        const int p = clampi(__builtin_amdgcn_readfirstlane(s_pos[wave][i]), 0, a.max_len - 1);  // (plain pointers here)
-        if (p > last_any) continue;
-        const size_t cached = (bh * (size_t)a.max_len + (size_t)p) * ROWB;
-        const char* krow = p >= new0 ? new_row(a.k_new, p - new0) : (const char*)a.k + cached;
-        const char* vrow_p = p >= new0 ? new_row(a.v_new, p - new0) : (const char*)a.v + cached;
-        float w[G];
+      for (int base = 0; base < wn; base += TR) {
+        const TileRows tr = load_k(base, wn);
+        load_v(base, tr);
+        f32x4 w[G][S];
+        take_scores(w);
+        softmax_step(w, base, tr);
+        uint32_t apart[S];  // bit i: row 16 s + i is not finite (wave-uniform)
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          float d = 0.f;
-#pragma unroll 1
-          for (int mm = 0; mm < NK; ++mm) {
-            const u32x4 kp = *reinterpret_cast<const u32x4*>(krow + 16 * (4 * mm + c4));
-            const u32x4 qp = *reinterpret_cast<const u32x4*>(&s_q[(16 * g + qi) * kQRow + 16 * (4 * mm + c4)]);
-            d += Elt::dot(kp, Elt::make_q(qp, 1.f));
+        for (int s = 0; s < S; ++s) {
+          apart[s] = 0;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            bool wild = false;
+#pragma unroll
+            for (int k = 0; k < VW; ++k) wild = wild || Elt::not_finite(vr[s][t][k]);
+            const uint64_t who = __builtin_amdgcn_ballot_w64(wild);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) apart[s] |= (who >> (16 * c) & 0xffffu) != 0 ? 1u << (4 * c + t) : 0u;
+            if ((who >> (16 * c4) & 0xffffu) != 0) {
+#pragma unroll
+              for (int k = 0; k < VW; ++k) vr[s][t][k] = 0u;
+            }
           }
-          d += __shfl_xor(d, 16, 64);
-          d += __shfl_xor(d, 32, 64);
-          d = p - lim0 <= 16 * g + qi ? d : -INFINITY;
-          const float ref_new = fmaxf(ref[g], d), ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
-          const float alpha = ref[g] == ref_new ? 1.f : __builtin_amdgcn_exp2f((ref[g] - ref_safe) * post);
-          ref[g] = ref_new;
-          w[g] = __builtin_amdgcn_exp2f((d - ref_safe) * post);
-          lsum[g] = lsum[g] * alpha + (c4 == 0 ? w[g] : 0.f);
-          w[g] *= Elt::kWeightScale;
-#pragma unroll
-          for (int e = 0; e < NE; ++e) O[g][e] *= alpha;
         }
+        add_outputs(w);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-#pragma unroll
-          for (int u = 0; u < NE / 4; ++u) {
-            float vf[4];
-            Elt::unpack4(vrow_p + column(4 * c4 + r, u) * Elt::kBytes, vf);
+        for (int s = 0; s < S; ++s) {
+#pragma unroll 1
+          for (uint32_t todo = apart[s]; todo != 0; todo &= todo - 1) {
+            const int i = __builtin_ctz(todo);
+            const int p = __builtin_amdgcn_readfirstlane(s_pos[wave][base + 16 * s + i]);
+            const __amdgpu_buffer_rsrc_t row = p >= new0 ? slab_resource(new_row(a.v_new, p - new0), ROWB) : vslab;
+            const uint32_t row_off = p >= new0 ? 0u : (uint32_t)p * ROWB;
+            float wi[G];  // the row's weight for query 16 g + qi: in lane (qi, i / 4), element i % 4
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-              if (p - lim0 <= 16 * g + qi) {
+              const float x = (i & 2) != 0 ? ((i & 1) != 0 ? w[g][s][3] : w[g][s][2]) : ((i & 1) != 0 ? w[g][s][1] : w[g][s][0]);
+              wi[g] = __shfl(x, 16 * (i >> 2) + qi, 64) * Elt::kWeightScale;
+            }
 #pragma unroll
-                for (int k = 0; k < 4; ++k) O[g][4 * u + k][r] = fmaf(w[g], vf[k], O[g][4 * u + k][r]);
+            for (int r = 0; r < 4; ++r) {
+#pragma unroll
+              for (int u = 0; u < NE / 4; ++u) {
+                float vf[4];
+                const uint32_t off = row_off + (uint32_t)(column(4 * c4 + r, u) * Elt::kBytes);
+                if constexpr (Elt::kBytes == 4) Elt::unpack4(load_piece(row, off), vf);
+                else Elt::unpack4(__builtin_amdgcn_raw_buffer_load_b64(row, off, 0, kRowPolicy), vf);
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                  if (p - lim0 <= 16 * g + qi) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) O[g][4 * u + k][r] = fmaf(wi[g], vf[k], O[g][4 * u + k][r]);
+                  }
+                }
               }
             }
           }
@@ -587,9 +605,9 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
         for (int r = 0; r < 4; ++r) z = fmaf(O[g][e][r], 0.f, z);
       }
     }
-    if (__builtin_amdgcn_ballot_w64(z != 0.f) != 0) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != 0.f) != 0, 0)) {
       clear_state();
-      stream_by_row();
+      stream_checked();
     }
   }
   SPAN_STAMP_AFTER(4, "v", O[0][0][0] + lsum[0]);

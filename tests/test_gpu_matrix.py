@@ -181,3 +181,36 @@ def test_any_workspace_from_the_least_on(dtype, D, q_len, counts, gpu_device):
     call.desc.workspace_bytes = least - 1
     with pytest.raises(span.SpanAttnError):
         call()
+
+
+@pytest.mark.parametrize("dtype,D,q_len", [("bf16", 128, 32), ("f16", 64, 9), ("f32", 128, 8)])
+def test_a_row_that_is_not_finite_costs_about_one_more_pass(dtype, D, q_len, gpu_device):
+    """The pass is taken again with the row apart, not every row of the slice singly (which took 6 to 17 times the clean
+    call).  Bound: two passes, the second without loads ahead, and a few microseconds for the row: 4 times and 20 us."""
+    cfg = DecodeConfig(107, "matrix-inf-time", 16, 16, D, 700, 700, dtype, TOL)
+    ctx = np.full(cfg.batch, cfg.max_len, np.int32)
+    sp = SpanBatch.from_lists([[(0, 700)]] * cfg.batch, ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=gpu_device)
+    q = draw_queries(cfg, q_len, device=gpu_device)
+    lists = [_dev(a, gpu_device) for a in (sp.offsets, sp.starts, sp.ends, (ctx - q_len).astype(np.int32))]
+    call = span.prepare_span_decode_attn_multi(q, K, V, *lists, np.float32(cfg.scale), max_tokens=700, tokens_per_seq=sp.tokens_per_seq())
+
+    def microseconds():
+        for _ in range(5):
+            call()
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3 / 20)
+        return min(times)
+
+    clean = microseconds()
+    V[:, :, 699] = float("inf")
+    poisoned = microseconds()
+    print(f"[time] {dtype} D={D} q_len={q_len}: {clean:.1f} us clean, {poisoned:.1f} us with a row of Inf", flush=True)
+    assert poisoned <= 4 * clean + 20
