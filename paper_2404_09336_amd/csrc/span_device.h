@@ -122,6 +122,20 @@ constexpr int kTraceStamps = 16;
   } while (0)
 #endif
 
+// matrix kernel, 16-bit types: q stays as stored but for the sign of the score scale; with scale 0 it becomes 0, and what is
+// not finite NaN, which is what the scaled scores are.
+struct HalfQuery {
+  static __device__ __forceinline__ float post_scale(float scale) { return scale == 0.f ? 1.f : fabsf(scale); }
+  template <uint32_t kExponent>  // exponent bits of a value
+  static __device__ __forceinline__ uint32_t scaled(uint32_t q, float scale) {
+    if (__builtin_expect(scale == 0.f, 0)) {
+      constexpr uint32_t kNan = kExponent | (kExponent >> 1);
+      return ((q & kExponent) == kExponent ? kNan : 0u) | ((q >> 16 & kExponent) == kExponent ? kNan << 16 : 0u);
+    }
+    return scale < 0.f ? q ^ 0x80008000u : q;
+  }
+};
+
 // ---- storage types ---------------------------------------------------------------------------------
 // unpack: 16 bytes of a row -> fp32 (for the V accumulation).
 // The q.k partial product of a lane's 16 bytes never unpacks the 16-bit types: q stays in its stored
@@ -132,6 +146,20 @@ struct F32 {
   static constexpr int kBytes = 4, kPerVec = 4;
   static constexpr bool kPostScale = false;
   static constexpr float kWeightScale = 1.f;
+  // matrix kernel: the score scale as (what q is multiplied by) x (a positive factor for the finished scores).  The sign and
+  // the power of two go into q, exactly, so that a score is not larger than the scaled one; a scale that is 0, denormal or
+  // not finite goes there as it is.
+  static __device__ __forceinline__ bool plain_scale(float scale) {
+    const uint32_t exponent = __builtin_bit_cast(uint32_t, scale) & 0x7f800000u;
+    return exponent != 0 && exponent != 0x7f800000u;
+  }
+  static __device__ __forceinline__ float post_scale(float scale) {
+    return plain_scale(scale) ? __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, scale) & 0x007fffffu) | 0x3f800000u) : 1.f;
+  }
+  static __device__ __forceinline__ uint32_t scale_query(uint32_t q, float scale) {
+    const float factor = plain_scale(scale) ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, scale) & 0xff800000u) : scale;
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, q) * factor);
+  }
   struct Q {
     float f[4];
   };
@@ -160,7 +188,7 @@ struct F32 {
     return d;
   }
 };
-struct F16 {
+struct F16 : HalfQuery {
   static constexpr int kBytes = 2, kPerVec = 8;
   static constexpr bool kPostScale = true;
   // weights (at most 1) enter the second product of the matrix kernel times 2^15, fp16's largest power of two: the step of
@@ -198,6 +226,7 @@ struct F16 {
       f[2 * i + 1] = (float)h.y;
     }
   }
+  static __device__ __forceinline__ uint32_t scale_query(uint32_t q, float scale) { return scaled<0x7c00u>(q, scale); }
   static __device__ __forceinline__ bool not_finite(uint32_t w) { return (w & 0x7c00u) == 0x7c00u || (w & 0x7c000000u) == 0x7c000000u; }
   static __device__ __forceinline__ void unpack4(u32x2 r, float* f) {
     const f16x4 v = __builtin_bit_cast(f16x4, r);
@@ -214,7 +243,7 @@ struct F16 {
     return d;
   }
 };
-struct BF16 {
+struct BF16 : HalfQuery {
   static constexpr int kBytes = 2, kPerVec = 8;
   static constexpr bool kPostScale = true;
   static constexpr float kWeightScale = 1.f;
@@ -245,6 +274,7 @@ struct BF16 {
       f[2 * i + 1] = __builtin_bit_cast(float, w & 0xffff0000u);
     }
   }
+  static __device__ __forceinline__ uint32_t scale_query(uint32_t q, float scale) { return scaled<0x7f80u>(q, scale); }
   static __device__ __forceinline__ bool not_finite(uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; }
   static __device__ __forceinline__ void unpack4(u32x2 r, float* f) {
     const uint32_t v0 = r[0], v1 = r[1];

@@ -182,9 +182,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   // A weight is exp2((score - reference) * post) with the largest unscaled score as reference: the heaviest row's weight is
   // exactly 1 and what is rounded is the distance from it, never the scaled score.  (A rounded scaled reference inside an fma
   // leaves the heaviest row 2^r, r the rounding of the product: for scaled scores from 2^29 on r is no longer small.)
-  // post is positive (a hidden row's -Inf stays -Inf); a negative scale goes into the sign of q.
-  const float post = a.scale_log2e == 0.f ? 1e-37f : fabsf(a.scale_log2e);
-  const uint32_t q_sign = a.scale_log2e < 0.f ? (Elt::kBytes == 2 ? 0x80008000u : 0x80000000u) : 0u;
+  // post is positive (a hidden row's -Inf stays -Inf); the rest of the scale goes into q: see Elt::scale_query.
+  const float post = Elt::post_scale(a.scale_log2e);
 
   // Causal limit: query token j sees no position after lim0 + j.  In the append form the call's tokens sit at
   // positions new0 .. new0 + q_len - 1; those rows come from k_new / v_new, never from the cache.
@@ -553,7 +552,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     const int idx = tid + i * kThreads, j = idx / kPieces;
     const uint32_t piece = 16u * (uint32_t)(idx % kPieces);
     if (NQ * kPieces % kThreads != 0 && idx >= NQ * kPieces) continue;
-    for (int k = 0; k < 4; ++k) q_piece[i][k] ^= q_sign;
+    for (int k = 0; k < 4; ++k) q_piece[i][k] = Elt::scale_query(q_piece[i][k], a.scale_log2e);
     *reinterpret_cast<u32x4*>(&s_q[j * kQRow + piece]) = q_piece[i];
     if (writes_new && j < nq_here) {
       const int p = new0 + q0 + j;

@@ -94,3 +94,37 @@ def test_large_scores_of_the_appended_row(dtype, D, dense, gpu_device):
             got = span.span_decode_attn_append(q, k_new, v_new, K, V, _dev(pos, gpu_device), _dev(sp.offsets, gpu_device),
                                                _dev(sp.starts, gpu_device), _dev(sp.ends, gpu_device), SCALE, num_splits=splits)
         _check(got, ref, f"append {dtype} D={D} dense={dense} splits={splits}")
+
+
+def _random_multi(cfg, q_len, q_size, k_size, scale, device):
+    ctx = np.full(cfg.batch, cfg.max_len, np.int32)
+    sp = SpanBatch.from_lists([[(3, 40), (100, 300)], [(0, 300)], [(290, 300)]], ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=device)
+    q = draw_queries(cfg, q_len, device=device)
+    K *= k_size
+    q *= q_size
+    pos = (ctx - q_len).astype(np.int32)
+    ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos, scale, dtype=cfg.dtype)
+    lists = [_dev(a, device) for a in (sp.offsets, sp.starts, sp.ends, pos)]
+    got = span.span_decode_attn_multi(q, K, V, *lists, scale, max_tokens=300, tokens_per_seq=sp.tokens_per_seq())
+    return got.cpu().numpy().astype(np.float64), ref
+
+
+@pytest.mark.parametrize("dtype,size", [("f32", 1e18), ("bf16", 1e18), ("f16", 1e3)])
+@pytest.mark.parametrize("q_len", [2, 6])
+def test_scale_zero_weighs_all_rows_alike_whatever_their_scores(dtype, size, q_len, gpu_device):
+    """Scores of 10^37 (fp16: 10^7) and scale 0: the mean of the V rows each token sees, as with scores of 1."""
+    cfg = DecodeConfig(108, "matrix-scale-0", 3, 4, 64, 300, 300, dtype, TOL)
+    got, ref = _random_multi(cfg, q_len, size, size, np.float32(0), gpu_device)
+    assert float(np.abs(got - ref).max()) <= TOL
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("scale", [1.2e-38, -1.2e-38])
+@pytest.mark.parametrize("q_len", [2, 6, 20])
+def test_fp32_scores_beyond_the_range_before_they_are_scaled(D, scale, q_len, gpu_device):
+    """fp32 q.K of 10^39 under a scale that brings it back to some tens: the scale's size goes into q ahead of the product.
+    Scores up to 200 with a sum's rounding of a few 2^-24: weights to 200 * 4 * 2^-24 = 5e-5, outputs (|V| <= 4.5) to 2e-4."""
+    cfg = DecodeConfig(109, "matrix-tiny-scale", 3, 4, D, 300, 300, "f32", TOL)
+    got, ref = _random_multi(cfg, q_len, 2e18, 1e20, np.float32(scale), gpu_device)
+    assert np.isfinite(got).all() and float(np.abs(got - ref).max()) <= 2e-4
