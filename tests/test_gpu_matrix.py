@@ -214,3 +214,13 @@ def test_a_row_that_is_not_finite_costs_about_one_more_pass(dtype, D, q_len, gpu
     poisoned = microseconds()
     print(f"[time] {dtype} D={D} q_len={q_len}: {clean:.1f} us clean, {poisoned:.1f} us with a row of Inf", flush=True)
     assert poisoned <= 4 * clean + 20
+
+
+@pytest.mark.parametrize("dtype,D,q_len", [("f16", 128, 2), ("bf16", 64, 9), ("f32", 128, 20)])
+def test_limits_far_below_and_beyond_the_cache(dtype, D, q_len, gpu_device):
+    """Any int32 is a limit: the smallest ones show a token nothing (zero rows), the largest everything."""
+    cfg = DecodeConfig(110, "matrix-limits", 5, 3, D, 200, 200, dtype, TOL)
+    q_pos = np.array([-2**31, -2**31 + 70, -q_len, 1 - q_len, 2**31 - 1], np.int32)
+    got, ref = _run(cfg, [[(0, 90), (95, 200)]] * 5, q_len, gpu_device, q_pos=q_pos)
+    assert float(np.abs(got - ref).max()) <= TOL
+    assert not got[:3].any() and got[3, -1].any() and got[4].any(axis=-1).all()
