@@ -124,6 +124,7 @@ class Workload:
         if q_len > 1:          # diagnostic runs of the few-query call: it takes the place of the span call
             self.span_calls = few_query_calls(self, q_len, device)
         self.plan = span.span_plan_query(self.span_calls[0].desc)
+        self.launch = span.span_launch_query(self.span_calls[0].desc)
         self.coverage = sum(self.coverages) / len(self.coverages)
 
 
@@ -199,7 +200,7 @@ def compact_row(wl, steps, dense_steps=None, rounds=3):
             "span_gbps": round(s["gbps_event"], 1), "span_pct_peak": round(100 * s["gbps_event"] / HBM_PEAK_GBPS, 2),
             "dense_us": round(d["us_per_call_event"], 2), "dense_gbps": round(d["gbps_event"], 1),
             "speedup_vs_dense": round(d["us_per_call_event"] / s["us_per_call_event"], 3),
-            "slices_per_pair": wl.plan["max_splits"], "workgroups": wl.plan["workgroups"]}
+            "slices_per_pair": wl.launch["max_splits"], "workgroups": wl.launch["workgroups"]}
 
 
 def few_query_calls(wl, q_len, device):
@@ -234,7 +235,7 @@ def few_query_table(wl, device, steps, single_us):
         table[f"q_len_{q_len}"] = {"us_per_call": round(us, 2), "us_per_token": round(us / q_len, 2),
                                    "tokens_per_s": round(cfg.batch * q_len / us * 1e6, 0),
                                    "speedup_per_token_vs_one_query": round(single_us * q_len / us, 3),
-                                   "passes_over_span": 1}
+                                   "passes_over_span": span.span_launch_query(calls[0].desc)["launches"]}
     return table
 
 
@@ -288,10 +289,10 @@ def secondary_bytes(wl):
     """Bytes a span call moves besides the K / V rows of the span (first rotated copy), itemised so that they
     cannot hide inside the headline figure: q, out, span metadata, and the slices' partial states (written once,
     read once by the merging workgroup) when a (batch, head) pair is cut into several slices."""
-    cfg, plan = wl.cfg, wl.plan
+    cfg = wl.cfg
     sp = wl.host[0][0]
     pairs = cfg.batch * cfg.heads
-    partial = 2 * plan["workgroups"] * plan["queries_per_pass"] * (cfg.head_dim + 2) * 4 if plan["max_splits"] > 1 else 0
+    partial = 2 * wl.launch["partial_states"] * (cfg.head_dim + 2) * 4
     return {"q": wl.q_len * pairs * cfg.head_dim * cfg.elt_bytes, "out": wl.q_len * pairs * cfg.head_dim * 4,
             "span_metadata": 8 * int(sp.starts.size) + 4 * (cfg.batch + 1),
             "partial_states_write_plus_read": partial}
@@ -432,7 +433,7 @@ def phase_trace(args, device):
     wl = Workload(cfg, args.copies or auto_copies(cfg), device, coverage=args.coverage, num_splits=args.num_splits,
                   exact=not args.uniform_grid, host_lists=not args.no_host_lists, q_len=args.q_len)
     calls = wl.span_calls if args.only != "dense" else wl.dense_calls
-    wgs = max(span.span_plan_query(c.desc)["workgroups"] for c in calls)
+    wgs = max(span.span_launch_query(c.desc)["workgroups"] for c in calls)
     buf = torch.zeros((wgs, 16), dtype=torch.int64, device=device)
     prewarm(calls)
     lib.span_debug_set_trace(ctypes.c_void_p(buf.data_ptr()), wgs)   # workgroups beyond `wgs` would not stamp
@@ -445,8 +446,7 @@ def phase_trace(args, device):
             calls[i % len(calls)]()
         torch.cuda.synchronize()
         last = calls[49 % len(calls)]                   # every workgroup of the last call has overwritten its row
-        stamps = buf.cpu().numpy()[:span.span_plan_query(last.desc)["workgroups"]]
-        samples.append(stamps[stamps[:, 0] > 0].copy())     # (a few-query call launches fewer workgroups than its workspace has slots)
+        samples.append(buf.cpu().numpy()[:span.span_launch_query(last.desc)["workgroups"]].copy())
     lib.span_debug_set_trace(None, 0)
     rows = {}
     spans_us = []
@@ -471,6 +471,7 @@ def phase_trace(args, device):
     idx = 49 % len(calls)
     print(json.dumps({"mode": "phase-trace", "config": cfg.cfg_id, "kernel": args.only if args.only != "all" else "span",
                       "traced_copy": idx, "plan": span.span_plan_query(calls[idx].desc),
+                      "launch": span.span_launch_query(calls[idx].desc),
                       "kv_bytes_of_traced_call": (wl.span_bytes if args.only != "dense" else wl.dense_bytes)[idx],
                       "first_entry_to_last_stamp_us": round(float(np.median(spans_us)), 2),
                       "us_per_call_hip_events_with_stamps": round(r["us_per_call_event"], 2),

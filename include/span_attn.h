@@ -98,7 +98,8 @@ typedef struct span_attn_desc {
                               every slice to its runs of cache positions on the host and passes the
                               runs in the kernel arguments in place of the slice table: the kernel
                               then reads no span metadata from device memory (about 2 % faster on
-                              raggedly sliced batches).  The result is the same, bit for bit.  They must
+                              raggedly sliced batches).  The result is the same, bit for bit
+                              (calls on the matrix cores take the counts only).  They must
                               describe the same spans as the device arrays (not checked; memory safety
                               does not depend on it) and are read during the call only.  Leave them
                               NULL when the device lists change without the host knowing (span_advance
@@ -254,10 +255,11 @@ int span_validate(int32_t batch, int32_t num_intervals, const int32_t* span_offs
  * cut into one slice has its output row written directly; with more slices the partial softmax
  * states go through the workspace and the workgroup that finishes last for the pair merges them by
  * log-sum-exp (still one launch).  Pure host arithmetic.
- */
-/* For few-query calls (q_len of three and more) this is the partition the workspace is sized for: slots of
- * queries_per_pass token states each.  The launch regroups them, all tokens of the call at once, into as many
- * slices as they hold.
+ *
+ * For calls on the matrix cores (three tokens and more, and the two-token calls named at
+ * span_decode_attn_multi) this is the partition whose pool of partial states, slots of
+ * queries_per_pass tokens, a workspace must hold at least.  The launch shares the states out
+ * again among all tokens of the call; span_launch_query tells what it runs.
  */
 typedef struct span_plan_info {
   int32_t exact;           /* 1: slices sized from tokens_per_seq (no idle workgroup); 0: every
@@ -265,13 +267,27 @@ typedef struct span_plan_info {
   int32_t slice_tokens;    /* attended positions per slice (upper bound in exact mode)            */
   int32_t max_splits;      /* most slices any (batch, head) pair is cut into                      */
   int32_t slice_limit;     /* most positions one slice can own (a constant of the build)                */
-  int64_t workgroups;      /* workgroups the call launches                                        */
+  int64_t workgroups;      /* workgroups of the partition (not on the matrix cores: of the launch)  */
   int64_t workspace_bytes; /* same value as span_workspace_bytes()                                */
   int32_t runs_in_arguments; /* 1: host_span_* were given and the plan fits: the slices' position runs
-                              travel in the kernel arguments (span form)                          */
+                              travel in the kernel arguments (span form; never on the matrix cores) */
   int32_t queries_per_pass;  /* query tokens whose partial states a slot of the workspace holds (1, 2, 4 or 16) */
 } span_plan_info_t;
 int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* info);
+
+/* What the call described by desc launches: with desc->workspace_bytes where desc->workspace is given, else with
+ * a workspace of span_workspace_bytes().  Pure host arithmetic. */
+typedef struct span_launch_info {
+  int32_t matrix_cores;    /* 1: the call runs on the matrix cores                                 */
+  int32_t launches;        /* kernel launches of the call                                         */
+  int32_t tokens;          /* query tokens of a launch (the last one may have fewer)                */
+  int32_t max_splits;      /* most slices any (batch, head) pair is cut into                      */
+  int32_t slice_tokens;    /* attended positions per slice (upper bound)                          */
+  int32_t query_blocks;    /* workgroups that share a slice, each for its own tokens                */
+  int64_t workgroups;      /* workgroups of the (first) launch                                    */
+  int64_t partial_states;  /* token states, of head_dim + 2 floats, that the call hands over          */
+} span_launch_info_t;
+int span_launch_query(const span_attn_desc_t* desc, span_launch_info_t* info);
 
 /* Bytes of device workspace the call described by desc wants (0 when one slice is used); desc->workspace and
  * desc->workspace_bytes are not looked at. */

@@ -10,5 +10,5 @@ from .binding import (  # noqa: F401
     prepare_span_decode_attn, prepare_dense_decode_attn, prepare_span_decode_attn_append,
     prepare_dense_decode_attn_append,
     span_validate, span_build, span_blocks_to_intervals, span_intervals_to_blocks,
-    span_plan_query, span_workspace_bytes, span_workspace_init, span_strerror,
+    span_plan_query, span_launch_query, span_workspace_bytes, span_workspace_init, span_strerror,
 )

@@ -42,6 +42,15 @@ class PlanInfo(ctypes.Structure):
                 "runs_in_arguments": bool(self.runs_in_arguments), "queries_per_pass": int(self.queries_per_pass)}
 
 
+class LaunchInfo(ctypes.Structure):
+    _fields_ = [("matrix_cores", ctypes.c_int32), ("launches", ctypes.c_int32), ("tokens", ctypes.c_int32),
+                ("max_splits", ctypes.c_int32), ("slice_tokens", ctypes.c_int32), ("query_blocks", ctypes.c_int32),
+                ("workgroups", ctypes.c_int64), ("partial_states", ctypes.c_int64)]
+
+    def as_dict(self):
+        return {"matrix_cores": bool(self.matrix_cores), **{n: getattr(self, n) for n, _ in self._fields_[1:]}}
+
+
 def lib_path() -> str:
     """The product library, or the measurement variant of it that SPAN_ATTN_VARIANT names (see build.py)."""
     variant = os.environ.get("SPAN_ATTN_VARIANT", "")
@@ -79,6 +88,8 @@ def load_library():
         lib.span_validate.restype = ctypes.c_int
         lib.span_plan_query.argtypes = [DP, ctypes.POINTER(PlanInfo)]
         lib.span_plan_query.restype = ctypes.c_int
+        lib.span_launch_query.argtypes = [DP, ctypes.POINTER(LaunchInfo)]
+        lib.span_launch_query.restype = ctypes.c_int
         lib.span_workspace_bytes.argtypes = [DP]
         lib.span_workspace_bytes.restype = ctypes.c_size_t
         lib.span_workspace_init.argtypes = [DP]
@@ -136,6 +147,14 @@ def span_plan_query(desc: _Desc) -> dict:
     rc = load_library().span_plan_query(ctypes.byref(desc), ctypes.byref(info))
     if rc != 0:
         raise SpanAttnError(rc, "span_plan_query")
+    return info.as_dict()
+
+
+def span_launch_query(desc: _Desc) -> dict:
+    info = LaunchInfo()
+    rc = load_library().span_launch_query(ctypes.byref(desc), ctypes.byref(info))
+    if rc != 0:
+        raise SpanAttnError(rc, "span_launch_query")
     return info.as_dict()
 
 

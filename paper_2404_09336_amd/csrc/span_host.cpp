@@ -524,7 +524,7 @@ extern "C" int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* i
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
   spanattn::RunTables runs;
-  const spanattn::Partition p = spanattn::plan_partition(desc, nullptr, &runs);
+  const spanattn::Partition p = spanattn::plan_partition(desc, nullptr, spanattn::runs_on_matrix_cores(desc) ? nullptr : &runs);
   info->runs_in_arguments = p.runs ? 1 : 0;
   info->queries_per_pass = p.queries_per_pass;
   info->exact = p.even ? 1 : 0;
@@ -533,6 +533,37 @@ extern "C" int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* i
   info->slice_limit = spanattn::kMaxSlice;
   info->workgroups = (int64_t)p.total_slices * desc->heads;
   info->workspace_bytes = (int64_t)spanattn::workspace_bytes(desc, p);
+  return SPAN_OK;
+}
+
+extern "C" int span_launch_query(const span_attn_desc_t* desc, span_launch_info_t* info) {
+  if (!info) return SPAN_ERR_NULL;
+  const int rc = spanattn::check_desc(desc);
+  if (rc != SPAN_OK) return rc;
+  const spanattn::Partition p = spanattn::plan_partition(desc);
+  const int64_t states = !desc->workspace ? spanattn::most_states(desc, p) : spanattn::states_that_fit(desc, p);
+  const int32_t n = spanattn::query_tokens(desc);
+  spanattn::MatrixPlan m;
+  std::vector<uint32_t> table((size_t)spanattn::kMaxPlanSlices);
+  if (spanattn::plan_matrix(desc, p, states, &m, table.data())) {
+    info->matrix_cores = 1;
+    info->launches = (n + m.tokens - 1) / m.tokens;
+    info->tokens = m.tokens;
+    info->max_splits = m.num_splits;
+    info->slice_tokens = m.slice_tokens;
+    info->query_blocks = (m.tokens + 16 * m.groups - 1) / (16 * m.groups);
+    info->workgroups = (int64_t)m.total_slices * desc->heads * info->query_blocks;
+    info->partial_states = m.states / m.tokens * n * desc->heads;
+  } else {
+    info->matrix_cores = 0;
+    info->launches = 1;
+    info->tokens = n;
+    info->max_splits = p.num_splits;
+    info->slice_tokens = p.slice_tokens;
+    info->query_blocks = 1;
+    info->workgroups = (int64_t)p.total_slices * desc->heads;
+    info->partial_states = p.num_splits > 1 ? info->workgroups * n : 0;
+  }
   return SPAN_OK;
 }
 

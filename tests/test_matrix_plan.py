@@ -27,3 +27,33 @@ def test_matrix_plan_covers_every_position_and_fits_the_workspace(tmp_path):
 def test_calls_that_are_not_sliced_ask_for_no_workspace(batch, positions, q_len):
     tok = np.full(batch, positions)
     assert binding.span_workspace_bytes(binding.make_desc(batch, 32, 128, 1000, 1, 10, positions, 0, tokens_per_seq=tok, q_len=q_len)) == 0
+
+
+@pytest.mark.parametrize("batch,heads,D,dtype,positions,q_len,want", [
+    (1, 4, 128, 1, [16], 64, dict(workgroups=16, query_blocks=4, max_splits=1, partial_states=0)),       # tokens shared out
+    (4, 32, 128, 1, [800] * 4, 8, dict(workgroups=512, query_blocks=1, max_splits=4, partial_states=4096)),
+    (8, 32, 128, 1, [600] * 8, 2, dict(workgroups=512, query_blocks=1, max_splits=2, partial_states=1024)),
+    (64, 32, 128, 1, [155] * 64, 16, dict(workgroups=2048, query_blocks=1, max_splits=1, partial_states=0)),
+    (30, 32, 128, 0, [500] * 30, 64, dict(workgroups=1920, query_blocks=2, max_splits=1, partial_states=0)),
+    (64, 32, 128, 1, [155] * 64, 2, dict(matrix_cores=False, workgroups=2048, max_splits=1, partial_states=0)),
+    (1, 32, 128, 1, [8000], 1, dict(matrix_cores=False, workgroups=512, max_splits=16, partial_states=512)),
+])
+def test_launch_query_tells_what_the_call_runs(batch, heads, D, dtype, positions, q_len, want):
+    """Against the launch rules by hand: 512 workgroups wanted, slices of 128 positions at least, 16 tokens per group."""
+    tok = np.array(positions)
+    off = np.arange(batch + 1, dtype=np.int32)
+    d = binding.make_desc(batch, heads, D, 8192, dtype, batch, int(tok.max()), 0, tokens_per_seq=tok, q_len=q_len,
+                          host_spans=(off, np.zeros(batch, np.int32), tok.astype(np.int32)))
+    got = binding.span_launch_query(d)
+    assert {k: got[k] for k in want} == want and got["launches"] == 1 and got["tokens"] == q_len
+    assert got["max_splits"] * got["slice_tokens"] >= tok.max()
+    if got["matrix_cores"]:
+        assert not binding.span_plan_query(d)["runs_in_arguments"]
+
+
+def test_launch_query_of_a_fixed_number_of_slices():
+    """num_splits stands: as many tokens a launch as a slot holds states (16 for 16-bit rows of 128, else 4)."""
+    for D, dtype, per in ((128, 1, 16), (64, 1, 4), (128, 0, 4)):
+        got = binding.span_launch_query(binding.make_desc(2, 8, D, 1000, dtype, 10, 1000, 5, q_len=20))
+        assert (got["launches"], got["tokens"], got["max_splits"]) == (-(-20 // per), per, 5)
+        assert got["workgroups"] == 2 * 8 * 5 and got["partial_states"] == 2 * 8 * 5 * 20
