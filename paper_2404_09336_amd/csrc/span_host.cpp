@@ -280,8 +280,8 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
     // Run mode pays where the launch carries a slice table anyway (sequences with different numbers of slices):
     // kernel arguments of that size cost a few tenths of a microsecond per launch, which a batch that needs no
     // table would pay on top (measured: batch 64 x 155 positions, one slice each, 27.7 -> 27.9 us with runs;
-    // batch 8 and batch 16 sliced raggedly, 24.1 -> 23.7 us and 31.1 -> 30.8 us).
-    if (lists && runs && p.exact) p.runs = plan_runs(d, tokens, p, runs);
+    // batch 8 and batch 16 sliced raggedly, 24.1 -> 23.7 us and 31.1 -> 30.8 us).  The matrix kernel takes no runs.
+    if (lists && runs && p.exact && !runs_on_matrix_cores(d)) p.runs = plan_runs(d, tokens, p, runs);
     return p;
   }
   const int64_t pairs = (int64_t)d->batch * d->heads;
@@ -524,7 +524,7 @@ extern "C" int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* i
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
   spanattn::RunTables runs;
-  const spanattn::Partition p = spanattn::plan_partition(desc, nullptr, spanattn::runs_on_matrix_cores(desc) ? nullptr : &runs);
+  const spanattn::Partition p = spanattn::plan_partition(desc, nullptr, &runs);
   info->runs_in_arguments = p.runs ? 1 : 0;
   info->queries_per_pass = p.queries_per_pass;
   info->exact = p.even ? 1 : 0;

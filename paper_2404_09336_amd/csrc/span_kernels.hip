@@ -719,7 +719,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
     own.host_span_offsets = own.host_span_starts = own.host_span_ends = nullptr;
     d = &own;
   }
-  const Partition p = plan_partition(d, a.table, kDense || runs_on_matrix_cores(d) ? nullptr : &runs);
+  const Partition p = plan_partition(d, a.table, kDense ? nullptr : &runs);
   const GridMode mode = p.runs ? GridMode::kRuns : (p.exact ? GridMode::kTable : GridMode::kPlain);
   const size_t need = workspace_least_bytes(d, p);
   if (need > 0 && (!d->workspace || ((uintptr_t)d->workspace & 255u) || d->workspace_bytes < need))
