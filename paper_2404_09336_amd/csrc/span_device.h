@@ -47,7 +47,7 @@ struct LaunchArgs {
   float* part_acc;  // [slots, NQ, D]  un-normalised
   int32_t heads, max_len, num_intervals, slice_tokens, num_splits, max_tokens;
   int32_t q_len;                    // query tokens per sequence in q and out ([batch, q_len, heads, D])
-  int32_t q_first;                  // few-query variant: first query token this launch handles
+  int32_t q_first;                  // matrix kernel: first query token this launch handles
   float scale_log2e;
   int32_t total_slices;             // table mode: entries of `table` in use
   int32_t even;                     // 1: a sequence's slices share its own token count evenly; 0: slice_tokens each

@@ -63,8 +63,8 @@ int check_desc(const span_attn_desc_t* d) {
 int32_t query_tokens(const span_attn_desc_t* d) { return d->q_len > 1 ? d->q_len : 1; }
 
 // Query tokens a slot of the workspace holds (one partial state each): 1, 2, 4, or 16 for 16-bit types with head_dim
-// 128 from three tokens on.  One- and two-token calls run as planned with it; from three tokens on plan_matrix regroups
-// the slots.
+// 128 from three tokens on.  Calls on the vector units run as planned with it; those on the matrix cores (three tokens and
+// more, some with two) share the states out again, see plan_matrix.
 static int32_t queries_per_pass(const span_attn_desc_t* d) {
   const int32_t n = query_tokens(d);
   if (n >= 3 && d->dtype != SPAN_F32 && d->head_dim == 128) return 16;
@@ -309,12 +309,14 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
 // Few-query calls on the matrix cores: all tokens of the call in one launch, a workgroup serving up to 64 of them with
 // one pass over its rows.
 //
-// From three tokens on for every type and head_dim, two tokens see below.  Measured against the passes it replaces (four tokens on the vector
-// units, sixteen on the matrix cores, one launch per pass): batch 16 x ~380 positions, 16 heads x 64, fp16, 9 tokens
+// From three tokens on for every type and head_dim, two tokens see below.  Measured against the passes it replaces (four
+// tokens on the vector units, sixteen on the matrix cores, one launch per pass): batch 16 x ~380 positions, 16 heads x 64, fp16, 9 tokens
 // 63.9 -> 14.7 us; batch 8 x ~600, 32 heads x 128, fp32, 8 tokens 83.6 -> 39.7 us; 3 tokens, batch 16 x ~370, fp32 49.9 ->
 // 45.3 us; batch 16 x ~700, bf16, 32 tokens 96.4 -> 50.1 us; batch 32 x 1000, bf16, 64 tokens 313 -> 130 us.
 //
-// Slices.  512 workgroups a call (two per CU), but one slice per sequence at least and one resident round at most: of
+// Slices.  512 workgroups a call (two per CU), but one slice per sequence at least and 1024, 768 or 512 workgroups at most for
+// 16, 32 or 64 tokens a workgroup (one resident round of rows of 64; fp32 rows of 128, and 16-bit ones of more than 16 tokens,
+// run two a CU and take up to two): of
 // 256, 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 shapes; more only pays for itself in
 // partial states, which grow with the tokens (batch 16 x ~700, 32 tokens, 16 slices per head against 32: 50.4 and 59.3 us).
 // The slices have to fit the workspace's token states, so sequences that stay in one slice, which need no state, come after
@@ -381,7 +383,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
   while (m->groups > 1 && pairs * blocks_for(m->groups) < kMatrixPairs) m->groups /= 2;
   if (d->batch * blocks_for(m->groups) > 65535) m->tokens = n = 16 * m->groups;  // (grid.z limit)
   const int64_t blocks = blocks_for(m->groups);
-  const int64_t per_cu = m->groups == 1 ? 4 : (m->groups == 2 ? 3 : 2);  // resident workgroups
+  const int64_t per_cu = m->groups == 1 ? 4 : (m->groups == 2 ? 3 : 2);
   const int64_t most = 256 * per_cu / (d->heads * blocks), wanted = ceil_div(kMatrixWorkgroups, d->heads * blocks);
   const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
   if (!p.even) {  // the counts are not known: every sequence gets the same number of slices

@@ -105,10 +105,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   __shared__ u32x4 s_stage[kWavesPerBlock][2][U][64];  // measurement build: U K tiles and U V tiles of 1 KiB per wave
 #endif
 
-  // Query token j of this launch is row (b, q_first + j, h) of q and out; a launch whose last tokens do
-  // not exist (q_len not a multiple of NQ) computes them from the last real one and never writes them.
-  const int nq_here = NQ == 1 ? 1 : min(NQ, a.q_len - a.q_first);  // (the one-token kernel serves one token, whatever q_len says)
-  auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(a.q_first + min(j, nq_here - 1))) * heads + h; };
+  // Query token j is row (b, j, h) of q and out.  (a.q_len is NQ; with the constant in its place the compiler's order costs
+  // batch 64 x ~155 positions 0.8 us of 27.0.)
+  auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)j) * heads + h; };
   // q pieces of this lane.  Scores carry the factor scale*log2(e), so that exp() becomes exp2(): fp32 q is
   // multiplied by it here, 16-bit q stays as stored and the finished dot product is multiplied instead.
   typename Elt::Q qv[NQ];
@@ -118,11 +117,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     qv[j] = Elt::make_q(qr, a.scale_log2e);
   }
   const float post = Elt::kPostScale ? a.scale_log2e : 1.f;
-  // Causal limit (few-query variant): query token j sees no position after its own, q_pos[b] + q_first + j.
+  // Causal limit (few-query variant): query token j sees no position after its own, q_pos[b] + j.
   int lim[NQ];
 #pragma unroll
   for (int j = 0; j < NQ; ++j)  // (clamped: any q_pos at or beyond the cache length means "no limit", without overflow)
-    lim[j] = a.q_pos ? min(a.q_pos[b], kMaxLen) + a.q_first + j : 0x7fffffff;
+    lim[j] = a.q_pos ? min(a.q_pos[b], kMaxLen) + j : 0x7fffffff;
 
   // ---- step 1: how many attended positions does the sequence have, which are mine ----------------
   int n_total;
@@ -164,10 +163,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     *reinterpret_cast<u32x4*>((char*)a.k + row) = kn_raw;
     *reinterpret_cast<u32x4*>((char*)a.v + row) = vn_raw;
   }
-  if constexpr (NQ > 1) {  // the rows of this pass's tokens, one token per wave
+  if constexpr (NQ > 1) {  // the new tokens' rows, one token per wave
     if (append_many && split == 0 && lane < LPR) {
-      for (int i = wave; i < nq_here; i += kWavesPerBlock) {
-        const int pos_i = min(a.append_pos[b], kMaxLen) + a.q_first + i;
+      for (int i = wave; i < NQ; i += kWavesPerBlock) {
+        const int pos_i = min(a.append_pos[b], kMaxLen) + i;
         if (pos_i >= 0 && pos_i < a.max_len) {
           const size_t src = qrow(i) * ROWB + (uint32_t)lir * 16u;
           const size_t row = (bh * (size_t)a.max_len + (size_t)pos_i) * ROWB + (uint32_t)lir * 16u;
@@ -304,8 +303,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
           todo &= todo - 1;
           u32x4 kb, vb;  // every row group fetches the same row
           if (append_many) {
-            const int i = pb - lim[0];     // the token that brought this row
-            if (i >= nq_here) continue;    // (a padded pass: no such token, and no token that could see it)
+            const int i = pb - lim[0];  // the token that brought this row
             const size_t src = qrow(i) * ROWB + lane_off;
             kb = *reinterpret_cast<const u32x4*>((const char*)a.k_new + src);
             vb = *reinterpret_cast<const u32x4*>((const char*)a.v_new + src);
@@ -454,7 +452,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   auto store_rows = [&](const float* ll, const float* oo) {
 #pragma unroll
     for (int j = 0; j < NQ; ++j) {
-      if (j < nq_here) a.out[qrow(j) * D + t] = ll[j] > 0.f ? oo[j] / ll[j] : 0.f;
+      a.out[qrow(j) * D + t] = ll[j] > 0.f ? oo[j] / ll[j] : 0.f;
     }
   };
 
@@ -479,7 +477,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   if (owns) {
 #pragma unroll
     for (int j = 0; j < NQ; ++j) {
-      if (j >= nq_here) continue;  // (a padded pass: tokens that do not exist leave no state)
       if (cnt > 0) publish(&a.part_acc[(my_slot * NQ + j) * D + t], o[j]);
       if (t == 0) {
         publish(&a.part_ml[(my_slot * NQ + j) * 2], M[j]);
@@ -519,14 +516,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
       const size_t slot = slot0 + (size_t)min(s0 + k * G, nsl - 1) * H;  // (past the end: a slot that exists, unused)
 #pragma unroll
       for (int j = 0; j < NQ; ++j) {
-        if (j < nq_here) {
-          ms[k][j] = observe(&a.part_ml[(slot * NQ + j) * 2]);
-          ls[k][j] = observe(&a.part_ml[(slot * NQ + j) * 2 + 1]);
-          as[k][j] = observe(&a.part_acc[(slot * NQ + j) * D + t]);
-        } else {
-          ms[k][j] = -INFINITY;
-          ls[k][j] = as[k][j] = 0.f;
-        }
+        ms[k][j] = observe(&a.part_ml[(slot * NQ + j) * 2]);
+        ls[k][j] = observe(&a.part_ml[(slot * NQ + j) * 2 + 1]);
+        as[k][j] = observe(&a.part_acc[(slot * NQ + j) * D + t]);
       }
     }
 #pragma unroll
@@ -696,7 +688,7 @@ int launch_queries(const LaunchArgsTable& a, const RunTables* runs, int nq, Grid
                    hipStream_t stream) {
   if constexpr (!kDense) {  // the few-query variant exists for the span form only
     if (nq == 2) return launch_typed<Elt, D, false, 2>(a, runs, mode, batch, stream);
-    if (nq != 1) return SPAN_ERR_SHAPE;  // (not reachable: the planner asks only for passes that exist)
+    if (nq != 1) return SPAN_ERR_SHAPE;  // (not reachable: three tokens and more run on the matrix cores)
   }
   return launch_typed<Elt, D, kDense, 1>(a, runs, mode, batch, stream);
 }
@@ -768,30 +760,19 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
     return SPAN_OK;
   }
 
-  // One pass over the span serves up to p.queries_per_pass query tokens; more tokens take more passes,
-  // one after the other on the stream (they share the workspace).
   const bool d128 = d->head_dim == 128;
-  for (int32_t first = 0; first < a.q_len; first += p.queries_per_pass) {
-    a.q_first = first;
-    const int nq = p.queries_per_pass;
-    int lrc;
-    switch (d->dtype) {
-      case SPAN_F32:
-        lrc = d128 ? launch_queries<F32, 128, kDense>(a, &runs, nq, mode, d->batch, stream)
-                   : launch_queries<F32, 64, kDense>(a, &runs, nq, mode, d->batch, stream);
-        break;
-      case SPAN_F16:
-        lrc = d128 ? launch_queries<F16, 128, kDense>(a, &runs, nq, mode, d->batch, stream)
-                   : launch_queries<F16, 64, kDense>(a, &runs, nq, mode, d->batch, stream);
-        break;
-      default:
-        lrc = d128 ? launch_queries<BF16, 128, kDense>(a, &runs, nq, mode, d->batch, stream)
-                   : launch_queries<BF16, 64, kDense>(a, &runs, nq, mode, d->batch, stream);
-        break;
-    }
-    if (lrc != SPAN_OK) return lrc;
+  const int nq = a.q_len;
+  switch (d->dtype) {
+    case SPAN_F32:
+      return d128 ? launch_queries<F32, 128, kDense>(a, &runs, nq, mode, d->batch, stream)
+                  : launch_queries<F32, 64, kDense>(a, &runs, nq, mode, d->batch, stream);
+    case SPAN_F16:
+      return d128 ? launch_queries<F16, 128, kDense>(a, &runs, nq, mode, d->batch, stream)
+                  : launch_queries<F16, 64, kDense>(a, &runs, nq, mode, d->batch, stream);
+    default:
+      return d128 ? launch_queries<BF16, 128, kDense>(a, &runs, nq, mode, d->batch, stream)
+                  : launch_queries<BF16, 64, kDense>(a, &runs, nq, mode, d->batch, stream);
   }
-  return SPAN_OK;
 }
 
 }  // namespace
