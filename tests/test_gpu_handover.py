@@ -94,8 +94,8 @@ def test_uniform_grid_with_empty_slices_is_bit_reproducible(gpu_device):
 
 @pytest.mark.parametrize("q_len", [2, 5, 16])
 def test_sliced_few_query_calls_are_bit_reproducible(q_len, gpu_device):
-    """The few-query passes hand over one state per query token and slice (two tokens: vector-ALU pass; five and
-    sixteen: the sixteen-token pass, five leaving eleven states of the slot unwritten)."""
+    """The matrix kernel hands over one state per query token and slice (two tokens on the vector units:
+    test_gpu_two_tokens.py)."""
     cfg = CONFIGS[2]
     sp = draw_spans(cfg)
     tok = sp.tokens_per_seq()

@@ -9,6 +9,7 @@ import torch
 
 import oracle
 import paper_2404_09336_amd as span
+from test_gpu_multi_append import run_case as run_append
 from workloads import DecodeConfig, SpanBatch, draw_qkv, draw_queries, to_host_raw
 
 pytestmark = pytest.mark.gpu
@@ -30,9 +31,13 @@ def _run(cfg, per_seq, q_len, device, q_pos="end", poison=None, **kw):
     code, _, _, tok = span.span_validate(sp.offsets, sp.starts, sp.ends, sp.ctx_lens)
     assert code == 0
     kw.setdefault("tokens_per_seq", tok)
-    out = span.span_decode_attn_multi(q, K, V, _dev(sp.offsets, device), _dev(sp.starts, device), _dev(sp.ends, device),
-                                      None if pos is None else _dev(pos, device), np.float32(cfg.scale),
-                                      max_tokens=int(tok.max()), **kw)
+    launched = kw.pop("launched", None)
+    call = span.prepare_span_decode_attn_multi(q, K, V, _dev(sp.offsets, device), _dev(sp.starts, device), _dev(sp.ends, device),
+                                               None if pos is None else _dev(pos, device), np.float32(cfg.scale),
+                                               max_tokens=int(tok.max()), **kw)
+    if launched is not None:
+        launched.update(span.span_launch_query(call.desc))
+    out = call()
     torch.cuda.synchronize()
     ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos,
                                  np.float32(cfg.scale), dtype=cfg.dtype)
@@ -43,8 +48,8 @@ def _run(cfg, per_seq, q_len, device, q_pos="end", poison=None, **kw):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("q_len", [3, 16, 17, 32, 33, 64])
 def test_tile_and_group_edges(dtype, D, q_len, gpu_device):
-    """Token counts around the groups of 16; rows per wave around the tiles of 16 and 32 rows, and a slice that takes
-    more than one position window of a wave (2048 rows a workgroup).  Many pairs: a workgroup serves all tokens."""
+    """Token counts around the groups of 16; rows per wave around the tiles of 16 and 32 rows; the long sequences in slices
+    of up to 261 rows (whole ones: test_large_slices).  Many pairs: a workgroup serves all tokens."""
     cfg = DecodeConfig(96, "matrix-edges", 10, 13, D, 2500, 2500, dtype, TOL)
     L = cfg.max_len
     spans = [1, 15, 16, 17, 61, 64, 65, 129, 700, 2347]
@@ -224,3 +229,70 @@ def test_limits_far_below_and_beyond_the_cache(dtype, D, q_len, gpu_device):
     got, ref = _run(cfg, [[(0, 90), (95, 200)]] * 5, q_len, gpu_device, q_pos=q_pos)
     assert float(np.abs(got - ref).max()) <= TOL
     assert not got[:3].any() and got[3, -1].any() and got[4].any(axis=-1).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len", [5, 20, 40])
+def test_large_slices(dtype, D, q_len, gpu_device):
+    """One slice per sequence (num_splits = 1) for 16, 32 and 64 tokens a workgroup: rows in quarters up to 383 positions a
+    slice, from 384 on tiles dealt to the waves in turn, and beyond 2048 (512 a wave) more than one position window."""
+    cfg = DecodeConfig(111, "matrix-large-slices", 6, 3, D, 4200, 4200, dtype, TOL)
+    L = cfg.max_len
+    for spans in ([353, 361, 367, 368, 17, 1], [383, 384, 385, 2047, 2048, 2049], [2060, 2081, 2112, 3000, 4099, 4195]):
+        per_seq = [[(3, 3 + n // 3), (L - (n - n // 3), L)] if n > 2 else [(L - n, L)] for n in spans]
+        launched = {}
+        got, ref = _run(cfg, per_seq, q_len, gpu_device, num_splits=1, tokens_per_seq=None, launched=launched)
+        assert launched["max_splits"] == 1 and launched["launches"] == 1 and max(spans) <= launched["slice_tokens"] < max(spans) + 16
+        assert (launched["slice_tokens"] >= 384) == (max(spans) >= 384)
+        assert launched["query_blocks"] == (2 if (q_len, D, dtype) == (40, 128, "f32") else 1)
+        assert np.isfinite(got).all() and float(np.abs(got - ref).max()) <= TOL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len", [17, 32, 40, 64])
+def test_many_tokens_a_workgroup_with_rows_that_are_not_finite(dtype, D, q_len, gpu_device):
+    """130 pairs: a workgroup serves 32 or 64 tokens.  +-Inf and NaN in V at the 10th token's row and later ones."""
+    cfg = DecodeConfig(112, "matrix-inf-groups", 10, 13, D, 500, 500, dtype, TOL)
+    q_pos = (400 + 3 * np.arange(10)).astype(np.int32)
+
+    def poison(K, V):
+        for b in range(10):
+            p = int(q_pos[b]) + q_len
+            V[b, :, p - 7, ::2] = float("inf")
+            V[b, :, p - 5, 1::4] = float("-inf")
+            V[b, :, p - 5, 3::4] = float("nan")
+            V[b, :, p - 3, ::4] = float("-inf")       # meets +inf: NaN
+
+    launched = {}
+    got, ref = _run(cfg, [[(0, 100 + b), (350, 500)] for b in range(10)], q_len, gpu_device, q_pos=q_pos, poison=poison, launched=launched)
+    assert launched["query_blocks"] == (2 if (dtype, D) == ("f32", 128) and q_len > 32 else 1)
+    assert np.isfinite(ref[:, :q_len - 7]).all() and np.isinf(ref).any() and np.isnan(ref).any()
+    ok = np.isfinite(ref)
+    assert np.array_equal(np.isfinite(got), ok) and float(np.abs(got[ok] - ref[ok]).max()) <= TOL
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len", [17, 32, 64])
+def test_many_tokens_a_workgroup_append_their_rows(dtype, D, q_len, gpu_device):
+    """130 pairs, as above, in the append form: outputs against the oracle on the updated cache, the cache bit for bit."""
+    cfg = DecodeConfig(113, "matrix-append-groups", 10, 13, D, 600, 600, dtype, TOL)
+    pos = (300 + 17 * np.arange(10)).astype(np.int32)
+    sp = SpanBatch.from_lists([[(0, 11), (40 + 3 * b, 150 + 7 * b), (int(pos[b]) - 20, int(pos[b]) + q_len)] for b in range(10)], pos + q_len)
+    run_append(cfg, sp, pos, q_len, gpu_device, what=f"130 pairs {dtype} D={D} q_len={q_len}")
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("q_len", [3, 16, 20])
+def test_whole_sequences_dealt_by_length(dtype, D, q_len, gpu_device):
+    """20 sequences x 32 heads, 301 .. 453 positions, are not sliced, more than one turn of 256 workgroups, and the longest
+    is 20 % over the mean: the table that deals them longest first, every second turn backwards."""
+    cfg = DecodeConfig(114, "matrix-dealt", 20, 32, D, 512, 512, dtype, TOL)
+    lengths = np.random.default_rng(5).permutation(301 + 8 * np.arange(20))
+    launched = {}
+    got, ref = _run(cfg, [[(0, int(n) - 100), (412, 512)] for n in lengths], q_len, gpu_device, launched=launched)
+    assert launched["max_splits"] == 1 and launched["workgroups"] == 640 and launched["slice_tokens"] == 453
+    assert np.isfinite(got).all() and float(np.abs(got - ref).max()) <= TOL

@@ -65,8 +65,8 @@ def test_workload_multi_parity(cid, q_len, gpu_device):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("q_len", [1, 2, 3, 4, 5, 8, 13, 16, 17, 40])
 def test_multi_all_kernel_instances(dtype, D, q_len, gpu_device):
-    """Every (type, head_dim) instance, token counts that pad a pass (3), fill it (2, 4) and need several (5, 8);
-    ragged sequences, forced slicing so that the cross-workgroup merge runs per query token."""
+    """Every type and head_dim; token counts on both sides of the groups of 16, and with forced slicing (so that the
+    cross-workgroup merge runs per query token) calls of one launch and of several; ragged sequences."""
     cfg = DecodeConfig(91, "multi", 3, 5, D, 700, 300, dtype, TOL[dtype])
     rng = np.random.default_rng(100 * D + q_len)
     ctx = rng.integers(cfg.min_len, cfg.max_len + 1, size=cfg.batch).astype(np.int32)
@@ -196,7 +196,8 @@ def test_poisoned_span_rows_past_the_limits_have_no_influence(dtype, D, q_len, g
     """GPU twin of the oracle pin of the same name (masked positions have no influence, Sec. 2.2 mask paragraph).
     Span rows after the last query token's causal limit hold NaN (K) and +-Inf (V), as an uninitialised
     pre-allocated cache may: every output row must still equal the oracle's, which never looks at them.  Runs the
-    one-token call with a limit, the 2- and 4-token kernels, padded and multi-pass token counts, unsplit and sliced."""
+    one-token call with a limit, two tokens (fp32 rows on the vector units, 16-bit ones on the matrix cores) and more,
+    unsplit and sliced."""
     cfg = DecodeConfig(93, "multi-poison", 3, 4, D, 420, 330, dtype, TOL[dtype])
     rng = np.random.default_rng(500 + q_len)
     ctx = rng.integers(cfg.min_len, cfg.max_len + 1, size=cfg.batch).astype(np.int32)
@@ -258,7 +259,7 @@ def test_a_row_only_later_tokens_see_does_not_touch_the_earlier_ones(dtype, q_le
 @pytest.mark.parametrize("q_len", [3, 16])
 def test_peaked_scores_with_a_long_light_tail_in_the_matrix_pass(dtype, q_len, gpu_device):
     """One span row outweighs every other by 2^15 and 2^20, but the other ~5000 rows together still carry 13 % and
-    0.5 % of the sum.  The sixteen-token pass feeds the weights to the matrix cores as 16-bit values: weights that far
+    0.5 % of the sum.  The matrix kernel feeds the weights to 16-bit rows as 16-bit terms: weights that far
     below the largest must neither vanish (fp16's normal range ends 2^14 below one) nor lose the sum's accuracy.
     Scores are set exactly through one non-zero query component."""
     L = 5000
