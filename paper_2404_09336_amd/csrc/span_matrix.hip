@@ -365,10 +365,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const bool ok = (tr.ok[s] >> (4 * c4 + t)) & 1u;
-          const int beyond = ok ? p4[t] - lim0 : 0x7fffffff;  // (no limit: lim0 is the largest int; a row that takes part is
-                                                              // at most lim0 + 63, however far below zero that is)
+          // (no limit: lim0 is the largest int.  Unsigned, as a row that takes no part may be any distance from the limit.)
+          const int beyond = (int)((ok ? (uint32_t)p4[t] : 0x7fffffffu) - (uint32_t)lim0);
 #pragma unroll
-          for (int g = 0; g < G; ++g) sc[g][s][t] = beyond <= 16 * g + qi ? sc[g][s][t] : -INFINITY;
+          for (int g = 0; g < G; ++g) sc[g][s][t] = ok && beyond <= 16 * g + qi ? sc[g][s][t] : -INFINITY;
         }
       }
     }
