@@ -330,7 +330,8 @@ constexpr int32_t kMatrixFromTokens = 3;
 // Two tokens: 16-bit rows and few (batch, head) pairs, where the start-up and the hand-over count and the matrix kernel's
 // are shorter; many pairs stream better through the vector kernel's 24 waves per CU.  us, vector -> matrix: 64 pairs of 128
 // 10.4 -> 9.4 (32 pairs), 20.3 -> 18.0 (192), 23.6 -> 22.4 (256), 28.4 -> 29.2 (384), 33.8 -> 35.7 (512); of 64 20.9 -> 16.3
-// (288), 23.8 -> 23.4 (512), 33.7 -> 36.8 (1536); fp32 rows 25.9 -> 26.8 (128), 49.9 -> 54.7 (1024).
+// (288), 23.8 -> 23.4 (512), 33.7 -> 36.8 (1536); fp32 rows 25.9 -> 26.8 (128), 49.9 -> 54.7 (1024).  (With fp16 weights in two
+// terms; the third that they have now costs 1 %.)
 constexpr int64_t kMatrixTwoTokenColumns = 32768;  // pairs x head_dim
 constexpr int64_t kMatrixWorkgroups = 512;
 constexpr int64_t kMatrixPairs = 128;

@@ -573,7 +573,8 @@ __global__ __launch_bounds__(256) void zero_words_kernel(uint32_t* p, size_t n) 
 
 // One wave per sequence: the span gains the positions after the ones just appended (see span_advance).  Bound by its chain
 // of trips to memory (arguments, list range, list): the lanes read 64 intervals at a time, where one thread per sequence
-// walked them one after the other (a group of 8 steps: 8 sequences of 6 - 14 intervals 183.9 -> 175.6 us, 4 of ~700 intervals 766 -> 151 us).
+// walked them one after the other (alone in a graph, us: 8 sequences of 10 intervals 2.4 -> 2.2, 64 of 10 2.7 -> 2.2, 4 of 700
+// 77 -> 4.0).
 __global__ __launch_bounds__(64) void advance_kernel(int max_len, int num_intervals, int count, const int32_t* offsets,
                                                      const int32_t* starts, int32_t* ends, int32_t* append_pos, int32_t* ctx_lens) {
   const int b = blockIdx.x, lane = threadIdx.x;

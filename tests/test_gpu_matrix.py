@@ -1,7 +1,7 @@
 """The matrix-core kernel of the few-query calls at the sizes where its tiling can go wrong, against the fp64 oracle.
 
 Tolerance: with fp32 outputs of unit-variance V rows the error of the sums is about 2^-23 times a few units, and of the
-weights 2^-23 (fp32 rows, fp16 as two terms, bf16 as three); 1e-5 is some ten times what that adds up to over the rows
+weights 2^-23 (fp32 rows, fp16 as two or three terms, bf16 as three); 1e-5 is some ten times what that adds up to over the rows
 attended here, and a thousand times less than one wrong row of the largest span would show."""
 import numpy as np
 import pytest
