@@ -17,7 +17,10 @@
 // merge count.  Its rounding is that of the vector kernels or less (measured against 64 bits, relative 2-norm: fp32 1.6e-7
 // for 1.8e-7, 16-bit rows of 64 1.45e-7 for 1.6e-7, 16-bit rows of 128 1.65e-7 for 1.75e-7).
 // K and V are streamed through registers: the next tile's K loads go out as soon as the scores of this one are taken,
-// its V loads as soon as the outputs are, so a wave always has loads in flight.
+// its V loads as soon as the outputs are, so a wave always has loads in flight.  (us with the next tile's loads behind a branch
+// and the K lines in halves, as it was -> now: 8 x 32 pairs x ~600 positions of 128, fp16, 2 tokens 22.9 -> 21.5; fp32, 8 tokens
+// 37.9 -> 36.2; 64 x 32 x ~155, fp16, 16 tokens 38.0 -> 36.2; 16 x 32 x ~700, bf16, 32 tokens 47.9 -> 45.9; 16 x 16 x ~380 of 64,
+// fp16, 9 tokens 13.6 -> 13.1.)
 #include "span_device.h"
 #include "span_matrix.h"
 
@@ -82,6 +85,13 @@ __device__ __forceinline__ float exchange_max(float x) {  // maximum over the fo
 // and keep all their operands in registers across them.
 __device__ __forceinline__ void pin(f32x4& v) { asm volatile("" : "+v"(v)); }
 
+// `from` of the lane eight further (within its 16) in the lanes of `kBanks` (0x3: lanes 0 - 7 of each 16, 0xc: 8 - 15), `keep` in
+// the others.
+template <int kBanks>
+__device__ __forceinline__ uint32_t swap_half(uint32_t keep, uint32_t from) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)keep, (int)from, 0x128, 0xf, kBanks, false);  // row_ror:8
+}
+
 // 16 bytes to / from memory that all XCDs share (sc1: written through, never served from a stale L2 line).
 constexpr int kThrough = 16;
 __device__ __forceinline__ void publish4(__amdgpu_buffer_rsrc_t slot, uint32_t byte_off, f32x4 v) {
@@ -108,6 +118,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   constexpr int kPieces = ROWB / 16;
   constexpr int kQRow = ROWB + 16;           // LDS rows of q, padded: operand reads spread over the banks
   constexpr int kAccRow = D + 4;
+  // Groups of rows that K loads alternate between, see load_k.  Rows of one line have nothing to gain from two, and pay for the
+  // second set of positions (16 x 16 pairs x ~380, fp16, 9 tokens 14.9 -> 15.1 us), and the fp32 shapes with the most tokens
+  // need the registers (8 x 32 x ~600, 24 tokens 50.0 -> 51.1; 16 x 16 x ~600 of 64, 60 tokens 53.1 -> 54.3).
+  constexpr int kKSets = NK == 2 || (Elt::kBytes == 4 && D / 64 * G >= 4) ? 1 : 2;
   constexpr bool kSplitPieces = VW == 8;     // the lane's V values are two pieces half a row apart
   static_assert(kMWin % TR == 0, "tiles do not straddle a window");
 
@@ -250,29 +264,64 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     uint32_t ok[S];         // bit i: row 16 s + i takes part
     bool plain;             // every row takes part and every query of the workgroup sees all of them
   };
+  // K rows come in loads of eight rows x 128 bytes (kKSets = 2): instructions 2 j and 2 j + 1 bring bytes 128 j .. of rows 0 - 7
+  // and 8 - 15, lane (i, c) the 16 bytes c of the line's half i / 8 of row i % 8; order_k puts the halves where the operand wants
+  // them.  (Loads of 16 rows x 64 bytes, which are the operand as they come, ask for every line twice: read alone and
+  // non-temporal they reach 5.5 TB/s where whole lines reach 6.5.)
   auto load_k = [&](int base, int wn) {
     TileRows tr;
     tr.plain = true;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const int r = base + 16 * s + qi;
-      const int p = s_pos[wave][r];
-      const bool ok = r < wn && p <= last_any;
-      tr.ok[s] = (uint32_t)__builtin_amdgcn_ballot_w64(ok) & 0xffffu;
-      tr.plain = tr.plain && tr.ok[s] == 0xffffu && __builtin_amdgcn_ballot_w64(p > lim0) == 0;
-      const uint32_t off = ok ? (uint32_t)p * ROWB + 16u * (uint32_t)c4 : kNoRow;
-      const bool fresh = ok && p >= new0;
+      uint32_t off[kKSets];
+      bool fresh[kKSets], any_fresh = false;
+      int p[kKSets];
+      tr.ok[s] = 0;
 #pragma unroll
-      for (int mm = 0; mm < NK; ++mm) kr[s][mm] = load_piece(kslab, (fresh ? kNoRow : off) + 64u * mm);
-      if (__builtin_amdgcn_ballot_w64(fresh) != 0) {  // (rare: the tiles of the call's own tokens)
-        if (fresh) {
-          const u32x4* src = reinterpret_cast<const u32x4*>(new_row(a.k_new, p - new0)) + c4;
+      for (int i = 0; i < kKSets; ++i) {
+        constexpr int kRows = 16 / kKSets;
+        const int r = base + 16 * s + kRows * i + qi % kRows;
+        p[i] = s_pos[wave][r];
+        const bool ok = r < wn && p[i] <= last_any;
+        tr.ok[s] |= ((uint32_t)__builtin_amdgcn_ballot_w64(ok) & ((1u << kRows) - 1u)) << (kRows * i);
+        tr.plain = tr.plain && __builtin_amdgcn_ballot_w64(p[i] > lim0) == 0;
+        fresh[i] = ok && p[i] >= new0;
+        any_fresh = any_fresh || fresh[i];
+        off[i] = ok && !fresh[i] ? (uint32_t)p[i] * ROWB + 64u * (uint32_t)(qi / kRows) + 16u * (uint32_t)c4 : kNoRow;
+      }
+      tr.plain = tr.plain && tr.ok[s] == 0xffffu;
 #pragma unroll
-          for (int mm = 0; mm < NK; ++mm) kr[s][mm] = src[4 * mm];
+      for (int mm = 0; mm < NK; ++mm) kr[s][mm] = load_piece(kslab, off[mm % kKSets] + 64u * kKSets * (mm / kKSets));
+      if (__builtin_amdgcn_ballot_w64(any_fresh) != 0) {  // (rare: the tiles of the call's own tokens)
+#pragma unroll
+        for (int i = 0; i < kKSets; ++i) {
+          if (fresh[i]) {
+            const u32x4* src = reinterpret_cast<const u32x4*>(new_row(a.k_new, p[i] - new0)) + 4 * (qi / (16 / kKSets)) + c4;
+#pragma unroll
+            for (int mm = i; mm < NK; mm += kKSets) kr[s][mm] = src[4 * kKSets * (mm / kKSets)];
+          }
         }
       }
     }
     return tr;
+  };
+  // Afterwards lane (i, c) holds the pieces 4 mm + c of row i: lanes i and i + 8 swap the second line half of row i (first
+  // load) for the first half of row i + 8 (second load).
+  auto order_k = [&]() {
+    if constexpr (kKSets == 2) {
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+#pragma unroll
+        for (int j = 0; j < NK / 2; ++j) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t x = kr[s][2 * j][k], y = kr[s][2 * j + 1][k];
+            kr[s][2 * j][k] = swap_half<0xc>(x, y);
+            kr[s][2 * j + 1][k] = swap_half<0x3>(y, x);
+          }
+        }
+      }
+    }
   };
   auto load_v = [&](int base, const TileRows& tr) {
     const uint32_t in_row = (kSplitPieces ? 16u : (uint32_t)(VW * 4)) * (uint32_t)qi;
@@ -320,6 +369,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   // accumulator chain: its rounding goes straight into the weight.
   auto take_scores = [&](f32x4 (&sc)[G][S]) {
     constexpr f32x4 kZero = {0.f, 0.f, 0.f, 0.f};
+    order_k();
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       const unsigned char* qrow_lds = &s_q[(16 * g + qi) * kQRow + 16 * c4];
@@ -578,15 +628,16 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       cur = load_k(0, wn);
       load_v(0, cur);
     }
-    for (int base = 0; base < wn; base += TR) {
+    // (the window's last tile apart: with the next tile's loads behind a branch the compiler could not count them, and would
+    // wait for all of them ahead of this tile's outputs)
+    int base = 0;
+    for (; base + TR < wn; base += TR) {
       f32x4 sc[G][S];
       take_scores(sc);
-      const bool more = base + TR < wn;
-      TileRows next = cur;
-      if (more) next = load_k(base + TR, wn);
+      const TileRows next = load_k(base + TR, wn);
       softmax_step(sc, base, cur);
       add_outputs(sc);
-      if (more) load_v(base + TR, next);
+      load_v(base + TR, next);
       cur = next;
 #ifdef SPAN_PHASE_TRACE
       if (w0 == 0 && base == 0) SPAN_STAMP_AFTER(3, "v", lsum[0]);
@@ -594,6 +645,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       // (the scheduler must not pull the next iteration's work up into this one: the registers would not suffice)
       asm volatile("" ::"v"(lsum[0]) : "memory");
     }
+    f32x4 sc[G][S];
+    take_scores(sc);
+    softmax_step(sc, base, cur);
+    add_outputs(sc);
   }
   {
     float z = 0.f;  // stays 0 unless some output is Inf or NaN
