@@ -51,6 +51,7 @@ struct LaunchArgs {
   float scale_log2e;
   int32_t total_slices;             // table mode: entries of `table` in use
   int32_t even;                     // 1: a sequence's slices share its own token count evenly; 0: slice_tokens each
+  int32_t entry_bits;               // table mode: Deal::b_bits | n_bits << 8 | dealt << 16
   int32_t interleave;               // 1: rows dealt to the waves round-robin (large slices); 0: contiguous quarters
 #ifdef SPAN_PHASE_TRACE
   unsigned long long* trace;        // diagnostic build only: [trace_workgroups, kTraceStamps] times of the phases, or null
@@ -76,6 +77,19 @@ struct LaunchArgsRuns : LaunchArgs {
   static constexpr bool kHasRuns = true;
   RunTables r;
 };
+
+// What a table entry names.
+struct SliceName {
+  int b, split, nsl;  // sequence, slice within it, slices of the sequence
+  int y0;             // slot of the sequence's first slice
+};
+__device__ __forceinline__ SliceName slice_name(const LaunchArgs& a, uint32_t entry, int y) {
+  const int bits = a.entry_bits, b_bits = bits & 255, n_bits = bits >> 8 & 255;
+  const uint32_t in_n = (1u << n_bits) - 1u;
+  const int split = (int)(entry >> b_bits & in_n);
+  const int slot = bits >> 16 ? (int)(entry >> (32 - kSlotBits)) : y;
+  return SliceName{(int)(entry & ((1u << b_bits) - 1u)), split, (int)(entry >> (b_bits + n_bits) & in_n), slot - split};
+}
 
 // Diagnostic build (-DSPAN_PHASE_TRACE): every workgroup reads the constant-rate (100 MHz) clock at the phase
 // boundaries named below into registers and thread 0 writes them out when the workgroup ends, so that taking a stamp

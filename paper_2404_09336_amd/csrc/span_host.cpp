@@ -358,6 +358,8 @@ int64_t most_states(const span_attn_desc_t* d, const Partition& p) {
   return std::max(least, std::min<int64_t>(slices, (int64_t)kMaxPlanSlices * p.queries_per_pass));
 }
 
+static int64_t matrix_workgroups_per_cu(int32_t groups) { return groups == 1 ? 4 : (groups == 2 ? 3 : 2); }
+
 bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
   int32_t n = query_tokens(d);
   if (!runs_on_matrix_cores(d)) return false;
@@ -384,8 +386,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
   while (m->groups > 1 && pairs * blocks_for(m->groups) < kMatrixPairs) m->groups /= 2;
   if (d->batch * blocks_for(m->groups) > 65535) m->tokens = n = 16 * m->groups;  // (grid.z limit)
   const int64_t blocks = blocks_for(m->groups);
-  const int64_t per_cu = m->groups == 1 ? 4 : (m->groups == 2 ? 3 : 2);
-  const int64_t most = 256 * per_cu / (d->heads * blocks), wanted = ceil_div(kMatrixWorkgroups, d->heads * blocks);
+  const int64_t most = 256 * matrix_workgroups_per_cu(m->groups) / (d->heads * blocks), wanted = ceil_div(kMatrixWorkgroups, d->heads * blocks);
   const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
   if (!p.even) {  // the counts are not known: every sequence gets the same number of slices
     if (!sliced) return true;
@@ -456,21 +457,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
   m->num_splits = (int32_t)most_s;
   m->slice_tokens = (int32_t)longest;
   m->total_slices = (int32_t)total;
-  // Whole sequences of unequal length: workgroups go to the CUs in turns of 256, so those of a CU are 256 apart.  The
-  // longest sequences are dealt first and every second turn runs backwards, which gives each CU long and short ones
-  // alike.  us in list order -> dealt: 16 x 700..1024 positions, 32 tokens 50.0 -> 46.2; 32 x 500..1000 fp32, 64 tokens
-  // 164.8 -> 154.3; 20 x ~600, 5 tokens 52.4 -> 49.1; 48 x 200..500 fp32 rows of 64, 10 tokens 36.0 -> 33.1.  Below 15 % over
-  // the mean the table in the arguments costs as much (64 x ~155, 16 tokens 39.9 -> 40.5).
-  const int64_t row = std::max<int64_t>(1, 256 / d->heads);
-  if (most_s == 1 && d->batch > row && d->batch <= kMaxPlanSlices && longest * 100 * d->batch > 115 * sum) {
-    std::vector<int32_t> order((size_t)d->batch);
-    for (int32_t b = 0; b < d->batch; ++b) order[(size_t)b] = b;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return tokens(x) > tokens(y); });
-    for (int64_t r = row; r < d->batch; r += 2 * row)
-      std::reverse(order.begin() + r, order.begin() + std::min<int64_t>(r + row, d->batch));
-    m->table = true;
-    for (int32_t y = 0; y < d->batch; ++y) table[y] = pack_slice((uint32_t)order[(size_t)y], 0, 1);
-  } else if (most_s != least_s) {
+  if (most_s != least_s) {
     m->table = true;
     int32_t y = 0;
     for (int pass = 0; pass < 2; ++pass) {
@@ -482,6 +469,110 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
     }
   }
   return true;
+}
+
+// Workgroups go to the CUs in turns of 256, heads fastest, so with 32 heads the table entries y, y + 8, y + 16, .. run on the same
+// CUs, and the launch lasts as long as the CU with the most rows (stamps by CU: its last row is read in step with its rows, correlation 0.7
+// to 0.94).  In plan order that is up to 30 % more than the mean (batch 16 x ~550 positions in 31 slices: 1454 rows on a CU, 1105 on
+// average).  So: the largest slices first, turn by turn, the largest of each turn to the CUs that have the least so far;
+// the smallest slices, which a last, partial turn will hold, are counted ahead.  With more workgroups than run at once the order
+// still is one of falling size, which is what free CUs should find.  us in plan order -> dealt, 32 heads x 128 unless said
+// otherwise: 32 x ~2700 positions in 64 slices, bf16 230 -> 222; 64 x ~800 121.5 -> 118.4; 40 x 400..2000 dense 127.5 -> 124.3; 32 x ~560, 64
+// tokens 117 -> 106; 60 x ~300 of 64, 5 tokens 55.4 -> 53.5; 8 x ~600 fp32, 24 tokens 49.7 -> 47.2; 16 x 16 heads x ~380 of 64, 9
+// tokens 14.4 -> 13.9; batch 16 x ~550 31.2 -> 30.2.  The host pays 0.3 us for 16 slices, 1.3 for 64, 3 for 120.
+// A launch whose plan needs no table carries one where that spares a CU 16 KB (its share of 0.6 us; the table's 3 KB of arguments
+// cost 0.35): 8 x 32 heads x 500..900, two slices each, 2 tokens 22.2 -> 21.9.
+constexpr int32_t kTurn = 256;              // CUs
+constexpr int64_t kDealTableBytes = 16384;  // bytes a CU must be spared for a launch to carry a table it can do without
+
+void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, bool table, uint32_t* entries, Deal* deal) {
+  deal->dealt = false;
+  const int32_t columns = (kTurn + d->heads / 2) / d->heads;  // table entries of a turn
+  if (columns < 2 || total <= columns || total > kMaxPlanSlices) return;
+  std::vector<int64_t> from_lists;
+  const int64_t* counts = d->tokens_per_seq;
+  if (has_host_lists(d)) {
+    tokens_from_host_lists(d, &from_lists);
+    counts = from_lists.data();
+  }
+  // rows of every slice, and what the CUs of a column get in plan order
+  uint64_t by_rows[kMaxPlanSlices];  // rows << 16 | slice
+  int64_t load[kTurn] = {};
+  int32_t b_last = 0, most = 1;
+  for (int32_t i = 0; i < total; ++i) {
+    const int32_t b = (int32_t)(entries[i] & 1023u), split = (int32_t)((entries[i] >> 10) & 2047u), nsl = (int32_t)(entries[i] >> 21);
+    const int64_t n = std::min<int64_t>(std::max<int64_t>(counts[b], 0), max_tokens), T = ceil_div(n, nsl);
+    const int64_t rows = std::min<int64_t>(std::max<int64_t>(n - split * T, 0), T);
+    by_rows[i] = (uint64_t)rows << 16 | (uint64_t)i;
+    load[i % columns] += rows;
+    b_last = std::max(b_last, b);
+    most = std::max(most, nsl);
+  }
+  const int64_t plain_most = *std::max_element(load, load + columns);
+  int32_t b_bits = 1;
+  while (b_last >> b_bits) ++b_bits;
+  const int32_t n_bits = (32 - kSlotBits - b_bits) / 2;
+  if (most >> n_bits) return;
+  std::sort(by_rows, by_rows + total, [](uint64_t x, uint64_t y) { return x > y; });
+  const int32_t turns = total / columns, rest = total % columns;  // whole turns, entries of the last one
+  uint16_t column[kTurn];
+  for (int32_t c = 0; c < columns; ++c) {
+    column[c] = (uint16_t)c;
+    load[c] = c < rest ? (int64_t)(by_rows[total - 1 - c] >> 16) : 0;
+  }
+  for (int32_t c = 0; c < rest; ++c) deal->at[by_rows[total - 1 - c] & 0xffff] = (uint16_t)(turns * columns + c);
+  for (int32_t t = 0; t < turns; ++t) {
+    std::sort(column, column + columns, [&](uint16_t x, uint16_t y) { return load[x] != load[y] ? load[x] < load[y] : x < y; });
+    for (int32_t k = 0; k < columns; ++k) {
+      const uint64_t s = by_rows[t * columns + k];
+      load[column[k]] += (int64_t)(s >> 16);
+      deal->at[s & 0xffff] = (uint16_t)(t * columns + column[k]);
+    }
+  }
+  const int64_t spared = plain_most - *std::max_element(load, load + columns);
+  const int64_t row_bytes = 2 * (int64_t)d->head_dim * (d->dtype == SPAN_F32 ? 4 : 2);
+  if (spared <= 0 || (!table && spared * row_bytes < kDealTableBytes)) return;
+  uint32_t dealt[kMaxPlanSlices];
+  for (int32_t i = 0; i < total; ++i)
+    dealt[deal->at[i]] = (entries[i] & 1023u) | ((entries[i] >> 10) & 2047u) << b_bits | (entries[i] >> 21) << (b_bits + n_bits) |
+                         (uint32_t)i << (32 - kSlotBits);
+  std::copy(dealt, dealt + total, entries);
+  deal->b_bits = b_bits;
+  deal->n_bits = n_bits;
+  deal->dealt = true;
+}
+
+// Entries of a plan whose sequences all have `slices` slices.
+static bool uniform_entries(int32_t batch, int32_t slices, uint32_t* entries) {
+  if (batch > kMaxPlanBatch || slices > kMaxPlanSplits || (int64_t)batch * slices > kMaxPlanSlices) return false;
+  for (int32_t b = 0; b < batch; ++b) {
+    for (int32_t s = 0; s < slices; ++s) entries[b * slices + s] = pack_slice((uint32_t)b, (uint32_t)s, (uint32_t)slices);
+  }
+  return true;
+}
+
+void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, RunTables* runs, Deal* deal) {
+  deal->dealt = false;
+  if (!p->even || (!p->exact && !uniform_entries(d->batch, p->num_splits, table))) return;
+  deal_slices(d, p->max_tokens, p->total_slices, p->exact, table, deal);
+  if (!deal->dealt) return;
+  p->exact = true;
+  if (p->runs) {
+    RunSlice slices[kMaxRunSlices];
+    for (int32_t i = 0; i < p->total_slices; ++i) {
+      slices[deal->at[i]] = runs->slices[i];
+      slices[deal->at[i]].reserved = i;
+    }
+    std::copy(slices, slices + p->total_slices, runs->slices);
+  }
+}
+
+void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal) {
+  deal->dealt = false;
+  const bool one_block = m->tokens <= 16 * m->groups;  // (workgroups that share a slice are a whole grid apart)
+  if (!m->even || !one_block || (!m->table && !uniform_entries(d->batch, m->num_splits, table))) return;
+  deal_slices(d, p.max_tokens, m->total_slices, m->table, table, deal);
+  m->table = m->table || deal->dealt;
 }
 
 size_t workspace_counter_bytes(const span_attn_desc_t* d) {

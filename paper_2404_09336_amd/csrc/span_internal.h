@@ -44,7 +44,7 @@ struct RunSlice {      // 16 bytes: one scalar load
   uint32_t entry;      // pack_slice(batch, slice, slices of the sequence), as in table mode
   uint32_t runs_of;    // first run | number of runs << 16
   int32_t rows;        // attended positions of the slice
-  int32_t reserved;
+  int32_t reserved;    // (of a dealt launch: the slice's slot)
 };
 struct RunTables {
   RunSlice slices[kMaxRunSlices];
@@ -53,6 +53,17 @@ struct RunTables {
 
 // Slice table entry (exact mode): batch index | slice index within the sequence | slices of the sequence.
 inline uint32_t pack_slice(uint32_t b, uint32_t split, uint32_t nsl) { return b | (split << 10) | (nsl << 21); }
+
+// A launch whose slices go out in another order than the plan names them (see deal_slices): a table entry then also says which
+// slice of the plan it is, which is the slice's slot in the workspace:
+// batch index (b_bits) | slice (n_bits) | slices of the sequence (n_bits) | slot (the ten highest bits).
+constexpr int kSlotBits = 10;
+static_assert(kMaxPlanSlices <= 1 << kSlotBits, "a slot fits an entry");
+struct Deal {
+  bool dealt = false;            // false: plan order, entries as pack_slice packs them, slot = entry index
+  int32_t b_bits = 10, n_bits = 11;
+  uint16_t at[kMaxPlanSlices];   // dealt: table index of slice i of the plan
+};
 
 struct Partition {
   bool exact;            // slices come from the table; otherwise the grid is (heads, num_splits, batch)
@@ -96,6 +107,13 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
 inline bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table) {
   return plan_matrix(d, p, least_states(p), m, table);
 }
+
+// Deals the slices of a plan that cuts its sequences evenly: `entries` holds them in plan order, as pack_slice packs them, and
+// is rewritten if the deal is worth it.  `table`: the launch carries a table anyway.
+void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, bool table, uint32_t* entries, Deal* deal);
+// The same for what the vector kernels and the matrix kernel launch; a plan without a table may get one.
+void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, RunTables* runs, Deal* deal);
+void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal);
 
 int check_desc(const span_attn_desc_t* d);
 int32_t query_tokens(const span_attn_desc_t* d);  // q_len of the descriptor, at least 1

@@ -61,13 +61,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   const int h = blockIdx.x;
   int b, split, nsl, y0;  // sequence, slice within it, slices of the sequence, first slice row of the sequence
   if constexpr (Args::kHasTable) {
-    uint32_t e;
-    if constexpr (Args::kHasRuns) e = a.r.slices[blockIdx.y].entry;
-    else e = a.table[blockIdx.y];
-    b = e & 1023u;
-    split = (e >> 10) & 2047u;
-    nsl = e >> 21;
-    y0 = blockIdx.y - split;
+    if constexpr (Args::kHasRuns) {
+      const uint32_t e = a.r.slices[blockIdx.y].entry;
+      b = e & 1023u;
+      split = (e >> 10) & 2047u;
+      nsl = e >> 21;
+      y0 = (a.entry_bits >> 16 ? a.r.slices[blockIdx.y].reserved : (int)blockIdx.y) - split;
+    } else {
+      const SliceName e = slice_name(a, a.table[blockIdx.y], (int)blockIdx.y);
+      b = e.b;
+      split = e.split;
+      nsl = e.nsl;
+      y0 = e.y0;
+    }
   } else {
     b = blockIdx.z;
     split = blockIdx.y;
@@ -694,6 +700,8 @@ int launch_queries(const LaunchArgsTable& a, const RunTables* runs, int nq, Grid
   return launch_typed<Elt, D, kDense, 1>(a, runs, mode, batch, stream);
 }
 
+int32_t entry_bits(const Deal& deal) { return deal.b_bits | deal.n_bits << 8 | (deal.dealt ? 1 << 16 : 0); }
+
 template <bool kDense>
 int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* v, const int32_t* offsets,
            const int32_t* starts, const int32_t* ends, const int32_t* ctx_lens, float scale, float* out,
@@ -712,8 +720,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
     own.host_span_offsets = own.host_span_starts = own.host_span_ends = nullptr;
     d = &own;
   }
-  const Partition p = plan_partition(d, a.table, kDense ? nullptr : &runs);
-  const GridMode mode = p.runs ? GridMode::kRuns : (p.exact ? GridMode::kTable : GridMode::kPlain);
+  Partition p = plan_partition(d, a.table, kDense ? nullptr : &runs);
   const size_t need = workspace_least_bytes(d, p);
   if (need > 0 && (!d->workspace || ((uintptr_t)d->workspace & 255u) || d->workspace_bytes < need))
     return SPAN_ERR_WORKSPACE;
@@ -743,7 +750,6 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
   a.max_tokens = p.max_tokens;
   a.even = p.even ? 1 : 0;
   a.interleave = p.slice_tokens >= kInterleaveFrom ? 1 : 0;
-  a.total_slices = p.total_slices;
   a.scale_log2e = scale * 1.4426950408889634f;
 #ifdef SPAN_PHASE_TRACE
   a.trace = g_trace;
@@ -751,8 +757,11 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
 #endif
   hipStream_t stream = (hipStream_t)d->stream;
 
+  Deal deal;
   MatrixPlan mp;
   if (!kDense && plan_matrix(d, p, states, &mp, a.table)) {
+    deal_matrix(d, p, &mp, a.table, &deal);
+    a.entry_bits = entry_bits(deal);
     const hipError_t err = launch_matrix(a, d->dtype, d->head_dim, mp, a.table, d->batch, stream);
     if (err != hipSuccess) {
       g_last_hip_error = (int)err;
@@ -761,6 +770,10 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
     return SPAN_OK;
   }
 
+  deal_partition(d, &p, a.table, &runs, &deal);
+  a.entry_bits = entry_bits(deal);
+  a.total_slices = p.total_slices;
+  const GridMode mode = p.runs ? GridMode::kRuns : (p.exact ? GridMode::kTable : GridMode::kPlain);
   const bool d128 = d->head_dim == 128;
   const int nq = a.q_len;
   switch (d->dtype) {

@@ -131,11 +131,11 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   const int h = blockIdx.x;
   int b, split, nsl, y0, qb;
   if constexpr (Args::kHasTable) {
-    const uint32_t e = a.table[blockIdx.y];
-    b = e & 1023u;
-    split = (e >> 10) & 2047u;
-    nsl = e >> 21;
-    y0 = blockIdx.y - split;
+    const SliceName e = slice_name(a, a.table[blockIdx.y], (int)blockIdx.y);
+    b = e.b;
+    split = e.split;
+    nsl = e.nsl;
+    y0 = e.y0;
     qb = blockIdx.z;
   } else {
     qb = 0;  // grid.z = sequences of block 0, then of block 1, ...
