@@ -419,8 +419,35 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float* acc, int 
 __device__ __forceinline__ int heads_with_arguments(const LaunchArgs& a) {
   int heads = a.heads;
   asm("" : "+s"(heads) : "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.offsets), "s"(a.starts), "s"(a.ends), "s"(a.append_pos), "s"(a.q_pos),
-      "s"(a.max_len), "s"(a.num_intervals), "s"(a.q_len), "s"(a.even), "s"(a.interleave));
+      "s"(a.k_new), "s"(a.v_new), "s"(a.max_len), "s"(a.num_intervals), "s"(a.q_len), "s"(a.even), "s"(a.interleave),
+      "s"(a.max_tokens), "s"(a.slice_tokens), "s"(a.scale_log2e));
   return heads;
+}
+
+// What a call says of sequence b, fetched together as well, where each used to be waited for ahead of the next: a pointer that is
+// null reads the list instead (one that is always there), and its value is not used.  With the positions' marks (tabulate_short), us:
+// batch 8 x ~560 appended 20.6 -> 20.1; 32 pairs x ~560, 3 tokens 9.5 -> 9.3; 8 x 32 x ~600, 2 tokens 21.3 -> 20.7; 64 x 24 heads x ~150 of 64,
+// 20 tokens 45.0 -> 43.8.
+struct SequenceWords {
+  int first, last;         // span form: its range of the interval lists; dense form: its length, twice
+  int append_pos, q_pos;
+};
+template <bool kDense>
+__device__ __forceinline__ SequenceWords sequence_words(const LaunchArgs& a, int b) {
+  const int32_t* list = kDense ? a.ctx_lens : a.offsets;
+  SequenceWords w;
+  w.first = __builtin_amdgcn_readfirstlane(list[b]);
+  w.last = kDense ? w.first : __builtin_amdgcn_readfirstlane(list[b + 1]);
+  w.append_pos = __builtin_amdgcn_readfirstlane((a.append_pos ? a.append_pos : list)[b]);
+  w.q_pos = __builtin_amdgcn_readfirstlane((a.q_pos ? a.q_pos : list)[b]);
+  return w;
+}
+// From here on the words are used (the vector loads of rows that are known from the arguments alone go out before).
+__device__ __forceinline__ void arrived(SequenceWords& w) { asm("" : "+s"(w.first) : "s"(w.last), "s"(w.append_pos), "s"(w.q_pos)); }
+
+// (n + parts - 1) / parts: both sides are below 2^23, which the compiler is told (a third of the instructions).
+__device__ __forceinline__ int even_share(int n, int parts) {
+  return (int)(((uint32_t)(n + parts - 1) & 0xffffffu) / ((uint32_t)parts & 0xffffffu));
 }
 
 // ---- the interval list of a sequence -----------------------------------------------------------------
@@ -437,9 +464,9 @@ struct IntervalTables {  // LDS of a workgroup
   int wave_sum[kWavesPerBlock];
 };
 
-__device__ __forceinline__ Intervals interval_range(const LaunchArgs& a, int b) {
-  const int lo = clampi(a.offsets[b], 0, a.num_intervals);
-  const int hi = clampi(a.offsets[b + 1], lo, a.num_intervals);
+__device__ __forceinline__ Intervals interval_range(const LaunchArgs& a, const SequenceWords& w) {
+  const int lo = clampi(w.first, 0, a.num_intervals);
+  const int hi = clampi(w.last, lo, a.num_intervals);
   return Intervals{__builtin_amdgcn_readfirstlane(hi - lo), __builtin_amdgcn_readfirstlane(lo), 0, 0, 0};
 }
 
@@ -518,12 +545,68 @@ __device__ __forceinline__ void place_chunk(const RowMap& vrow, int w0, int wn, 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// What the lanes of this wave wrote to LDS is read back by others of them (LDS executes a wave's requests in order).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inclusive maximum over the lanes up to each, all values >= 0.
+__device__ __forceinline__ int wave_inclusive_max(int x, int lane) {
+  x = max(x, dpp_i<0x111>(x));
+  x = max(x, dpp_i<0x112>(x));
+  x = max(x, dpp_i<0x114>(x));
+  x = max(x, dpp_i<0x118>(x));
+  const int t0 = __builtin_amdgcn_readlane(x, 15);
+  const int t1 = max(t0, __builtin_amdgcn_readlane(x, 31));
+  const int t2 = max(t1, __builtin_amdgcn_readlane(x, 47));
+  const int row = lane >> 4;
+  return max(x, row == 0 ? 0 : (row == 1 ? t0 : (row == 2 ? t1 : t2)));
+}
+
 // Cache positions of the wave's first rows 0 .. wn - 1 into `pos` for a list of up to 64 intervals, which are still in
-// registers from count_positions; row r is virtual token vrow(r) of the sequence.
-template <class RowMap>
-__device__ __forceinline__ void tabulate_short(const LaunchArgs& a, const Intervals& iv, const RowMap& vrow, int wn, int wave,
+// registers from count_positions; row r is virtual token vbase + r + (r / kUnit) * vgap of the sequence (vgap 0, or three units).
+// Every interval marks the wave's first row at or after its first token with its number, the largest where several meet; a row's
+// interval is the largest mark up to it (an inclusive maximum over the lanes).  Three trips to LDS for 128 rows, where a binary
+// search of the prefix sums takes seven for every 64 (place_chunk, which lists of several chunks still use: a chunk holds a few
+// of the wave's rows there).
+template <int kUnit, int kRows>
+__device__ __forceinline__ void tabulate_short(const LaunchArgs& a, const Intervals& iv, int vbase, int vgap, int wn, int wave,
                                                int lane, IntervalTables& tab, int* pos) {
-  place_chunk(vrow, 0, wn, lane, iv.count, 0, iv.st0, iv.len0, iv.incl0, a.max_len, tab.chunk[wave], pos);
+  IntervalTables::Chunk& chunk = tab.chunk[wave];
+  const int before = iv.incl0 - iv.len0, x = before - vbase;
+  chunk.start[lane] = iv.st0 - before;
+  constexpr int kPair = 128;  // rows taken together: two per lane
+#pragma unroll
+  for (int r0 = 0; r0 < kRows; r0 += kPair) {
+    if (r0 < wn) pos[r0 + lane] = pos[r0 + 64 + lane] = 0;
+  }
+  wave_lds_order();
+  const uint32_t ux = (uint32_t)x;
+  const uint32_t row = vgap == 0 ? ux : ux / (4u * kUnit) * kUnit + min(ux % (4u * kUnit), (uint32_t)kUnit);
+  if (iv.len0 > 0 && (x < 0 || row < (uint32_t)wn))
+    __hip_atomic_fetch_max(&pos[x < 0 ? 0u : row], lane + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  wave_lds_order();
+  int carry = 1;
+  for (int r0 = 0; r0 < wn; r0 += kPair) {
+    int m[2], base[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) m[k] = pos[r0 + 64 * k + lane];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      m[k] = max(wave_inclusive_max(m[k], lane), carry);
+      carry = __builtin_amdgcn_readlane(m[k], 63);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) base[k] = chunk.start[m[k] - 1];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int r = r0 + 64 * k + lane;
+      pos[r] = clampi(base[k] + vbase + r + r / kUnit * vgap, 0, a.max_len - 1);
+    }
+  }
+  wave_lds_order();
 }
 
 // The same for rows w0 .. w0 + wn - 1 and any list: re-reads the intervals, so that nothing stays live across the

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   // With several query tokens (NQ > 1) every token brings a row, for positions append_pos[b] + token; they are
   // handled with the rows that only some tokens of the pass see (below) and new_pos stays unused.
   const bool append_many = NQ > 1 && a.append_pos != nullptr;
-  const int new_pos = (NQ == 1 && a.append_pos) ? a.append_pos[b] : -2;  // -2 matches no position
+  SequenceWords words = sequence_words<kDense>(a, b);
   u32x4 kn_raw = {0u, 0u, 0u, 0u}, vn_raw = {0u, 0u, 0u, 0u};
   if (NQ == 1 && a.append_pos) {
     kn_raw = *reinterpret_cast<const u32x4*>((const char*)a.k_new + bh * ROWB + (uint32_t)lir * 16u);
@@ -123,11 +123,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     qv[j] = Elt::make_q(qr, a.scale_log2e);
   }
   const float post = Elt::kPostScale ? a.scale_log2e : 1.f;
+  arrived(words);
+  const int new_pos = (NQ == 1 && a.append_pos) ? words.append_pos : -2;  // -2 matches no position
   // Causal limit (few-query variant): query token j sees no position after its own, q_pos[b] + j.
   int lim[NQ];
 #pragma unroll
   for (int j = 0; j < NQ; ++j)  // (clamped: any q_pos at or beyond the cache length means "no limit", without overflow)
-    lim[j] = a.q_pos ? min(a.q_pos[b], kMaxLen) + j : 0x7fffffff;
+    lim[j] = a.q_pos ? min(words.q_pos, kMaxLen) + j : 0x7fffffff;
 
   // ---- step 1: how many attended positions does the sequence have, which are mine ----------------
   int n_total;
@@ -135,9 +137,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   if constexpr (Args::kHasRuns) {
     n_total = 0;  // the slice's rows come from the arguments, see below
   } else if (kDense) {
-    n_total = clampi(a.ctx_lens[b], 0, a.max_len);
+    n_total = clampi(words.first, 0, a.max_len);
   } else {
-    intervals = interval_range(a, b);
+    intervals = interval_range(a, words);
     SPAN_STAMP_AFTER(10, "s", intervals.count);
     n_total = count_positions(a, intervals, wave, lane, s_tab);
   }
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     slice_begin = 0;
     cnt = clampi(a.r.slices[blockIdx.y].rows, 0, kMaxRunSliceRows);
   } else {
-    const int T = a.even ? (n_total + nsl - 1) / nsl : a.slice_tokens;
+    const int T = a.even ? even_share(n_total, nsl) : a.slice_tokens;
     slice_begin = split * T;
     cnt = __builtin_amdgcn_readfirstlane(clampi(n_total - slice_begin, 0, T));
   }
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
   if constexpr (NQ > 1) {  // the new tokens' rows, one token per wave
     if (append_many && split == 0 && lane < LPR) {
       for (int i = wave; i < NQ; i += kWavesPerBlock) {
-        const int pos_i = min(a.append_pos[b], kMaxLen) + i;
+        const int pos_i = min(words.append_pos, kMaxLen) + i;
         if (pos_i >= 0 && pos_i < a.max_len) {
           const size_t src = qrow(i) * ROWB + (uint32_t)lir * 16u;
           const size_t row = (bh * (size_t)a.max_len + (size_t)pos_i) * ROWB + (uint32_t)lir * 16u;
@@ -268,7 +270,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   } else {
-    if (!kDense && nrows > 0 && __builtin_expect(intervals.count <= 64, 1)) tabulate_short(a, intervals, vrow, min(kWin, nrows), wave, lane, s_tab, s_pos[wave]);
+    if (!kDense && nrows > 0 && __builtin_expect(intervals.count <= 64, 1)) tabulate_short<RPL, kWin>(a, intervals, vbase, vgap, min(kWin, nrows), wave, lane, s_tab, s_pos[wave]);
   }
   SPAN_STAMP_AFTER(2, "v", lane_off);
 

@@ -177,6 +177,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   const int nq_here = min(NQ, a.q_first + a.tokens - q0);
   auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(q0 + min(j, nq_here - 1))) * heads + h; };
 
+  SequenceWords words = sequence_words<false>(a, b);
   // q goes to LDS (the same for the four waves).  It is fetched here, as are the append form's new rows for the cache
   // (written by the first slice's workgroup, whatever the span holds); both have arrived when the rows' positions are known.
   constexpr int kQLoads = (NQ * kPieces + kThreads - 1) / kThreads;
@@ -199,20 +200,21 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   // post is positive (a hidden row's -Inf stays -Inf); the rest of the scale goes into q: see Elt::scale_query.
   const float post = Elt::post_scale(a.scale_log2e);
 
+  arrived(words);
   // Causal limit: query token j sees no position after lim0 + j.  In the append form the call's tokens sit at
   // positions new0 .. new0 + q_len - 1; those rows come from k_new / v_new, never from the cache.
   // (clamped: any q_pos at or beyond the cache length means "no limit", without overflow)
   const bool limited = a.q_pos != nullptr;
-  const int pos0 = limited ? min(a.q_pos[b], kMaxLen) : 0;
+  const int pos0 = limited ? min(words.q_pos, kMaxLen) : 0;
   const int lim0 = limited ? pos0 + q0 : 0x7fffffff;
   const int last_any = limited ? lim0 + nq_here - 1 : 0x7fffffff;
-  const int new0 = append ? min(a.append_pos[b], kMaxLen) : 0x7fffffff;
+  const int new0 = append ? min(words.append_pos, kMaxLen) : 0x7fffffff;
 
-  Intervals intervals = interval_range(a, b);
+  Intervals intervals = interval_range(a, words);
   SPAN_STAMP_AFTER(10, "s", intervals.count);
   int n_total = count_positions(a, intervals, wave, lane, s_u.st.tab);
   n_total = n_total < a.max_tokens ? n_total : a.max_tokens;
-  const int T = a.even ? (n_total + nsl - 1) / nsl : a.slice_tokens;
+  const int T = a.even ? even_share(n_total, nsl) : a.slice_tokens;
   const int slice_begin = split * T;
   const int cnt = __builtin_amdgcn_readfirstlane(clampi(n_total - slice_begin, 0, T));
   SPAN_STAMP_AFTER(1, "s", cnt);
@@ -236,7 +238,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   }
   auto vrow = [&](int r) { return vbase + r + (r / TR) * vgap; };
   if (nrows > 0) {
-    if (__builtin_expect(intervals.count <= 64, 1)) tabulate_short(a, intervals, vrow, min(kMWin, nrows), wave, lane, s_u.st.tab, s_pos[wave]);
+    if (__builtin_expect(intervals.count <= 64, 1)) tabulate_short<TR, kMWin>(a, intervals, vbase, vgap, min(kMWin, nrows), wave, lane, s_u.st.tab, s_pos[wave]);
     else tabulate_positions(a, intervals, vrow, 0, min(kMWin, nrows), wave, lane, s_u.st.tab, s_pos[wave]);
   }
   SPAN_STAMP_AFTER(2, "s", cnt);
