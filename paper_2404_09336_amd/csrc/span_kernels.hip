@@ -41,12 +41,15 @@ namespace {
 
 // ---- the streaming kernel ------------------------------------------------------------------------
 // NQ query tokens per sequence are served by one pass over the span's rows (NQ = 1: the decode step proper).
-// The register budget is 64 per lane for one query (8 waves per SIMD) and 80 for two (6).
-constexpr int waves_per_simd(int nq) { return nq == 1 ? 8 : 6; }
+// The register budget is 64 per lane for one query (8 waves per SIMD) and 80 for two (6); 128 (4) where a wave has twice the loads
+// in flight.
+enum class Stream { kDefault, kBoost, kWide };  // see launch_typed
+constexpr int waves_per_simd(int nq, Stream stream) { return stream == Stream::kWide ? 4 : (nq == 1 ? 8 : 6); }
 
-template <class Elt, int D, bool kDense, int U, int NQ, class Args, bool kBoost = false>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NQ), waves_per_simd(NQ)))) void decode_kernel(
-    const Args a) {
+template <class Elt, int D, bool kDense, int U, int NQ, class Args, Stream kStream = Stream::kDefault>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NQ, kStream), waves_per_simd(NQ, kStream)))) void
+decode_kernel(const Args a) {
+  constexpr bool kBoost = kStream == Stream::kBoost;
   constexpr int EPL = Elt::kPerVec;        // elements per lane (one 128-bit piece)
   constexpr int LPR = D / EPL;             // lanes per row
   constexpr int RPL = 64 / LPR;            // rows per wave-wide load
@@ -645,6 +648,15 @@ int static_scratch(void** ptr) {
   return SPAN_OK;
 }
 
+// Twice the loads in flight (kWide), for launches of few workgroups with little to read: nothing but the trips to memory bounds
+// them, and a slice of the planner's smallest size is then one batch per wave instead of two.  us, default -> wide: one request of ~560 positions,
+// 32 heads x 128, fp16, appended 8.92 -> 8.54; ~560 fp32 10.6 -> 10.25; one of 600..4000 in 512 workgroups 12.0 -> 11.6; 4 workgroups x 80
+// positions of fp32 rows of 64 4.70 -> 4.40; 12 x 5 heads x ~1000 13.95 -> 13.55.  The line: two batches a wave gain nothing any more with two
+// workgroups per CU (4 x ~560 in 512: 13.5 -> 13.65), and where the rate of the memory counts it costs the resident waves (64 x ~155:
+// 27.8 -> 30.6; dense rows of 64, 576 workgroups x 250 positions 15.1 -> 15.65).
+constexpr int64_t kWideUpToWorkgroups = 512;     // slices of one (wide) batch of rows per wave
+constexpr int64_t kWideTwiceUpToWorkgroups = 384;  // of two
+
 // How the grid names its slices.
 enum class GridMode { kPlain, kTable, kRuns };
 
@@ -662,27 +674,43 @@ int launch_typed(const LaunchArgsTable& a, const RunTables* runs, GridMode mode,
   // short slices of 16-bit rows, one token: the instances that send a wave's first batch at raised priority
   constexpr bool kCanBoost = NQ == 1 && Elt::kBytes == 2 && D == 128 && SPAN_FIRST_BATCH_PRIORITY > 0;
   const bool boost = kCanBoost && a.slice_tokens <= kBoostUpToBatches * kWavesPerBlock * kRowsPerLoad * kInFlight;
+  // few workgroups with little to read, one token: twice the loads in flight
+  constexpr bool kCanWiden = NQ == 1;
+  const int64_t workgroups = (int64_t)a.heads * (mode == GridMode::kPlain ? (int64_t)a.num_splits * batch : a.total_slices);
+  constexpr int kWideRows = kWavesPerBlock * kRowsPerLoad * 2 * kInFlight;  // of a slice
+  const bool wide = kCanWiden && workgroups <= (a.slice_tokens <= kWideRows ? kWideUpToWorkgroups : kWideTwiceUpToWorkgroups) &&
+                    a.slice_tokens <= 2 * kWideRows;
+  auto start = [&](const auto& args, dim3 grid) {
+    using Args = std::decay_t<decltype(args)>;
+    if constexpr (kCanWiden) {
+      if (wide) {
+        hipLaunchKernelGGL((decode_kernel<Elt, D, kDense, 2 * kInFlight, NQ, Args, Stream::kWide>), grid, dim3(kThreads), 0, stream, args);
+        return;
+      }
+    }
+    if constexpr (kCanBoost) {
+      if (boost) {
+        hipLaunchKernelGGL((decode_kernel<Elt, D, kDense, kInFlight, NQ, Args, Stream::kBoost>), grid, dim3(kThreads), 0, stream, args);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((decode_kernel<Elt, D, kDense, kInFlight, NQ, Args>), grid, dim3(kThreads), 0, stream, args);
+  };
   if (mode == GridMode::kRuns) {
     if constexpr (!kDense) {
-      const dim3 grid((unsigned)a.heads, (unsigned)a.total_slices, 1u);
       LaunchArgsRuns ra;
       static_cast<LaunchArgs&>(ra) = static_cast<const LaunchArgs&>(a);
       ra.r = *runs;
-      if (boost) hipLaunchKernelGGL((decode_kernel<Elt, D, false, kInFlight, NQ, LaunchArgsRuns, kCanBoost>), grid, dim3(kThreads), 0, stream, ra);
-      else hipLaunchKernelGGL((decode_kernel<Elt, D, false, kInFlight, NQ, LaunchArgsRuns>), grid, dim3(kThreads), 0, stream, ra);
+      start(ra, dim3((unsigned)a.heads, (unsigned)a.total_slices, 1u));
     } else {
       return SPAN_ERR_SHAPE;  // (not reachable: the dense form never plans runs)
     }
   } else if (mode == GridMode::kTable) {
-    const dim3 grid((unsigned)a.heads, (unsigned)a.total_slices, 1u);
-    if (boost) hipLaunchKernelGGL((decode_kernel<Elt, D, kDense, kInFlight, NQ, LaunchArgsTable, kCanBoost>), grid, dim3(kThreads), 0, stream, a);
-    else hipLaunchKernelGGL((decode_kernel<Elt, D, kDense, kInFlight, NQ, LaunchArgsTable>), grid, dim3(kThreads), 0, stream, a);
+    start(a, dim3((unsigned)a.heads, (unsigned)a.total_slices, 1u));
   } else {
-    const dim3 grid((unsigned)a.heads, (unsigned)a.num_splits, (unsigned)batch);
     LaunchArgsPlain plain;
     static_cast<LaunchArgs&>(plain) = static_cast<const LaunchArgs&>(a);
-    if (boost) hipLaunchKernelGGL((decode_kernel<Elt, D, kDense, kInFlight, NQ, LaunchArgsPlain, kCanBoost>), grid, dim3(kThreads), 0, stream, plain);
-    else hipLaunchKernelGGL((decode_kernel<Elt, D, kDense, kInFlight, NQ, LaunchArgsPlain>), grid, dim3(kThreads), 0, stream, plain);
+    start(plain, dim3((unsigned)a.heads, (unsigned)a.num_splits, (unsigned)batch));
   }
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) {
