@@ -480,8 +480,9 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
 // otherwise: 32 x ~2700 positions in 64 slices, bf16 230 -> 222; 64 x ~800 121.5 -> 118.4; 40 x 400..2000 dense 127.5 -> 124.3; 32 x ~560, 64
 // tokens 117 -> 106; 60 x ~300 of 64, 5 tokens 55.4 -> 53.5; 8 x ~600 fp32, 24 tokens 49.7 -> 47.2; 16 x 16 heads x ~380 of 64, 9
 // tokens 14.4 -> 13.9; batch 16 x ~550 31.2 -> 30.2.  The host pays 0.3 us for 16 slices, 1.3 for 64, 3 for 120.
-// A launch whose plan needs no table carries one where that spares a CU 16 KB (its share of 0.6 us; the table's 3 KB of arguments
-// cost 0.35): 8 x 32 heads x 500..900, two slices each, 2 tokens 22.2 -> 21.9.
+// A launch whose plan needs no table carries one where that spares a CU 5 % and 16 KB (its share of 0.6 us; the table's 3 KB of
+// arguments cost 0.35): 60 x 32 heads x ~300 of 64, 5 tokens 57.1 -> 53.4; 8 x 32 x 500..900, two slices each, 2 tokens 21.0 -> 20.9.  Sequences of
+// almost the same length have nothing to win (64 x 144..168 positions: 28.4 with and without).
 constexpr int32_t kTurn = 256;              // CUs
 constexpr int64_t kDealTableBytes = 16384;  // bytes a CU must be spared for a launch to carry a table it can do without
 
@@ -529,9 +530,9 @@ void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, b
       deal->at[s & 0xffff] = (uint16_t)(t * columns + column[k]);
     }
   }
-  const int64_t spared = plain_most - *std::max_element(load, load + columns);
+  const int64_t dealt_most = *std::max_element(load, load + columns), spared = plain_most - dealt_most;
   const int64_t row_bytes = 2 * (int64_t)d->head_dim * (d->dtype == SPAN_F32 ? 4 : 2);
-  if (spared <= 0 || (!table && spared * row_bytes < kDealTableBytes)) return;
+  if (spared <= 0 || (!table && (spared * row_bytes < kDealTableBytes || spared * 20 < dealt_most))) return;
   uint32_t dealt[kMaxPlanSlices];
   for (int32_t i = 0; i < total; ++i)
     dealt[deal->at[i]] = (entries[i] & 1023u) | ((entries[i] >> 10) & 2047u) << b_bits | (entries[i] >> 21) << (b_bits + n_bits) |
