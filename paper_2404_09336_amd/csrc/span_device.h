@@ -50,7 +50,7 @@ struct LaunchArgs {
   int32_t q_first;                  // matrix kernel: first query token this launch handles
   float scale_log2e;
   int32_t total_slices;             // table mode: entries of `table` in use
-  int32_t even;                     // 1: a sequence's slices share its own token count evenly; 0: slice_tokens each
+  int32_t even;                     // > 0: a sequence's slices share its own token count evenly, `even` positions each at least; 0: slice_tokens each
   int32_t entry_bits;               // table mode: Deal::b_bits | n_bits << 8 | dealt << 16
   int32_t interleave;               // 1: rows dealt to the waves round-robin (large slices); 0: contiguous quarters
 #ifdef SPAN_PHASE_TRACE
@@ -445,9 +445,10 @@ __device__ __forceinline__ SequenceWords sequence_words(const LaunchArgs& a, int
 // From here on the words are used (the vector loads of rows that are known from the arguments alone go out before).
 __device__ __forceinline__ void arrived(SequenceWords& w) { asm("" : "+s"(w.first) : "s"(w.last), "s"(w.append_pos), "s"(w.q_pos)); }
 
-// (n + parts - 1) / parts: both sides are below 2^23, which the compiler is told (a third of the instructions).
-__device__ __forceinline__ int even_share(int n, int parts) {
-  return (int)(((uint32_t)(n + parts - 1) & 0xffffffu) / ((uint32_t)parts & 0xffffffu));
+// Positions of a slice: (n + parts - 1) / parts where a sequence's slices share its positions evenly.  Both sides are below 2^23, which the compiler is told (a third of the instructions).
+__device__ __forceinline__ int slice_size(const LaunchArgs& a, int n, int parts) {
+  if (a.even == 0) return a.slice_tokens;
+  return max((int)(((uint32_t)(n + parts - 1) & 0xffffffu) / ((uint32_t)parts & 0xffffffu)), a.even);
 }
 
 // ---- the interval list of a sequence -----------------------------------------------------------------

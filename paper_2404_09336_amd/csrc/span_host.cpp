@@ -187,6 +187,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   }
   p->exact = most != least;  // same count for every sequence: a (heads, slices, batch) grid says it all
   p->even = true;
+  p->least_slice = 0;
   p->num_splits = (int32_t)most;
   p->slice_tokens = (int32_t)largest;
   p->max_tokens = (int32_t)max_tok;
@@ -261,10 +262,15 @@ static bool plan_runs(const span_attn_desc_t* d, const int64_t* tokens_per_seq, 
   return y == p.total_slices;
 }
 
-// Uniform mode: every sequence gets the same number of slices, sized so that a call puts about
-// kTargetWorkgroups workgroups on the chip (256 CUs x 8 resident workgroups), never fewer than kMinSlice
-// positions per slice, never more than the kMaxSlice the kernel's position table holds.
-Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* runs) {
+// Uniform mode: every sequence gets the same number of slices, sized from the bound so that a call puts about as many workgroups
+// on the chip as slice_room says, never fewer than kMinSlice positions per slice.  The kernel counts every sequence itself and shares
+// its positions evenly between its slices (least_slice) - cut at the bound's size, all but the first were short or empty.  us, cut
+// at the bound -> shared: 32 x 32 heads x 5..50 % of 4096..16384, bf16 274 -> 236; 16 x 32 x ~560, fp16 38.7 -> 35.7; 20 x 32 x 300..1000
+// dense 42.9 -> 38.4; 40 x 16 x 300..900 dense of 64 23.5 -> 22.5.  With kBoundSlice as well (span form): 24 x 12 x 5..50 % of 2000..5000,
+// bf16 41.0 -> 31.0 (38.9 shared alone), 16 x 16 x 5..50 % of 1200..4000 fp32 of 64 24.6 -> 19.2 (22.7); slices of up to 256 or 384 win and
+// lose 5 % against 512; dense contexts, which are less ragged, lose by more slices (8 x 32 x 600..2000 33.4 -> 36.2), and few sequences
+// have enough as it is (6 x 16 x ~400 10.0 and 10.0, 10 x 8 x ~560 11.5 and 11.5).
+Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* runs, bool spans) {
   const int64_t max_tok = (d->max_tokens > 0 && d->max_tokens < d->max_len) ? d->max_tokens : d->max_len;
   Partition p;
   // Host copies of the span lists, when given, are the authority on the token counts (tokens_per_seq is then not
@@ -286,6 +292,11 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
   }
   const int64_t pairs = (int64_t)d->batch * d->heads;
   int64_t splits = d->num_splits > 0 ? d->num_splits : slice_room(d) / d->batch;  // stay within one round
+  if (d->num_splits == 0 && spans && query_tokens(d) == 1 && d->batch > kBoundSliceFromBatch) {
+    // A bound far above what most sequences attend leaves few large slices for the longest: up to kBoundSlice each.
+    const int64_t in_round = target_workgroups(d) / d->heads / d->batch;
+    while (splits > 0 && splits < in_round && ceil_div(max_tok, splits) > kBoundSlice) ++splits;
+  }
   const int64_t most = ceil_div(max_tok, kMinSlice);
   if (d->num_splits == 0 && splits > most) splits = most;
   if (splits > max_tok) splits = max_tok;
@@ -296,6 +307,7 @@ Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* 
   splits = ceil_div(max_tok, slice);
   p.exact = false;
   p.even = false;
+  p.least_slice = d->num_splits == 0 ? kLeastSlice : 0;
   p.num_splits = (int32_t)splits;
   p.slice_tokens = (int32_t)slice;
   p.max_tokens = (int32_t)max_tok;
@@ -368,6 +380,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
   m->tokens = n;
   m->table = false;
   m->even = p.even;
+  m->least_slice = p.least_slice;
   m->num_splits = p.num_splits;
   m->slice_tokens = p.slice_tokens;
   m->total_slices = p.total_slices;

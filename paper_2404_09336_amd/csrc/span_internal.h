@@ -15,6 +15,9 @@ constexpr int kMaxSlice = 1 << 22;         // a slice may be a whole sequence (p
 #define SPAN_MIN_SLICE 128
 #endif
 constexpr int kMinSlice = SPAN_MIN_SLICE;  // do not cut work finer than this many positions
+constexpr int kBoundSlice = 512;           // slices planned from a bound alone hold at most this many positions where a round has room for them
+constexpr int kBoundSliceFromBatch = 8;    // ... of batches larger than this
+constexpr int kLeastSlice = 64;            // positions of a slice whose size the kernel chooses, see Partition::least_slice
 constexpr int kSliceGranule = 16;
 constexpr int kUnsplitFromPairs = 512;     // level batches with at least this many (batch, head) pairs are not sliced
 #ifndef SPAN_LARGE_SLICE
@@ -68,6 +71,7 @@ struct Deal {
 struct Partition {
   bool exact;            // slices come from the table; otherwise the grid is (heads, num_splits, batch)
   bool even;             // a sequence's slices share its own token count evenly (needs the caller's counts)
+  int32_t least_slice;   // not even: 0, or the kernel shares a sequence's positions evenly between its slices, this many each at least
   int32_t num_splits;    // uniform: KV slices per (batch, head); exact: most slices of any sequence
   int32_t slice_tokens;  // attended positions per slice (exact: upper bound)
   int32_t max_tokens;    // bound on attended positions per sequence
@@ -78,8 +82,10 @@ struct Partition {
 };
 
 // Fills `table` (kMaxPlanSlices entries) when the partition is exact; table may be null to only size it.
+// `spans`: the span form (of one token, whose slices are cut finer where only a bound is known; the dense form may need fewer states
+// than the workspace that is sized without knowing the form).
 // With `runs` given (span form only) and host copies of the span lists in the descriptor, tries run mode first.
-Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* runs = nullptr);
+Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* runs = nullptr, bool spans = true);
 inline Partition plan_partition(const span_attn_desc_t* d) { return plan_partition(d, nullptr, nullptr); }
 
 // How a few-query call runs on the matrix cores (span_matrix.hip).  The workspace holds partial states of query tokens: at
@@ -91,6 +97,7 @@ struct MatrixPlan {
   bool table;            // slices from the table: sequences with several slices first, so an entry's index is its slot;
                          // whole sequences in the order that levels the CUs
   bool even;             // as in Partition
+  int32_t least_slice;   // as in Partition
   int32_t num_splits;    // as in Partition
   int32_t slice_tokens;  // as in Partition
   int32_t total_slices;  // table entries, or batch * num_splits

@@ -214,7 +214,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   SPAN_STAMP_AFTER(10, "s", intervals.count);
   int n_total = count_positions(a, intervals, wave, lane, s_u.st.tab);
   n_total = n_total < a.max_tokens ? n_total : a.max_tokens;
-  const int T = a.even ? even_share(n_total, nsl) : a.slice_tokens;
+  const int T = slice_size(a, n_total, nsl);
   const int slice_begin = split * T;
   const int cnt = __builtin_amdgcn_readfirstlane(clampi(n_total - slice_begin, 0, T));
   SPAN_STAMP_AFTER(1, "s", cnt);
@@ -815,7 +815,7 @@ void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* t
     m.num_splits = p.num_splits;
     m.slice_tokens = p.slice_tokens;
     m.total_slices = p.total_slices;
-    m.even = p.even ? 1 : 0;
+    m.even = p.even ? 1 : p.least_slice;
     m.interleave = p.slice_tokens >= kInterleaveFrom ? 1 : 0;
   };
   auto start = [&](auto shared, auto two_tokens) {
