@@ -55,6 +55,11 @@ struct MatrixShape {
   // register file, and 16 tokens of 16-bit rows of 128 at four waves per SIMD (batch 64 x ~155 positions, 16 tokens: 40.4
   // us against 44.2 with two and three waves).
   static constexpr int S = Elt::kBytes == 4 || G == 4 || (G == 1 && D == 128) ? 1 : 2;
+  // Up to 32 tokens of 16-bit rows of 128 have both (kOneGroup): with two groups a tile is 16 KB, and the workgroups of a single
+  // round, all asking at once, get their first one late and unevenly; with one the matrix cores do half as much per
+  // instruction.  us, two -> one: 512 workgroups, 16 x ~700 positions, bf16, 32 tokens 40.6 -> 39.0, appended 45.6 -> 44.1; in several rounds
+  // 64 x 32 pairs x ~220, bf16, 24 tokens 91.9 -> 97.0, 64 x 32 x ~400 fp16, 20 tokens 113.5 -> 119.8.
+  static constexpr bool kHasBoth = S == 2 && D == 128;
   // Waves per SIMD: the most whose registers hold the state (4 NE per group), a tile and its weights without spills.
   static constexpr int kWaves = D == 128 ? (G == 1 && Elt::kBytes == 2 ? 4 : 2) : (G == 1 ? 4 : (G == 2 ? 3 : 2));
 };
@@ -105,13 +110,13 @@ __device__ __forceinline__ f32x4 observe4(__amdgpu_buffer_rsrc_t slot, uint32_t 
 // the later readers find them in the L2; otherwise every row is used once and streams past it.  Inputs that no cache
 // holds from call to call: 32 pairs x ~5500 positions, 20 tokens 29.6 -> 25.2 us; 96 pairs x ~900, 60 tokens 30.1 -> 26.5; 32 pairs
 // x 1500 fp32, 30 tokens 30.8 -> 28.0; without query blocks it loses (64 x ~155, 16 tokens 39.8 -> 43.7).
-template <class Elt, int D, int G, class Args, bool kShared, int kTerms>
+template <class Elt, int D, int G, bool kOneGroup, class Args, bool kShared, int kTerms>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<Elt, D, G>::kWaves))) void matrix_kernel(const Args a) {
   using Shape = MatrixShape<Elt, D, G>;
   constexpr int kRowPolicy = kShared ? 0 : kRowLoadPolicy;
   auto load_piece = [](__amdgpu_buffer_rsrc_t slab, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(slab, off, 0, kRowPolicy); };
-  constexpr int NK = Shape::NK, NE = Shape::NE, VW = Shape::VW, S = Shape::S;
+  constexpr int NK = Shape::NK, NE = Shape::NE, VW = Shape::VW, S = kOneGroup ? 1 : Shape::S;
   constexpr int TR = 16 * S;                 // rows of a tile
   constexpr uint32_t ROWB = Shape::kRowBytes;
   constexpr int NQ = 16 * G;
@@ -802,6 +807,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   SPAN_TRACE_FLUSH();
 }
 
+constexpr int64_t kOneRoundOfTwo = 512;  // workgroups, two per CU
+
 template <class Elt, int D, int G>
 void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* table, int batch, int q_first, int tokens, hipStream_t stream) {
   const int blocks = (tokens + 16 * G - 1) / (16 * G);
@@ -818,21 +825,28 @@ void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* t
     m.even = p.even ? 1 : p.least_slice;
     m.interleave = p.slice_tokens >= kInterleaveFrom ? 1 : 0;
   };
-  auto start = [&](auto shared, auto two_tokens) {
-    constexpr bool kShared = decltype(shared)::value;
+  auto start_tiled = [&](auto one_group, auto shared, auto two_tokens) {
+    constexpr bool kOneGroup = decltype(one_group)::value, kShared = decltype(shared)::value;
     constexpr int kTerms = weight_terms<Elt, D>(decltype(two_tokens)::value);
     if (p.table) {
       MatrixArgsTable m;
       fill(m);
       for (int i = 0; i < p.total_slices; ++i) m.table[i] = table[i];
-      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsTable, kShared, kTerms>),
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, kOneGroup, MatrixArgsTable, kShared, kTerms>),
                          dim3((unsigned)base.heads, (unsigned)p.total_slices, (unsigned)blocks), dim3(kThreads), 0, stream, m);
     } else {
       MatrixArgsPlain m;
       fill(m);
-      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, MatrixArgsPlain, kShared, kTerms>),
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, kOneGroup, MatrixArgsPlain, kShared, kTerms>),
                          dim3((unsigned)base.heads, (unsigned)p.num_splits, (unsigned)(batch * blocks)), dim3(kThreads), 0, stream, m);
     }
+  };
+  auto start = [&](auto shared, auto two_tokens) {
+    if constexpr (MatrixShape<Elt, D, G>::kHasBoth) {
+      const int64_t workgroups = (int64_t)base.heads * blocks * (p.table ? p.total_slices : (int64_t)p.num_splits * batch);
+      if (workgroups <= kOneRoundOfTwo) return start_tiled(std::true_type{}, shared, two_tokens);
+    }
+    start_tiled(std::false_type{}, shared, two_tokens);
   };
   if constexpr (G < 4) {  // (64 tokens are a call's most: one block)
     if (blocks > 1) return start(std::true_type{}, std::false_type{});
