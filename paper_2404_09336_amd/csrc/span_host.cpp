@@ -606,6 +606,11 @@ size_t workspace_bytes_for(const span_attn_desc_t* d, int64_t states) {
 
 size_t workspace_least_bytes(const span_attn_desc_t* d, const Partition& p) { return workspace_bytes_for(d, least_states(p)); }
 
+Partition plan_for_workspace(const span_attn_desc_t* d, uint32_t* table, RunTables* runs, bool spans) {
+  const Partition p = plan_partition(d, table, runs, spans);
+  return spans && workspace_least_bytes(d, p) > d->workspace_bytes ? plan_partition(d, table, runs, false) : p;
+}
+
 size_t workspace_bytes(const span_attn_desc_t* d, const Partition& p) {
   int64_t states = least_states(p);
   const int64_t most = most_states(d, p);
@@ -648,7 +653,7 @@ extern "C" int span_launch_query(const span_attn_desc_t* desc, span_launch_info_
   if (!info) return SPAN_ERR_NULL;
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
-  const spanattn::Partition p = spanattn::plan_partition(desc);
+  const spanattn::Partition p = desc->workspace ? spanattn::plan_for_workspace(desc, nullptr, nullptr, true) : spanattn::plan_partition(desc);
   const int64_t states = !desc->workspace ? spanattn::most_states(desc, p) : spanattn::states_that_fit(desc, p);
   const int32_t n = spanattn::query_tokens(desc);
   spanattn::MatrixPlan m;

@@ -87,6 +87,8 @@ struct Partition {
 // With `runs` given (span form only) and host copies of the span lists in the descriptor, tries run mode first.
 Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* runs = nullptr, bool spans = true);
 inline Partition plan_partition(const span_attn_desc_t* d) { return plan_partition(d, nullptr, nullptr); }
+// The same with the descriptor's workspace: where it does not hold the finer cut of a bound it holds, as ever, the coarser one.
+Partition plan_for_workspace(const span_attn_desc_t* d, uint32_t* table, RunTables* runs, bool spans);
 
 // How a few-query call runs on the matrix cores (span_matrix.hip).  The workspace holds partial states of query tokens: at
 // least those of the Partition above, total_slices * queries_per_pass per head, and more where the caller brings them; the

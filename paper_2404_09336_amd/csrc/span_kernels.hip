@@ -754,7 +754,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
     own.host_span_offsets = own.host_span_starts = own.host_span_ends = nullptr;
     d = &own;
   }
-  Partition p = plan_partition(d, a.table, kDense ? nullptr : &runs, !kDense);
+  Partition p = plan_for_workspace(d, a.table, kDense ? nullptr : &runs, !kDense);
   const size_t need = workspace_least_bytes(d, p);
   if (need > 0 && (!d->workspace || ((uintptr_t)d->workspace & 255u) || d->workspace_bytes < need))
     return SPAN_ERR_WORKSPACE;
@@ -923,7 +923,7 @@ extern "C" int span_advance(const span_attn_desc_t* desc, const int32_t* span_of
 extern "C" int span_workspace_init(const span_attn_desc_t* desc) {
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
-  const spanattn::Partition p = spanattn::plan_partition(desc);
+  const spanattn::Partition p = spanattn::plan_for_workspace(desc, nullptr, nullptr, true);
   const size_t need = spanattn::workspace_least_bytes(desc, p);
   if (need == 0) return SPAN_OK;
   if (!desc->workspace || ((uintptr_t)desc->workspace & 255u) || desc->workspace_bytes < need) return SPAN_ERR_WORKSPACE;

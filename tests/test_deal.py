@@ -64,3 +64,15 @@ def test_dealt_calls(tokens, dtype, D, q_len, lists, gpu_device):
     err = float(np.abs(a.cpu().numpy().astype(np.float64) - ref).max())
     print(f"[parity] dealt {dtype} D={D} q_len={q_len} lists={lists}: {err:.3e}", flush=True)
     assert err <= cfg.tol
+
+
+def test_the_finer_cut_of_a_bound_needs_its_workspace():
+    """What the coarser cut asks for is enough: 9 x 16 pairs, 4000 positions at most, three slices where eight are wanted."""
+    from paper_2404_09336_amd import binding
+    desc = lambda size: binding.make_desc(9, 16, 64, 4000, 0, 10, 4000, 0, workspace_ptr=4096, workspace_bytes=size)  # noqa: E731
+    full = span.span_plan_query(binding.make_desc(9, 16, 64, 4000, 0, 10, 4000, 0))
+    assert full["max_splits"] == 8
+    states = 3 * 9 * 16
+    coarse = 768 + (states * 8 + 255) // 256 * 256 + states * 64 * 4
+    splits = [span.span_launch_query(desc(size))["max_splits"] for size in (coarse, full["workspace_bytes"] - 1, full["workspace_bytes"])]
+    assert splits == [3, 3, 8]

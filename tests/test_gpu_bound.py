@@ -54,3 +54,32 @@ def test_shares_of_a_bound(form, dtype, D, batch, heads, gpu_device):
     err = float(np.abs(out.cpu().numpy().astype(np.float64) - ref).max())
     print(f"[parity] bound {form} {dtype} D={D} batch={batch}: {err:.3e}", flush=True)
     assert err <= cfg.tol
+
+
+@pytest.mark.parametrize("given", ["coarse", "between", "full"])
+def test_the_workspace_of_the_coarse_cut_is_enough(given, gpu_device):
+    """A bound's finer cut wants a larger workspace; one that holds the coarse cut is
+    taken as before, and nothing past its size is written.  Tolerance as above."""
+    cfg = DecodeConfig(93, "bound-workspace", 9, 16, 64, 4000, 4000, "f32", 1e-5)
+    ctx = np.full(cfg.batch, cfg.max_len, np.int32)
+    q, K, V = draw_qkv(cfg, ctx, device=gpu_device, seed=23)
+    sp = SpanBatch.from_lists([[(5, 5 + 90 * (b + 1)), (3000, 3007 + 100 * b)] for b in range(cfg.batch)], ctx)
+    lists = [torch.from_numpy(np.ascontiguousarray(a)).to(gpu_device) for a in (sp.offsets, sp.starts, sp.ends)]
+    kw = dict(max_tokens=cfg.max_len)
+    full = span.span_plan_query(span.prepare_span_decode_attn(q, K, V, *lists, None, np.float32(cfg.scale), **kw).desc)
+    states = 3 * cfg.batch * cfg.heads                      # (three slices a sequence)
+    coarse = 768 + (states * 8 + 255) // 256 * 256 + states * cfg.head_dim * 4
+    size = {"coarse": coarse, "between": full["workspace_bytes"] - 256, "full": full["workspace_bytes"]}[given]
+    assert full["max_splits"] == 8 and coarse < size or given == "coarse"
+    buffer = torch.full((full["workspace_bytes"] + 4096,), 0x5a, dtype=torch.uint8, device=gpu_device)
+    buffer[:768] = 0                                        # the ticket counters
+    call = span.prepare_span_decode_attn(q, K, V, *lists, None, np.float32(cfg.scale), workspace=buffer[:size], **kw)
+    assert span.span_launch_query(call.desc)["max_splits"] == (8 if given == "full" else 3)
+    ref = oracle.span_attn(*(to_host_raw(x) for x in (q, K, V)), sp.offsets, sp.starts, sp.ends, np.float32(cfg.scale), dtype="f32")
+    for _ in range(3):
+        call.out.fill_(float("nan"))
+        assert float(np.abs(call().cpu().numpy().astype(np.float64) - ref).max()) <= cfg.tol
+    assert bool((buffer[size:] == 0x5a).all()) and not bool(buffer[:768].any())
+    call.desc.workspace_bytes = coarse - 1
+    with pytest.raises(span.SpanAttnError):
+        call()
