@@ -512,6 +512,7 @@ void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, b
   // rows of every slice, and what the CUs of a column get in plan order
   uint64_t by_rows[kMaxPlanSlices];  // rows << 16 | slice
   int64_t load[kTurn] = {};
+  int64_t all_rows = 0;
   int32_t b_last = 0, most = 1;
   for (int32_t i = 0; i < total; ++i) {
     const int32_t b = (int32_t)(entries[i] & 1023u), split = (int32_t)((entries[i] >> 10) & 2047u), nsl = (int32_t)(entries[i] >> 21);
@@ -519,10 +520,17 @@ void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, b
     const int64_t rows = std::min<int64_t>(std::max<int64_t>(n - split * T, 0), T);
     by_rows[i] = (uint64_t)rows << 16 | (uint64_t)i;
     load[i % columns] += rows;
+    all_rows += rows;
     b_last = std::max(b_last, b);
     most = std::max(most, nsl);
   }
   const int64_t plain_most = *std::max_element(load, load + columns);
+  const int64_t row_bytes = 2 * (int64_t)d->head_dim * (d->dtype == SPAN_F32 ? 4 : 2);
+  auto pays = [&](int64_t dealt_most) {
+    const int64_t spared = plain_most - dealt_most;
+    return spared > 0 && (table || (spared * row_bytes >= kDealTableBytes && spared * 20 >= dealt_most));
+  };
+  if (!pays(ceil_div(all_rows, columns))) return;  // (not even with the rows shared perfectly)
   int32_t b_bits = 1;
   while (b_last >> b_bits) ++b_bits;
   const int32_t n_bits = (32 - kSlotBits - b_bits) / 2;
@@ -543,9 +551,7 @@ void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, b
       deal->at[s & 0xffff] = (uint16_t)(t * columns + column[k]);
     }
   }
-  const int64_t dealt_most = *std::max_element(load, load + columns), spared = plain_most - dealt_most;
-  const int64_t row_bytes = 2 * (int64_t)d->head_dim * (d->dtype == SPAN_F32 ? 4 : 2);
-  if (spared <= 0 || (!table && (spared * row_bytes < kDealTableBytes || spared * 20 < dealt_most))) return;
+  if (!pays(*std::max_element(load, load + columns))) return;
   uint32_t dealt[kMaxPlanSlices];
   for (int32_t i = 0; i < total; ++i)
     dealt[deal->at[i]] = (entries[i] & 1023u) | ((entries[i] >> 10) & 2047u) << b_bits | (entries[i] >> 21) << (b_bits + n_bits) |
