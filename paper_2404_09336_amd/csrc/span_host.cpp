@@ -590,6 +590,10 @@ void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, Ru
 void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal) {
   deal->dealt = false;
   const bool one_block = m->tokens <= 16 * m->groups;  // (workgroups that share a slice are a whole grid apart)
+  // More than 16 tokens a workgroup and less than two turns: plan order.  Most CUs hold one workgroup, whose own trips and products bound the
+  // launch, not the CU's rows.  us, dealt -> plan order: fp32, 35 x 8 heads x ~110 positions, 17 tokens 26.2 -> 24.6; 40 x 8 x ~110 of 64,
+  // 40 tokens 25.7 -> 24.95; from two turns on the deal gains: 8 x 32 x ~600, 24 tokens 44.8 dealt, 49.7 in plan order.
+  if (m->groups > 1 && (int64_t)m->total_slices * d->heads < 2 * kTurn) return;
   if (!m->even || !one_block || (!m->table && !uniform_entries(d->batch, m->num_splits, table))) return;
   deal_slices(d, p.max_tokens, m->total_slices, m->table, table, deal);
   m->table = m->table || deal->dealt;
