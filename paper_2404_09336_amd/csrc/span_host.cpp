@@ -370,7 +370,9 @@ int64_t most_states(const span_attn_desc_t* d, const Partition& p) {
   return std::max(least, std::min<int64_t>(slices, (int64_t)kMaxPlanSlices * p.queries_per_pass));
 }
 
-static int64_t matrix_workgroups_per_cu(int32_t groups) { return groups == 1 ? 4 : (groups == 2 ? 3 : 2); }
+// Workgroups go to the CUs in turns of 256, heads fastest: table entries of a turn.
+constexpr int32_t kTurn = 256;  // CUs
+static int32_t turn_entries(int32_t heads) { return (kTurn + heads / 2) / heads; }
 
 bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
   int32_t n = query_tokens(d);
@@ -384,7 +386,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
   m->num_splits = p.num_splits;
   m->slice_tokens = p.slice_tokens;
   m->total_slices = p.total_slices;
-  const int32_t max_groups = kMatrixMaxGroups(d->dtype == SPAN_F32 ? 4 : 2, d->head_dim);
+  const int32_t elt_bytes = d->dtype == SPAN_F32 ? 4 : 2, max_groups = kMatrixMaxGroups(elt_bytes, d->head_dim);
   auto groups_for = [&](int64_t tokens) { return std::min<int32_t>(max_groups, tokens <= 16 ? 1 : (tokens <= 32 ? 2 : 4)); };
   if (d->num_splits > 0) {  // the caller's number of slices stands: as many tokens a launch as their states fit
     if (sliced && n > p.queries_per_pass) m->tokens = p.queries_per_pass;
@@ -399,7 +401,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
   while (m->groups > 1 && pairs * blocks_for(m->groups) < kMatrixPairs) m->groups /= 2;
   if (d->batch * blocks_for(m->groups) > 65535) m->tokens = n = 16 * m->groups;  // (grid.z limit)
   const int64_t blocks = blocks_for(m->groups);
-  const int64_t most = 256 * matrix_workgroups_per_cu(m->groups) / (d->heads * blocks), wanted = ceil_div(kMatrixWorkgroups, d->heads * blocks);
+  const int64_t most = kTurn * kMatrixWorkgroupsPerCu(2, 64, m->groups) / (d->heads * blocks), wanted = ceil_div(kMatrixWorkgroups, d->heads * blocks);
   const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
   if (!p.even) {  // the counts are not known: every sequence gets the same number of slices
     if (!sliced) return true;
@@ -470,7 +472,23 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
   m->num_splits = (int32_t)most_s;
   m->slice_tokens = (int32_t)longest;
   m->total_slices = (int32_t)total;
-  if (most_s != least_s) {
+  // Whole sequences of unequal length, more workgroups than run at once, in launches that deal_slices does not take: several
+  // query blocks, each a grid of its own behind the last, or heads that fill a turn alone.  The longest go first, which is what free CUs
+  // should find, and every second turn runs backwards, so that the CUs get long and short ones alike.  us in list order -> so:
+  // fp32 rows of 128, 16 x 32 heads x 400..1000 positions, 64 tokens 167.0 -> 159.9; 48 x 16 x 200..900, 48 tokens 212.3 -> 193.1; 36 x 12 x 300..1000, 40
+  // tokens 150.2 -> 127.3 (dealt by the rule for one block 146.2); rows of 64, 200..900: 12 x 200, fp16, 8 tokens 61.4 -> 57.6; 8 x 256 fp32, 64 tokens
+  // 231.9 -> 223.4; all at once, where the table is all that it adds: 5 x 200, 8 tokens 26.4 -> 26.8, 3 x 300 26.8 -> 27.4.
+  const int64_t at_once = (int64_t)kTurn * kMatrixWorkgroupsPerCu(elt_bytes, d->head_dim, m->groups);
+  const int32_t row = std::max<int32_t>(1, kTurn / d->heads);
+  if (most_s == 1 && (blocks > 1 || turn_entries(d->heads) < 2) && d->batch > row && d->batch <= kMaxPlanSlices && pairs * blocks > at_once &&
+      longest * 100 * d->batch > 115 * sum) {
+    uint64_t by_length[kMaxPlanSlices];  // positions << 16 | sequence
+    for (int32_t b = 0; b < d->batch; ++b) by_length[b] = (uint64_t)tokens(b) << 16 | (uint64_t)b;
+    std::sort(by_length, by_length + d->batch, [](uint64_t x, uint64_t y) { return x > y; });
+    for (int32_t r = row; r < d->batch; r += 2 * row) std::reverse(by_length + r, by_length + std::min(r + row, d->batch));
+    m->table = true;
+    for (int32_t y = 0; y < d->batch; ++y) table[y] = pack_slice((uint32_t)(by_length[y] & 0xffff), 0, 1);
+  } else if (most_s != least_s) {
     m->table = true;
     int32_t y = 0;
     for (int pass = 0; pass < 2; ++pass) {
@@ -496,12 +514,11 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
 // A launch whose plan needs no table carries one where that spares a CU 5 % and 16 KB (its share of 0.6 us; the table's 3 KB of
 // arguments cost 0.35): 60 x 32 heads x ~300 of 64, 5 tokens 57.1 -> 53.4; 8 x 32 x 500..900, two slices each, 2 tokens 21.0 -> 20.9.  Sequences of
 // almost the same length have nothing to win (64 x 144..168 positions: 28.4 with and without).
-constexpr int32_t kTurn = 256;              // CUs
 constexpr int64_t kDealTableBytes = 16384;  // bytes a CU must be spared for a launch to carry a table it can do without
 
 void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, bool table, uint32_t* entries, Deal* deal) {
   deal->dealt = false;
-  const int32_t columns = (kTurn + d->heads / 2) / d->heads;  // table entries of a turn
+  const int32_t columns = turn_entries(d->heads);
   if (columns < 2 || total <= columns || total > kMaxPlanSlices) return;
   std::vector<int64_t> from_lists;
   const int64_t* counts = d->tokens_per_seq;
@@ -589,7 +606,7 @@ void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, Ru
 
 void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal) {
   deal->dealt = false;
-  const bool one_block = m->tokens <= 16 * m->groups;  // (workgroups that share a slice are a whole grid apart)
+  const bool one_block = m->tokens <= 16 * m->groups;  // (several: see plan_matrix)
   // More than 16 tokens a workgroup and less than two turns: plan order.  Most CUs hold one workgroup, whose own trips and products bound the
   // launch, not the CU's rows.  us, dealt -> plan order: fp32, 35 x 8 heads x ~110 positions, 17 tokens 26.2 -> 24.6; 40 x 8 x ~110 of 64,
   // 40 tokens 25.7 -> 24.95; from two turns on the deal gains: 8 x 32 x ~600, 24 tokens 44.8 dealt, 49.7 in plan order.

@@ -107,6 +107,11 @@ struct MatrixPlan {
 };
 // Most groups a workgroup serves: the state of 64 tokens of fp32 rows of 128 does not fit the registers next to a tile.
 constexpr int kMatrixMaxGroups(int elt_bytes, int head_dim) { return elt_bytes == 4 && head_dim == 128 ? 2 : 4; }
+// Workgroups of the matrix kernel that a CU runs at once, one wave per SIMD each: the most whose registers hold the state, a tile and
+// its weights.
+constexpr int kMatrixWorkgroupsPerCu(int elt_bytes, int head_dim, int groups) {
+  return head_dim == 128 ? (groups == 1 && elt_bytes == 2 ? 4 : 2) : (groups == 1 ? 4 : (groups == 2 ? 3 : 2));
+}
 bool runs_on_matrix_cores(const span_attn_desc_t* d);
 int64_t least_states(const Partition& p);                             // token states per head a call must bring
 int64_t most_states(const span_attn_desc_t* d, const Partition& p);   // ... it can use

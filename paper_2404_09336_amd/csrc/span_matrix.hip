@@ -60,8 +60,7 @@ struct MatrixShape {
   // instruction.  us, two -> one: 512 workgroups, 16 x ~700 positions, bf16, 32 tokens 40.6 -> 39.0, appended 45.6 -> 44.1; in several rounds
   // 64 x 32 pairs x ~220, bf16, 24 tokens 91.9 -> 97.0, 64 x 32 x ~400 fp16, 20 tokens 113.5 -> 119.8.
   static constexpr bool kHasBoth = S == 2 && D == 128;
-  // Waves per SIMD: the most whose registers hold the state (4 NE per group), a tile and its weights without spills.
-  static constexpr int kWaves = D == 128 ? (G == 1 && Elt::kBytes == 2 ? 4 : 2) : (G == 1 ? 4 : (G == 2 ? 3 : 2));
+  static constexpr int kWaves = kMatrixWorkgroupsPerCu(Elt::kBytes, D, G);  // per SIMD
 };
 
 // Terms of a weight in the storage type.  Three hold all 24 bits of the fp32 weight; bf16 rows need them.  Of fp16 rows the

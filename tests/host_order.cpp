@@ -1,0 +1,99 @@
+// The order in which whole sequences of unequal length go out: every sequence once, and no CU with many more rows than the others.
+// Workgroups go to the CUs in turns of 256, heads fastest.
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <random>
+#include <vector>
+
+#include "span_internal.h"
+
+#define REQUIRE(c)                                                                 \
+  do {                                                                             \
+    if (!(c)) {                                                                    \
+      std::printf("%s:%d: %s (%s)\n", __FILE__, __LINE__, #c, name);               \
+      std::abort();                                                                \
+    }                                                                              \
+  } while (0)
+
+using namespace spanattn;
+
+struct Order {
+  MatrixPlan plan;
+  Deal deal;
+  std::vector<int32_t> sequence, split, slices;  // of the table's entries
+  double fullest;                                // rows of the fullest column of CUs over the mean, in the first query block
+};
+
+static Order order(const char* name, int dtype, int batch, int heads, int head_dim, int least, int most, int tokens) {
+  std::mt19937 rng(batch * 1000 + heads);
+  span_attn_desc_t d = {};
+  d.batch = batch;
+  d.heads = heads;
+  d.head_dim = head_dim;
+  d.dtype = dtype;
+  d.max_len = most;
+  d.q_len = tokens;
+  std::vector<int64_t> counts(batch);
+  for (auto& n : counts) n = least + (int)(rng() % (unsigned)(most - least + 1));
+  d.tokens_per_seq = counts.data();
+  std::vector<uint32_t> table(kMaxPlanSlices);
+  const Partition p = plan_partition(&d, table.data());
+  Order o;
+  REQUIRE(plan_matrix(&d, p, most_states(&d, p), &o.plan, table.data()));
+  deal_matrix(&d, p, &o.plan, table.data(), &o.deal);
+  const int columns = std::max(1, 256 / heads);
+  std::vector<int64_t> load(columns, 0);
+  int64_t sum = 0;
+  std::vector<int> seen((size_t)batch, 0);
+  for (int y = 0; y < o.plan.total_slices; ++y) {
+    const uint32_t e = o.plan.table ? table[y] : pack_slice(y / o.plan.num_splits, y % o.plan.num_splits, o.plan.num_splits);
+    const uint32_t in_n = (1u << o.deal.n_bits) - 1;
+    const int b = e & ((1u << o.deal.b_bits) - 1), split = e >> o.deal.b_bits & in_n, n = e >> (o.deal.b_bits + o.deal.n_bits) & in_n;
+    REQUIRE(b < batch && split < n);
+    ++seen[b];
+    const int64_t T = (counts[b] + n - 1) / n, rows = std::min(std::max<int64_t>(counts[b] - split * T, 0), T);
+    load[y % columns] += rows;
+    sum += rows;
+    o.sequence.push_back(b);
+    o.split.push_back(split);
+    o.slices.push_back(n);
+  }
+  for (int y = 0; y < o.plan.total_slices; ++y) REQUIRE(seen[o.sequence[y]] == o.slices[y]);
+  o.fullest = (double)*std::max_element(load.begin(), load.end()) * columns / (double)sum;
+  std::printf("%-28s slices %d groups %d table %d dealt %d fullest %.3f\n", name, o.plan.total_slices, o.plan.groups, o.plan.table, o.deal.dealt,
+              o.fullest);
+  return o;
+}
+
+// Launches of several query blocks, and those whose heads fill a turn alone.
+static void several_blocks() {
+  struct Shape {
+    const char* name;
+    int dtype, batch, heads, head_dim, least, most, tokens;
+    double fullest;
+  } shapes[] = {{"32x32 two blocks", SPAN_F32, 32, 32, 128, 500, 1000, 64, 1.05}, {"64x16 two blocks", SPAN_F32, 64, 16, 128, 300, 900, 48, 1.06},
+                {"16x32 two blocks", SPAN_F32, 16, 32, 128, 400, 1000, 33, 1.08},  {"24x64 two blocks", SPAN_F32, 24, 64, 128, 100, 400, 40, 1.05}};
+  for (const Shape& s : shapes) {
+    const char* name = s.name;
+    const Order o = order(s.name, s.dtype, s.batch, s.heads, s.head_dim, s.least, s.most, s.tokens);
+    REQUIRE(o.plan.num_splits == 1 && o.plan.tokens > 16 * o.plan.groups);
+    REQUIRE(o.plan.table && o.fullest < s.fullest);
+  }
+  for (int heads : {192, 256, 300}) {
+    const char* name = "heads fill a turn";
+    const Order o = order(name, SPAN_F16, 10, heads, 64, 200, 900, 20);
+    REQUIRE(o.plan.table && !o.deal.dealt);
+  }
+  for (int tokens : {64, 8}) {  // lengths almost alike: no table
+    const char* name = "level";
+    REQUIRE(!order(name, SPAN_F32, 32, tokens == 64 ? 32 : 200, 128, 990, 1000, tokens).plan.table);
+  }
+}
+
+int main() {
+  several_blocks();
+  std::puts("host_order: ok");
+  return 0;
+}
