@@ -514,9 +514,15 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
 // A launch whose plan needs no table carries one where that spares a CU 5 % and 16 KB (its share of 0.6 us; the table's 3 KB of
 // arguments cost 0.35): 60 x 32 heads x ~300 of 64, 5 tokens 57.1 -> 53.4; 8 x 32 x 500..900, two slices each, 2 tokens 21.0 -> 20.9.  Sequences of
 // almost the same length have nothing to win (64 x 144..168 positions: 28.4 with and without).
+// In less than two turns of workgroups of more than 16 tokens most CUs hold one, and the hand-over of a slice's states counts as well: as this many
+// rows, which puts the slices of cut sequences ahead of short whole ones.  us in plan order -> dealt by rows alone -> with the hand-over:
+// fp32, 35 x 8 heads x 60..160 positions, 17 tokens 21.1 -> 24.1 -> 21.4; 40 x 8 x ~110 of 64, 40 tokens 23.0 -> 23.3 -> 22.7; 41 x 12 x 599..999 of
+// 64, 47 tokens 95.1 -> 81.3 -> 81.1; 12 x 32 x ~200, 24 tokens 35.1 -> 33.6 -> 33.3 (64 rows do as well but for 30 x 12 x 60..250, 20 tokens, 25.7 ->
+// 26.9 and 25.6 with 128).  Whole sequences, 63 x 8 x 53..268, fp16, 59 tokens 26.5 -> 23.3; 12 x 40 x 345..1151, bf16, 46 tokens 57.6 -> 50.8.
+constexpr int32_t kHandOverRows = 128;
 constexpr int64_t kDealTableBytes = 16384;  // bytes a CU must be spared for a launch to carry a table it can do without
 
-void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, bool table, uint32_t* entries, Deal* deal) {
+void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, int32_t hand_over, bool table, uint32_t* entries, Deal* deal) {
   deal->dealt = false;
   const int32_t columns = turn_entries(d->heads);
   if (columns < 2 || total <= columns || total > kMaxPlanSlices) return;
@@ -534,7 +540,7 @@ void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, b
   for (int32_t i = 0; i < total; ++i) {
     const int32_t b = (int32_t)(entries[i] & 1023u), split = (int32_t)((entries[i] >> 10) & 2047u), nsl = (int32_t)(entries[i] >> 21);
     const int64_t n = std::min<int64_t>(std::max<int64_t>(counts[b], 0), max_tokens), T = ceil_div(n, nsl);
-    const int64_t rows = std::min<int64_t>(std::max<int64_t>(n - split * T, 0), T);
+    const int64_t rows = std::min<int64_t>(std::max<int64_t>(n - split * T, 0), T) + (nsl > 1 ? hand_over : 0);
     by_rows[i] = (uint64_t)rows << 16 | (uint64_t)i;
     load[i % columns] += rows;
     all_rows += rows;
@@ -569,6 +575,16 @@ void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, b
     }
   }
   if (!pays(*std::max_element(load, load + columns))) return;
+  if (hand_over > 0) {  // (an estimate: the rows alone must get more level as well)
+    int64_t rows_plain[kTurn] = {}, rows_dealt[kTurn] = {};
+    for (int32_t k = 0; k < total; ++k) {
+      const int32_t i = (int32_t)(by_rows[k] & 0xffff);
+      const int64_t rows = (int64_t)(by_rows[k] >> 16) - (entries[i] >> 21 > 1 ? hand_over : 0);
+      rows_plain[i % columns] += rows;
+      rows_dealt[deal->at[i] % columns] += rows;
+    }
+    if (*std::max_element(rows_dealt, rows_dealt + columns) >= *std::max_element(rows_plain, rows_plain + columns)) return;
+  }
   uint32_t dealt[kMaxPlanSlices];
   for (int32_t i = 0; i < total; ++i)
     dealt[deal->at[i]] = (entries[i] & 1023u) | ((entries[i] >> 10) & 2047u) << b_bits | (entries[i] >> 21) << (b_bits + n_bits) |
@@ -591,7 +607,7 @@ static bool uniform_entries(int32_t batch, int32_t slices, uint32_t* entries) {
 void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, RunTables* runs, Deal* deal) {
   deal->dealt = false;
   if (!p->even || (!p->exact && !uniform_entries(d->batch, p->num_splits, table))) return;
-  deal_slices(d, p->max_tokens, p->total_slices, p->exact, table, deal);
+  deal_slices(d, p->max_tokens, p->total_slices, 0, p->exact, table, deal);
   if (!deal->dealt) return;
   p->exact = true;
   if (p->runs) {
@@ -607,12 +623,9 @@ void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, Ru
 void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal) {
   deal->dealt = false;
   const bool one_block = m->tokens <= 16 * m->groups;  // (several: see plan_matrix)
-  // More than 16 tokens a workgroup and less than two turns: plan order.  Most CUs hold one workgroup, whose own trips and products bound the
-  // launch, not the CU's rows.  us, dealt -> plan order: fp32, 35 x 8 heads x ~110 positions, 17 tokens 26.2 -> 24.6; 40 x 8 x ~110 of 64,
-  // 40 tokens 25.7 -> 24.95; from two turns on the deal gains: 8 x 32 x ~600, 24 tokens 44.8 dealt, 49.7 in plan order.
-  if (m->groups > 1 && (int64_t)m->total_slices * d->heads < 2 * kTurn) return;
   if (!m->even || !one_block || (!m->table && !uniform_entries(d->batch, m->num_splits, table))) return;
-  deal_slices(d, p.max_tokens, m->total_slices, m->table, table, deal);
+  const int32_t hand_over = m->groups > 1 && (int64_t)m->total_slices * d->heads < 2 * kTurn ? kHandOverRows : 0;
+  deal_slices(d, p.max_tokens, m->total_slices, hand_over, m->table, table, deal);
   m->table = m->table || deal->dealt;
 }
 

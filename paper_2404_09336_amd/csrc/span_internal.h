@@ -123,8 +123,9 @@ inline bool plan_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPla
 }
 
 // Deals the slices of a plan that cuts its sequences evenly: `entries` holds them in plan order, as pack_slice packs them, and
-// is rewritten if the deal is worth it.  `table`: the launch carries a table anyway.
-void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, bool table, uint32_t* entries, Deal* deal);
+// is rewritten if the deal is worth it.  `hand_over`: rows that a slice of a sequence with several counts more; `table`: the launch carries
+// a table anyway.
+void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, int32_t hand_over, bool table, uint32_t* entries, Deal* deal);
 // The same for what the vector kernels and the matrix kernel launch; a plan without a table may get one.
 void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, RunTables* runs, Deal* deal);
 void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal);

@@ -92,8 +92,30 @@ static void several_blocks() {
   }
 }
 
+// Less than two turns of workgroups with more than 16 tokens each.
+static void less_than_two_turns() {
+  struct Shape {
+    const char* name;
+    int dtype, batch, heads, head_dim, least, most, tokens;
+    double fullest;
+  } shapes[] = {{"60x8", SPAN_F16, 60, 8, 128, 53, 268, 59, 1.2}, {"58x8", SPAN_F32, 58, 8, 64, 32, 107, 44, 1.2},
+                {"53x8", SPAN_F32, 53, 8, 128, 123, 206, 22, 1.4}, {"41x12", SPAN_F32, 41, 12, 64, 599, 999, 47, 1.2}};
+  for (const Shape& s : shapes) {
+    const char* name = s.name;
+    const Order o = order(s.name, s.dtype, s.batch, s.heads, s.head_dim, s.least, s.most, s.tokens);
+    REQUIRE(o.plan.total_slices * s.heads < 512 && o.plan.groups > 1);
+    REQUIRE(o.deal.dealt && o.fullest < s.fullest);
+  }
+  // Short sequences, some of them cut: the cut ones' slices, which have a hand-over ahead of them, go out in the first turn, as in plan order.
+  const char* name = "35x8";
+  const Order o = order(name, SPAN_F32, 35, 8, 128, 60, 160, 17);
+  REQUIRE(o.plan.num_splits == 2);
+  for (int y = 32; y < o.plan.total_slices; ++y) REQUIRE(o.slices[y] == 1);
+}
+
 int main() {
   several_blocks();
+  less_than_two_turns();
   std::puts("host_order: ok");
   return 0;
 }
