@@ -202,18 +202,19 @@ static bool has_host_lists(const span_attn_desc_t* d) {
   return d->host_span_offsets && (d->num_intervals == 0 || (d->host_span_starts && d->host_span_ends));
 }
 
-// Attended positions of every sequence from the host copies of the span lists, with the clamps the kernel applies
-// to the device lists (interval indices to [0, num_intervals], lengths to [0, max_len]).
-static void tokens_from_host_lists(const span_attn_desc_t* d, std::vector<int64_t>* tokens) {
-  tokens->assign((size_t)d->batch, 0);
+// From the host copies of the span lists the positions are counted with the clamps the kernel applies to the device lists (interval
+// indices to [0, num_intervals], lengths to [0, max_len]).
+TokenCounts::TokenCounts(const span_attn_desc_t* d) : from_lists(has_host_lists(d) && d->batch <= kMaxPlanBatch), of(d->tokens_per_seq) {
+  if (!from_lists) return;
   for (int32_t b = 0; b < d->batch; ++b) {
     const int32_t lo = std::min(std::max(d->host_span_offsets[b], 0), d->num_intervals);
     const int32_t hi = std::min(std::max(d->host_span_offsets[b + 1], lo), d->num_intervals);
     int64_t n = 0;
     for (int32_t i = lo; i < hi; ++i)
       n += std::min<int64_t>(std::max<int64_t>((int64_t)d->host_span_ends[i] - d->host_span_starts[i], 0), d->max_len);
-    (*tokens)[(size_t)b] = n;
+    counted_[b] = n;
   }
+  of = counted_;
 }
 
 // Run mode: resolves each slice of an exact plan to its runs of consecutive cache positions.  Sequence b has
@@ -270,24 +271,15 @@ static bool plan_runs(const span_attn_desc_t* d, const int64_t* tokens_per_seq, 
 // bf16 41.0 -> 31.0 (38.9 shared alone), 16 x 16 x 5..50 % of 1200..4000 fp32 of 64 24.6 -> 19.2 (22.7); slices of up to 256 or 384 win and
 // lose 5 % against 512; dense contexts, which are less ragged, lose by more slices (8 x 32 x 600..2000 33.4 -> 36.2), and few sequences
 // have enough as it is (6 x 16 x ~400 10.0 and 10.0, 10 x 8 x ~560 11.5 and 11.5).
-Partition plan_partition(const span_attn_desc_t* d, uint32_t* table, RunTables* runs, bool spans) {
+Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans) {
   const int64_t max_tok = (d->max_tokens > 0 && d->max_tokens < d->max_len) ? d->max_tokens : d->max_len;
   Partition p;
-  // Host copies of the span lists, when given, are the authority on the token counts (tokens_per_seq is then not
-  // consulted), in every function that plans from this descriptor, so that they all agree.
-  const int64_t* tokens = d->tokens_per_seq;
-  std::vector<int64_t> from_lists;
-  const bool lists = has_host_lists(d) && d->batch <= kMaxPlanBatch;
-  if (lists) {
-    tokens_from_host_lists(d, &from_lists);
-    tokens = from_lists.data();
-  }
-  if (plan_exact(d, tokens, max_tok, &p, table)) {
+  if (plan_exact(d, counts.of, max_tok, &p, table)) {
     // Run mode pays where the launch carries a slice table anyway (sequences with different numbers of slices):
     // kernel arguments of that size cost a few tenths of a microsecond per launch, which a batch that needs no
     // table would pay on top (measured: batch 64 x 155 positions, one slice each, 27.7 -> 27.9 us with runs;
     // batch 8 and batch 16 sliced raggedly, 24.1 -> 23.7 us and 31.1 -> 30.8 us).  The matrix kernel takes no runs.
-    if (lists && runs && p.exact && !runs_on_matrix_cores(d)) p.runs = plan_runs(d, tokens, p, runs);
+    if (counts.from_lists && runs && p.exact && !runs_on_matrix_cores(d)) p.runs = plan_runs(d, counts.of, p, runs);
     return p;
   }
   const int64_t pairs = (int64_t)d->batch * d->heads;
@@ -371,10 +363,10 @@ int64_t most_states(const span_attn_desc_t* d, const Partition& p) {
 }
 
 // Workgroups go to the CUs in turns of 256, heads fastest: table entries of a turn.
-constexpr int32_t kTurn = 256;  // CUs
+constexpr int32_t kTurn = 256;  // CUs (a column fits 8 bits)
 static int32_t turn_entries(int32_t heads) { return (kTurn + heads / 2) / heads; }
 
-bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
+bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
   int32_t n = query_tokens(d);
   if (!runs_on_matrix_cores(d)) return false;
   const bool sliced = p.num_splits > 1;
@@ -415,13 +407,7 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
     if (m->num_splits > 1) m->states = (int64_t)m->total_slices * n;
     return true;
   }
-  std::vector<int64_t> from_lists;
-  const int64_t* counts = d->tokens_per_seq;
-  if (has_host_lists(d) && d->batch <= kMaxPlanBatch) {
-    tokens_from_host_lists(d, &from_lists);
-    counts = from_lists.data();
-  }
-  auto tokens = [&](int32_t b) { return std::min<int64_t>(std::max<int64_t>(counts[b], 0), p.max_tokens); };
+  auto tokens = [&](int32_t b) { return std::min<int64_t>(std::max<int64_t>(counts.of[b], 0), p.max_tokens); };
   int64_t sum = 0;
   for (int32_t b = 0; b < d->batch; ++b) sum += tokens(b);
   // `cap` slices at most, and those of the sequences with several fit the slots
@@ -510,7 +496,8 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
 // still is one of falling size, which is what free CUs should find.  us in plan order -> dealt, 32 heads x 128 unless said
 // otherwise: 32 x ~2700 positions in 64 slices, bf16 230 -> 222; 64 x ~800 121.5 -> 118.4; 40 x 400..2000 dense 127.5 -> 124.3; 32 x ~560, 64
 // tokens 117 -> 106; 60 x ~300 of 64, 5 tokens 55.4 -> 53.5; 8 x ~600 fp32, 24 tokens 49.7 -> 47.2; 16 x 16 heads x ~380 of 64, 9
-// tokens 14.4 -> 13.9; batch 16 x ~550 31.2 -> 30.2.  The host pays 0.3 us for 16 slices, 1.3 for 64, 3 for 120.
+// tokens 14.4 -> 13.9; batch 16 x ~550 31.2 -> 30.2.  The host pays 0.5 us for 30 slices, 1 for 64, 2.5 for 165 (the whole plan
+// 1.3 -> 1.9 us, 2.8 -> 3.7, 5.5 -> 8.0).
 // A launch whose plan needs no table carries one where that spares a CU 5 % and 16 KB (its share of 0.6 us; the table's 3 KB of
 // arguments cost 0.35): 60 x 32 heads x ~300 of 64, 5 tokens 57.1 -> 53.4; 8 x 32 x 500..900, two slices each, 2 tokens 21.0 -> 20.9.  Sequences of
 // almost the same length have nothing to win (64 x 144..168 positions: 28.4 with and without).
@@ -522,27 +509,25 @@ bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, 
 constexpr int32_t kHandOverRows = 128;
 constexpr int64_t kDealTableBytes = 16384;  // bytes a CU must be spared for a launch to carry a table it can do without
 
-void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, int32_t hand_over, bool table, uint32_t* entries, Deal* deal) {
+void deal_slices(const span_attn_desc_t* d, const TokenCounts& counts, int64_t max_tokens, int32_t total, int32_t hand_over, bool table,
+                 uint32_t* entries, Deal* deal) {
   deal->dealt = false;
   const int32_t columns = turn_entries(d->heads);
   if (columns < 2 || total <= columns || total > kMaxPlanSlices) return;
-  std::vector<int64_t> from_lists;
-  const int64_t* counts = d->tokens_per_seq;
-  if (has_host_lists(d)) {
-    tokens_from_host_lists(d, &from_lists);
-    counts = from_lists.data();
-  }
   // rows of every slice, and what the CUs of a column get in plan order
   uint64_t by_rows[kMaxPlanSlices];  // rows << 16 | slice
   int64_t load[kTurn] = {};
   int64_t all_rows = 0;
   int32_t b_last = 0, most = 1;
-  for (int32_t i = 0; i < total; ++i) {
+  for (int32_t i = 0, column = 0; i < total; ++i, column = column + 1 < columns ? column + 1 : 0) {
     const int32_t b = (int32_t)(entries[i] & 1023u), split = (int32_t)((entries[i] >> 10) & 2047u), nsl = (int32_t)(entries[i] >> 21);
-    const int64_t n = std::min<int64_t>(std::max<int64_t>(counts[b], 0), max_tokens), T = ceil_div(n, nsl);
-    const int64_t rows = std::min<int64_t>(std::max<int64_t>(n - split * T, 0), T) + (nsl > 1 ? hand_over : 0);
+    int32_t rows = (int32_t)std::min<int64_t>(std::max<int64_t>(counts.of[b], 0), max_tokens);
+    if (nsl > 1) {
+      const int32_t T = (int32_t)(((uint32_t)rows + (uint32_t)nsl - 1) / (uint32_t)nsl);
+      rows = std::min(std::max(rows - split * T, 0), T) + hand_over;
+    }
     by_rows[i] = (uint64_t)rows << 16 | (uint64_t)i;
-    load[i % columns] += rows;
+    load[column] += rows;
     all_rows += rows;
     b_last = std::max(b_last, b);
     most = std::max(most, nsl);
@@ -560,21 +545,18 @@ void deal_slices(const span_attn_desc_t* d, int64_t max_tokens, int32_t total, i
   if (most >> n_bits) return;
   std::sort(by_rows, by_rows + total, [](uint64_t x, uint64_t y) { return x > y; });
   const int32_t turns = total / columns, rest = total % columns;  // whole turns, entries of the last one
-  uint16_t column[kTurn];
-  for (int32_t c = 0; c < columns; ++c) {
-    column[c] = (uint16_t)c;
-    load[c] = c < rest ? (int64_t)(by_rows[total - 1 - c] >> 16) : 0;
-  }
+  uint64_t by_load[kTurn];  // rows so far << 8 | column
+  for (int32_t c = 0; c < columns; ++c) by_load[c] = (c < rest ? by_rows[total - 1 - c] >> 16 << 8 : 0) | (uint64_t)c;
   for (int32_t c = 0; c < rest; ++c) deal->at[by_rows[total - 1 - c] & 0xffff] = (uint16_t)(turns * columns + c);
   for (int32_t t = 0; t < turns; ++t) {
-    std::sort(column, column + columns, [&](uint16_t x, uint16_t y) { return load[x] != load[y] ? load[x] < load[y] : x < y; });
+    std::sort(by_load, by_load + columns);
     for (int32_t k = 0; k < columns; ++k) {
       const uint64_t s = by_rows[t * columns + k];
-      load[column[k]] += (int64_t)(s >> 16);
-      deal->at[s & 0xffff] = (uint16_t)(t * columns + column[k]);
+      deal->at[s & 0xffff] = (uint16_t)(t * columns + (int32_t)(by_load[k] & 0xff));
+      by_load[k] += s >> 16 << 8;
     }
   }
-  if (!pays(*std::max_element(load, load + columns))) return;
+  if (!pays((int64_t)(*std::max_element(by_load, by_load + columns) >> 8))) return;
   if (hand_over > 0) {  // (an estimate: the rows alone must get more level as well)
     int64_t rows_plain[kTurn] = {}, rows_dealt[kTurn] = {};
     for (int32_t k = 0; k < total; ++k) {
@@ -604,10 +586,10 @@ static bool uniform_entries(int32_t batch, int32_t slices, uint32_t* entries) {
   return true;
 }
 
-void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, RunTables* runs, Deal* deal) {
+void deal_partition(const span_attn_desc_t* d, const TokenCounts& counts, Partition* p, uint32_t* table, RunTables* runs, Deal* deal) {
   deal->dealt = false;
   if (!p->even || (!p->exact && !uniform_entries(d->batch, p->num_splits, table))) return;
-  deal_slices(d, p->max_tokens, p->total_slices, 0, p->exact, table, deal);
+  deal_slices(d, counts, p->max_tokens, p->total_slices, 0, p->exact, table, deal);
   if (!deal->dealt) return;
   p->exact = true;
   if (p->runs) {
@@ -620,12 +602,12 @@ void deal_partition(const span_attn_desc_t* d, Partition* p, uint32_t* table, Ru
   }
 }
 
-void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal) {
+void deal_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, MatrixPlan* m, uint32_t* table, Deal* deal) {
   deal->dealt = false;
   const bool one_block = m->tokens <= 16 * m->groups;  // (several: see plan_matrix)
   if (!m->even || !one_block || (!m->table && !uniform_entries(d->batch, m->num_splits, table))) return;
   const int32_t hand_over = m->groups > 1 && (int64_t)m->total_slices * d->heads < 2 * kTurn ? kHandOverRows : 0;
-  deal_slices(d, p.max_tokens, m->total_slices, hand_over, m->table, table, deal);
+  deal_slices(d, counts, p.max_tokens, m->total_slices, hand_over, m->table, table, deal);
   m->table = m->table || deal->dealt;
 }
 
@@ -646,18 +628,18 @@ size_t workspace_bytes_for(const span_attn_desc_t* d, int64_t states) {
 
 size_t workspace_least_bytes(const span_attn_desc_t* d, const Partition& p) { return workspace_bytes_for(d, least_states(p)); }
 
-Partition plan_for_workspace(const span_attn_desc_t* d, uint32_t* table, RunTables* runs, bool spans) {
-  const Partition p = plan_partition(d, table, runs, spans);
-  return spans && workspace_least_bytes(d, p) > d->workspace_bytes ? plan_partition(d, table, runs, false) : p;
+Partition plan_for_workspace(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans) {
+  const Partition p = plan_partition(d, counts, table, runs, spans);
+  return spans && workspace_least_bytes(d, p) > d->workspace_bytes ? plan_partition(d, counts, table, runs, false) : p;
 }
 
-size_t workspace_bytes(const span_attn_desc_t* d, const Partition& p) {
+size_t workspace_bytes(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p) {
   int64_t states = least_states(p);
   const int64_t most = most_states(d, p);
   if (most > states) {  // (a few-query call whose pool may be larger: as much as its plan uses)
     MatrixPlan m;
-    std::vector<uint32_t> table((size_t)kMaxPlanSlices);
-    if (plan_matrix(d, p, most, &m, table.data())) states = std::max(states, m.states);
+    uint32_t table[kMaxPlanSlices];
+    if (plan_matrix(d, counts, p, most, &m, table)) states = std::max(states, m.states);
   }
   return workspace_bytes_for(d, states);
 }
@@ -677,7 +659,8 @@ extern "C" int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* i
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
   spanattn::RunTables runs;
-  const spanattn::Partition p = spanattn::plan_partition(desc, nullptr, &runs);
+  const spanattn::TokenCounts counts(desc);
+  const spanattn::Partition p = spanattn::plan_partition(desc, counts, nullptr, &runs, true);
   info->runs_in_arguments = p.runs ? 1 : 0;
   info->queries_per_pass = p.queries_per_pass;
   info->exact = p.even ? 1 : 0;
@@ -685,7 +668,7 @@ extern "C" int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* i
   info->max_splits = p.num_splits;
   info->slice_limit = spanattn::kMaxSlice;
   info->workgroups = (int64_t)p.total_slices * desc->heads;
-  info->workspace_bytes = (int64_t)spanattn::workspace_bytes(desc, p);
+  info->workspace_bytes = (int64_t)spanattn::workspace_bytes(desc, counts, p);
   return SPAN_OK;
 }
 
@@ -693,12 +676,14 @@ extern "C" int span_launch_query(const span_attn_desc_t* desc, span_launch_info_
   if (!info) return SPAN_ERR_NULL;
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
-  const spanattn::Partition p = desc->workspace ? spanattn::plan_for_workspace(desc, nullptr, nullptr, true) : spanattn::plan_partition(desc);
+  const spanattn::TokenCounts counts(desc);
+  const spanattn::Partition p = desc->workspace ? spanattn::plan_for_workspace(desc, counts, nullptr, nullptr, true)
+                                                : spanattn::plan_partition(desc, counts, nullptr, nullptr, true);
   const int64_t states = !desc->workspace ? spanattn::most_states(desc, p) : spanattn::states_that_fit(desc, p);
   const int32_t n = spanattn::query_tokens(desc);
   spanattn::MatrixPlan m;
-  std::vector<uint32_t> table((size_t)spanattn::kMaxPlanSlices);
-  if (spanattn::plan_matrix(desc, p, states, &m, table.data())) {
+  uint32_t table[spanattn::kMaxPlanSlices];
+  if (spanattn::plan_matrix(desc, counts, p, states, &m, table)) {
     info->matrix_cores = 1;
     info->launches = (n + m.tokens - 1) / m.tokens;
     info->tokens = m.tokens;
@@ -722,7 +707,8 @@ extern "C" int span_launch_query(const span_attn_desc_t* desc, span_launch_info_
 
 extern "C" size_t span_workspace_bytes(const span_attn_desc_t* desc) {
   if (spanattn::check_desc(desc) != SPAN_OK) return 0;
-  return spanattn::workspace_bytes(desc, spanattn::plan_partition(desc));
+  const spanattn::TokenCounts counts(desc);
+  return spanattn::workspace_bytes(desc, counts, spanattn::plan_partition(desc, counts, nullptr, nullptr, true));
 }
 
 // ---- blocked encoding (block index + in-block bit mask) <-> interval lists ---------------------------

@@ -754,7 +754,8 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
     own.host_span_offsets = own.host_span_starts = own.host_span_ends = nullptr;
     d = &own;
   }
-  Partition p = plan_for_workspace(d, a.table, kDense ? nullptr : &runs, !kDense);
+  const TokenCounts counts(d);
+  Partition p = plan_for_workspace(d, counts, a.table, kDense ? nullptr : &runs, !kDense);
   const size_t need = workspace_least_bytes(d, p);
   if (need > 0 && (!d->workspace || ((uintptr_t)d->workspace & 255u) || d->workspace_bytes < need))
     return SPAN_ERR_WORKSPACE;
@@ -793,8 +794,8 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
 
   Deal deal;
   MatrixPlan mp;
-  if (!kDense && plan_matrix(d, p, states, &mp, a.table)) {
-    deal_matrix(d, p, &mp, a.table, &deal);
+  if (!kDense && plan_matrix(d, counts, p, states, &mp, a.table)) {
+    deal_matrix(d, counts, p, &mp, a.table, &deal);
     a.entry_bits = entry_bits(deal);
     const hipError_t err = launch_matrix(a, d->dtype, d->head_dim, mp, a.table, d->batch, stream);
     if (err != hipSuccess) {
@@ -805,7 +806,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
   }
 
   if (kDense && (int64_t)d->batch * d->heads <= kDenseFixedUpToPairs) a.even = p.even ? 1 : 0;
-  deal_partition(d, &p, a.table, &runs, &deal);
+  deal_partition(d, counts, &p, a.table, &runs, &deal);
   a.entry_bits = entry_bits(deal);
   a.total_slices = p.total_slices;
   const GridMode mode = p.runs ? GridMode::kRuns : (p.exact ? GridMode::kTable : GridMode::kPlain);
@@ -843,8 +844,11 @@ extern "C" int span_decode_attn_static(const span_attn_desc_t* desc, const void*
   span_attn_desc_t d = *desc;
   d.workspace = nullptr;
   d.workspace_bytes = 0;
-  const spanattn::Partition p = spanattn::plan_partition(&d);
-  const size_t need = spanattn::workspace_bytes(&d, p);
+  size_t need;
+  {
+    const spanattn::TokenCounts counts(&d);
+    need = spanattn::workspace_bytes(&d, counts, spanattn::plan_partition(&d, counts, nullptr, nullptr, true));
+  }
   if (need > SPAN_STATIC_SCRATCH_BYTES) return SPAN_ERR_SCRATCH_LIMIT;
   if (need > 0) {
     void* ptr = nullptr;
@@ -923,7 +927,7 @@ extern "C" int span_advance(const span_attn_desc_t* desc, const int32_t* span_of
 extern "C" int span_workspace_init(const span_attn_desc_t* desc) {
   const int rc = spanattn::check_desc(desc);
   if (rc != SPAN_OK) return rc;
-  const spanattn::Partition p = spanattn::plan_for_workspace(desc, nullptr, nullptr, true);
+  const spanattn::Partition p = spanattn::plan_for_workspace(desc, spanattn::TokenCounts(desc), nullptr, nullptr, true);
   const size_t need = spanattn::workspace_least_bytes(desc, p);
   if (need == 0) return SPAN_OK;
   if (!desc->workspace || ((uintptr_t)desc->workspace & 255u) || desc->workspace_bytes < need) return SPAN_ERR_WORKSPACE;

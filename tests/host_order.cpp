@@ -113,9 +113,51 @@ static void less_than_two_turns() {
   for (int y = 32; y < o.plan.total_slices; ++y) REQUIRE(o.slices[y] == 1);
 }
 
+// The host lists are walked when they are counted and, for the runs of a plan, once more; never for a deal.
+static void lists_are_counted_once() {
+  for (int tokens : {1, 2, 9, 40}) {
+    const char* name = "counted once";
+    const int batch = 24, each = 30;
+    std::mt19937 rng(9);
+    std::vector<int32_t> offsets(1, 0), starts, ends;
+    for (int b = 0; b < batch; ++b) {
+      for (int i = 0, at = 0; i < each + b; ++i, at += 40) {
+        starts.push_back(at);
+        ends.push_back(at + 1 + (int32_t)(rng() % 39u));
+      }
+      offsets.push_back((int32_t)starts.size());
+    }
+    span_attn_desc_t d = {};
+    d.batch = batch;
+    d.heads = 32;
+    d.head_dim = 128;
+    d.dtype = SPAN_F16;
+    d.max_len = 4000;
+    d.q_len = tokens;
+    d.num_intervals = (int32_t)starts.size();
+    d.host_span_offsets = offsets.data();
+    d.host_span_starts = starts.data();
+    d.host_span_ends = ends.data();
+    std::vector<uint32_t> table[2];
+    Deal deal[2];
+    for (int gone : {0, 1}) {
+      table[gone].assign(kMaxPlanSlices, 0);
+      const TokenCounts counts(&d);
+      REQUIRE(counts.from_lists);
+      if (gone) std::fill(ends.begin(), ends.end(), 0);  // the lists as they are no longer attend anything
+      Partition p = plan_partition(&d, counts, table[gone].data(), nullptr, true);
+      MatrixPlan m;
+      if (plan_matrix(&d, counts, p, most_states(&d, p), &m, table[gone].data())) deal_matrix(&d, counts, p, &m, table[gone].data(), &deal[gone]);
+      else deal_partition(&d, counts, &p, table[gone].data(), nullptr, &deal[gone]);
+    }
+    REQUIRE(deal[0].dealt && deal[1].dealt && table[0] == table[1]);
+  }
+}
+
 int main() {
   several_blocks();
   less_than_two_turns();
+  lists_are_counted_once();
   std::puts("host_order: ok");
   return 0;
 }
