@@ -60,7 +60,9 @@ struct MatrixShape {
   // instruction.  us, two -> one: 512 workgroups, 16 x ~700 positions, bf16, 32 tokens 40.6 -> 39.0, appended 45.6 -> 44.1; in several rounds
   // 64 x 32 pairs x ~220, bf16, 24 tokens 91.9 -> 97.0, 64 x 32 x ~400 fp16, 20 tokens 113.5 -> 119.8.
   static constexpr bool kHasBoth = S == 2 && D == 128;
-  static constexpr int kWaves = kMatrixWorkgroupsPerCu(Elt::kBytes, D, G);  // per SIMD
+  // Waves per SIMD.  64 tokens of 16-bit rows of 128 spill 30 (fp16) and 38 (bf16) registers, all of them in the pass for V rows that are
+  // not finite (stream_checked).
+  static constexpr int kWaves = kMatrixWorkgroupsPerCu(Elt::kBytes, D, G);
 };
 
 // Terms of a weight in the storage type.  Three hold all 24 bits of the fp32 weight; bf16 rows need them.  Of fp16 rows the
@@ -274,7 +276,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   // and 8 - 15, lane (i, c) the 16 bytes c of the line's half i / 8 of row i % 8; order_k puts the halves where the operand wants
   // them.  (Loads of 16 rows x 64 bytes, which are the operand as they come, ask for every line twice: read alone and
   // non-temporal they reach 5.5 TB/s where whole lines reach 6.5.)
-  auto load_k = [&](int base, int wn) {
+  auto load_k = [&](int base, int wn, int ln) {
+    const int qi = ln & 15, c4 = ln >> 4;
     TileRows tr;
     tr.plain = true;
 #pragma unroll
@@ -329,7 +332,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       }
     }
   };
-  auto load_v = [&](int base, const TileRows& tr) {
+  auto load_v = [&](int base, const TileRows& tr, int ln) {
+    const int qi = ln & 15, c4 = ln >> 4;
     const uint32_t in_row = (kSplitPieces ? 16u : (uint32_t)(VW * 4)) * (uint32_t)qi;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -534,8 +538,8 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       tabulate_positions(a, intervals, vrow, w0, wn, wave, lane, s_u.st.tab, s_pos[wave]);
 #pragma unroll 1
       for (int base = 0; base < wn; base += TR) {
-        const TileRows tr = load_k(base, wn);
-        load_v(base, tr);
+        const TileRows tr = load_k(base, wn, lane);
+        load_v(base, tr, lane);
         f32x4 w[G][S];
         take_scores(w);
         softmax_step(w, base, tr);
@@ -622,17 +626,24 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   }
   TileRows cur = {};
   if (nrows > 0) {
-    cur = load_k(0, min(kMWin, nrows));
-    load_v(0, cur);
+    cur = load_k(0, min(kMWin, nrows), lane);
+    load_v(0, cur, lane);
   }
   __syncthreads();  // q is in LDS
   clear_state();
   for (int w0 = 0; w0 < nrows; w0 += kMWin) {
     const int wn = min(kMWin, nrows - w0);
     if (__builtin_expect(w0 > 0, 0)) {
-      tabulate_positions(a, intervals, vrow, w0, wn, wave, lane, s_u.st.tab, s_pos[wave]);
-      cur = load_k(0, wn);
-      load_v(0, cur);
+      // The lane's addresses are computed here and not ahead of the loop, where the compiler would move them: kept across the tiles they
+      // cost registers that 32 tokens of 16-bit rows of 64 and of fp32 rows of 128 do not have (2 to 5 spilled, and with them the set-up
+      // of scratch memory for every wave; now none, in the plain grid of the former one, the thread's index, which is read after the
+      // loop).  us, with the spills -> without: 64 x 12 heads x 200..500 of 64, bf16, 32 tokens 22.1 -> 21.0, level ones of ~490, fp16 25.5 -> 23.6; 16 x 32 x
+      // 400..800, fp16, 20 tokens 20.6 -> 19.3; 8 x 32 x ~600 fp32 of 128, 24 tokens 44.2 -> 43.8.
+      int ln = 16 * c4 + qi;
+      asm volatile("" : "+v"(ln));
+      tabulate_positions(a, intervals, vrow, w0, wn, wave, ln, s_u.st.tab, s_pos[wave]);
+      cur = load_k(0, wn, ln);
+      load_v(0, cur, ln);
     }
     // (the window's last tile apart: with the next tile's loads behind a branch the compiler could not count them, and would
     // wait for all of them ahead of this tile's outputs)
@@ -640,10 +651,10 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     for (; base + TR < wn; base += TR) {
       f32x4 sc[G][S];
       take_scores(sc);
-      const TileRows next = load_k(base + TR, wn);
+      const TileRows next = load_k(base + TR, wn, lane);
       softmax_step(sc, base, cur);
       add_outputs(sc);
-      load_v(base + TR, next);
+      load_v(base + TR, next, lane);
       cur = next;
 #ifdef SPAN_PHASE_TRACE
       if (w0 == 0 && base == 0) SPAN_STAMP_AFTER(3, "v", lsum[0]);

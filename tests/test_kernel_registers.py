@@ -1,0 +1,38 @@
+"""Registers of the kernels in the built library, as the compiler wrote them down: no spills, which cost every wave the set-up of scratch
+memory, but for the instances named here."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2404_09336_amd as span
+
+LLVM = "/opt/rocm/llvm/bin"
+
+
+def _kernels(tmp_path):
+    """(name, spilled vector registers, bytes of scratch memory) of every kernel."""
+    span.load_library()
+    lib = tmp_path / "lib.so"
+    shutil.copy(os.path.join(os.path.dirname(span.__file__), "libspanattn.so"), lib)
+    subprocess.run([f"{LLVM}/llvm-objdump", "--offloading", str(lib)], check=True, stdout=subprocess.DEVNULL, cwd=tmp_path)
+    for part in sorted(tmp_path.glob("lib.so.*gfx950*")):
+        notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(part)], check=True, stdout=subprocess.PIPE, text=True).stdout
+        for scratch, name, spilled in re.findall(r"private_segment_fixed_size: (\d+).*?\.symbol: +'?(\S+?)\.kd.*?\.vgpr_spill_count: (\d+)", notes, re.S):
+            yield name, int(spilled), int(scratch)
+
+
+@pytest.mark.skipif(not os.path.exists(f"{LLVM}/llvm-objdump"), reason="needs the compiler's own tools")
+def test_no_spills(tmp_path):
+    seen = 0
+    for name, spilled, scratch in _kernels(tmp_path):
+        seen += 1
+        if re.search(r"matrix_kernelINS_(3F16|4BF16)ELi128ELi4E", name):  # 64 tokens: in the pass for V rows that are not finite
+            assert spilled <= 38, name
+        elif re.search(r"matrix_kernelINS_(3F16|4BF16)ELi64ELi2E.*Plain", name):  # the thread's index, read after the loop
+            assert spilled <= 1 and scratch <= 8, name
+        else:
+            assert spilled == 0 and scratch == 0, name
+    assert seen > 100
