@@ -126,8 +126,11 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   constexpr int kAccRow = D + 4;
   // Groups of rows that K loads alternate between, see load_k.  Rows of one line have nothing to gain from two, and pay for the
   // second set of positions (16 x 16 pairs x ~380, fp16, 9 tokens 14.9 -> 15.1 us), and the fp32 shapes with the most tokens
-  // need the registers (8 x 32 x ~600, 24 tokens 50.0 -> 51.1; 16 x 16 x ~600 of 64, 60 tokens 53.1 -> 54.3).
-  constexpr int kKSets = NK == 2 || (Elt::kBytes == 4 && D / 64 * G >= 4) ? 1 : 2;
+  // need the registers (8 x 32 x ~600, 24 tokens 50.0 -> 51.1; 16 x 16 x ~600 of 64, 60 tokens 53.1 -> 54.3).  Workgroups that share
+  // rows find the second half of a line in the L2 anyway, and gain more from one set less: us, two -> one, fp32 of 64, 32 heads x 6000, 24
+  // tokens 31.8 -> 29.9, 4 x 8 x 6000, 64 tokens 52.0 -> 47.7, 2 x 16 x 9000..16000, 32 tokens 62.6 -> 59.4; of 128, 32 x 6000, 64 tokens 85.1 -> 80.2;
+  // fp16 of 128, 8 x 12 x 600..2000, 60 tokens 31.6 -> 30.8, bf16, 32 x 5500, 20 tokens 24.8 -> 24.4.
+  constexpr int kKSets = NK == 2 || kShared || (Elt::kBytes == 4 && D / 64 * G >= 4) ? 1 : 2;
   constexpr bool kSplitPieces = VW == 8;     // the lane's V values are two pieces half a row apart
   static_assert(kMWin % TR == 0, "tiles do not straddle a window");
 
