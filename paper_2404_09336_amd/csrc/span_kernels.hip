@@ -95,7 +95,12 @@ decode_kernel(const Args a) {
   // With several query tokens (NQ > 1) every token brings a row, for positions append_pos[b] + token; they are
   // handled with the rows that only some tokens of the pass see (below) and new_pos stays unused.
   const bool append_many = NQ > 1 && a.append_pos != nullptr;
-  SequenceWords words = sequence_words<kDense>(a, b);
+  // Run mode reads nothing of the lists (its launches are promised not to), so no null pointer is replaced by them, and what is given is
+  // waited for where it is used.
+  SequenceWords words = {};
+  if constexpr (!Args::kHasRuns) words = sequence_words<kDense>(a, b);
+  auto append_position = [&]() { return Args::kHasRuns ? a.append_pos[b] : words.append_pos; };
+  auto query_position = [&]() { return Args::kHasRuns ? a.q_pos[b] : words.q_pos; };
   u32x4 kn_raw = {0u, 0u, 0u, 0u}, vn_raw = {0u, 0u, 0u, 0u};
   if (NQ == 1 && a.append_pos) {
     kn_raw = *reinterpret_cast<const u32x4*>((const char*)a.k_new + bh * ROWB + (uint32_t)lir * 16u);
@@ -126,13 +131,13 @@ decode_kernel(const Args a) {
     qv[j] = Elt::make_q(qr, a.scale_log2e);
   }
   const float post = Elt::kPostScale ? a.scale_log2e : 1.f;
-  arrived(words);
-  const int new_pos = (NQ == 1 && a.append_pos) ? words.append_pos : -2;  // -2 matches no position
+  if constexpr (!Args::kHasRuns) arrived(words);
+  const int new_pos = (NQ == 1 && a.append_pos) ? append_position() : -2;  // -2 matches no position
   // Causal limit (few-query variant): query token j sees no position after its own, q_pos[b] + j.
   int lim[NQ];
 #pragma unroll
   for (int j = 0; j < NQ; ++j)  // (clamped: any q_pos at or beyond the cache length means "no limit", without overflow)
-    lim[j] = a.q_pos ? min(words.q_pos, kMaxLen) + j : 0x7fffffff;
+    lim[j] = a.q_pos ? min(query_position(), kMaxLen) + j : 0x7fffffff;
 
   // ---- step 1: how many attended positions does the sequence have, which are mine ----------------
   int n_total;
@@ -177,7 +182,7 @@ decode_kernel(const Args a) {
   if constexpr (NQ > 1) {  // the new tokens' rows, one token per wave
     if (append_many && split == 0 && lane < LPR) {
       for (int i = wave; i < NQ; i += kWavesPerBlock) {
-        const int pos_i = min(words.append_pos, kMaxLen) + i;
+        const int pos_i = min(append_position(), kMaxLen) + i;
         if (pos_i >= 0 && pos_i < a.max_len) {
           const size_t src = qrow(i) * ROWB + (uint32_t)lir * 16u;
           const size_t row = (bh * (size_t)a.max_len + (size_t)pos_i) * ROWB + (uint32_t)lir * 16u;
