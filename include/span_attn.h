@@ -61,8 +61,11 @@ typedef struct span_attn_desc {
   int32_t head_dim;        /* 64 or 128                                                          */
   int32_t max_len;         /* rows allocated per (batch, head) in the caches, <= 2^22            */
   int32_t dtype;           /* span_dtype_t of q, k_cache, v_cache                                */
-  int32_t num_intervals;   /* entries held by span_starts / span_ends (span entry point only);
-                              interval indices are clamped to it on the device                  */
+  int32_t num_intervals;   /* entries held by span_starts / span_ends (span entry points only);
+                              interval indices are clamped to it on the device.  0 describes a
+                              dense call to span_plan_query, span_launch_query and
+                              span_workspace_bytes: one-token calls planned from a bound alone
+                              are cut coarser there                                              */
   int32_t max_tokens;      /* upper bound on the attended positions of any one sequence (span
                               tokens, or ctx_lens for the dense call); sizes the grid.
                               0 = unknown, use max_len.  Positions beyond it are NOT attended.   */
@@ -276,7 +279,7 @@ typedef struct span_plan_info {
 } span_plan_info_t;
 int span_plan_query(const span_attn_desc_t* desc, span_plan_info_t* info);
 
-/* What the call described by desc launches: with desc->workspace_bytes where desc->workspace is given, else with
+/* What the call described by desc launches (a one-token call with num_intervals > 0 as a span call, else as a dense one): with desc->workspace_bytes where desc->workspace is given, else with
  * a workspace of span_workspace_bytes().  Pure host arithmetic. */
 typedef struct span_launch_info {
   int32_t matrix_cores;    /* 1: the call runs on the matrix cores                                 */

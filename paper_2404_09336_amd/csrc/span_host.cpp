@@ -284,7 +284,7 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
   }
   const int64_t pairs = (int64_t)d->batch * d->heads;
   int64_t splits = d->num_splits > 0 ? d->num_splits : slice_room(d) / d->batch;  // stay within one round
-  if (d->num_splits == 0 && spans && query_tokens(d) == 1 && d->batch > kBoundSliceFromBatch) {
+  if (d->num_splits == 0 && spans && d->num_intervals > 0 && query_tokens(d) == 1 && d->batch > kBoundSliceFromBatch) {
     // A bound far above what most sequences attend leaves few large slices for the longest: up to kBoundSlice each.
     const int64_t in_round = target_workgroups(d) / d->heads / d->batch;
     while (splits > 0 && splits < in_round && ceil_div(max_tok, splits) > kBoundSlice) ++splits;

@@ -96,8 +96,8 @@ struct TokenCounts {
 };
 
 // Fills `table` (kMaxPlanSlices entries) when the partition is exact; table may be null to only size it.
-// `spans`: the span form (of one token, whose slices are cut finer where only a bound is known; the dense form may need fewer states
-// than the workspace that is sized without knowing the form).
+// `spans`: may be the span form, whose slices of one token are cut finer where only a bound is known (false: the dense entry points, and
+// where a workspace does not hold the finer cut).  A descriptor without intervals is a dense call's to every function.
 // With `runs` given (span form only) and host copies of the span lists in the descriptor, tries run mode first.
 Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans);
 inline Partition plan_partition(const span_attn_desc_t* d, uint32_t* table = nullptr, RunTables* runs = nullptr, bool spans = true) {
