@@ -113,6 +113,50 @@ static void less_than_two_turns() {
   for (int y = 32; y < o.plan.total_slices; ++y) REQUIRE(o.slices[y] == 1);
 }
 
+// The calls that test_deal.py and test_order.py run on the GPU as dealt ones are.
+static bool is_dealt(int dtype, int head_dim, int heads, int tokens, const std::vector<int64_t>& counts, int max_len) {
+  span_attn_desc_t d = {};
+  d.batch = (int32_t)counts.size();
+  d.heads = heads;
+  d.head_dim = head_dim;
+  d.dtype = dtype;
+  d.max_len = max_len;
+  d.max_tokens = (int32_t)*std::max_element(counts.begin(), counts.end());
+  d.q_len = tokens;
+  d.tokens_per_seq = counts.data();
+  std::vector<uint32_t> table(kMaxPlanSlices);
+  Partition p = plan_partition(&d, table.data());
+  MatrixPlan m;
+  Deal deal;
+  if (plan_matrix(&d, p, most_states(&d, p), &m, table.data())) deal_matrix(&d, p, &m, table.data(), &deal);
+  else deal_partition(&d, &p, table.data(), nullptr, &deal);
+  return deal.dealt;
+}
+
+static void tested_calls_are_dealt() {
+  const char* name = "tested calls";
+  std::vector<int64_t> many;
+  for (int i = 0; i < 30; ++i) many.push_back(200 + 31 * (i % 7));
+  const std::vector<std::vector<int64_t>> counts = {{500, 500, 720, 720, 500, 500, 720, 720}, {60, 130, 900, 880, 300, 20, 700, 700, 410, 1}, many};
+  struct Call {
+    int dtype, head_dim, tokens;
+  } calls[] = {{SPAN_F16, 128, 1}, {SPAN_F32, 64, 1}, {SPAN_F32, 128, 2}, {SPAN_BF16, 128, 16}, {SPAN_F16, 64, 9}};
+  int dealt = 0;
+  for (const auto& n : counts) {
+    for (const Call& c : calls) dealt += is_dealt(c.dtype, c.head_dim, 32, c.tokens, n, 1000);
+  }
+  std::printf("test_deal.py: %d of 15 calls are dealt\n", dealt);
+  REQUIRE(dealt == 15);
+  struct Other {
+    int dtype, head_dim, heads, batch, tokens;
+  } others[] = {{SPAN_F16, 128, 8, 60, 59}, {SPAN_F32, 64, 12, 41, 33}, {SPAN_F16, 128, 8, 60, 1}, {SPAN_F32, 64, 5, 90, 2}};
+  for (const Other& o : others) {
+    std::vector<int64_t> n;
+    for (int i = 0; i < o.batch; ++i) n.push_back(60 + 37 * i % 131);
+    REQUIRE(is_dealt(o.dtype, o.head_dim, o.heads, o.tokens, n, 200));
+  }
+}
+
 // The host lists are walked when they are counted and, for the runs of a plan, once more; never for a deal.
 static void lists_are_counted_once() {
   for (int tokens : {1, 2, 9, 40}) {
@@ -158,6 +202,7 @@ int main() {
   several_blocks();
   less_than_two_turns();
   lists_are_counted_once();
+  tested_calls_are_dealt();
   std::puts("host_order: ok");
   return 0;
 }

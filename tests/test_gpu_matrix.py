@@ -289,7 +289,7 @@ def test_many_tokens_a_workgroup_append_their_rows(dtype, D, q_len, gpu_device):
 @pytest.mark.parametrize("q_len", [3, 16, 20])
 def test_whole_sequences_dealt_by_length(dtype, D, q_len, gpu_device):
     """20 sequences x 32 heads, 301 .. 453 positions, are not sliced, more than one turn of 256 workgroups, and the longest
-    is 20 % over the mean: the table that deals them longest first, every second turn backwards."""
+    is 20 % over the mean: the table that deals them longest first, each to the CUs that have the least (tests/host_order.cpp)."""
     cfg = DecodeConfig(114, "matrix-dealt", 20, 32, D, 512, 512, dtype, TOL)
     lengths = np.random.default_rng(5).permutation(301 + 8 * np.arange(20))
     launched = {}

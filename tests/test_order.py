@@ -30,7 +30,8 @@ def test_unequal_sequences_go_out_level(tmp_path):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,D,heads,batch,q_len", [("f32", 128, 16, 36, 48), ("f32", 128, 12, 36, 33),  # two query blocks
                                                        ("f16", 64, 200, 6, 5), ("bf16", 128, 300, 4, 20),    # heads that fill a turn
-                                                       ("f16", 128, 8, 60, 59), ("f32", 64, 12, 41, 33)])    # dealt, less than two turns
+                                                       ("f16", 128, 8, 60, 59), ("f32", 64, 12, 41, 33),     # dealt, less than two turns
+                                                       ("f16", 128, 8, 60, 1), ("f32", 64, 5, 90, 2)])       # dealt, on the vector units
 def test_order_of_whole_sequences(dtype, D, heads, batch, q_len, gpu_device):
     """Tolerance as in test_gpu_matrix.py: fp32 sums of unit-variance rows, 1e-5 is ten times what they add up to."""
     L = 200
