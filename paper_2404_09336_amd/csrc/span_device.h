@@ -64,7 +64,7 @@ struct LaunchArgs {
 struct LaunchArgsTable : LaunchArgs {
   static constexpr bool kHasTable = true;
   static constexpr bool kHasRuns = false;
-  uint32_t table[kMaxPlanSlices];   // pack_slice(batch, slice, slices of the sequence)
+  uint32_t table[kMaxPlanSlices];   // read by slice_name alone: dealt entries have other fields than pack_slice's, and any order
 };
 struct LaunchArgsPlain : LaunchArgs {
   static constexpr bool kHasTable = false;

@@ -269,8 +269,10 @@ static bool plan_runs(const span_attn_desc_t* d, const int64_t* tokens_per_seq, 
 // at the bound -> shared: 32 x 32 heads x 5..50 % of 4096..16384, bf16 274 -> 236; 16 x 32 x ~560, fp16 38.7 -> 35.7; 20 x 32 x 300..1000
 // dense 42.9 -> 38.4; 40 x 16 x 300..900 dense of 64 23.5 -> 22.5.  With kBoundSlice as well (span form): 24 x 12 x 5..50 % of 2000..5000,
 // bf16 41.0 -> 31.0 (38.9 shared alone), 16 x 16 x 5..50 % of 1200..4000 fp32 of 64 24.6 -> 19.2 (22.7); slices of up to 256 or 384 win and
-// lose 5 % against 512; dense contexts, which are less ragged, lose by more slices (8 x 32 x 600..2000 33.4 -> 36.2), and few sequences
-// have enough as it is (6 x 16 x ~400 10.0 and 10.0, 10 x 8 x ~560 11.5 and 11.5).
+// lose 5 % against 512.  Dense contexts, which are less ragged, lose by more slices (8 x 32 x 600..2000 33.4 -> 36.2), and so do up to eight
+// sequences whose spans come near the bound, fp16: 4 x 32 x 3000..3100 36.8 -> 38.7, 8 x 16 x 3000..3200 37.3 -> 39.3, 8 x 32 x 1500..1600 35.7 -> 36.5;
+// with more they do not (9 x 32 x 1500..1600 41.8, 45.3 in three slices).  It costs small batches far below their bound what it gains large
+// ones: 8 x 32 x 5..50 % of 2000..16000 64.3, 44.7 if cut, 4 x 32 x 5..50 % of 4000..16000 35.9 and 29.3.
 Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans) {
   const int64_t max_tok = (d->max_tokens > 0 && d->max_tokens < d->max_len) ? d->max_tokens : d->max_len;
   Partition p;
@@ -498,16 +500,17 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
 // tokens 117 -> 106; 60 x ~300 of 64, 5 tokens 55.4 -> 53.5; 8 x ~600 fp32, 24 tokens 49.7 -> 47.2; 16 x 16 heads x ~380 of 64, 9
 // tokens 14.4 -> 13.9; batch 16 x ~550 31.2 -> 30.2.  The host pays 0.5 us for 30 slices, 1 for 64, 2.5 for 165 (the whole plan
 // 1.3 -> 1.9 us, 2.8 -> 3.7, 5.5 -> 8.0).
-// A launch whose plan needs no table carries one where that spares a CU 5 % and 16 KB (its share of 0.6 us; the table's 3 KB of
-// arguments cost 0.35): 60 x 32 heads x ~300 of 64, 5 tokens 57.1 -> 53.4; 8 x 32 x 500..900, two slices each, 2 tokens 21.0 -> 20.9.  Sequences of
-// almost the same length have nothing to win (64 x 144..168 positions: 28.4 with and without).
 // In less than two turns of workgroups of more than 16 tokens most CUs hold one, and the hand-over of a slice's states counts as well: as this many
 // rows, which puts the slices of cut sequences ahead of short whole ones.  us in plan order -> dealt by rows alone -> with the hand-over:
 // fp32, 35 x 8 heads x 60..160 positions, 17 tokens 21.1 -> 24.1 -> 21.4; 40 x 8 x ~110 of 64, 40 tokens 23.0 -> 23.3 -> 22.7; 41 x 12 x 599..999 of
 // 64, 47 tokens 95.1 -> 81.3 -> 81.1; 12 x 32 x ~200, 24 tokens 35.1 -> 33.6 -> 33.3 (64 rows do as well but for 30 x 12 x 60..250, 20 tokens, 25.7 ->
 // 26.9 and 25.6 with 128).  Whole sequences, 63 x 8 x 53..268, fp16, 59 tokens 26.5 -> 23.3; 12 x 40 x 345..1151, bf16, 46 tokens 57.6 -> 50.8.
 constexpr int32_t kHandOverRows = 128;
-constexpr int64_t kDealTableBytes = 16384;  // bytes a CU must be spared for a launch to carry a table it can do without
+// A launch whose plan needs no table carries one where that spares the fullest CU 5 % and this many bytes (its share of 0.6 us; the table's
+// 3 KB of arguments cost 0.35).  us, without -> with: 64 x 12 heads x 60..200 of 64, 16 tokens 10.5 -> 9.65; 8 x 32 x 500..900, two slices each, two
+// tokens 20.0 -> 19.5; 10 x 32 x 300..500, two tokens 16.7 -> 16.2; 64 x 32 x 100..300, one token 35.1 -> 34.4; 60 x 32 x 150..450 of 64, 5 tokens 29.9 -> 29.4.
+// Less to spare is left alone: 64 x 144..168 28.4 with and without; 28 x 160 x 200..900 of 64, 8 tokens 111.3, 108.9 with.
+constexpr int64_t kDealTableBytes = 16384;
 
 void deal_slices(const span_attn_desc_t* d, const TokenCounts& counts, int64_t max_tokens, int32_t total, int32_t hand_over, bool table,
                  uint32_t* entries, Deal* deal) {

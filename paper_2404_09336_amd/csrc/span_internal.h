@@ -16,7 +16,7 @@ constexpr int kMaxSlice = 1 << 22;         // a slice may be a whole sequence (p
 #endif
 constexpr int kMinSlice = SPAN_MIN_SLICE;  // do not cut work finer than this many positions
 constexpr int kBoundSlice = 512;           // slices planned from a bound alone hold at most this many positions where a round has room for them
-constexpr int kBoundSliceFromBatch = 8;    // ... of batches larger than this
+constexpr int kBoundSliceFromBatch = 8;    // ... of batches larger than this (both sides: see plan_partition)
 constexpr int kLeastSlice = 64;            // positions of a slice whose size the kernel chooses, see Partition::least_slice
 constexpr int kSliceGranule = 16;
 constexpr int kUnsplitFromPairs = 512;     // level batches with at least this many (batch, head) pairs are not sliced
@@ -44,7 +44,7 @@ constexpr int kMaxRuns = 288;              // runs of all slices
 constexpr int kMaxRunSliceRows = 1024;     // rows of one slice: every wave's rows fit one position window
 
 struct RunSlice {      // 16 bytes: one scalar load
-  uint32_t entry;      // pack_slice(batch, slice, slices of the sequence), as in table mode
+  uint32_t entry;      // pack_slice(batch, slice, slices of the sequence), dealt or not
   uint32_t runs_of;    // first run | number of runs << 16
   int32_t rows;        // attended positions of the slice
   int32_t reserved;    // (of a dealt launch: the slice's slot)
@@ -54,7 +54,7 @@ struct RunTables {
   int32_t run[kMaxRuns][2];  // a run covers cache positions [run[.][0], run[.][0] + run[.][1])
 };
 
-// Slice table entry (exact mode): batch index | slice index within the sequence | slices of the sequence.
+// Slice table entry (exact mode) as planned: batch index | slice index within the sequence | slices of the sequence.
 inline uint32_t pack_slice(uint32_t b, uint32_t split, uint32_t nsl) { return b | (split << 10) | (nsl << 21); }
 
 // A launch whose slices go out in another order than the plan names them (see deal_slices): a table entry then also says which
@@ -112,8 +112,8 @@ Partition plan_for_workspace(const span_attn_desc_t* d, const TokenCounts& count
 struct MatrixPlan {
   int32_t tokens;        // query tokens of one launch (all of the call's unless the caller fixed the number of slices)
   int32_t groups;        // groups of 16 tokens a workgroup serves with one pass over its rows: 1, 2 or 4
-  bool table;            // slices from the table: sequences with several slices first, so an entry's index is its slot;
-                         // whole sequences in the order that levels the CUs
+  bool table;            // slices from the table.  As planned: sequences with several slices first, so an entry's index is its slot;
+                         // whole sequences, which have no slot, in any order.  After a deal only Deal and slice_name can read it.
   bool even;             // as in Partition
   int32_t least_slice;   // as in Partition
   int32_t num_splits;    // as in Partition

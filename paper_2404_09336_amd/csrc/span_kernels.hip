@@ -655,8 +655,9 @@ int static_scratch(void** ptr) {
 
 // Twice the loads in flight (kWide), for launches of few workgroups with little to read: nothing but the trips to memory bounds
 // them, and a slice of the planner's smallest size is then one batch per wave instead of two.  us, default -> wide: one request of ~560 positions,
-// 32 heads x 128, fp16, appended 8.92 -> 8.54; ~560 fp32 10.6 -> 10.25; one of 600..4000 in 512 workgroups 12.0 -> 11.6; 4 workgroups x 80
-// positions of fp32 rows of 64 4.70 -> 4.40; 12 x 5 heads x ~1000 13.95 -> 13.55.  The line: two batches a wave gain nothing any more with two
+// 32 heads x 128, fp16, appended 8.20 -> 7.65, of 64 7.61 -> 7.09; 2 x 12 x ~560 of 64 7.60 -> 7.06; 6 x 8 x 200..250 of 64 7.14 -> 6.62; 4 x 5 x 100..250 fp16
+// 7.01 -> 6.57; 2 x 16 x ~400 fp32 of 64 8.07 -> 7.69; 4 workgroups x 80 positions 4.17 -> 3.88; 12 x 5 heads x ~1000 11.5 -> 10.8, of 64 9.66 -> 9.28.
+// The line: with 512 workgroups of one batch it is even (16 x 32 x 100..200 of 64 7.80 and 7.78), two batches a wave gain nothing any more with two
 // workgroups per CU (4 x ~560 in 512: 13.5 -> 13.65), and where the rate of the memory counts it costs the resident waves (64 x ~155:
 // 27.8 -> 30.6; dense rows of 64, 576 workgroups x 250 positions 15.1 -> 15.65).
 constexpr int64_t kWideUpToWorkgroups = 512;     // slices of one (wide) batch of rows per wave
@@ -737,8 +738,10 @@ int launch_queries(const LaunchArgsTable& a, const RunTables* runs, int nq, Grid
 
 int32_t entry_bits(const Deal& deal) { return deal.b_bits | deal.n_bits << 8 | (deal.dealt ? 1 << 16 : 0); }
 
-// The dense form, planned from a bound: up to here slices of a fixed size (as many sequences then have empty slices, which end at once; us,
-// fixed -> shared: 8 x 32 heads x 600..2000 33.4 -> 33.8, 4 x 32 x 1000..2000 fp32 37.1 -> 37.5, 12 x 32 x 1200..3000 70.1 -> 67.2).
+// The dense form, planned from a bound: up to here slices of a fixed size (as many sequences then have empty slices, which end at once).
+// us, fixed -> shared: 8 x 32 heads x 600..2000 32.7 -> 33.3, 4 x 32 x 1000..2000 fp32 33.5 -> 34.5, 4 x 16 x 300..1500 of 64 8.62 -> 8.90; but 16 x 16 x
+// 200..900 of 64 12.4 -> 12.0, 2 x 32 x 2000..8000 30.3 -> 29.4; more pairs: 20 x 12 x 333..1000 of 64 13.1 (at 240 pairs) -> 12.8, 12 x 32 x 1200..3000
+// 70.1 -> 67.2, 20 x 32 x 300..1000 42.9 -> 38.4.
 constexpr int64_t kDenseFixedUpToPairs = 256;
 
 template <bool kDense>

@@ -41,7 +41,7 @@ struct MatrixArgsPlain : MatrixArgs {
 };
 struct MatrixArgsTable : MatrixArgs {
   static constexpr bool kHasTable = true;
-  uint32_t table[kMaxPlanSlices];  // entries of sequences with several slices come first: their index is the slot
+  uint32_t table[kMaxPlanSlices];  // as in LaunchArgsTable
 };
 
 // Shape of one instance.
@@ -669,6 +669,9 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     take_scores(sc);
     softmax_step(sc, base, cur);
     add_outputs(sc);
+#ifdef SPAN_PHASE_TRACE
+    if (w0 == 0 && base == 0) SPAN_STAMP_AFTER(3, "v", lsum[0]);
+#endif
   }
   {
     float z = 0.f;  // stays 0 unless some output is Inf or NaN
