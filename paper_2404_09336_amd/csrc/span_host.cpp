@@ -500,11 +500,13 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
 // tokens 117 -> 106; 60 x ~300 of 64, 5 tokens 55.4 -> 53.5; 8 x ~600 fp32, 24 tokens 49.7 -> 47.2; 16 x 16 heads x ~380 of 64, 9
 // tokens 14.4 -> 13.9; batch 16 x ~550 31.2 -> 30.2.  The host pays 0.5 us for 30 slices, 1 for 64, 2.5 for 165 (the whole plan
 // 1.3 -> 1.9 us, 2.8 -> 3.7, 5.5 -> 8.0).
-// In less than two turns of workgroups of more than 16 tokens most CUs hold one, and the hand-over of a slice's states counts as well: as this many
+// In less than two turns of few-query workgroups most CUs hold one, and the hand-over of a slice's states counts as well: as this many
 // rows, which puts the slices of cut sequences ahead of short whole ones.  us in plan order -> dealt by rows alone -> with the hand-over:
-// fp32, 35 x 8 heads x 60..160 positions, 17 tokens 21.1 -> 24.1 -> 21.4; 40 x 8 x ~110 of 64, 40 tokens 23.0 -> 23.3 -> 22.7; 41 x 12 x 599..999 of
-// 64, 47 tokens 95.1 -> 81.3 -> 81.1; 12 x 32 x ~200, 24 tokens 35.1 -> 33.6 -> 33.3 (64 rows do as well but for 30 x 12 x 60..250, 20 tokens, 25.7 ->
-// 26.9 and 25.6 with 128).  Whole sequences, 63 x 8 x 53..268, fp16, 59 tokens 26.5 -> 23.3; 12 x 40 x 345..1151, bf16, 46 tokens 57.6 -> 50.8.
+// fp32, 35 x 8 heads x 60..160 positions, 17 tokens 21.1 -> 24.1 -> 21.4; 25 x 8 x ~150 of 64, 3 tokens 9.05 -> 9.63 -> 9.04; bf16, 25 x 16 x 108..216 of
+// 64, two tokens 7.99 -> 8.81 -> 8.38; 41 x 12 x 599..999 fp32 of 64, 47 tokens 95.1 -> 81.3 -> 81.1; 12 x 32 x ~200, 24 tokens 35.1 -> 33.6 -> 33.3; the most it
+// costs: bf16, 14 x 16 x ~600, 13 tokens 21.9 -> 20.7 -> 21.1.  (64 rows do as well but for 30 x 12 x 60..250, 20 tokens, 25.7 -> 26.9 and 25.6 with
+// 128.)  Whole sequences, 63 x 8 x 53..268, fp16, 59 tokens 26.5 -> 23.3; 12 x 40 x 345..1151, bf16, 46 tokens 57.6 -> 50.8.  One-token launches, whose
+// hand-over is a single state, gain nothing by it (geometric mean of 100 shapes 1.000).
 constexpr int32_t kHandOverRows = 128;
 // A launch whose plan needs no table carries one where that spares the fullest CU 5 % and this many bytes (its share of 0.6 us; the table's
 // 3 KB of arguments cost 0.35).  us, without -> with: 64 x 12 heads x 60..200 of 64, 16 tokens 10.5 -> 9.65; 8 x 32 x 500..900, two slices each, two
@@ -609,7 +611,7 @@ void deal_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   deal->dealt = false;
   const bool one_block = m->tokens <= 16 * m->groups;  // (several: see plan_matrix)
   if (!m->even || !one_block || (!m->table && !uniform_entries(d->batch, m->num_splits, table))) return;
-  const int32_t hand_over = m->groups > 1 && (int64_t)m->total_slices * d->heads < 2 * kTurn ? kHandOverRows : 0;
+  const int32_t hand_over = (int64_t)m->total_slices * d->heads < 2 * kTurn ? kHandOverRows : 0;
   deal_slices(d, counts, p.max_tokens, m->total_slices, hand_over, m->table, table, deal);
   m->table = m->table || deal->dealt;
 }

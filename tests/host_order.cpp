@@ -107,10 +107,20 @@ static void less_than_two_turns() {
     REQUIRE(o.deal.dealt && o.fullest < s.fullest);
   }
   // Short sequences, some of them cut: the cut ones' slices, which have a hand-over ahead of them, go out in the first turn, as in plan order.
-  const char* name = "35x8";
-  const Order o = order(name, SPAN_F32, 35, 8, 128, 60, 160, 17);
-  REQUIRE(o.plan.num_splits == 2);
-  for (int y = 32; y < o.plan.total_slices; ++y) REQUIRE(o.slices[y] == 1);
+  struct Cut {
+    int dtype, batch, heads, head_dim, least, most, tokens;
+  } cut[] = {{SPAN_F32, 35, 8, 128, 60, 160, 17}, {SPAN_BF16, 25, 15, 64, 108, 190, 2}, {SPAN_F32, 40, 8, 64, 80, 150, 3}};
+  for (const Cut& s : cut) {
+    const char* name = "short, some cut";
+    const Order o = order(name, s.dtype, s.batch, s.heads, s.head_dim, s.least, s.most, s.tokens);
+    REQUIRE(o.plan.num_splits == 2 && o.plan.total_slices * s.heads < 512);
+    int last_cut = 0, first_whole = o.plan.total_slices;
+    for (int y = 0; y < o.plan.total_slices; ++y) {
+      if (o.slices[y] > 1) last_cut = y;
+      else first_whole = std::min(first_whole, y);
+    }
+    REQUIRE(last_cut < (256 + s.heads / 2) / s.heads || last_cut < first_whole);
+  }
 }
 
 // The calls that test_deal.py and test_order.py run on the GPU as dealt ones are.
