@@ -657,11 +657,12 @@ int static_scratch(void** ptr) {
 // them, and a slice of the planner's smallest size is then one batch per wave instead of two.  us, default -> wide: one request of ~560 positions,
 // 32 heads x 128, fp16, appended 8.20 -> 7.65, of 64 7.61 -> 7.09; 2 x 12 x ~560 of 64 7.60 -> 7.06; 6 x 8 x 200..250 of 64 7.14 -> 6.62; 4 x 5 x 100..250 fp16
 // 7.01 -> 6.57; 2 x 16 x ~400 fp32 of 64 8.07 -> 7.69; 4 workgroups x 80 positions 4.17 -> 3.88; 12 x 5 heads x ~1000 11.5 -> 10.8, of 64 9.66 -> 9.28.
-// The line: with 512 workgroups of one batch it is even (16 x 32 x 100..200 of 64 7.80 and 7.78), two batches a wave gain nothing any more with two
-// workgroups per CU (4 x ~560 in 512: 13.5 -> 13.65), and where the rate of the memory counts it costs the resident waves (64 x ~155:
-// 27.8 -> 30.6; dense rows of 64, 576 workgroups x 250 positions 15.1 -> 15.65).
-constexpr int64_t kWideUpToWorkgroups = 512;     // slices of one (wide) batch of rows per wave
-constexpr int64_t kWideTwiceUpToWorkgroups = 384;  // of two
+// The line, dense calls, default over wide (more: wide is faster): one batch of rows of 128 bytes 1.04 - 1.14 up to 512 workgroups, of 256 bytes
+// 1.03 - 1.09 up to one workgroup per CU, 0.98 - 1.04 up to two; two batches, which fp32 rows of 128 have at the planner's smallest size,
+// 1.02 - 1.11 up to 240 workgroups, 1.00 at 256, but 0.93 - 0.97 with 288 to 384 (7 x 16 heads x 276..346 10.0 -> 10.8 us): there the rate of the
+// memory counts and it costs the resident waves (64 x ~155: 27.8 -> 30.6; dense rows of 64, 576 workgroups x 250 positions 15.1 -> 15.65).
+constexpr int64_t kWideUpToWorkgroups = 512;       // slices of one (wide) batch of rows per wave
+constexpr int64_t kWideTwiceUpToWorkgroups = 256;  // of two
 
 // How the grid names its slices.
 enum class GridMode { kPlain, kTable, kRuns };
