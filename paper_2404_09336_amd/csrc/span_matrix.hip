@@ -111,10 +111,14 @@ __device__ __forceinline__ f32x4 observe4(__amdgpu_buffer_rsrc_t slot, uint32_t 
 // the later readers find them in the L2; otherwise every row is used once and streams past it.  Inputs that no cache
 // holds from call to call: 32 pairs x ~5500 positions, 20 tokens 29.6 -> 25.2 us; 96 pairs x ~900, 60 tokens 30.1 -> 26.5; 32 pairs
 // x 1500 fp32, 30 tokens 30.8 -> 28.0; without query blocks it loses (64 x ~155, 16 tokens 39.8 -> 43.7).
-template <class Elt, int D, int G, bool kOneGroup, class Args, bool kShared, int kTerms>
+// kInStep: ... and wait for all of their loads ahead of a tile's outputs, which keeps the two workgroups of a slice at the same rows, see
+// keep_in_step.
+enum class Rows { kAlone, kShared, kInStep };
+template <class Elt, int D, int G, bool kOneGroup, class Args, Rows kSharing, int kTerms>
 __global__ __launch_bounds__(kThreads)
 __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<Elt, D, G>::kWaves))) void matrix_kernel(const Args a) {
   using Shape = MatrixShape<Elt, D, G>;
+  constexpr bool kShared = kSharing != Rows::kAlone;
   constexpr int kRowPolicy = kShared ? 0 : kRowLoadPolicy;
   auto load_piece = [](__amdgpu_buffer_rsrc_t slab, uint32_t off) { return __builtin_amdgcn_raw_buffer_load_b128(slab, off, 0, kRowPolicy); };
   constexpr int NK = Shape::NK, NE = Shape::NE, VW = Shape::VW, S = kOneGroup ? 1 : Shape::S;
@@ -656,6 +660,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
       take_scores(sc);
       const TileRows next = load_k(base + TR, wn, lane);
       softmax_step(sc, base, cur);
+      if constexpr (kSharing == Rows::kInStep) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
       add_outputs(sc);
       load_v(base + TR, next, lane);
       cur = next;
@@ -825,6 +830,17 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 
 constexpr int64_t kOneRoundOfTwo = 512;  // workgroups, two per CU
 
+// Two workgroups of 16 tokens of rows of 128 that share a slice find each other's rows in their XCD's L2 as long as neither runs ahead.  With the next
+// tile's loads counted they drift, the further the longer the slice, and from 400 KB of rows a slice on that costs more than it gains.
+// They have to be on one XCD (workgroups go to the eight in turn) and to run at once.  us with the loads counted -> in step:
+// fp32, 6 x 16 heads x 9000..12000 positions, 20 tokens 353.6 -> 313.7, 7 x 16 x 3000..4000, 17 tokens 126.5 -> 118.8, 2 x 16 x 9000..12000, 32 tokens 107.8 ->
+// 101.6, slices of 450 KB 36.5 -> 35.7, of 180 25.8 -> 26.9; 16 bits, 6 x 16 x 9000..12000 129.2 -> 120.8, slices of 450 KB 18.8 -> 17.9, of 340 30.35 -> 30.9.  Not so
+// with four workgroups a slice (151.5 -> 156.8), on different XCDs (3 x 5 69.0 -> 73.2), more of them than run at once (2 x 24 fp32 82.5 -> 84.4), rows
+// of 64, or 32 tokens a workgroup (6 x 16 fp32, 40 tokens 113 -> 117).
+bool keep_in_step(int64_t of_a_block, int blocks, int per_cu, int64_t slice_bytes) {
+  return blocks == 2 && of_a_block % 8 == 0 && of_a_block * blocks <= 256 * per_cu && slice_bytes >= 400000;
+}
+
 template <class Elt, int D, int G>
 void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* table, int batch, int q_first, int tokens, hipStream_t stream) {
   const int blocks = (tokens + 16 * G - 1) / (16 * G);
@@ -841,36 +857,42 @@ void launch_shape(const LaunchArgs& base, const MatrixPlan& p, const uint32_t* t
     m.even = p.even ? 1 : p.least_slice;
     m.interleave = p.slice_tokens >= kInterleaveFrom ? 1 : 0;
   };
-  auto start_tiled = [&](auto one_group, auto shared, auto two_tokens) {
-    constexpr bool kOneGroup = decltype(one_group)::value, kShared = decltype(shared)::value;
+  auto start_tiled = [&](auto one_group, auto rows, auto two_tokens) {
+    constexpr bool kOneGroup = decltype(one_group)::value;
+    constexpr Rows kSharing = decltype(rows)::value;
     constexpr int kTerms = weight_terms<Elt, D>(decltype(two_tokens)::value);
     if (p.table) {
       MatrixArgsTable m;
       fill(m);
       for (int i = 0; i < p.total_slices; ++i) m.table[i] = table[i];
-      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, kOneGroup, MatrixArgsTable, kShared, kTerms>),
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, kOneGroup, MatrixArgsTable, kSharing, kTerms>),
                          dim3((unsigned)base.heads, (unsigned)p.total_slices, (unsigned)blocks), dim3(kThreads), 0, stream, m);
     } else {
       MatrixArgsPlain m;
       fill(m);
-      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, kOneGroup, MatrixArgsPlain, kShared, kTerms>),
+      hipLaunchKernelGGL((matrix_kernel<Elt, D, G, kOneGroup, MatrixArgsPlain, kSharing, kTerms>),
                          dim3((unsigned)base.heads, (unsigned)p.num_splits, (unsigned)(batch * blocks)), dim3(kThreads), 0, stream, m);
     }
   };
-  auto start = [&](auto shared, auto two_tokens) {
+  const int64_t of_a_block = (int64_t)base.heads * (p.table ? p.total_slices : (int64_t)p.num_splits * batch);  // workgroups
+  auto start = [&](auto rows, auto two_tokens) {
     if constexpr (MatrixShape<Elt, D, G>::kHasBoth) {
-      const int64_t workgroups = (int64_t)base.heads * blocks * (p.table ? p.total_slices : (int64_t)p.num_splits * batch);
-      if (workgroups <= kOneRoundOfTwo) return start_tiled(std::true_type{}, shared, two_tokens);
+      if (of_a_block * blocks <= kOneRoundOfTwo) return start_tiled(std::true_type{}, rows, two_tokens);
     }
-    start_tiled(std::false_type{}, shared, two_tokens);
+    start_tiled(std::false_type{}, rows, two_tokens);
   };
+  constexpr std::integral_constant<Rows, Rows::kAlone> alone{};
   if constexpr (G < 4) {  // (64 tokens are a call's most: one block)
-    if (blocks > 1) return start(std::true_type{}, std::false_type{});
+    if constexpr (G == 1 && D == 128) {
+      if (keep_in_step(of_a_block, blocks, MatrixShape<Elt, D, G>::kWaves, (int64_t)p.slice_tokens * 2 * MatrixShape<Elt, D, G>::kRowBytes))
+        return start(std::integral_constant<Rows, Rows::kInStep>{}, std::false_type{});
+    }
+    if (blocks > 1) return start(std::integral_constant<Rows, Rows::kShared>{}, std::false_type{});
   }
   if constexpr (G == 1) {
-    if (base.q_len == 2) return start(std::false_type{}, std::true_type{});
+    if (base.q_len == 2) return start(alone, std::true_type{});
   }
-  start(std::false_type{}, std::false_type{});
+  start(alone, std::false_type{});
 }
 
 template <class Elt, int D>
