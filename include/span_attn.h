@@ -101,8 +101,8 @@ typedef struct span_attn_desc {
                               and <= 288 position runs in all, <= 1024 positions per slice), resolves
                               every slice to its runs of cache positions on the host and passes the
                               runs in the kernel arguments in place of the slice table: the kernel
-                              then reads no span metadata from device memory (about 2 % faster on
-                              raggedly sliced batches).  The result is the same, bit for bit
+                              then reads no span metadata from device memory (within 3 % of the
+                              time either way).  The result is the same, bit for bit
                               (calls on the matrix cores take the counts only).  They must
                               describe the same spans as the device arrays (not checked; memory safety
                               does not depend on it) and are read during the call only.  Leave them

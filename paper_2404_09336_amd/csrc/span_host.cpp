@@ -277,10 +277,11 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
   const int64_t max_tok = (d->max_tokens > 0 && d->max_tokens < d->max_len) ? d->max_tokens : d->max_len;
   Partition p;
   if (plan_exact(d, counts.of, max_tok, &p, table)) {
-    // Run mode pays where the launch carries a slice table anyway (sequences with different numbers of slices):
+    // Run mode is used where the launch carries a slice table anyway (sequences with different numbers of slices):
     // kernel arguments of that size cost a few tenths of a microsecond per launch, which a batch that needs no
-    // table would pay on top (measured: batch 64 x 155 positions, one slice each, 27.7 -> 27.9 us with runs;
-    // batch 8 and batch 16 sliced raggedly, 24.1 -> 23.7 us and 31.1 -> 30.8 us).  The matrix kernel takes no runs.
+    // table would pay on top (measured: batch 64 x 155 positions, one slice each, 27.7 -> 27.9 us with runs).  Against the table and the
+    // device lists, on the same buffers: 10 x 12 heads x ~560, fp16 12.1 -> 11.7, 8 x 32 x ~560 18.0 -> 17.9, 16 x 32 x ~550 30.6 and 30.6, 12 x 32 x ~500,
+    // bf16 22.3 -> 22.7, 20 x 16 x ~500 20.65 -> 21.2.  The matrix kernel takes no runs.
     if (counts.from_lists && runs && p.exact && !runs_on_matrix_cores(d)) p.runs = plan_runs(d, counts.of, p, runs);
     return p;
   }
