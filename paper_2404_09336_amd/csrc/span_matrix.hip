@@ -87,6 +87,17 @@ __device__ __forceinline__ float exchange_max(float x) {  // maximum over the fo
   return fmaxf(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
 }
 
+__device__ __forceinline__ float exchange_sum(float x) {  // sum over the four lanes qi + 16 c
+  const uint32_t u = __builtin_bit_cast(uint32_t, x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t a0 = a[0], a1 = a[1];
+  const float y = __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
+  const uint32_t w = __builtin_bit_cast(uint32_t, y);
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  const uint32_t b0 = b[0], b1 = b[1];
+  return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
+}
+
 // The value is computed here and not later: the compiler would otherwise sink the additions below the next tile's loads,
 // and keep all their operands in registers across them.
 __device__ __forceinline__ void pin(f32x4& v) { asm volatile("" : "+v"(v)); }
@@ -128,6 +139,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   constexpr int kPieces = ROWB / 16;
   constexpr int kQRow = ROWB + 16;           // LDS rows of q, padded: operand reads spread over the banks
   constexpr int kAccRow = D + 4;
+  constexpr int kAtOnce = G == 4 && D == 128 ? 2 : G;  // groups whose waves' states meet in LDS together (68 KB at most, two workgroups per CU)
   // Groups of rows that K loads alternate between, see load_k.  Rows of one line have nothing to gain from two, and pay for the
   // second set of positions (16 x 16 pairs x ~380, fp16, 9 tokens 14.9 -> 15.1 us), and the fp32 shapes with the most tokens
   // need the registers (8 x 32 x ~600, 24 tokens 50.0 -> 51.1; 16 x 16 x ~600 of 64, 60 tokens 53.1 -> 54.3).  Workgroups that share
@@ -171,15 +183,15 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     IntervalTables tab;
     unsigned char q[NQ * kQRow] __attribute__((aligned(16)));
   };
-  struct WaveStates {  // of one group of 16 tokens at a time
-    float acc[kWavesPerBlock][16][kAccRow];
+  struct WaveStates {  // of kAtOnce groups of 16 tokens
+    float acc[kWavesPerBlock][16 * kAtOnce][kAccRow];
   };
   union Overlaid {
     StreamTables st;
     WaveStates ws;
   };
   __shared__ __attribute__((aligned(16))) Overlaid s_u;
-  __shared__ float s_ml[kWavesPerBlock][NQ][2];
+  __shared__ __attribute__((aligned(16))) f32x2 s_ml[NQ][kWavesPerBlock];
   __shared__ uint32_t s_ticket;
   auto& s_pos = s_u.st.pos;
   auto& s_q = s_u.st.q;
@@ -679,90 +691,104 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 #endif
   }
   {
-    float z = 0.f;  // stays 0 unless some output is Inf or NaN
+    float z[4] = {0.f, 0.f, 0.f, 0.f};  // stay 0 unless some output is Inf or NaN
 #pragma unroll
     for (int g = 0; g < G; ++g) {
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z = fmaf(O[g][e][r], 0.f, z);
+        for (int r = 0; r < 4; ++r) z[r] = fmaf(O[g][e][r], 0.f, z[r]);
       }
     }
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(z != 0.f) != 0, 0)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64((z[0] + z[1]) + (z[2] + z[3]) != 0.f) != 0, 0)) {
       clear_state();
       stream_checked();
     }
   }
   SPAN_STAMP_AFTER(4, "v", O[0][0][0] + lsum[0]);
 
-  // ---- the waves' states are merged in LDS, 16 tokens at a time ------------------------------------------
+  // ---- the waves' states are merged in LDS, the tokens of kAtOnce groups together -----------------------
+  // (What counts here are a wave's own instructions, about five cycles each, and trips to LDS: as few rounds as LDS allows, and a
+  // thread stays with one token, whose weights it works out once.  us with 16 tokens a round, weights worked out for every quad of
+  // columns and slices merged one after the other -> so: 16 x 8 heads x ~600 positions, bf16, 28 tokens, up to 5 slices 23.9 -> 19.5; 6 x 32 x ~400 of 64, fp16,
+  // 62 tokens 21.5 -> 19.1; 2 x 5 x 500..5000, 48 tokens, 22 slices 25.3 -> 21.7; 45 x 32 x ~130, bf16, 60 tokens, whole sequences 78.6 -> 72.9; 16 x 32 x ~700,
+  // 32 tokens 39.8 -> 38.9; 64 x 32 x ~155, fp16, 16 tokens 35.5 -> 35.1; 55 shapes of 2 to 64 tokens 1.052 times on average, none slower by 1 %.)
+  // (The lane is found again: kept from the start it would cost the tiles a register, where they have none.)
+  const int lane_here = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), thread = 64 * wave + lane_here;
+  const int qn = lane_here & 15, cn = lane_here >> 4;  // qi and c4
 #pragma unroll
   for (int g = 0; g < G; ++g) {  // the four lanes of a query hold the weights of disjoint rows
-    lsum[g] += __shfl_xor(lsum[g], 16, 64);
-    lsum[g] += __shfl_xor(lsum[g], 32, 64);
-    lsum[g] *= Elt::kWeightScale;
-    if (c4 == 0) {
-      s_ml[wave][16 * g + qi][0] = ref[g];
-      s_ml[wave][16 * g + qi][1] = lsum[g];
-    }
+    lsum[g] = exchange_sum(lsum[g]) * Elt::kWeightScale;
+    if (cn == 0) s_ml[16 * g + qn][wave] = f32x2{ref[g], lsum[g]};
   }
-  // A thread finishes quads of four columns: quad i of a group is columns 4 (i % (D / 4)) .. + 3 of token i / (D / 4).
-  constexpr int kQuadsPerToken = D / 4, kQuads = 16 * kQuadsPerToken / kThreads;
-  static_assert(16 * kQuadsPerToken % kThreads == 0, "whole quads per thread");
+  // Of 16 kAtOnce tokens a thread finishes `part`'s quads of columns of token `mine`: columns 4 (part + kPerToken i) .. + 3.
+  constexpr int kPerToken = kThreads / (16 * kAtOnce), kQuads = D / 4 / kPerToken;
+  static_assert(kQuads >= 1, "a quad per thread at least");
+  const int mine = thread / kPerToken, part = thread % kPerToken;
   const bool direct = nsl == 1;
   const size_t slot_floats = (size_t)a.slot_tokens * D;
   const size_t slot0 = (size_t)y0 * heads + h, my_slot = slot0 + (size_t)split * heads;
   const uint32_t q_in_slot = (uint32_t)(q0 - a.q_first);
   auto acc_slot = [&](size_t slot) { return slab_resource(a.part_acc + slot * slot_floats, (uint32_t)(slot_floats * 4)); };
+  auto ml_slot = [&](size_t slot) { return slab_resource(a.part_ml + slot * (size_t)a.slot_tokens * 2, (uint32_t)a.slot_tokens * 8u); };
+  auto store_row = [&](int token, float L, const f32x4 (&o)[kQuads]) {
+    const float sum = L != 0.f ? L : 1.f;
+    float* row = a.out + qrow(token) * D + 4 * part;
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    if (16 * g >= nq_here) break;  // (workgroup-uniform: groups without a real token)
-    __syncthreads();  // the streaming tables, or the states of the group before, are no longer read
-    if (16 * g + qi < nq_here) {
+    for (int i = 0; i < kQuads; ++i) *reinterpret_cast<f32x4*>(row + 4 * kPerToken * i) = f32x4{o[i][0] / sum, o[i][1] / sum, o[i][2] / sum, o[i][3] / sum};
+  };
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
+  for (int g0 = 0; g0 < G; g0 += kAtOnce) {
+    if (16 * g0 >= nq_here) break;  // (workgroup-uniform: groups without a real token)
+    __syncthreads();  // the (reference, sum) pairs are in LDS; the streaming tables, or the states of the groups before, are no longer read
 #pragma unroll
-        for (int u = 0; u < NE / 4; ++u)
-          *reinterpret_cast<f32x4*>(&s_u.ws.acc[wave][qi][column(4 * c4 + r, u)]) =
-              f32x4{O[g][4 * u][r], O[g][4 * u + 1][r], O[g][4 * u + 2][r], O[g][4 * u + 3][r]};
+    for (int g = g0; g < g0 + kAtOnce; ++g) {
+      if (16 * g + qn < nq_here) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+          for (int u = 0; u < NE / 4; ++u)
+            *reinterpret_cast<f32x4*>(&s_u.ws.acc[wave][16 * (g - g0) + qn][column(4 * cn + r, u)]) =
+                f32x4{O[g][4 * u][r], O[g][4 * u + 1][r], O[g][4 * u + 2][r], O[g][4 * u + 3][r]};
+        }
+      }
+    }
+    const int token = 16 * g0 + mine;
+    float weight[kWavesPerBlock], M = -INFINITY, L = 0.f;
+    {
+      f32x2 ml[kWavesPerBlock];
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) ml[w] = s_ml[token][w];
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w)
+        if (ml[w][1] != 0.f) M = fmaxf(M, ml[w][0]);  // (a NaN sum counts: it has to reach the output)
+#pragma unroll
+      for (int w = 0; w < kWavesPerBlock; ++w) {  // (a wave without rows for the token: weight 0, states 0)
+        weight[w] = ml[w][1] != 0.f ? __builtin_amdgcn_exp2f((ml[w][0] - M) * post) : 0.f;
+        L = fmaf(weight[w], ml[w][1], L);
       }
     }
     __syncthreads();
+    if (token < nq_here) {
+      f32x4 o[kQuads];
 #pragma unroll
-    for (int i = 0; i < kQuads; ++i) {
-      const int j = (tid + i * kThreads) / kQuadsPerToken, col = 4 * ((tid + i * kThreads) % kQuadsPerToken);
-      const int token = 16 * g + j;
-      if (token >= nq_here) continue;
-      float m[kWavesPerBlock], l[kWavesPerBlock], M = -INFINITY, L = 0.f;
+      for (int i = 0; i < kQuads; ++i) {
+        o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w) {
-        m[w] = s_ml[w][token][0];
-        l[w] = s_ml[w][token][1];
-        if (l[w] != 0.f) M = fmaxf(M, m[w]);  // (a NaN sum counts: it has to reach the output)
-      }
-      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+          const f32x4 ow = *reinterpret_cast<const f32x4*>(&s_u.ws.acc[w][mine][4 * (part + kPerToken * i)]);
 #pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w) {
-        const float wgt = l[w] != 0.f ? __builtin_amdgcn_exp2f((m[w] - M) * post) : 0.f;
-        const f32x4 ow = *reinterpret_cast<const f32x4*>(&s_u.ws.acc[w][j][col]);
-        L = fmaf(wgt, l[w], L);
-        if (l[w] != 0.f) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) o[k] = fmaf(wgt, ow[k], o[k]);
+          for (int k = 0; k < 4; ++k) o[i][k] = fmaf(weight[w], ow[k], o[i][k]);
         }
       }
       if (direct) {
-        const float sum = L != 0.f ? L : 1.f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) o[k] /= sum;
-        *reinterpret_cast<f32x4*>(a.out + qrow(token) * D + col) = o;
+        store_row(token, L, o);
       } else {
-        publish4(acc_slot(my_slot), ((q_in_slot + (uint32_t)token) * D + (uint32_t)col) * 4u, o);
-        if (col == 0) {
-          float* ml = a.part_ml + (my_slot * (size_t)a.slot_tokens + q_in_slot + (size_t)token) * 2;
-          publish(ml, M);
-          publish(ml + 1, L);
-        }
+        const uint32_t at = q_in_slot + (uint32_t)token;
+        const __amdgpu_buffer_rsrc_t slot = acc_slot(my_slot);
+#pragma unroll
+        for (int i = 0; i < kQuads; ++i) publish4(slot, (at * D + (uint32_t)(4 * (part + kPerToken * i))) * 4u, o[i]);
+        if (part == 0) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f32x2{M, L}), ml_slot(my_slot), at * 8u, 0, kThrough);
       }
     }
   }
@@ -779,7 +805,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   SPAN_STAMP_AFTER(7, "s", 0);
   const int field = a.query_blocks > 1 ? 8 * qb : 0;
   const uint32_t field_mask = a.query_blocks > 1 ? 0xffu : 0xffffffffu;
-  if (tid == 0)
+  if (thread == 0)
     s_ticket = (uint32_t)__hip_atomic_fetch_add(&a.counters[bh], (int)(1u << field), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   SPAN_STAMP_AFTER(8, "v", s_ticket);
@@ -787,43 +813,66 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     SPAN_TRACE_FLUSH();
     return;
   }
-  for (int i = tid; i < nq_here * kQuadsPerToken; i += kThreads) {
-    const int token = i / kQuadsPerToken, col = 4 * (i % kQuadsPerToken);
-    const uint32_t off = ((q_in_slot + (uint32_t)token) * D + (uint32_t)col) * 4u;
-    float M = -INFINITY, L = 0.f;
-    f32x4 o = {0.f, 0.f, 0.f, 0.f};
-    constexpr int kBatch = 4;  // slices fetched together
-    for (int s0 = 0; s0 < nsl; s0 += kBatch) {
-      float m[kBatch], l[kBatch];
-      f32x4 os[kBatch];
+  // Slices are merged several at a time: all their states are asked for together and their weights worked out ahead of the sums.  A
+  // state costs its instructions whether it is there or not, so up to four slices are merged by code for four (us, by that for eight ->
+  // so: 8 x 32 heads x ~300 positions, fp16, 20 tokens 13.8 -> 12.4; 9 x 12 x ~600 of 64, 37 tokens 15.2 -> 14.3; 48 shapes of 2 to 64 tokens 1.027
+  // times on average, none slower by 1 %).
+  auto merge = [&](int token, auto at_once) {
+    constexpr int kMerge = decltype(at_once)::value;
+    const uint32_t at = q_in_slot + (uint32_t)token;
+    f32x4 o[kQuads];
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
+    for (int i = 0; i < kQuads; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float M = -INFINITY, L = 0.f;
+    for (int s0 = 0; s0 < nsl; s0 += kMerge) {
+      f32x2 ml[kMerge];
+      f32x4 os[kMerge][kQuads];
+#pragma unroll
+      for (int k = 0; k < kMerge; ++k) {
         const size_t slot = slot0 + (size_t)min(s0 + k, nsl - 1) * heads;  // (past the end: a slot that exists, unused)
-        const float* ml = a.part_ml + (slot * (size_t)a.slot_tokens + q_in_slot + (size_t)token) * 2;
-        m[k] = observe(ml);
-        l[k] = observe(ml + 1);
-        os[k] = observe4(acc_slot(slot), off);
+        ml[k] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(ml_slot(slot), at * 8u, 0, kThrough));
+        const __amdgpu_buffer_rsrc_t states = acc_slot(slot);
+#pragma unroll
+        for (int i = 0; i < kQuads; ++i) os[k][i] = observe4(states, (at * D + (uint32_t)(4 * (part + kPerToken * i))) * 4u);
+      }
+      const float before = M;
+#pragma unroll
+      for (int k = 0; k < kMerge; ++k) {
+        if (s0 + k >= nsl) ml[k][1] = 0.f;
+        if (ml[k][1] != 0.f) M = fmaxf(M, ml[k][0]);
+      }
+      const float safe = M == -INFINITY ? 0.f : M;
+      if (s0 > 0) {
+        const float old = __builtin_amdgcn_exp2f((before - safe) * post);
+        L *= old;
+#pragma unroll
+        for (int i = 0; i < kQuads; ++i) o[i] *= old;
       }
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
-        if (s0 + k < nsl && l[k] != 0.f) {
-          const float mn = fmaxf(M, m[k]);
-          const float ms = mn == -INFINITY ? 0.f : mn;
-          const float wa = __builtin_amdgcn_exp2f((M - ms) * post), wb = __builtin_amdgcn_exp2f((m[k] - ms) * post);
-          L = fmaf(L, wa, l[k] * wb);
+      for (int k = 0; k < kMerge; ++k) {
+        if (s0 + k < nsl) {
+          const float w = ml[k][1] != 0.f ? __builtin_amdgcn_exp2f((ml[k][0] - safe) * post) : 0.f;  // (weight 0: states 0)
+          L = fmaf(w, ml[k][1], L);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) o[c] = fmaf(o[c], wa, os[k][c] * wb);
-          M = mn;
+          for (int i = 0; i < kQuads; ++i) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o[i][c] = fmaf(w, os[k][i][c], o[i][c]);
+          }
         }
       }
     }
-    const float sum = L != 0.f ? L : 1.f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] /= sum;
-    *reinterpret_cast<f32x4*>(a.out + qrow(token) * D + col) = o;
+    store_row(token, L, o);
+  };
+#pragma unroll 1
+  for (int g0 = 0; g0 < G; g0 += kAtOnce) {
+    const int token = 16 * g0 + mine;
+    if (token < nq_here) {
+      if (nsl <= 4) merge(token, std::integral_constant<int, 4>{});
+      else merge(token, std::integral_constant<int, 8>{});
+    }
   }
   // leave this block's part of the ticket counter ready for the next call
-  if (tid == 0) __hip_atomic_fetch_add(&a.counters[bh], (int)(0u - ((uint32_t)nsl << field)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (thread == 0) __hip_atomic_fetch_add(&a.counters[bh], (int)(0u - ((uint32_t)nsl << field)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   SPAN_STAMP_ACKED(9);
   SPAN_TRACE_FLUSH();
 }
