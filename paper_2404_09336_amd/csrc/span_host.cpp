@@ -321,7 +321,8 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
 // 63.9 -> 14.7 us; batch 8 x ~600, 32 heads x 128, fp32, 8 tokens 83.6 -> 39.7 us; 3 tokens, batch 16 x ~370, fp32 49.9 ->
 // 45.3 us; batch 16 x ~700, bf16, 32 tokens 96.4 -> 50.1 us; batch 32 x 1000, bf16, 64 tokens 313 -> 130 us.
 //
-// Slices.  512 workgroups a call (two per CU), but one slice per sequence at least and 1024, 768 or 512 workgroups at most for
+// Slices.  512 workgroups a call (two per CU; no more where no more run at once: a few workgroups in a second round double the time, 43 slices
+// per head of 12 heads are 516: us, 43 -> 42: 8 x 12 x ~1800 positions fp32, 6 tokens 54.8 -> 42.3; 24 x 5 x ~1700 fp16, 46 tokens 58.3 -> 49.8; 4 x 12 x 300..2800 fp32, 4 tokens 23.5 -> 22.2), but one slice per sequence at least and 1024, 768 or 512 workgroups at most for
 // 16, 32 or 64 tokens a workgroup (one resident round of rows of 64; fp32 rows of 128, and 16-bit ones of more than 16 tokens,
 // run two a CU and take up to two): of
 // 256, 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 shapes; more only pays for itself in
@@ -396,7 +397,9 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   while (m->groups > 1 && pairs * blocks_for(m->groups) < kMatrixPairs) m->groups /= 2;
   if (d->batch * blocks_for(m->groups) > 65535) m->tokens = n = 16 * m->groups;  // (grid.z limit)
   const int64_t blocks = blocks_for(m->groups);
-  const int64_t most = kTurn * kMatrixWorkgroupsPerCu(2, 64, m->groups) / (d->heads * blocks), wanted = ceil_div(kMatrixWorkgroups, d->heads * blocks);
+  const int64_t at_once = (int64_t)kTurn * kMatrixWorkgroupsPerCu(elt_bytes, d->head_dim, m->groups);
+  const int64_t most = kTurn * kMatrixWorkgroupsPerCu(2, 64, m->groups) / (d->heads * blocks);
+  const int64_t wanted = std::min<int64_t>(ceil_div(kMatrixWorkgroups, d->heads * blocks), std::max<int64_t>(1, at_once / (d->heads * blocks)));
   const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
   if (!p.even) {  // the counts are not known: every sequence gets the same number of slices
     if (!sliced) return true;
@@ -467,7 +470,6 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   // fp32 rows of 128, 16 x 32 heads x 400..1000 positions, 64 tokens 167.0 -> 159.9; 48 x 16 x 200..900, 48 tokens 212.3 -> 193.1; 36 x 12 x 300..1000, 40
   // tokens 150.2 -> 127.3 (dealt by the rule for one block 146.2); rows of 64, 200..900: 12 x 200, fp16, 8 tokens 61.4 -> 57.6; 8 x 256 fp32, 64 tokens
   // 231.9 -> 223.4; all at once, where the table is all that it adds: 5 x 200, 8 tokens 26.4 -> 26.8, 3 x 300 26.8 -> 27.4.
-  const int64_t at_once = (int64_t)kTurn * kMatrixWorkgroupsPerCu(elt_bytes, d->head_dim, m->groups);
   const int32_t row = std::max<int32_t>(1, kTurn / d->heads);
   if (most_s == 1 && (blocks > 1 || turn_entries(d->heads) < 2) && d->batch > row && d->batch <= kMaxPlanSlices && pairs * blocks > at_once &&
       longest * 100 * d->batch > 115 * sum) {
