@@ -42,7 +42,7 @@ struct LaunchArgs {
   const void* v_new;
   const int32_t* append_pos;   // append variant: [batch] cache row that receives them
   const int32_t* q_pos;        // few-query variant: [batch] cache position of query token 0 (causal limit), or null
-  int32_t* counters;  // [batch*heads] arrival tickets of the slices; zero between calls
+  int32_t* counters;  // [batch*heads] arrival tickets of the slices, counter_stride words apart; zero between calls
   // one slot per workgroup, slot = (first slice row of the sequence + slice) * heads + head:
   float* part_ml;   // [slots, NQ, 2]  (m in log2 units, l)
   float* part_acc;  // [slots, NQ, D]  un-normalised
@@ -53,6 +53,7 @@ struct LaunchArgs {
   int32_t total_slices;             // table mode: entries of `table` in use
   int32_t even;                     // > 0: a sequence's slices share its own token count evenly, `even` positions each at least; 0: slice_tokens each
   int32_t entry_bits;               // table mode: Deal::b_bits | n_bits << 8 | dealt << 16
+  int32_t counter_stride;
   int32_t interleave;               // 1: rows dealt to the waves round-robin (large slices); 0: contiguous quarters
 #ifdef SPAN_PHASE_TRACE
   unsigned long long* trace;        // diagnostic build only: [trace_workgroups, kTraceStamps] times of the phases, or null
@@ -383,6 +384,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_resource(const void* slab
 __device__ __forceinline__ u32x4 load_row_piece(__amdgpu_buffer_rsrc_t slab, uint32_t byte_off) {
   return __builtin_amdgcn_raw_buffer_load_b128(slab, byte_off, 0, kRowLoadPolicy);
 }
+
+// Arrival tickets of a (batch, head) pair's slices.
+__device__ __forceinline__ int32_t* ticket_counter(const LaunchArgs& a, size_t bh) { return a.counters + bh * (size_t)a.counter_stride; }
 
 // Device-coherent store / load of one float that another workgroup reads / wrote in the same kernel.
 __device__ __forceinline__ void publish(float* p, float v) {

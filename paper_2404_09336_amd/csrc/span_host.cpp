@@ -624,6 +624,10 @@ size_t workspace_counter_bytes(const span_attn_desc_t* d) {
   return (n + 255) & ~(size_t)255;
 }
 
+int32_t counter_stride(const span_attn_desc_t* d) {
+  return (int32_t)(workspace_counter_bytes(d) / sizeof(int32_t) / ((size_t)d->batch * d->heads));
+}
+
 size_t workspace_ml_bytes(const span_attn_desc_t* d, int64_t states) {
   const size_t n = (size_t)states * d->heads * 2 * sizeof(float);
   return (n + 255) & ~(size_t)255;

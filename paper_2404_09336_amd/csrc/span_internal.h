@@ -159,6 +159,11 @@ inline void deal_matrix(const span_attn_desc_t* d, const Partition& p, MatrixPla
 int check_desc(const span_attn_desc_t* d);
 int32_t query_tokens(const span_attn_desc_t* d);  // q_len of the descriptor, at least 1
 size_t workspace_counter_bytes(const span_attn_desc_t* d);
+// Words from one pair's ticket counter to the next: the counters' part of the workspace is a multiple of 256 bytes, and few pairs spread over all of it.
+// Tickets of one 64-byte line are drawn one after the other, about 10 ns each, and with several hundred workgroups of few pairs a launch waited for them up to 2.5 us.  us, side by
+// side -> apart: 2 x 8 heads x ~3200 positions dense of 64 10.8 -> 8.2; 2 x 8 x ~4500 fp32 of 64 19.1 -> 16.2; 3 x 5 x ~600 of 64, 2 tokens 11.2 -> 10.0; 4 x 5 x ~2900
+// appended 15.7 -> 14.4; 4 x 5 x 100..1200 fp32 9.6 -> 9.15; 89 shapes of up to 128 pairs 1.01 times on average, most of them with as many lines as before.
+int32_t counter_stride(const span_attn_desc_t* d);
 size_t workspace_ml_bytes(const span_attn_desc_t* d, int64_t states);
 size_t workspace_bytes_for(const span_attn_desc_t* d, int64_t states);
 size_t workspace_least_bytes(const span_attn_desc_t* d, const Partition& p);  // with less the call is refused

@@ -503,7 +503,7 @@ decode_kernel(const Args a) {
   }
   __syncthreads();
   SPAN_STAMP_AFTER(7, "s", 0);
-  if (tid == 0) s_ticket = __hip_atomic_fetch_add(&a.counters[bh], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) s_ticket = __hip_atomic_fetch_add(ticket_counter(a, bh), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   SPAN_STAMP_AFTER(8, "v", s_ticket);
   if (s_ticket != nsl - 1) {
@@ -575,7 +575,7 @@ decode_kernel(const Args a) {
     }
     store_rows(ll, oo);
     // leave the ticket counter ready for the next call (same device-coherent access path as the tickets)
-    if (tid == 0) __hip_atomic_store(&a.counters[bh], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_store(ticket_counter(a, bh), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   SPAN_STAMP_ACKED(9);
   SPAN_TRACE_FLUSH();
@@ -786,6 +786,7 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
   a.counters = need ? (int32_t*)d->workspace : nullptr;
   a.part_ml = need ? (float*)((char*)d->workspace + workspace_counter_bytes(d)) : nullptr;
   a.part_acc = need ? (float*)((char*)d->workspace + workspace_counter_bytes(d) + workspace_ml_bytes(d, states)) : nullptr;
+  a.counter_stride = counter_stride(d);
   a.heads = d->heads;
   a.max_len = d->max_len;
   a.num_intervals = d->num_intervals;

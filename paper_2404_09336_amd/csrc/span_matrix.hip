@@ -806,7 +806,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   const int field = a.query_blocks > 1 ? 8 * qb : 0;
   const uint32_t field_mask = a.query_blocks > 1 ? 0xffu : 0xffffffffu;
   if (thread == 0)
-    s_ticket = (uint32_t)__hip_atomic_fetch_add(&a.counters[bh], (int)(1u << field), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_ticket = (uint32_t)__hip_atomic_fetch_add(ticket_counter(a, bh), (int)(1u << field), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   SPAN_STAMP_AFTER(8, "v", s_ticket);
   if (((s_ticket >> field) & field_mask) != (uint32_t)(nsl - 1)) {
@@ -872,7 +872,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     }
   }
   // leave this block's part of the ticket counter ready for the next call
-  if (thread == 0) __hip_atomic_fetch_add(&a.counters[bh], (int)(0u - ((uint32_t)nsl << field)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (thread == 0) __hip_atomic_fetch_add(ticket_counter(a, bh), (int)(0u - ((uint32_t)nsl << field)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   SPAN_STAMP_ACKED(9);
   SPAN_TRACE_FLUSH();
 }
