@@ -403,6 +403,85 @@ __device__ __forceinline__ float rounded(float x) {
   return x;
 }
 
+// Both of v_permlane16_swap's (kApart = 16) or v_permlane32_swap's results: lanes 16 (32) apart of `low` and `high` are exchanged, so that
+// first + second is, in the lanes with bit kApart clear, the sum over the two of `low`, in the others that of `high`.
+struct Swapped {
+  float first, second;
+};
+template <int kApart>
+__device__ __forceinline__ Swapped swap_lanes(float low, float high) {
+  static_assert(kApart == 16 || kApart == 32, "what the instructions exchange");
+  const uint32_t l = __builtin_bit_cast(uint32_t, low), h = __builtin_bit_cast(uint32_t, high);
+  uint32_t a, b;
+  if constexpr (kApart == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(l, h, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(l, h, false, false);
+    a = r[0];
+    b = r[1];
+  }
+  return Swapped{__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)};
+}
+
+// Maximum / sum over the lanes lir, lir + kLanes, lir + 2 kLanes .. of the wave (kLanes = 8, 16 or 32); every lane gets it.
+template <int kLanes>
+__device__ __forceinline__ float across_groups_max(float x) {
+  if (kLanes <= 8) x = fmaxf(x, dpp_f<0x128>(x));  // row_ror:8
+  if (kLanes <= 16) {
+    const Swapped s = swap_lanes<16>(x, x);
+    x = fmaxf(s.first, s.second);
+  }
+  const Swapped s = swap_lanes<32>(x, x);
+  return fmaxf(s.first, s.second);
+}
+template <int kLanes>
+__device__ __forceinline__ float across_groups_sum(float x) {
+  if (kLanes <= 8) x += dpp_f<0x128>(x);  // row_ror:8
+  if (kLanes <= 16) {
+    const Swapped s = swap_lanes<16>(x, x);
+    x = s.first + s.second;
+  }
+  const Swapped s = swap_lanes<32>(x, x);
+  return s.first + s.second;
+}
+
+// The states of a wave's row groups become one.  Lane lir + kLanes i comes with group i's state of columns kPer lir .. + kPer - 1, relative to its
+// own m; afterwards m and l are the wave's in every lane, and acc[0 .. kOwn - 1] the wave's sums of the lane's own columns, own_column() on.
+// The lanes share the columns' sums out as they are added: half as many with every exchange.
+template <int kLanes, int kPer>
+struct GroupMerge {
+  static constexpr int kOwn = kLanes == 32 ? kPer / 2 : kPer / 4;
+  static_assert(kOwn >= 1, "a column per lane at least");
+  static __device__ __forceinline__ int own_column(int lane) {
+    return kPer * (lane % kLanes) + (lane & 32 ? kPer / 2 : 0) + (kLanes <= 16 && (lane & 16) ? kPer / 4 : 0);
+  }
+  static __device__ __forceinline__ void merge(float& m, float& l, float* acc) {
+    const float all = across_groups_max<kLanes>(m);
+    const float f = __builtin_amdgcn_exp2f(m - (all == -INFINITY ? 0.f : all));
+    m = all;
+    l = across_groups_sum<kLanes>(l * f);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      acc[i] *= f;
+      if (kLanes <= 8) acc[i] += dpp_f<0x128>(acc[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer / 2; ++i) {
+      const Swapped s = swap_lanes<32>(acc[i], acc[i + kPer / 2]);
+      acc[i] = s.first + s.second;
+    }
+    if constexpr (kLanes <= 16) {
+#pragma unroll
+      for (int i = 0; i < kPer / 4; ++i) {
+        const Swapped s = swap_lanes<16>(acc[i], acc[i + kPer / 4]);
+        acc[i] = s.first + s.second;
+      }
+    }
+  }
+};
+
 // Merge two un-normalised softmax states held in log2 units.
 __device__ __forceinline__ void merge_state(float& m, float& l, float* acc, int n, float m2, float l2,
                                             const float* acc2) {

@@ -111,9 +111,7 @@ decode_kernel(const Args a) {
   __shared__ IntervalTables s_tab;
   __shared__ __attribute__((aligned(16))) float s_acc[kWavesPerBlock][NQ][D];
   __shared__ u32x4 s_new[NQ == 1 ? kWavesPerBlock : 1][2][LPR];  // append variant: the new K / V row, parked until its owner needs it
-  __shared__ float s_ml[kWavesPerBlock][NQ][2];
-  constexpr int kSliceGroups = kThreads / D;  // thread groups of the slice merge, see step 5
-  __shared__ float s_gm[kSliceGroups][NQ], s_gl[kSliceGroups][NQ];
+  __shared__ f32x2 s_ml[kWavesPerBlock][NQ];
   __shared__ int s_ticket;
 #ifdef SPAN_STAGE_LDS
   __shared__ u32x4 s_stage[kWavesPerBlock][2][U][64];  // measurement build: U K tiles and U V tiles of 1 KiB per wave
@@ -173,6 +171,35 @@ decode_kernel(const Args a) {
     L[j] = 0.f;
     o[j] = 0.f;
   }
+  // A wave's state goes to LDS, and thread t < D makes one of the four.
+  auto leave_state = [&](auto shape, int j, float wave_m, float wave_l, const float* wave_acc) {
+    using Shape = decltype(shape);
+    float* to = &s_acc[wave][j][Shape::own_column(lane)];
+    if constexpr (Shape::kOwn == 2) *reinterpret_cast<f32x2*>(to) = f32x2{wave_acc[0], wave_acc[1]};
+    else to[0] = wave_acc[0];
+    if (lane == 0) s_ml[wave][j] = f32x2{wave_m, wave_l};
+  };
+  auto merge_waves = [&]() {
+    if (tid < D) {
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) {
+        float top = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) top = fmaxf(top, s_ml[w][j][0]);
+        const float safe = top == -INFINITY ? 0.f : top;  // (a wave without rows: -Inf, weight 0, sums 0)
+        float sum = 0.f, out = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+          const float wgt = __builtin_amdgcn_exp2f(s_ml[w][j][0] - safe);
+          sum = fmaf(wgt, s_ml[w][j][1], sum);
+          out = fmaf(wgt, s_acc[w][j][tid], out);
+        }
+        M[j] = top;
+        L[j] = sum;
+        o[j] = out;
+      }
+    }
+  };
   // Append variant: the first slice's workgroup writes the new row into the cache, whatever the span holds.
   if (NQ == 1 && a.append_pos && split == 0 && wave == 0 && lane < LPR && new_pos >= 0 && new_pos < a.max_len) {
     const size_t row = (bh * (size_t)a.max_len + (size_t)new_pos) * ROWB + (uint32_t)lir * 16u;
@@ -426,41 +453,14 @@ decode_kernel(const Args a) {
   }  // windows
   SPAN_STAMP_AFTER(4, "v", acc[0][0]);
 
-  // ---- step 4: merge row groups (shuffles), then waves (LDS) ------------------------------------
+  // ---- step 4: merge row groups (lane exchanges), then waves (LDS) --------------------------------
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
-#pragma unroll
-    for (int off = LPR; off < 64; off <<= 1) {
-      const float m2 = __shfl_xor(m[j], off, 64), l2 = __shfl_xor(l[j], off, 64);
-      float acc2[EPL];
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) acc2[i] = __shfl_xor(acc[j][i], off, 64);
-      merge_state(m[j], l[j], acc[j], EPL, m2, l2, acc2);
-    }
-    if (lane < LPR) {
-#pragma unroll
-      for (int i = 0; i < EPL; ++i) s_acc[wave][j][lir * EPL + i] = acc[j][i];
-      if (lane == 0) {
-        s_ml[wave][j][0] = m[j];
-        s_ml[wave][j][1] = l[j];
-      }
-    }
+    GroupMerge<LPR, EPL>::merge(m[j], l[j], acc[j]);
+    leave_state(GroupMerge<LPR, EPL>{}, j, m[j], l[j], acc[j]);
   }
   __syncthreads();
-  if (tid < D) {
-#pragma unroll
-    for (int j = 0; j < NQ; ++j) {
-#pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w)
-        if (s_ml[w][j][1] > 0.f) M[j] = fmaxf(M[j], s_ml[w][j][0]);
-#pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w) {
-        const float wgt = s_ml[w][j][1] > 0.f ? __builtin_amdgcn_exp2f(s_ml[w][j][0] - M[j]) : 0.f;
-        L[j] = fmaf(wgt, s_ml[w][j][1], L[j]);
-        o[j] = fmaf(wgt, s_acc[w][j][tid], o[j]);
-      }
-    }
-  }
+  merge_waves();
   }  // cnt > 0
   SPAN_STAMP_AFTER(5, "v", o[0]);
 
@@ -511,72 +511,51 @@ decode_kernel(const Args a) {
     return;
   }
 
-  // Column t is merged by G threads, each over every G-th slice.
-  constexpr int G = kSliceGroups;
-  const int g = tid / D;
+  // The slices are dealt to groups of D / 4 threads, four columns each: a group merges its slices, then the groups are merged as the row
+  // groups of a slice are.  What counts is the workgroup's own instructions, about five cycles each for a wave alone.  us, each column
+  // by two threads, slice after slice, and row groups merged whole in every lane (GroupMerge) -> so: 1 x 12 heads x ~2500 positions dense, 20 slices 8.3 -> 7.3;
+  // 5 x 32 x ~80 of 64 6.9 -> 6.2; 1 x 16 x ~760 6.8 -> 6.3; 5 x 32 x ~530 12.2 -> 11.5; 20 x 32 x ~600 39.8 -> 39.2; 71 shapes 1.045 times on average,
+  // none slower.
+  constexpr int kColThreads = D / 4, kGroups = kThreads / kColThreads;
+  const int part = tid / kColThreads, col = 4 * (tid % kColThreads);
   const size_t slot0 = (size_t)y0 * H + h;  // slice s of this (b, h) is slot0 + s * H
-  float mm[NQ], ll[NQ], oo[NQ];
+  typedef uint64_t u64;
+  auto observe2 = [](const float* p) {
+    return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const u64*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  };
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
-    mm[j] = -INFINITY;
-    ll[j] = 0.f;
-    oo[j] = 0.f;
-  }
-  // The states are fetched a batch at a time, all loads of a batch in flight together (one trip to memory for up
-  // to kBatch * G slices), and merged in slice order.
-  constexpr int kBatch = NQ == 1 ? 8 : 4;
-  for (int s0 = g; s0 < nsl; s0 += G * kBatch) {
-    float ms[kBatch][NQ], ls[kBatch][NQ], as[kBatch][NQ];
+    float mm = -INFINITY, ll = 0.f, oo[4] = {0.f, 0.f, 0.f, 0.f};
+    auto merge_slices = [&](auto at_once) {  // so many of the group's slices, all of whose states are asked for together
+      constexpr int kBatch = decltype(at_once)::value;
+      for (int s0 = part; s0 < nsl; s0 += kGroups * kBatch) {
+        f32x2 ml[kBatch], lo[kBatch], hi[kBatch];
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const size_t slot = slot0 + (size_t)min(s0 + k * G, nsl - 1) * H;  // (past the end: a slot that exists, unused)
+        for (int k = 0; k < kBatch; ++k) {
+          const size_t state = (slot0 + (size_t)min(s0 + k * kGroups, nsl - 1) * H) * NQ + j;  // (past the end: a slot that exists, unused)
+          ml[k] = observe2(&a.part_ml[state * 2]);
+          lo[k] = observe2(&a.part_acc[state * D + col]);
+          hi[k] = observe2(&a.part_acc[state * D + col + 2]);
+        }
 #pragma unroll
-      for (int j = 0; j < NQ; ++j) {
-        ms[k][j] = observe(&a.part_ml[(slot * NQ + j) * 2]);
-        ls[k][j] = observe(&a.part_ml[(slot * NQ + j) * 2 + 1]);
-        as[k][j] = observe(&a.part_acc[(slot * NQ + j) * D + t]);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      if (s0 + k * G < nsl) {
-#pragma unroll
-        for (int j = 0; j < NQ; ++j) {
-          const bool full = ls[k][j] > 0.f;  // slot of an empty slice is never written: select, do not scale
-          const float av = full ? as[k][j] : 0.f;
-          merge_state(mm[j], ll[j], &oo[j], 1, full ? ms[k][j] : -INFINITY, full ? ls[k][j] : 0.f, &av);
+        for (int k = 0; k < kBatch; ++k) {
+          if (s0 + k * kGroups < nsl && ml[k][1] > 0.f) {  // (the slot of an empty slice is never written)
+            const float oo2[4] = {lo[k][0], lo[k][1], hi[k][0], hi[k][1]};
+            merge_state(mm, ll, oo, 4, ml[k][0], ml[k][1], oo2);
+          }
         }
       }
-    }
+    };
+    if (nsl <= kGroups) merge_slices(std::integral_constant<int, 1>{});
+    else merge_slices(std::integral_constant<int, 4>{});
+    GroupMerge<kColThreads, 4>::merge(mm, ll, oo);
+    leave_state(GroupMerge<kColThreads, 4>{}, j, mm, ll, oo);
   }
-  if constexpr (G > 1) {
-    if (g > 0) {
-#pragma unroll
-      for (int j = 0; j < NQ; ++j) {
-        s_acc[g][j][t] = oo[j];
-        if (t == 0) {
-          s_gm[g][j] = mm[j];
-          s_gl[g][j] = ll[j];
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (g == 0) {
-    if constexpr (G > 1) {
-#pragma unroll
-      for (int j = 0; j < NQ; ++j) {
-#pragma unroll
-        for (int k = 1; k < G; ++k) {
-          const float o2 = s_acc[k][j][t];
-          merge_state(mm[j], ll[j], &oo[j], 1, s_gm[k][j], s_gl[k][j], &o2);
-        }
-      }
-    }
-    store_rows(ll, oo);
-    // leave the ticket counter ready for the next call (same device-coherent access path as the tickets)
-    if (tid == 0) __hip_atomic_store(ticket_counter(a, bh), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  __syncthreads();
+  merge_waves();
+  if (owns) store_rows(L, o);
+  // leave the ticket counter ready for the next call (same device-coherent access path as the tickets)
+  if (tid == 0) __hip_atomic_store(ticket_counter(a, bh), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   SPAN_STAMP_ACKED(9);
   SPAN_TRACE_FLUSH();
 }
