@@ -425,7 +425,7 @@ __device__ __forceinline__ Swapped swap_lanes(float low, float high) {
   return Swapped{__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)};
 }
 
-// Maximum / sum over the lanes lir, lir + kLanes, lir + 2 kLanes .. of the wave (kLanes = 8, 16 or 32); every lane gets it.
+// Maximum over the lanes lir, lir + kLanes, lir + 2 kLanes .. of the wave (kLanes = 8, 16 or 32); every lane gets it.
 template <int kLanes>
 __device__ __forceinline__ float across_groups_max(float x) {
   if (kLanes <= 8) x = fmaxf(x, dpp_f<0x128>(x));  // row_ror:8
@@ -436,17 +436,6 @@ __device__ __forceinline__ float across_groups_max(float x) {
   const Swapped s = swap_lanes<32>(x, x);
   return fmaxf(s.first, s.second);
 }
-template <int kLanes>
-__device__ __forceinline__ float across_groups_sum(float x) {
-  if (kLanes <= 8) x += dpp_f<0x128>(x);  // row_ror:8
-  if (kLanes <= 16) {
-    const Swapped s = swap_lanes<16>(x, x);
-    x = s.first + s.second;
-  }
-  const Swapped s = swap_lanes<32>(x, x);
-  return s.first + s.second;
-}
-
 // The states of a wave's row groups become one.  Lane lir + kLanes i comes with group i's state of columns kPer lir .. + kPer - 1, relative to its
 // own m; afterwards m and l are the wave's in every lane, and acc[0 .. kOwn - 1] the wave's sums of the lane's own columns, own_column() on.
 // The lanes share the columns' sums out as they are added: half as many with every exchange.
@@ -461,23 +450,26 @@ struct GroupMerge {
     const float all = across_groups_max<kLanes>(m);
     const float f = __builtin_amdgcn_exp2f(m - (all == -INFINITY ? 0.f : all));
     m = all;
-    l = across_groups_sum<kLanes>(l * f);
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      acc[i] *= f;
-      if (kLanes <= 8) acc[i] += dpp_f<0x128>(acc[i]);
-    }
+    const Swapped fs = swap_lanes<32>(f, f), ls = swap_lanes<32>(l, l);
+    l = fmaf(ls.first, fs.first, ls.second * fs.second);
 #pragma unroll
     for (int i = 0; i < kPer / 2; ++i) {
       const Swapped s = swap_lanes<32>(acc[i], acc[i + kPer / 2]);
-      acc[i] = s.first + s.second;
+      acc[i] = fmaf(s.first, fs.first, s.second * fs.second);
     }
     if constexpr (kLanes <= 16) {
+      const Swapped s = swap_lanes<16>(l, l);
+      l = s.first + s.second;
 #pragma unroll
       for (int i = 0; i < kPer / 4; ++i) {
         const Swapped s = swap_lanes<16>(acc[i], acc[i + kPer / 4]);
         acc[i] = s.first + s.second;
       }
+    }
+    if constexpr (kLanes <= 8) {
+      l += dpp_f<0x128>(l);  // row_ror:8
+#pragma unroll
+      for (int i = 0; i < kOwn; ++i) acc[i] += dpp_f<0x128>(acc[i]);
     }
   }
 };
