@@ -102,7 +102,26 @@ static int64_t slice_room(const span_attn_desc_t* d) {
 // So the aim is ONE resident round: the smallest slice size T for which all slices of all sequences,
 // times heads, fit into kTargetWorkgroups.  Sequence b gets ceil(n_b / T) slices, which the kernel makes
 // equal-sized.  When batch * heads alone exceeds a round, every sequence is one slice.
-static int64_t slices_for(int64_t n, int64_t T) { return n <= 0 ? 1 : ceil_div(n, T); }
+static int64_t slices_for(int64_t n, int64_t T, int64_t whole) { return n <= std::max<int64_t>(whole, 0) ? 1 : ceil_div(n, T); }
+
+// fp32 rows of 128, one token: slices of half kMinSlice where a call has no more of them than it aims at.  A wave's batch of rows (16 KB with twice the
+// loads in flight, see launch_typed) is 16 such rows, and 32 of the others: a slice that fills it is read in one trip.  us, slices of 128 -> of 64: 8 pairs x
+// 256 positions 7.15 -> 6.11, x 512 7.58 -> 6.27; 32 pairs x 320 8.0 -> 6.9, x 512 8.4 -> 7.9, x 1000 10.5 -> 10.3; 64 x 400 10.0 -> 9.4, x 512 10.6
+// -> 10.7. Slices between 64 and 128 are two batches all the same: 32 pairs, up to 3250 positions planned from a bound 15.8 -> 16.2.
+static bool fine_slices(const span_attn_desc_t* d) { return query_tokens(d) == 1 && d->dtype == SPAN_F32 && d->head_dim == 128; }
+constexpr int64_t kFineSlice = kMinSlice / 2;
+
+// A sequence of up to so many positions stays in one slice however few the pairs, one or two tokens: two batches of rows a wave take less than the
+// hand-over of the slices. us, in two slices -> whole, 256 positions, 8, 32, 96, 160 and 256 pairs: fp16 rows of 128 6.3, 6.4, 7.2, 8.7, 9.9 -> 5.9,
+// 6.0, 6.7, 7.2, 8.5, of 64 5.9, 5.75, 6.3, 6.9, 7.6 -> 4.7, 4.7, 5.1, 5.4, 5.9, fp32 of 64 6.1, 6.2, 7.1, 8.5, 9.75 -> 5.7, 5.8, 6.5, 7.0, 8.3; 136
+// positions 5.9 -> 4.6, 5.6 -> 4.0, 5.9 -> 4.6 (8 pairs). 320 positions in three: 6.2 -> 7.3, 5.7 -> 6.0, 6.05 -> 7.3 (8 pairs), 11.4 -> 10.3 (256,
+// see level below). fp32 rows of 128 up to 128: 256 pairs x 50..100 8.1 -> 7.0; 136 positions, 8 pairs 6.1 -> 5.9, 160 6.1 -> 6.9, 32 pairs 6.3 ->
+// 7.4. Two tokens, 256 positions: fp16 of 128 7.8 -> 7.8 (32 pairs), 10.7 -> 8.9 (256); fp32 of 64, 160 positions 7.9 -> 6.6 (32), 256 8.65 -> 8.85.
+static int64_t whole_up_to(const span_attn_desc_t* d) {
+  if (query_tokens(d) > 2 || (runs_on_matrix_cores(d) && (int64_t)d->batch * d->heads > 256)) return 0;  // (the matrix kernel's: see plan_matrix)
+  if (d->dtype == SPAN_F32) return d->head_dim == 128 ? kMinSlice : (query_tokens(d) == 1 ? 256 : 160);
+  return 256;
+}
 
 static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq, int64_t max_tok, Partition* p,
                        uint32_t* table) {
@@ -111,9 +130,11 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
     const int64_t n = tokens_per_seq[b];
     return n < 0 ? (int64_t)0 : (n > max_tok ? max_tok : n);
   };
+  const int64_t whole = whole_up_to(d);
+  auto cut = [&](int64_t n, int64_t T) { return slices_for(n, T, whole); };
   auto count = [&](int64_t T) {
     int64_t c = 0;
-    for (int32_t b = 0; b < d->batch; ++b) c += slices_for(tokens(b), T);
+    for (int32_t b = 0; b < d->batch; ++b) c += cut(tokens(b), T);
     return c;
   };
   int64_t sum = 0, longest = 0;
@@ -124,14 +145,21 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   int64_t room = slice_room(d);  // slices (per head) the call aims at, at most one resident round
   if (room > kMaxPlanSlices) room = kMaxPlanSlices;
   int64_t T = ceil_div(sum, room);
-  if (T < kMinSlice) T = kMinSlice;
+  if (T < kMinSlice) T = fine_slices(d) && count(kFineSlice) <= room ? kFineSlice : kMinSlice;
   int64_t total = count(T);
   // A quarter of the chip's wavefront slots (512 workgroups) already keeps the memory system busy, and a
   // pair that is one workgroup needs no partial states and no tickets.  So a batch of at least 512 (batch,
   // head) pairs whose longest sequence is within 35 % of the mean runs unsplit (measured 5-10 % faster than
   // filling the round with slices: batch 16 x 555 tokens +-25 % 30.6 -> 27.9 us, batch 48 x 300 44.6 -> 42.3 us);
   // more ragged batches need the slices to level the work (batch 16, 112..1100 tokens: 30.3 split, 30.9 unsplit).
-  const bool level = (int64_t)d->batch * d->heads >= kUnsplitFromPairs && longest * 100 * d->batch <= 135 * sum;
+  // From one workgroup per CU on so do short sequences, one token, if they are level: us, sliced -> whole, fp16 rows of 128: 256 pairs x 400
+  // positions 13.4 -> 12.4, x 700 18.7 -> 17.7, x 1000 25.6 -> 28.8; 384 x 448 18.6 -> 17.6, x 700 26.9 -> 25.6, x 1000 38.1 -> 39.4; 448 x 700 31.7
+  // -> 27.9; fp32: 256 x 700 33.0 -> 32.6, x 1000 49.7 -> 52.9; fp16 of 64: 256 x 320 8.6 -> 7.4, x 448 9.95 -> 10.15; 320 x 448 11.1 -> 10.6, x 700
+  // 14.7 -> 14.9; 448 x 448 13.6 -> 11.6.
+  const int64_t pairs = (int64_t)d->batch * d->heads;
+  const int64_t short_up_to = d->dtype != SPAN_F32 && d->head_dim == 64 ? pairs * 3 / 2 : 768;
+  const bool level = (pairs >= kUnsplitFromPairs && longest * 100 * d->batch <= 135 * sum) ||
+                     (pairs >= kUnsplitFromPairs / 2 && query_tokens(d) == 1 && longest <= short_up_to && longest * 100 * d->batch <= 108 * sum);
   if (room < d->batch || level) {  // whole sequences (batch * heads alone exceeds a round, or a level batch)
     T = max_tok > 0 ? max_tok : 1;
     total = count(T);
@@ -154,7 +182,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   {
     int64_t largest_now = 1;
     for (int32_t b = 0; b < d->batch; ++b) {
-      const int64_t n = tokens(b), per = ceil_div(n, slices_for(n, T));
+      const int64_t n = tokens(b), per = ceil_div(n, cut(n, T));
       if (per > largest_now) largest_now = per;
     }
     if (largest_now > kLargeSlice && 2 * largest_now * total > 3 * sum) {
@@ -168,7 +196,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   }
   int64_t most = 1, least = kMaxPlanSplits + 1, largest = 1;
   for (int32_t b = 0; b < d->batch; ++b) {
-    const int64_t n = tokens(b), nsl = slices_for(n, T);
+    const int64_t n = tokens(b), nsl = cut(n, T);
     if (nsl > most) most = nsl;
     if (nsl < least) least = nsl;
     if (ceil_div(n, nsl) > largest) largest = ceil_div(n, nsl);
@@ -178,7 +206,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
     if (table) {
       int32_t y = 0;
       for (int32_t b = 0; b < d->batch; ++b) {
-        const int64_t nsl = slices_for(tokens(b), T);
+        const int64_t nsl = cut(tokens(b), T);
         for (int64_t s = 0; s < nsl; ++s) table[y++] = pack_slice((uint32_t)b, (uint32_t)s, (uint32_t)nsl);
       }
     }
@@ -194,6 +222,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   p->total_slices = (int32_t)total;
   p->queries_per_pass = queries_per_pass(d);
   p->granule = (int32_t)T;
+  p->whole = (int32_t)whole;
   p->runs = false;
   return true;
 }
@@ -218,7 +247,7 @@ TokenCounts::TokenCounts(const span_attn_desc_t* d) : from_lists(has_host_lists(
 }
 
 // Run mode: resolves each slice of an exact plan to its runs of consecutive cache positions.  Sequence b has
-// n_b attended positions, numbered 0 .. n_b-1 along its interval list, and ceil(n_b / granule) slices that share
+// n_b attended positions, numbered 0 .. n_b-1 along its interval list, and ceil(n_b / granule) slices (or one) that share
 // them evenly (as the kernel cuts them when it walks the device lists itself).  False if the plan does not fit the
 // tables or a slice is larger than one position window per wave allows.
 static bool plan_runs(const span_attn_desc_t* d, const int64_t* tokens_per_seq, const Partition& p, RunTables* r) {
@@ -227,7 +256,7 @@ static bool plan_runs(const span_attn_desc_t* d, const int64_t* tokens_per_seq, 
   for (int32_t b = 0; b < d->batch; ++b) {
     int64_t n = tokens_per_seq[b] < 0 ? 0 : tokens_per_seq[b];
     if (n > p.max_tokens) n = p.max_tokens;
-    const int64_t nsl = slices_for(n, p.granule), T = ceil_div(n, nsl);
+    const int64_t nsl = slices_for(n, p.granule, p.whole), T = ceil_div(n, nsl);
     if (T > kMaxRunSliceRows || nsl > kMaxPlanSplits) return false;
     const int32_t lo = std::min(std::max(d->host_span_offsets[b], 0), d->num_intervals);
     const int32_t hi = std::min(std::max(d->host_span_offsets[b + 1], lo), d->num_intervals);
@@ -292,7 +321,8 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
     const int64_t in_round = target_workgroups(d) / d->heads / d->batch;
     while (splits > 0 && splits < in_round && ceil_div(max_tok, splits) > kBoundSlice) ++splits;
   }
-  const int64_t most = ceil_div(max_tok, kMinSlice);
+  const int64_t fine = slices_for(max_tok, kFineSlice, whole_up_to(d));
+  const int64_t most = fine_slices(d) && fine <= splits ? fine : slices_for(max_tok, kMinSlice, whole_up_to(d));
   if (d->num_splits == 0 && splits > most) splits = most;
   if (splits > max_tok) splits = max_tok;
   if (splits < 1) splits = 1;
@@ -309,6 +339,7 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
   p.total_slices = (int32_t)(splits * d->batch);
   p.queries_per_pass = queries_per_pass(d);
   p.granule = (int32_t)slice;
+  p.whole = 0;
   p.runs = false;
   return p;
 }
@@ -322,18 +353,15 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
 // 45.3 us; batch 16 x ~700, bf16, 32 tokens 96.4 -> 50.1 us; batch 32 x 1000, bf16, 64 tokens 313 -> 130 us.
 //
 // Slices.  512 workgroups a call (two per CU; no more where no more run at once: a few workgroups in a second round double the time, 43 slices
-// per head of 12 heads are 516: us, 43 -> 42: 8 x 12 x ~1800 positions fp32, 6 tokens 54.8 -> 42.3; 24 x 5 x ~1700 fp16, 46 tokens 58.3 -> 49.8; 4 x 12 x 300..2800 fp32, 4 tokens 23.5 -> 22.2), but one slice per sequence at least and 1024, 768 or 512 workgroups at most for
-// 16, 32 or 64 tokens a workgroup (one resident round of rows of 64; fp32 rows of 128, and 16-bit ones of more than 16 tokens,
-// run two a CU and take up to two): of
-// 256, 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 shapes; more only pays for itself in
-// partial states, which grow with the tokens (batch 16 x ~700, 32 tokens, 16 slices per head against 32: 50.4 and 59.3 us).
-// The slices have to fit the workspace's token states, so sequences that stay in one slice, which need no state, come after
-// the others in the table.
-//
-// Groups.  A workgroup that serves all tokens reads every row once; where the batch has too few (batch, head) pairs to
-// fill the chip that way (fewer than 128 workgroups before slicing), several workgroups share a slice's rows through the
-// L2, each for its own tokens: 12 heads x 8, 60 tokens 36.1 us with 64 tokens a workgroup, 29.2 us with 32; 32 pairs x 1500
-// fp32 positions, 30 tokens 38.9 -> 31.1 us; 256 pairs, 24 tokens 22.2 us in two workgroups, 18.9 us in one.
+// per head of 12 heads are 516: us, 43 -> 42: 8 x 12 x ~1800 positions fp32, 6 tokens 54.8 -> 42.3; 24 x 5 x ~1700 fp16, 46 tokens 58.3 -> 49.8; 4 x
+// 12 x 300..2800 fp32, 4 tokens 23.5 -> 22.2), but one slice per sequence at least and 1024, 768 or 512 workgroups at most for 16, 32 or 64 tokens a
+// workgroup (one resident round of rows of 64; fp32 rows of 128, and 16-bit ones of more than 16 tokens, run two a CU and take up to two): of 256,
+// 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 shapes; more only pays for itself in partial states, which grow with the
+// tokens (batch 16 x ~700, 32 tokens, 16 slices per head against 32: 50.4 and 59.3 us). The slices have to fit the workspace's token states, so
+// sequences that stay in one slice, which need no state, come after the others in the table. Groups. A workgroup that serves all tokens reads every
+// row once; where the batch has too few (batch, head) pairs to fill the chip that way (fewer than 128 workgroups before slicing), several workgroups
+// share a slice's rows through the L2, each for its own tokens: 12 heads x 8, 60 tokens 36.1 us with 64 tokens a workgroup, 29.2 us with 32; 32 pairs
+// x 1500 fp32 positions, 30 tokens 38.9 -> 31.1 us; 256 pairs, 24 tokens 22.2 us in two workgroups, 18.9 us in one.
 constexpr int32_t kMatrixFromTokens = 3;
 // Two tokens: 16-bit rows and few (batch, head) pairs, where the start-up and the hand-over count and the matrix kernel's
 // are shorter; many pairs stream better through the vector kernel's 24 waves per CU.  us, vector -> matrix: 64 pairs of 128
@@ -370,6 +398,33 @@ int64_t most_states(const span_attn_desc_t* d, const Partition& p) {
 constexpr int32_t kTurn = 256;  // CUs (a column fits 8 bits)
 static int32_t turn_entries(int32_t heads) { return (kTurn + heads / 2) / heads; }
 
+// Slices of a few-query call: one workgroup per CU at most, or the 512 wanted? Where both run at once a second workgroup on a CU costs almost what it
+// does, so the plan with one pays (where the lengths are known) unless its largest slice is longer than what the fullest CU gets of the other plan,
+// by a factor that is how much better two hide each other's trips. It pays a hand-over's worth more if it cuts nothing. us, up to 512 workgroups ->
+// up to 256, level sequences: fp16 rows of 128, 4 tokens: 96 pairs x 300 positions 9.4 -> 9.1, 128 x 512 11.4 -> 11.1, 160 x 256 9.5 -> 8.2, x 400
+// 11.5 -> 10.9, x 640 14.5 -> 15.9, 224 x 512 15.4 -> 13.8, 256 x 400 14.4 -> 12.3; 16 tokens: 32 x 1500 12.9 -> 11.1, 128 x 512 12.6 -> 11.6, 160 x
+// 512 14.1 -> 13.7, x 1000 21.2 -> 22.9, 224 x 512 17.0 -> 14.3; 32 tokens: 256 x 256 14.9 -> 11.4; 64 tokens: 160 x 256 20.2 -> 15.6, 256 x 400 26.1
+// -> 21.7; fp32, 4 tokens: 128 x 512 18.3 -> 17.2, 160 x 300 16.9 -> 16.0, x 512 21.2 -> 22.8, 256 x 400 25.1 -> 22.35; 32 tokens: 160 x 400 28.8 ->
+// 30.0; fp16 of 64, 4 tokens: 96 x 512 8.85 -> 8.5, x 640 9.0 -> 9.6, 192 x 512 10.15 -> 9.9; fp32 of 64, whole: 192 x 400 14.4 -> 14.2, x 512 14.9
+// -> 16.4, 256 x 400 15.0 -> 13.7, but not cut: 64 x 640 in four 10.4 -> 10.95, 65 x ~800 11.2 -> 11.55. Longer slices gain less, and fewer
+// workgroups than five in eight CUs lose (3 workgroups a slice, 48 pairs x ~300, 44 tokens 11.4 -> 12.3): both are left as they were. Where the
+// (batch, head) pairs alone are no more than one per CU, a sequence of up to 256 positions (fp32 rows of 64: 192; of 128: 128) stays whole anyway,
+// three or four tiles a wave: 256 positions in two slices -> whole, fp16 of 128, 16 tokens: 8 pairs 7.6 -> 7.4, 96 8.4 -> 8.05, 256 12.2 -> 9.4; of
+// 64 6.7 -> 5.9, 7.2 -> 6.6, 9.2 -> 7.0; fp32 of 64, 160 positions 8.1 -> 7.6 (8 pairs), 200 8.0 -> 8.9.
+struct SliceCost {
+  int64_t slices, largest, rows;  // slices, positions of the largest, positions of all
+  bool cuts;                      // some sequence has several
+};
+static bool one_per_cu_pays(const span_attn_desc_t* d, int64_t workgroups_per_slice, const SliceCost& one, const SliceCost& more) {
+  constexpr int64_t kFrom = 160;  // workgroups
+  constexpr int64_t kWholeUpTo = 512, kSliceUpTo = 384, kStart = 64, kHandOver = 64;  // positions
+  if (one.largest > (one.cuts ? kSliceUpTo : kWholeUpTo) || one.slices * workgroups_per_slice < kFrom) return false;
+  if (one.cuts && d->dtype == SPAN_F32 && d->head_dim == 64) return false;
+  const int64_t percent = d->dtype == SPAN_F32 ? (d->head_dim == 128 ? 95 : 65) : (d->head_dim == 128 ? 110 : 90);
+  const int64_t turns = ceil_div(more.slices * workgroups_per_slice, 256), fullest = std::max(more.largest, turns * ceil_div(more.rows, more.slices));
+  return one.largest * 100 <= fullest * percent + 100 * (kStart + (!one.cuts && more.cuts ? kHandOver : 0));
+}
+
 bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
   int32_t n = query_tokens(d);
   if (!runs_on_matrix_cores(d)) return false;
@@ -401,10 +456,12 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   const int64_t most = kTurn * kMatrixWorkgroupsPerCu(2, 64, m->groups) / (d->heads * blocks);
   const int64_t wanted = std::min<int64_t>(ceil_div(kMatrixWorkgroups, d->heads * blocks), std::max<int64_t>(1, at_once / (d->heads * blocks)));
   const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
+  const int64_t whole = pairs * blocks > kTurn ? 0 : (elt_bytes == 2 ? 256 : (d->head_dim == 64 ? 192 : 0));  // see one_per_cu_pays
+  auto cut = [&](int64_t length, int64_t t) { return slices_for(length, t, whole); };
   if (!p.even) {  // the counts are not known: every sequence gets the same number of slices
     if (!sliced) return true;
     int64_t splits = std::min<int64_t>(room / d->batch, states / ((int64_t)d->batch * n));
-    splits = std::min<int64_t>(std::min<int64_t>(splits, blocks > 1 ? kMatrixMaxFieldSlices : 65535), ceil_div(p.max_tokens, kMinSlice));
+    splits = std::min<int64_t>(std::min<int64_t>(splits, blocks > 1 ? kMatrixMaxFieldSlices : 65535), cut(p.max_tokens, kMinSlice));
     if (splits < 1) splits = 1;
     int64_t slice = std::min<int64_t>(ceil_div(ceil_div(p.max_tokens, splits), kSliceGranule) * kSliceGranule, kMaxSlice);
     m->num_splits = (int32_t)ceil_div(p.max_tokens, slice);
@@ -417,44 +474,58 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   int64_t sum = 0;
   for (int32_t b = 0; b < d->batch; ++b) sum += tokens(b);
   // `cap` slices at most, and those of the sequences with several fit the slots
-  auto fits = [&](int64_t t, int64_t cap) {
+  auto fits = [&](int64_t t, int64_t cap, int64_t room_for) {
     int64_t total = 0, in_slots = 0;
     for (int32_t b = 0; b < d->batch; ++b) {
-      const int64_t s = slices_for(tokens(b), t);
+      const int64_t s = cut(tokens(b), t);
       if (s > (blocks > 1 ? kMatrixMaxFieldSlices : kMaxPlanSplits)) return false;
       total += s;
       if (s > 1) in_slots += s;
     }
-    return total <= cap && in_slots * n <= states;
+    return total <= cap && in_slots * n <= room_for;
   };
   int64_t T = std::max<int64_t>(p.max_tokens, 1);
   // smallest slice size from `from` on that fits (the counts fall as it grows); T where none below it does
-  auto smallest_fit = [&](int64_t from, int64_t cap) {
+  auto smallest_fit = [&](int64_t from, int64_t cap, int64_t room_for) {
     int64_t lo = 0, hi = T > from ? ceil_div(T - from, kSliceGranule) : 0;  // in granules above `from`; hi always fits
     while (lo < hi) {
       const int64_t mid = (lo + hi) / 2;
-      if (fits(from + mid * kSliceGranule, cap)) hi = mid;
+      if (fits(from + mid * kSliceGranule, cap, room_for)) hi = mid;
       else lo = mid + 1;
     }
     return std::min(T, from + hi * kSliceGranule);
   };
   if (sliced) {
     if (room >= d->batch) {
-      const int64_t cap = std::min<int64_t>(room, kMaxPlanSlices);
-      T = smallest_fit(std::max<int64_t>(kMinSlice, ceil_div(sum, cap)), cap);
+      auto smallest = [&](int64_t cap, int64_t room_for) { return smallest_fit(std::max<int64_t>(kMinSlice, ceil_div(sum, cap)), cap, room_for); };
+      const int64_t cap = std::min<int64_t>(room, kMaxPlanSlices), fewer = std::min(cap, kTurn / (d->heads * blocks));
+      // (chosen as with the largest workspace the call can use, so that what span_workspace_bytes asks for is enough for the same plan)
+      const int64_t all = most_states(d, p), T_cap = smallest(cap, all), T_fewer = fewer >= d->batch ? smallest(fewer, all) : T_cap;
+      auto cost = [&](int64_t t) {
+        SliceCost c{0, 0, sum, false};
+        for (int32_t b = 0; b < d->batch; ++b) {
+          const int64_t s = cut(tokens(b), t);
+          c.slices += s;
+          c.largest = std::max(c.largest, ceil_div(tokens(b), s));
+          c.cuts = c.cuts || s > 1;
+        }
+        return c;
+      };
+      const bool fewer_pay = T_fewer > T_cap && one_per_cu_pays(d, d->heads * blocks, cost(T_fewer), cost(T_cap));
+      T = smallest(fewer_pay ? fewer : cap, states);
     }
     // as in plan_exact: slices well above the average and large in themselves run in several rounds of smaller ones
     int64_t total = 0, largest = 1;
     for (int32_t b = 0; b < d->batch; ++b) {
-      const int64_t s = slices_for(tokens(b), T);
+      const int64_t s = cut(tokens(b), T);
       total += s;
       largest = std::max(largest, ceil_div(tokens(b), s));
     }
-    if (largest > kLargeSlice && 2 * largest * total > 3 * sum) T = smallest_fit(kLargeSlice, kMaxPlanSlices);
+    if (largest > kLargeSlice && 2 * largest * total > 3 * sum) T = smallest_fit(kLargeSlice, kMaxPlanSlices, states);
   }
   int64_t total = 0, longest = 1, most_s = 1, least_s = kMaxPlanSplits + 1;
   for (int32_t b = 0; b < d->batch; ++b) {
-    const int64_t s = slices_for(tokens(b), T);
+    const int64_t s = cut(tokens(b), T);
     total += s;
     if (s > 1) m->states += s * n;
     most_s = std::max(most_s, s);
@@ -484,7 +555,7 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
     int32_t y = 0;
     for (int pass = 0; pass < 2; ++pass) {
       for (int32_t b = 0; b < d->batch; ++b) {
-        const int64_t s = slices_for(tokens(b), T);
+        const int64_t s = cut(tokens(b), T);
         if ((s > 1) != (pass == 0)) continue;
         for (int64_t i = 0; i < s; ++i) table[y++] = pack_slice((uint32_t)b, (uint32_t)i, (uint32_t)s);
       }
@@ -506,15 +577,15 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
 // In less than two turns of few-query workgroups most CUs hold one, and the hand-over of a slice's states counts as well: as this many
 // rows, which puts the slices of cut sequences ahead of short whole ones.  us in plan order -> dealt by rows alone -> with the hand-over:
 // fp32, 35 x 8 heads x 60..160 positions, 17 tokens 21.1 -> 24.1 -> 21.4; 25 x 8 x ~150 of 64, 3 tokens 9.05 -> 9.63 -> 9.04; bf16, 25 x 16 x 108..216 of
-// 64, two tokens 7.99 -> 8.81 -> 8.38; 41 x 12 x 599..999 fp32 of 64, 47 tokens 95.1 -> 81.3 -> 81.1; 12 x 32 x ~200, 24 tokens 35.1 -> 33.6 -> 33.3; the most it
-// costs: bf16, 14 x 16 x ~600, 13 tokens 21.9 -> 20.7 -> 21.1.  (64 rows do as well but for 30 x 12 x 60..250, 20 tokens, 25.7 -> 26.9 and 25.6 with
-// 128.)  Whole sequences, 63 x 8 x 53..268, fp16, 59 tokens 26.5 -> 23.3; 12 x 40 x 345..1151, bf16, 46 tokens 57.6 -> 50.8.  One-token launches, whose
-// hand-over is a single state, gain nothing by it (geometric mean of 100 shapes 1.000).
+// 64, two tokens 7.99 -> 8.81 -> 8.38; 41 x 12 x 599..999 fp32 of 64, 47 tokens 95.1 -> 81.3 -> 81.1; 12 x 32 x ~200, 24 tokens 35.1 -> 33.6 -> 33.3;
+// the most it costs: bf16, 14 x 16 x ~600, 13 tokens 21.9 -> 20.7 -> 21.1. (64 rows do as well but for 30 x 12 x 60..250, 20 tokens, 25.7 -> 26.9 and
+// 25.6 with 128.) Whole sequences, 63 x 8 x 53..268, fp16, 59 tokens 26.5 -> 23.3; 12 x 40 x 345..1151, bf16, 46 tokens 57.6 -> 50.8. One-token
+// launches, whose hand-over is a single state, gain nothing by it (geometric mean of 100 shapes 1.000).
 constexpr int32_t kHandOverRows = 128;
 // A launch whose plan needs no table carries one where that spares the fullest CU 5 % and this many bytes (its share of 0.6 us; the table's
 // 3 KB of arguments cost 0.35).  us, without -> with: 64 x 12 heads x 60..200 of 64, 16 tokens 10.5 -> 9.65; 8 x 32 x 500..900, two slices each, two
-// tokens 20.0 -> 19.5; 10 x 32 x 300..500, two tokens 16.7 -> 16.2; 64 x 32 x 100..300, one token 35.1 -> 34.4; 60 x 32 x 150..450 of 64, 5 tokens 29.9 -> 29.4.
-// Less to spare is left alone: 64 x 144..168 28.4 with and without; 28 x 160 x 200..900 of 64, 8 tokens 111.3, 108.9 with.
+// tokens 20.0 -> 19.5; 10 x 32 x 300..500, two tokens 16.7 -> 16.2; 64 x 32 x 100..300, one token 35.1 -> 34.4; 60 x 32 x 150..450 of 64, 5 tokens
+// 29.9 -> 29.4. Less to spare is left alone: 64 x 144..168 28.4 with and without; 28 x 160 x 200..900 of 64, 8 tokens 111.3, 108.9 with.
 constexpr int64_t kDealTableBytes = 16384;
 
 void deal_slices(const span_attn_desc_t* d, const TokenCounts& counts, int64_t max_tokens, int32_t total, int32_t hand_over, bool table,

@@ -77,7 +77,8 @@ struct Partition {
   int32_t max_tokens;    // bound on attended positions per sequence
   int32_t total_slices;  // exact: table entries (grid.y); uniform: batch * num_splits
   int32_t queries_per_pass;  // query tokens whose states a slot of the workspace holds (1, 2, 4 or 16)
-  int32_t granule;       // exact: sequence b is cut into ceil(n_b / granule) slices
+  int32_t granule;       // exact: sequence b is cut into ceil(n_b / granule) slices,
+  int32_t whole;         // ... or stays whole up to so many positions
   bool runs;             // the slices' position runs were resolved on the host (RunTables filled)
 };
 

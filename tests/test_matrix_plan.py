@@ -69,3 +69,24 @@ def test_slices_run_at_once(batch, heads, D, dtype, q_len, fit):
     for kw in (dict(tokens_per_seq=tok), dict()):
         got = binding.span_launch_query(binding.make_desc(batch, heads, D, 5000, dtype, 10, 5000, 0, q_len=q_len, **kw))
         assert 0 < got["workgroups"] <= fit, (kw, got)
+
+
+@pytest.mark.parametrize("q_len,dtype,D,batch,heads,positions,slices", [
+    # one or two tokens: up to two batches of rows a wave in one slice, few pairs or many
+    (1, 1, 128, 1, 8, 256, 1), (1, 1, 128, 1, 8, 257, 3), (1, 2, 64, 5, 32, 256, 1), (1, 0, 64, 2, 12, 256, 1), (1, 0, 128, 1, 8, 128, 1),
+    (2, 1, 64, 2, 32, 256, 1), (2, 0, 64, 2, 32, 160, 1), (2, 0, 64, 2, 32, 161, 2),
+    # fp32 rows of 128: slices of 64 where there is room for them
+    (1, 0, 128, 1, 8, 129, 3), (1, 0, 128, 1, 32, 640, 10), (1, 0, 128, 4, 32, 640, 4),
+    # level batches of one workgroup per CU
+    (1, 1, 128, 8, 32, 768, 1), (1, 1, 128, 8, 32, 769, 2), (1, 1, 64, 8, 32, 384, 1), (1, 1, 64, 8, 32, 385, 2), (1, 1, 128, 7, 32, 700, 2),
+    # a few tokens: whole up to three or four tiles, then one workgroup per CU at most
+    (4, 1, 128, 3, 32, 256, 1), (16, 2, 64, 5, 32, 256, 1), (4, 0, 64, 2, 32, 192, 1), (4, 0, 64, 2, 32, 193, 2), (4, 0, 128, 2, 32, 129, 2),
+    (16, 1, 128, 8, 32, 512, 1), (16, 1, 128, 8, 32, 513, 2), (4, 1, 128, 3, 32, 512, 2), (4, 1, 128, 3, 32, 800, 5),
+])
+def test_where_sequences_are_cut(q_len, dtype, D, batch, heads, positions, slices):
+    """The rules for short sequences and for one workgroup per CU, at their lines; the workspace follows."""
+    tok = np.full(batch, positions, np.int64)
+    d = binding.make_desc(batch, heads, D, positions, dtype, batch, positions, 0, tokens_per_seq=tok, q_len=q_len)
+    assert binding.span_launch_query(d)["max_splits"] == slices
+    if q_len < 3:
+        assert (binding.span_workspace_bytes(d) == 0) == (slices == 1)
