@@ -332,17 +332,16 @@ __device__ __forceinline__ float group_allreduce_sum(float x) {
   return x;
 }
 
-// Inclusive prefix sum over the 64 lanes.
-__device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
+// Inclusive prefix sum over the 64 lanes.  The rows of 16 are joined by the broadcasts of their last lanes: with a readlane and a select for each
+// row, here and in wave_inclusive_max, a scan was some ten instructions longer, in the serial chain ahead of the first rows.  us: 5 x 16 heads x
+// ~5000 positions 10.2 -> 10.0; 3 x 12 x ~130 4.97 -> 4.85; 3 x 5 x ~400, 27 tokens 6.12 -> 5.96; 1.006 times over 72 shapes of small calls.
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
   x += dpp_i<0x111>(x);  // row_shr:1   (lanes without a source inside their row of 16 add 0)
   x += dpp_i<0x112>(x);  // row_shr:2
   x += dpp_i<0x114>(x);  // row_shr:4
   x += dpp_i<0x118>(x);  // row_shr:8
-  const int t0 = __builtin_amdgcn_readlane(x, 15);
-  const int t1 = __builtin_amdgcn_readlane(x, 31);
-  const int t2 = __builtin_amdgcn_readlane(x, 47);
-  const int row = lane >> 4;
-  x += (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15, rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31, rows 2 and 3
   return x;
 }
 
@@ -562,7 +561,7 @@ __device__ __forceinline__ int count_positions(const LaunchArgs& a, Intervals& i
     iv.st0 = a.starts[iv.first + lane];
     iv.len0 = clampi(a.ends[iv.first + lane] - iv.st0, 0, a.max_len);
   }
-  iv.incl0 = wave_inclusive_scan(iv.len0, lane);
+  iv.incl0 = wave_inclusive_scan(iv.len0);
   int n = __builtin_amdgcn_readlane(iv.incl0, 63);
   if (__builtin_expect(iv.count > 64, 0)) {
     const int chunks = (iv.count + 63) / 64;
@@ -578,7 +577,7 @@ __device__ __forceinline__ int count_positions(const LaunchArgs& a, Intervals& i
       }
 #pragma unroll
       for (int k = 0; k < kInFlight; ++k) {
-        const int total = __builtin_amdgcn_readlane(wave_inclusive_scan(len[k], lane), 63);
+        const int total = __builtin_amdgcn_readlane(wave_inclusive_scan(len[k]), 63);
         mine += total;
         if (lane == 0 && c + k * kWavesPerBlock < min(chunks, kChunkTotals)) tab.total[c + k * kWavesPerBlock] = total;
       }
@@ -630,16 +629,13 @@ __device__ __forceinline__ void wave_lds_order() {
 }
 
 // Inclusive maximum over the lanes up to each, all values >= 0.
-__device__ __forceinline__ int wave_inclusive_max(int x, int lane) {
+__device__ __forceinline__ int wave_inclusive_max(int x) {
   x = max(x, dpp_i<0x111>(x));
   x = max(x, dpp_i<0x112>(x));
   x = max(x, dpp_i<0x114>(x));
   x = max(x, dpp_i<0x118>(x));
-  const int t0 = __builtin_amdgcn_readlane(x, 15);
-  const int t1 = max(t0, __builtin_amdgcn_readlane(x, 31));
-  const int t2 = max(t1, __builtin_amdgcn_readlane(x, 47));
-  const int row = lane >> 4;
-  return max(x, row == 0 ? 0 : (row == 1 ? t0 : (row == 2 ? t1 : t2)));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // as above; 0 is the neutral element
+  return max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
 }
 
 // Cache positions of the wave's first rows 0 .. wn - 1 into `pos` for a list of up to 64 intervals, which are still in
@@ -672,7 +668,7 @@ __device__ __forceinline__ void tabulate_short(const LaunchArgs& a, const Interv
     for (int k = 0; k < 2; ++k) m[k] = pos[r0 + 64 * k + lane];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      m[k] = max(wave_inclusive_max(m[k], lane), carry);
+      m[k] = max(wave_inclusive_max(m[k]), carry);
       carry = __builtin_amdgcn_readlane(m[k], 63);
     }
 #pragma unroll
@@ -696,7 +692,7 @@ __device__ __forceinline__ void tabulate_positions(const LaunchArgs& a, const In
   if (iv.count > 64) {    // skip the chunks before the window
     const int known = min((iv.count + 63) / 64, kChunkTotals);
     for (int t0 = 0; t0 < known; t0 += 64) {
-      const int incl = wave_inclusive_scan(t0 + lane < known ? tab.total[t0 + lane] : 0, lane);
+      const int incl = wave_inclusive_scan(t0 + lane < known ? tab.total[t0 + lane] : 0);
       const int skip = __popcll(__builtin_amdgcn_ballot_w64(t0 + lane < known && carry + incl <= vbeg));
       if (skip > 0) carry += __builtin_amdgcn_readlane(incl, skip - 1);
       c0 = (t0 + skip) * 64;
@@ -713,7 +709,7 @@ __device__ __forceinline__ void tabulate_positions(const LaunchArgs& a, const In
   };
   load_chunk(c0);
   while (c0 < iv.count) {
-    const int incl = wave_inclusive_scan(len, lane), chunk_total = __builtin_amdgcn_readlane(incl, 63);
+    const int incl = wave_inclusive_scan(len), chunk_total = __builtin_amdgcn_readlane(incl, 63);
     const int here = c0, here_carry = carry, here_st = st, here_len = len;
     c0 += 64;
     carry += chunk_total;
