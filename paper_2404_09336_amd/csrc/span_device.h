@@ -54,6 +54,7 @@ struct LaunchArgs {
   int32_t even;                     // > 0: a sequence's slices share its own token count evenly, `even` positions each at least; 0: slice_tokens each
   int32_t entry_bits;               // table mode: Deal::b_bits | n_bits << 8 | dealt << 16
   int32_t counter_stride;
+  int32_t intervals_per_seq;        // mean, in 65536ths, for list_window; -1: no window
   int32_t interleave;               // 1: rows dealt to the waves round-robin (large slices); 0: contiguous quarters
 #ifdef SPAN_PHASE_TRACE
   unsigned long long* trace;        // diagnostic build only: [trace_workgroups, kTraceStamps] times of the phases, or null
@@ -529,7 +530,7 @@ __device__ __forceinline__ int slice_size(const LaunchArgs& a, int n, int parts)
 // ---- the interval list of a sequence -----------------------------------------------------------------
 struct Intervals {
   int count, first;     // intervals first .. first + count - 1 of the lists (scalar)
-  int st0, len0, incl0; // this lane's interval of the first 64: start, length, inclusive prefix sum of the lengths
+  int st0, len0, incl0; // this lane's interval of the first 64: start, length (0: none), inclusive prefix sum of the lengths
 };
 constexpr int kChunkTotals = 256;  // chunks of 64 intervals whose position counts are kept (16384 intervals)
 struct IntervalTables {  // LDS of a workgroup
@@ -548,7 +549,43 @@ __device__ __forceinline__ Intervals interval_range(const LaunchArgs& a, const S
 
 __device__ __forceinline__ int interval_length(const LaunchArgs& a, int i) { return clampi(a.ends[i] - a.starts[i], 0, a.max_len); }
 
-// Positions of the sequence's list; fills the first chunk's lane values.  Called by all waves of the workgroup.
+// 64 intervals of the lists around where sequence b's would be if all sequences had as many, fetched next to its range instead of after it:
+// a trip to memory less at the head of the call wherever they hold all of the sequence's.  Few-query kernel only: us, lists fetched after their range ->
+// so: 15 x 32 heads x ~170, 56 tokens 19.5 -> 18.7; 33 x 8 x 1849, 39 tokens 30.1 -> 29.3; 12 x 32 x ~450, 34 tokens 27.4 -> 26.7; 9 x 5 x ~150 fp32, 22
+// tokens 10.7 -> 10.4.  One-token calls gain nothing by it (their longer lists lose 1 %: the wave fetches twice).  Lists of a
+// mean beyond the window do without; they lose up to 1 % in the few-query kernel (8 x 12 x ~8900, 2200 intervals each, 19 tokens 87.9 -> 88.6).
+constexpr int kNoWindow = 0x7fffffff - 64;  // first of a window that holds nothing
+struct ListWindow {
+  int first;       // number of lane 0's interval (scalar)
+  int start, end;  // this lane's
+};
+__device__ __forceinline__ ListWindow list_window(const LaunchArgs& a, int b, int lane) {
+  const bool none = a.intervals_per_seq < 0;
+  const int centre = (b * a.intervals_per_seq + (a.intervals_per_seq >> 1)) >> 16;
+  ListWindow w = {none ? kNoWindow : clampi(centre - 32, 0, max(a.num_intervals - 64, 0)), 0, 0};
+  if (w.first + lane < a.num_intervals) {
+    w.start = a.starts[w.first + lane];
+    w.end = a.ends[w.first + lane];
+  }
+  return w;
+}
+
+// The sequence's first 64 intervals into the lanes: one each from lane 0 on ...
+__device__ __forceinline__ void fetch_first(const LaunchArgs& a, Intervals& iv, int lane) {
+  if (lane < iv.count) {
+    iv.st0 = a.starts[iv.first + lane];
+    iv.len0 = clampi(a.ends[iv.first + lane] - iv.st0, 0, a.max_len);
+  }
+}
+// ... or where the window has them, with lanes of no length around them.
+__device__ __forceinline__ void fetch_first(const LaunchArgs& a, Intervals& iv, const ListWindow& window, int lane) {
+  const int ahead = iv.first - window.first;
+  if (__builtin_expect(ahead < 0 || ahead + iv.count > 64, 0)) return fetch_first(a, iv, lane);
+  iv.st0 = window.start;
+  iv.len0 = (uint32_t)(lane - ahead) < (uint32_t)iv.count ? clampi(window.end - window.start, 0, a.max_len) : 0;
+}
+
+// Positions of the sequence's list, whose first intervals are in the lanes (fetch_first).  Called by all waves of the workgroup.
 // Up to 64 intervals every wave counts for itself and no barrier is met.  Longer lists (a mask in which every token
 // decides for itself has an interval per four positions) are a chain of dependent trips to memory if walked chunk by
 // chunk, and nothing hides them when few workgroups run: the waves share the chunks, four in flight each, and leave the
@@ -557,10 +594,6 @@ __device__ __forceinline__ int interval_length(const LaunchArgs& a, int i) { ret
 // the rows): no change.  The long walk is kept out of the straight path: code that is jumped over costs a call of few
 // workgroups 0.2 - 0.4 us of instruction fetch.
 __device__ __forceinline__ int count_positions(const LaunchArgs& a, Intervals& iv, int wave, int lane, IntervalTables& tab) {
-  if (lane < iv.count) {
-    iv.st0 = a.starts[iv.first + lane];
-    iv.len0 = clampi(a.ends[iv.first + lane] - iv.st0, 0, a.max_len);
-  }
   iv.incl0 = wave_inclusive_scan(iv.len0);
   int n = __builtin_amdgcn_readlane(iv.incl0, 63);
   if (__builtin_expect(iv.count > 64, 0)) {

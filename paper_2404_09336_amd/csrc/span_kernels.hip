@@ -147,6 +147,7 @@ decode_kernel(const Args a) {
   } else {
     intervals = interval_range(a, words);
     SPAN_STAMP_AFTER(10, "s", intervals.count);
+    fetch_first(a, intervals, lane);
     n_total = count_positions(a, intervals, wave, lane, s_tab);
   }
   n_total = n_total < a.max_tokens ? n_total : a.max_tokens;
@@ -769,6 +770,8 @@ int launch(const span_attn_desc_t* d, const void* q, const void* k, const void* 
   a.heads = d->heads;
   a.max_len = d->max_len;
   a.num_intervals = d->num_intervals;
+  // (a mean beyond the window's 64 would be fetched for nothing, and the kernel multiplies it by the batch in 31 bits)
+  a.intervals_per_seq = d->num_intervals <= 0x7fff && d->num_intervals <= 64 * (int64_t)d->batch ? d->num_intervals * 65536 / d->batch : -1;
   a.slice_tokens = p.slice_tokens;
   a.num_splits = p.num_splits;
   a.max_tokens = p.max_tokens;

@@ -203,6 +203,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   auto qrow = [&](int j) { return ((size_t)b * a.q_len + (size_t)(q0 + min(j, nq_here - 1))) * heads + h; };
 
   SequenceWords words = sequence_words<false>(a, b);
+  const ListWindow window = list_window(a, b, lane);
   // q goes to LDS (the same for the four waves).  It is fetched here, as are the append form's new rows for the cache
   // (written by the first slice's workgroup, whatever the span holds); both have arrived when the rows' positions are known.
   constexpr int kQLoads = (NQ * kPieces + kThreads - 1) / kThreads;
@@ -237,6 +238,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
 
   Intervals intervals = interval_range(a, words);
   SPAN_STAMP_AFTER(10, "s", intervals.count);
+  fetch_first(a, intervals, window, lane);
   int n_total = count_positions(a, intervals, wave, lane, s_u.st.tab);
   n_total = n_total < a.max_tokens ? n_total : a.max_tokens;
   const int T = slice_size(a, n_total, nsl);
