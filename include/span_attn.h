@@ -80,7 +80,8 @@ typedef struct span_attn_desc {
                               dropped; memory safety does not depend on it.  Ignored when
                               num_splits > 0 or batch > 1024.                                    */
   void* workspace;         /* device, 256-byte aligned, >= span_workspace_bytes(); may be NULL
-                              when that is 0.  Its leading ticket counters must be zero before the
+                              when that is 0.  Its leading ticket counters (the first
+                              4 * batch * heads bytes, rounded up to 256) must be zero before the
                               first call that uses it (span_workspace_init, or zero the buffer);
                               every call leaves them zero again.  Two calls that may overlap in
                               time must not share a workspace.  Few-query calls of three and more

@@ -356,7 +356,7 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
 // per head of 12 heads are 516: us, 43 -> 42: 8 x 12 x ~1800 positions fp32, 6 tokens 54.8 -> 42.3; 24 x 5 x ~1700 fp16, 46 tokens 58.3 -> 49.8; 4 x
 // 12 x 300..2800 fp32, 4 tokens 23.5 -> 22.2), but one slice per sequence at least and 1024, 768 or 512 workgroups at most for 16, 32 or 64 tokens a
 // workgroup (one resident round of rows of 64; fp32 rows of 128, and 16-bit ones of more than 16 tokens, run two a CU and take up to two): of 256,
-// 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 shapes; more only pays for itself in partial states, which grow with the
+// 512, 768 and 1024, 512 is within 3 % of the best or the best at 18 of 20 larger shapes (for smaller ones see one_per_cu_pays); more only pays for itself in partial states, which grow with the
 // tokens (batch 16 x ~700, 32 tokens, 16 slices per head against 32: 50.4 and 59.3 us). The slices have to fit the workspace's token states, so
 // sequences that stay in one slice, which need no state, come after the others in the table. Groups. A workgroup that serves all tokens reads every
 // row once; where the batch has too few (batch, head) pairs to fill the chip that way (fewer than 128 workgroups before slicing), several workgroups

@@ -22,7 +22,7 @@
 //   * one 64-lane buffer load fetches 1 KiB = whole rows: D*sizeof(elt)/16 lanes per row, each lane a
 //     128-bit piece, non-temporal.  The q.k dot product is finished with DPP adds inside those lanes;
 //     every row group of a wavefront carries its own online-softmax state (m, l, acc), merged by
-//     log-sum-exp at the end: first across row groups (shuffles), then across wavefronts (LDS), then
+//     log-sum-exp at the end: first across row groups (lane exchanges), then across wavefronts (LDS), then
 //     - only if the (batch, head) pair has more than one slice - across slices: every workgroup
 //     publishes its state and takes a ticket; the one that arrives last for its pair merges them all,
 //     so the whole call is a single launch.
