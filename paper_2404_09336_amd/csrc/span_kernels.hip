@@ -465,11 +465,12 @@ decode_kernel(const Args a) {
   }  // cnt > 0
   SPAN_STAMP_AFTER(5, "v", o[0]);
 
-  // Output column t of an un-normalised state.
+  // Output column t of an un-normalised state.  (A sum that is NaN, of a visible row whose score is NaN or +Inf, is none of an empty one's: it
+  // reaches the output, here and through the slices below, however the sequence is cut.)
   auto store_rows = [&](const float* ll, const float* oo) {
 #pragma unroll
     for (int j = 0; j < NQ; ++j) {
-      a.out[qrow(j) * D + t] = ll[j] > 0.f ? oo[j] / ll[j] : 0.f;
+      a.out[qrow(j) * D + t] = ll[j] != 0.f ? oo[j] / ll[j] : 0.f;
     }
   };
 
@@ -540,7 +541,7 @@ decode_kernel(const Args a) {
         }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
-          if (s0 + k * kGroups < nsl && ml[k][1] > 0.f) {  // (the slot of an empty slice is never written)
+          if (s0 + k * kGroups < nsl && ml[k][1] != 0.f) {  // (an empty slice's sums are never written)
             const float oo2[4] = {lo[k][0], lo[k][1], hi[k][0], hi[k][1]};
             merge_state(mm, ll, oo, 4, ml[k][0], ml[k][1], oo2);
           }
