@@ -87,8 +87,9 @@ typedef struct span_attn_desc {
                               time must not share a workspace.  Few-query calls of three and more
                               tokens also take what span_workspace_bytes() gives for any other
                               such q_len of the shape, and then cut the spans into fewer slices
-                              if it is less than their own; one-token calls planned from a
-                              bound alone (max_tokens, no counts) cut coarser slices likewise.   */
+                              if it is less than their own; one- and two-token calls cut coarser
+                              slices likewise (one-token calls planned from a bound alone,
+                              short sequences).                                                  */
   size_t workspace_bytes;
   void* stream;            /* hipStream_t; NULL = the default stream                             */
   int32_t q_len;           /* query tokens per sequence: 0 or 1 for every entry point but

@@ -123,14 +123,28 @@ static int64_t whole_up_to(const span_attn_desc_t* d) {
   return 256;
 }
 
-static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq, int64_t max_tok, Partition* p,
+// One token: a level batch of at least one workgroup per CU is not sliced up to so many positions (see plan_exact).
+static int64_t level_up_to(const span_attn_desc_t* d) {
+  const int64_t pairs = (int64_t)d->batch * d->heads;
+  if (query_tokens(d) != 1 || pairs < kUnsplitFromPairs / 2) return 0;
+  return d->dtype != SPAN_F32 && d->head_dim == 64 ? pairs * 3 / 2 : 768;
+}
+
+// Up to so many positions no sequence is sliced, under these rules.
+static int64_t unsliced_up_to(const span_attn_desc_t* d, ShortRules rules) {
+  if (rules == ShortRules::kApplied) return whole_up_to(d);
+  return rules == ShortRules::kWhole && (int64_t)d->batch * d->heads < kUnsplitFromPairs ? level_up_to(d) : 0;
+}
+
+static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq, int64_t max_tok, ShortRules rules, Partition* p,
                        uint32_t* table) {
   if (!tokens_per_seq || d->num_splits != 0 || d->batch > kMaxPlanBatch) return false;
   auto tokens = [&](int32_t b) {
     const int64_t n = tokens_per_seq[b];
     return n < 0 ? (int64_t)0 : (n > max_tok ? max_tok : n);
   };
-  const int64_t whole = whole_up_to(d);
+  const bool short_rules = rules == ShortRules::kApplied;
+  const int64_t whole = unsliced_up_to(d, rules);
   auto cut = [&](int64_t n, int64_t T) { return slices_for(n, T, whole); };
   auto count = [&](int64_t T) {
     int64_t c = 0;
@@ -145,7 +159,7 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   int64_t room = slice_room(d);  // slices (per head) the call aims at, at most one resident round
   if (room > kMaxPlanSlices) room = kMaxPlanSlices;
   int64_t T = ceil_div(sum, room);
-  if (T < kMinSlice) T = fine_slices(d) && count(kFineSlice) <= room ? kFineSlice : kMinSlice;
+  if (T < kMinSlice) T = short_rules && fine_slices(d) && count(kFineSlice) <= room ? kFineSlice : kMinSlice;
   int64_t total = count(T);
   // A quarter of the chip's wavefront slots (512 workgroups) already keeps the memory system busy, and a
   // pair that is one workgroup needs no partial states and no tickets.  So a batch of at least 512 (batch,
@@ -157,9 +171,8 @@ static bool plan_exact(const span_attn_desc_t* d, const int64_t* tokens_per_seq,
   // -> 27.9; fp32: 256 x 700 33.0 -> 32.6, x 1000 49.7 -> 52.9; fp16 of 64: 256 x 320 8.6 -> 7.4, x 448 9.95 -> 10.15; 320 x 448 11.1 -> 10.6, x 700
   // 14.7 -> 14.9; 448 x 448 13.6 -> 11.6.
   const int64_t pairs = (int64_t)d->batch * d->heads;
-  const int64_t short_up_to = d->dtype != SPAN_F32 && d->head_dim == 64 ? pairs * 3 / 2 : 768;
   const bool level = (pairs >= kUnsplitFromPairs && longest * 100 * d->batch <= 135 * sum) ||
-                     (pairs >= kUnsplitFromPairs / 2 && query_tokens(d) == 1 && longest <= short_up_to && longest * 100 * d->batch <= 108 * sum);
+                     (short_rules && longest <= level_up_to(d) && longest * 100 * d->batch <= 108 * sum);
   if (room < d->batch || level) {  // whole sequences (batch * heads alone exceeds a round, or a level batch)
     T = max_tok > 0 ? max_tok : 1;
     total = count(T);
@@ -302,10 +315,10 @@ static bool plan_runs(const span_attn_desc_t* d, const int64_t* tokens_per_seq, 
 // sequences whose spans come near the bound, fp16: 4 x 32 x 3000..3100 36.8 -> 38.7, 8 x 16 x 3000..3200 37.3 -> 39.3, 8 x 32 x 1500..1600 35.7 -> 36.5;
 // with more they do not (9 x 32 x 1500..1600 41.8, 45.3 in three slices).  It costs small batches far below their bound what it gains large
 // ones: 8 x 32 x 5..50 % of 2000..16000 64.3, 44.7 if cut, 4 x 32 x 5..50 % of 4000..16000 35.9 and 29.3.
-Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans) {
+Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans, ShortRules rules) {
   const int64_t max_tok = (d->max_tokens > 0 && d->max_tokens < d->max_len) ? d->max_tokens : d->max_len;
   Partition p;
-  if (plan_exact(d, counts.of, max_tok, &p, table)) {
+  if (plan_exact(d, counts.of, max_tok, rules, &p, table)) {
     // Run mode is used where the launch carries a slice table anyway (sequences with different numbers of slices):
     // kernel arguments of that size cost a few tenths of a microsecond per launch, which a batch that needs no
     // table would pay on top (measured: batch 64 x 155 positions, one slice each, 27.7 -> 27.9 us with runs).  Against the table and the
@@ -321,8 +334,8 @@ Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, u
     const int64_t in_round = target_workgroups(d) / d->heads / d->batch;
     while (splits > 0 && splits < in_round && ceil_div(max_tok, splits) > kBoundSlice) ++splits;
   }
-  const int64_t fine = slices_for(max_tok, kFineSlice, whole_up_to(d));
-  const int64_t most = fine_slices(d) && fine <= splits ? fine : slices_for(max_tok, kMinSlice, whole_up_to(d));
+  const int64_t whole = unsliced_up_to(d, rules), fine = slices_for(max_tok, kFineSlice, whole);
+  const int64_t most = rules == ShortRules::kApplied && fine_slices(d) && fine <= splits ? fine : slices_for(max_tok, kMinSlice, whole);
   if (d->num_splits == 0 && splits > most) splits = most;
   if (splits > max_tok) splits = max_tok;
   if (splits < 1) splits = 1;
@@ -712,8 +725,17 @@ size_t workspace_bytes_for(const span_attn_desc_t* d, int64_t states) {
 size_t workspace_least_bytes(const span_attn_desc_t* d, const Partition& p) { return workspace_bytes_for(d, least_states(p)); }
 
 Partition plan_for_workspace(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans) {
-  const Partition p = plan_partition(d, counts, table, runs, spans);
-  return spans && workspace_least_bytes(d, p) > d->workspace_bytes ? plan_partition(d, counts, table, runs, false) : p;
+  auto fits = [&](const Partition& p) { return workspace_least_bytes(d, p) <= d->workspace_bytes; };
+  Partition p = plan_partition(d, counts, table, runs, spans);
+  if (fits(p)) return p;
+  for (const ShortRules rules : {ShortRules::kApplied, ShortRules::kNone, ShortRules::kWhole}) {
+    for (const bool finer : {true, false}) {
+      if (finer && (!spans || rules == ShortRules::kApplied)) continue;  // (is the other one, or the first plan)
+      p = plan_partition(d, counts, table, runs, finer, rules);
+      if (fits(p)) return p;
+    }
+  }
+  return p;  // (refused: the last is the least demanding)
 }
 
 size_t workspace_bytes(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p) {

@@ -96,15 +96,23 @@ struct TokenCounts {
   int64_t counted_[kMaxPlanBatch];
 };
 
+// The planner's rules for short sequences of one and two tokens: whole up to some length, fp32 rows of 128 in half-size slices, short level batches not
+// sliced.  kNone is the cut without them, which a workspace sized for longer sequences of the same shape holds where it does not hold half-size
+// slices (1 x 32 heads: 266496 bytes for 1000 positions, 150016 for 1025; in slices of kMinSlice 133376 for 1000).  kWhole is for 256 to 511 pairs, where a
+// level batch asks for no workspace at all: every sequence up to that length is then left whole.
+enum class ShortRules { kApplied, kNone, kWhole };
+
 // Fills `table` (kMaxPlanSlices entries) when the partition is exact; table may be null to only size it.
 // `spans`: may be the span form, whose slices of one token are cut finer where only a bound is known (false: the dense entry points, and
 // where a workspace does not hold the finer cut).  A descriptor without intervals is a dense call's to every function.
 // With `runs` given (span form only) and host copies of the span lists in the descriptor, tries run mode first.
-Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans);
+Partition plan_partition(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans,
+                         ShortRules rules = ShortRules::kApplied);
 inline Partition plan_partition(const span_attn_desc_t* d, uint32_t* table = nullptr, RunTables* runs = nullptr, bool spans = true) {
   return plan_partition(d, TokenCounts(d), table, runs, spans);
 }
-// The same with the descriptor's workspace: where it does not hold the finer cut of a bound it holds, as ever, the coarser one.
+// The same with the descriptor's workspace: where it does not hold the plan, as ever, the first coarser cut that it holds (not from a bound's finer one, by
+// kNone, by kWhole).
 Partition plan_for_workspace(const span_attn_desc_t* d, const TokenCounts& counts, uint32_t* table, RunTables* runs, bool spans);
 
 // How a few-query call runs on the matrix cores (span_matrix.hip).  The workspace holds partial states of query tokens: at
