@@ -438,7 +438,7 @@ static bool one_per_cu_pays(const span_attn_desc_t* d, int64_t workgroups_per_sl
   return one.largest * 100 <= fullest * percent + 100 * (kStart + (!one.cuts && more.cuts ? kHandOver : 0));
 }
 
-bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
+bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table, bool two_per_cu) {
   int32_t n = query_tokens(d);
   if (!runs_on_matrix_cores(d)) return false;
   const bool sliced = p.num_splits > 1;
@@ -467,9 +467,9 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   const int64_t blocks = blocks_for(m->groups);
   const int64_t at_once = (int64_t)kTurn * kMatrixWorkgroupsPerCu(elt_bytes, d->head_dim, m->groups);
   const int64_t most = kTurn * kMatrixWorkgroupsPerCu(2, 64, m->groups) / (d->heads * blocks);
-  const int64_t wanted = std::min<int64_t>(ceil_div(kMatrixWorkgroups, d->heads * blocks), std::max<int64_t>(1, at_once / (d->heads * blocks)));
+  const int64_t wanted = std::min<int64_t>(ceil_div(kMatrixWorkgroups, d->heads * blocks), two_per_cu ? most : std::max<int64_t>(1, at_once / (d->heads * blocks)));
   const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
-  const int64_t whole = pairs * blocks > kTurn ? 0 : (elt_bytes == 2 ? 256 : (d->head_dim == 64 ? 192 : 0));  // see one_per_cu_pays
+  const int64_t whole = two_per_cu || pairs * blocks > kTurn ? 0 : (elt_bytes == 2 ? 256 : (d->head_dim == 64 ? 192 : 0));  // see one_per_cu_pays
   auto cut = [&](int64_t length, int64_t t) { return slices_for(length, t, whole); };
   if (!p.even) {  // the counts are not known: every sequence gets the same number of slices
     if (!sliced) return true;
@@ -524,7 +524,7 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
         }
         return c;
       };
-      const bool fewer_pay = T_fewer > T_cap && one_per_cu_pays(d, d->heads * blocks, cost(T_fewer), cost(T_cap));
+      const bool fewer_pay = !two_per_cu && T_fewer > T_cap && one_per_cu_pays(d, d->heads * blocks, cost(T_fewer), cost(T_cap));
       T = smallest(fewer_pay ? fewer : cap, states);
     }
     // as in plan_exact: slices well above the average and large in themselves run in several rounds of smaller ones
@@ -741,10 +741,11 @@ Partition plan_for_workspace(const span_attn_desc_t* d, const TokenCounts& count
 size_t workspace_bytes(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p) {
   int64_t states = least_states(p);
   const int64_t most = most_states(d, p);
-  if (most > states) {  // (a few-query call whose pool may be larger: as much as its plan uses)
+  if (most > states) {  // (a few-query call whose pool may be larger: as much as its plan uses, or the cut that holds shorter calls of the shape)
     MatrixPlan m;
     uint32_t table[kMaxPlanSlices];
-    if (plan_matrix(d, counts, p, most, &m, table)) states = std::max(states, m.states);
+    for (const bool two_per_cu : {false, true})
+      if (plan_matrix(d, counts, p, most, &m, table, two_per_cu)) states = std::max(states, m.states);
   }
   return workspace_bytes_for(d, states);
 }

@@ -141,8 +141,11 @@ bool runs_on_matrix_cores(const span_attn_desc_t* d);
 int64_t least_states(const Partition& p);                             // token states per head a call must bring
 int64_t most_states(const span_attn_desc_t* d, const Partition& p);   // ... it can use
 // False if the call does not run on the matrix cores.  `p` is the call's partition, `states` what the workspace holds per
-// head (least_states at least), `table` has kMaxPlanSlices entries.
-bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table);
+// head (least_states at least), `table` has kMaxPlanSlices entries.  `two_per_cu`: 512 workgroups whatever fewer would gain, no sequence whole for being
+// short; not for a launch, but what a workspace is asked for at least: a shorter call of the shape may want more slices (3 x 5 heads of 64, 16 bits, 3
+// tokens, level: 253696 bytes hold the plan for 3013 positions, 285440 also that for 2061).
+bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table,
+                 bool two_per_cu = false);
 inline bool plan_matrix(const span_attn_desc_t* d, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table) {
   return plan_matrix(d, TokenCounts(d), p, states, m, table);
 }

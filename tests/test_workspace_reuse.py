@@ -63,6 +63,15 @@ def test_lengths_around_what_stays_whole(batch, dtype, D, longest, shortest):
     assert gave_way > 0
 
 
+@pytest.mark.parametrize("batch,heads,D,dtype,longest,n", [(3, 5, 64, 1, 3013, 2061), (6, 2, 128, 0, 3498, 2591)])
+def test_shorter_few_query_calls(batch, heads, D, dtype, longest, n):
+    """Three tokens: what the plan for fewer positions must bring at least is in what a longer level call asks for, though that launches fewer slices."""
+    desc = lambda n: binding.make_desc(batch, heads, D, 8000, dtype, 10, n, 0, tokens_per_seq=np.full(batch, n, np.int64), q_len=3)  # noqa: E731
+    plan = binding.span_plan_query(desc(n))
+    states = plan["workgroups"] * plan["queries_per_pass"]
+    assert plan["max_splits"] > 1 and 256 + (8 * states + 255) // 256 * 256 + 4 * D * states <= binding.span_workspace_bytes(desc(longest))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("batch,heads,dtype,lengths,size", [(1, 32, "f32", [1000], 150016), (8, 32, "f16", [700, 100, 650, 3, 512, 256, 257, 700], 0)])
 def test_outputs_in_a_smaller_workspace(batch, heads, dtype, lengths, size, gpu_device):
