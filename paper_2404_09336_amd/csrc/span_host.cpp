@@ -428,14 +428,20 @@ struct SliceCost {
   int64_t slices, largest, rows;  // slices, positions of the largest, positions of all
   bool cuts;                      // some sequence has several
 };
+constexpr int64_t kOnePerCuFrom = 160;  // workgroups
+constexpr int64_t kOnePerCuWholeUpTo = 512, kOnePerCuSliceUpTo = 384;  // positions
 static bool one_per_cu_pays(const span_attn_desc_t* d, int64_t workgroups_per_slice, const SliceCost& one, const SliceCost& more) {
-  constexpr int64_t kFrom = 160;  // workgroups
-  constexpr int64_t kWholeUpTo = 512, kSliceUpTo = 384, kStart = 64, kHandOver = 64;  // positions
-  if (one.largest > (one.cuts ? kSliceUpTo : kWholeUpTo) || one.slices * workgroups_per_slice < kFrom) return false;
+  constexpr int64_t kStart = 64, kHandOver = 64;  // positions
+  if (one.largest > (one.cuts ? kOnePerCuSliceUpTo : kOnePerCuWholeUpTo) || one.slices * workgroups_per_slice < kOnePerCuFrom) return false;
   if (one.cuts && d->dtype == SPAN_F32 && d->head_dim == 64) return false;
   const int64_t percent = d->dtype == SPAN_F32 ? (d->head_dim == 128 ? 95 : 65) : (d->head_dim == 128 ? 110 : 90);
   const int64_t turns = ceil_div(more.slices * workgroups_per_slice, 256), fullest = std::max(more.largest, turns * ceil_div(more.rows, more.slices));
   return one.largest * 100 <= fullest * percent + 100 * (kStart + (!one.cuts && more.cuts ? kHandOver : 0));
+}
+
+// False if no plan of up to `most_slices` slices could: known from the lengths alone, without looking for its slices.
+static bool one_per_cu_may_pay(int64_t workgroups_per_slice, int64_t most_slices, int64_t longest, int64_t rows) {
+  return most_slices * workgroups_per_slice >= kOnePerCuFrom && (longest <= kOnePerCuWholeUpTo || ceil_div(rows, most_slices) <= kOnePerCuSliceUpTo);
 }
 
 bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Partition& p, int64_t states, MatrixPlan* m, uint32_t* table, bool two_per_cu) {
@@ -470,11 +476,10 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   const int64_t wanted = std::min<int64_t>(ceil_div(kMatrixWorkgroups, d->heads * blocks), two_per_cu ? most : std::max<int64_t>(1, at_once / (d->heads * blocks)));
   const int64_t room = std::max<int64_t>(1, std::min(std::max<int64_t>(wanted, d->batch), most));
   const int64_t whole = two_per_cu || pairs * blocks > kTurn ? 0 : (elt_bytes == 2 ? 256 : (d->head_dim == 64 ? 192 : 0));  // see one_per_cu_pays
-  auto cut = [&](int64_t length, int64_t t) { return slices_for(length, t, whole); };
   if (!p.even) {  // the counts are not known: every sequence gets the same number of slices
     if (!sliced) return true;
     int64_t splits = std::min<int64_t>(room / d->batch, states / ((int64_t)d->batch * n));
-    splits = std::min<int64_t>(std::min<int64_t>(splits, blocks > 1 ? kMatrixMaxFieldSlices : 65535), cut(p.max_tokens, kMinSlice));
+    splits = std::min<int64_t>(std::min<int64_t>(splits, blocks > 1 ? kMatrixMaxFieldSlices : 65535), slices_for(p.max_tokens, kMinSlice, whole));
     if (splits < 1) splits = 1;
     int64_t slice = std::min<int64_t>(ceil_div(ceil_div(p.max_tokens, splits), kSliceGranule) * kSliceGranule, kMaxSlice);
     m->num_splits = (int32_t)ceil_div(p.max_tokens, slice);
@@ -483,15 +488,24 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
     if (m->num_splits > 1) m->states = (int64_t)m->total_slices * n;
     return true;
   }
-  auto tokens = [&](int32_t b) { return std::min<int64_t>(std::max<int64_t>(counts.of[b], 0), p.max_tokens); };
+  // (Clamped once and divided in 32 bits, and no second search where the first one's size fits: host time is what a plan costs, every call has one.  us, plan and
+  // order of the slices, in 64 bits, clamped each time, searched for up to three times -> so: 8 x 32 heads x 400..700, 8 tokens 1.19 -> 0.75; 30 x 8 x
+  // 100..500, 12 tokens 4.0 -> 3.1; 64 x 5 x 300..3000, 20 tokens 12 -> 9; 200 x 2 x 300..3000, 8 tokens 36 -> 25.)
+  uint32_t length[kMaxPlanBatch];
+  uint32_t longest_of_all = 1;
   int64_t sum = 0;
-  for (int32_t b = 0; b < d->batch; ++b) sum += tokens(b);
+  for (int32_t b = 0; b < d->batch; ++b) {
+    length[b] = (uint32_t)std::min<int64_t>(std::max<int64_t>(counts.of[b], 0), p.max_tokens);
+    longest_of_all = std::max(longest_of_all, length[b]);
+    sum += length[b];
+  }
+  auto cut_sequence = [&](int32_t b, int64_t t) { return length[b] <= (uint32_t)whole ? 1u : (length[b] + (uint32_t)t - 1) / (uint32_t)t; };
   // `cap` slices at most, and those of the sequences with several fit the slots
   auto fits = [&](int64_t t, int64_t cap, int64_t room_for) {
     int64_t total = 0, in_slots = 0;
     for (int32_t b = 0; b < d->batch; ++b) {
-      const int64_t s = cut(tokens(b), t);
-      if (s > (blocks > 1 ? kMatrixMaxFieldSlices : kMaxPlanSplits)) return false;
+      const uint32_t s = cut_sequence(b, t);
+      if (s > (uint32_t)(blocks > 1 ? kMatrixMaxFieldSlices : kMaxPlanSplits)) return false;
       total += s;
       if (s > 1) in_slots += s;
     }
@@ -512,38 +526,47 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
     if (room >= d->batch) {
       auto smallest = [&](int64_t cap, int64_t room_for) { return smallest_fit(std::max<int64_t>(kMinSlice, ceil_div(sum, cap)), cap, room_for); };
       const int64_t cap = std::min<int64_t>(room, kMaxPlanSlices), fewer = std::min(cap, kTurn / (d->heads * blocks));
-      // (chosen as with the largest workspace the call can use, so that what span_workspace_bytes asks for is enough for the same plan)
-      const int64_t all = most_states(d, p), T_cap = smallest(cap, all), T_fewer = fewer >= d->batch ? smallest(fewer, all) : T_cap;
       auto cost = [&](int64_t t) {
         SliceCost c{0, 0, sum, false};
         for (int32_t b = 0; b < d->batch; ++b) {
-          const int64_t s = cut(tokens(b), t);
+          const uint32_t s = cut_sequence(b, t);
           c.slices += s;
-          c.largest = std::max(c.largest, ceil_div(tokens(b), s));
+          c.largest = std::max<int64_t>(c.largest, (length[b] + s - 1) / s);
           c.cuts = c.cuts || s > 1;
         }
         return c;
       };
-      const bool fewer_pay = !two_per_cu && T_fewer > T_cap && one_per_cu_pays(d, d->heads * blocks, cost(T_fewer), cost(T_cap));
-      T = smallest(fewer_pay ? fewer : cap, states);
+      // (chosen as with the largest workspace the call can use, so that what span_workspace_bytes asks for is enough for the same plan)
+      const int64_t all = most_states(d, p), per_slice = d->heads * blocks;
+      int64_t chosen = cap, T_chosen = 0;  // slices at most, and the size that `all` states allow (0: not looked for)
+      if (!two_per_cu && fewer >= d->batch && fewer < cap && one_per_cu_may_pay(per_slice, fewer, longest_of_all, sum)) {
+        const int64_t T_cap = smallest(cap, all), T_fewer = smallest(fewer, all);
+        T_chosen = T_cap;
+        if (T_fewer > T_cap && one_per_cu_pays(d, per_slice, cost(T_fewer), cost(T_cap))) {
+          chosen = fewer;
+          T_chosen = T_fewer;
+        }
+      }
+      // (the smallest that fits more states is the smallest here too if it fits)
+      T = T_chosen > 0 && (states >= all || fits(T_chosen, chosen, states)) ? T_chosen : smallest(chosen, states);
     }
     // as in plan_exact: slices well above the average and large in themselves run in several rounds of smaller ones
     int64_t total = 0, largest = 1;
     for (int32_t b = 0; b < d->batch; ++b) {
-      const int64_t s = cut(tokens(b), T);
+      const uint32_t s = cut_sequence(b, T);
       total += s;
-      largest = std::max(largest, ceil_div(tokens(b), s));
+      largest = std::max<int64_t>(largest, (length[b] + s - 1) / s);
     }
     if (largest > kLargeSlice && 2 * largest * total > 3 * sum) T = smallest_fit(kLargeSlice, kMaxPlanSlices, states);
   }
   int64_t total = 0, longest = 1, most_s = 1, least_s = kMaxPlanSplits + 1;
   for (int32_t b = 0; b < d->batch; ++b) {
-    const int64_t s = cut(tokens(b), T);
+    const int64_t s = cut_sequence(b, T);
     total += s;
     if (s > 1) m->states += s * n;
     most_s = std::max(most_s, s);
     least_s = std::min(least_s, s);
-    longest = std::max(longest, ceil_div(tokens(b), s));
+    longest = std::max<int64_t>(longest, (length[b] + (uint32_t)s - 1) / (uint32_t)s);
   }
   m->num_splits = (int32_t)most_s;
   m->slice_tokens = (int32_t)longest;
@@ -558,7 +581,7 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
   if (most_s == 1 && (blocks > 1 || turn_entries(d->heads) < 2) && d->batch > row && d->batch <= kMaxPlanSlices && pairs * blocks > at_once &&
       longest * 100 * d->batch > 115 * sum) {
     uint64_t by_length[kMaxPlanSlices];  // positions << 16 | sequence
-    for (int32_t b = 0; b < d->batch; ++b) by_length[b] = (uint64_t)tokens(b) << 16 | (uint64_t)b;
+    for (int32_t b = 0; b < d->batch; ++b) by_length[b] = (uint64_t)length[b] << 16 | (uint64_t)b;
     std::sort(by_length, by_length + d->batch, [](uint64_t x, uint64_t y) { return x > y; });
     for (int32_t r = row; r < d->batch; r += 2 * row) std::reverse(by_length + r, by_length + std::min(r + row, d->batch));
     m->table = true;
@@ -568,7 +591,7 @@ bool plan_matrix(const span_attn_desc_t* d, const TokenCounts& counts, const Par
     int32_t y = 0;
     for (int pass = 0; pass < 2; ++pass) {
       for (int32_t b = 0; b < d->batch; ++b) {
-        const int64_t s = cut(tokens(b), T);
+        const int64_t s = cut_sequence(b, T);
         if ((s > 1) != (pass == 0)) continue;
         for (int64_t i = 0; i < s; ++i) table[y++] = pack_slice((uint32_t)b, (uint32_t)i, (uint32_t)s);
       }
