@@ -32,3 +32,28 @@ def test_lengths_around_the_lines(dtype, D, q_len, lengths, plan, gpu_device):
         got = span.span_decode_attn_multi(q, K, V, *lists, dev(pos), np.float32(cfg.scale), **kw)
     ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos, np.float32(cfg.scale), dtype=dtype)
     assert float(np.abs(got.cpu().numpy().astype(np.float64) - ref).max()) <= TOL
+
+
+@pytest.mark.parametrize("dtype,D,q_len,batch,positions,slices", [
+    ("f16", 128, 1, 8, 768, 1), ("f16", 128, 1, 8, 769, 2), ("bf16", 64, 1, 8, 384, 1), ("bf16", 64, 1, 8, 385, 2), ("f32", 64, 1, 11, 700, 1),  # level batches
+    ("f16", 128, 16, 8, 512, 1), ("f16", 128, 16, 8, 513, 2), ("f32", 64, 4, 8, 300, 1), ("f16", 128, 4, 3, 512, 3), ("f16", 128, 4, 7, 512, 1),  # a few tokens: one workgroup per CU
+])
+def test_batches_of_one_workgroup_per_cu(dtype, D, q_len, batch, positions, slices, gpu_device):
+    """32 heads, the rules' lines: lengths a little unequal, as far as a level batch may be, and cut as the rules say."""
+    cfg = DecodeConfig(142, "per-cu", batch, 32, D, 800, 800, dtype, TOL)
+    ctx = np.full(cfg.batch, cfg.max_len, np.int32)
+    lengths = [positions - 3 * (b % 3) for b in range(batch)]
+    sp = SpanBatch.from_lists([[(1, n // 4), (n // 4 + 20, n + 21)] for n in lengths], ctx)
+    _, K, V = draw_qkv(cfg, ctx, device=gpu_device)
+    q = draw_queries(cfg, q_len, device=gpu_device)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(gpu_device)  # noqa: E731
+    lists, pos = [dev(a) for a in (sp.offsets, sp.starts, sp.ends)], (ctx - q_len).astype(np.int32)
+    kw = dict(max_tokens=positions, tokens_per_seq=sp.tokens_per_seq())
+    if q_len == 1:
+        call = span.prepare_span_decode_attn(q[:, 0].contiguous(), K, V, *lists, None, np.float32(cfg.scale), **kw)
+    else:
+        call = span.prepare_span_decode_attn_multi(q, K, V, *lists, dev(pos), np.float32(cfg.scale), **kw)
+    assert span.span_launch_query(call.desc)["max_splits"] == slices
+    ref = oracle.span_attn_multi(to_host_raw(q), to_host_raw(K), to_host_raw(V), sp.offsets, sp.starts, sp.ends, pos, np.float32(cfg.scale), dtype=dtype)
+    got = call().cpu().numpy().astype(np.float64).reshape(ref.shape)
+    assert float(np.abs(got - ref).max()) <= TOL
