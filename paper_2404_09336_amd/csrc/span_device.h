@@ -388,12 +388,12 @@ __device__ __forceinline__ u32x4 load_row_piece(__amdgpu_buffer_rsrc_t slab, uin
 // Arrival tickets of a (batch, head) pair's slices.
 __device__ __forceinline__ int32_t* ticket_counter(const LaunchArgs& a, size_t bh) { return a.counters + bh * (size_t)a.counter_stride; }
 
-// Device-coherent store / load of one float that another workgroup reads / wrote in the same kernel.
+// Device-coherent store of one float that another workgroup reads in the same kernel / load of two that another one wrote.
 __device__ __forceinline__ void publish(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float observe(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ f32x2 observe2(const float* p) {
+  return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
 // The product x, rounded: the compiler must not contract it into the subtraction of the reference that follows.  There the
@@ -425,7 +425,7 @@ __device__ __forceinline__ Swapped swap_lanes(float low, float high) {
   return Swapped{__builtin_bit_cast(float, a), __builtin_bit_cast(float, b)};
 }
 
-// Maximum over the lanes lir, lir + kLanes, lir + 2 kLanes .. of the wave (kLanes = 8, 16 or 32); every lane gets it.
+// Maximum / sum over the lanes lir, lir + kLanes, lir + 2 kLanes .. of the wave (maximum: kLanes = 8, 16 or 32; sum: 16); every lane gets it.
 template <int kLanes>
 __device__ __forceinline__ float across_groups_max(float x) {
   if (kLanes <= 8) x = fmaxf(x, dpp_f<0x128>(x));  // row_ror:8
@@ -436,6 +436,15 @@ __device__ __forceinline__ float across_groups_max(float x) {
   const Swapped s = swap_lanes<32>(x, x);
   return fmaxf(s.first, s.second);
 }
+template <int kLanes>
+__device__ __forceinline__ float across_groups_sum(float x) {
+  static_assert(kLanes == 16, "what the matrix kernel adds up");
+  const Swapped s = swap_lanes<16>(x, x);
+  const float y = s.first + s.second;
+  const Swapped t = swap_lanes<32>(y, y);
+  return t.first + t.second;
+}
+
 // The states of a wave's row groups become one.  Lane lir + kLanes i comes with group i's state of columns kPer lir .. + kPer - 1, relative to its
 // own m; afterwards m and l are the wave's in every lane, and acc[0 .. kOwn - 1] the wave's sums of the lane's own columns, own_column() on.
 // The lanes share the columns' sums out as they are added: half as many with every exchange.
@@ -554,6 +563,9 @@ __device__ __forceinline__ int interval_length(const LaunchArgs& a, int i) { ret
 // so: 15 x 32 heads x ~170, 56 tokens 19.5 -> 18.7; 33 x 8 x 1849, 39 tokens 30.1 -> 29.3; 12 x 32 x ~450, 34 tokens 27.4 -> 26.7; 9 x 5 x ~150 fp32, 22
 // tokens 10.7 -> 10.4.  One-token calls gain nothing by it (their longer lists lose 1 %: the wave fetches twice).  Lists of a
 // mean beyond the window do without; they lose up to 1 % in the few-query kernel (8 x 12 x ~8900, 2200 intervals each, 19 tokens 87.9 -> 88.6).
+// The mean is the arrays' entries per sequence.  Arrays kept with room for more put the window beyond the lists of the later sequences, which are
+// then fetched after their range as without it: us, arrays filled, 3 times as long, 12 times (no window): 12 x 32 x ~450, 34 tokens 27.9, 28.1, 28.2; 9 x 5 x ~150 fp32, 22 tokens
+// 10.2, 10.6, 10.5; 16 x 16 x ~380 of 64, 9 tokens 7.78, 7.87, 7.88.
 constexpr int kNoWindow = 0x7fffffff - 64;  // first of a window that holds nothing
 struct ListWindow {
   int first;       // number of lane 0's interval (scalar)

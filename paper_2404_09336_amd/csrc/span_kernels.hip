@@ -521,10 +521,6 @@ decode_kernel(const Args a) {
   constexpr int kColThreads = D / 4, kGroups = kThreads / kColThreads;
   const int part = tid / kColThreads, col = 4 * (tid % kColThreads);
   const size_t slot0 = (size_t)y0 * H + h;  // slice s of this (b, h) is slot0 + s * H
-  typedef uint64_t u64;
-  auto observe2 = [](const float* p) {
-    return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const u64*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  };
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
     float mm = -INFINITY, ll = 0.f, oo[4] = {0.f, 0.f, 0.f, 0.f};

@@ -60,7 +60,7 @@ struct MatrixShape {
   // instruction.  us, two -> one: 512 workgroups, 16 x ~700 positions, bf16, 32 tokens 40.6 -> 39.0, appended 45.6 -> 44.1; in several rounds
   // 64 x 32 pairs x ~220, bf16, 24 tokens 91.9 -> 97.0, 64 x 32 x ~400 fp16, 20 tokens 113.5 -> 119.8.
   static constexpr bool kHasBoth = S == 2 && D == 128;
-  // Waves per SIMD.  64 tokens of 16-bit rows of 128 spill 30 (fp16) and 38 (bf16) registers, all of them in the pass for V rows that are
+  // Waves per SIMD.  64 tokens of 16-bit rows of 128 spill 31 (fp16) and 38 (bf16) registers, all of them in the pass for V rows that are
   // not finite (stream_checked).
   static constexpr int kWaves = kMatrixWorkgroupsPerCu(Elt::kBytes, D, G);
 };
@@ -74,28 +74,6 @@ struct MatrixShape {
 template <class Elt, int D>
 constexpr int weight_terms(bool two_tokens) {
   return std::is_same<Elt, F16>::value && D == 128 && !two_tokens ? 2 : 3;
-}
-
-__device__ __forceinline__ float exchange_max(float x) {  // maximum over the four lanes qi + 16 c
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const uint32_t a0 = a[0], a1 = a[1];
-  const float y = fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1));
-  const uint32_t w = __builtin_bit_cast(uint32_t, y);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  const uint32_t b0 = b[0], b1 = b[1];
-  return fmaxf(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
-}
-
-__device__ __forceinline__ float exchange_sum(float x) {  // sum over the four lanes qi + 16 c
-  const uint32_t u = __builtin_bit_cast(uint32_t, x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const uint32_t a0 = a[0], a1 = a[1];
-  const float y = __builtin_bit_cast(float, a0) + __builtin_bit_cast(float, a1);
-  const uint32_t w = __builtin_bit_cast(uint32_t, y);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  const uint32_t b0 = b[0], b1 = b[1];
-  return __builtin_bit_cast(float, b0) + __builtin_bit_cast(float, b1);
 }
 
 // The value is computed here and not later: the compiler would otherwise sink the additions below the next tile's loads,
@@ -462,7 +440,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
         for (int t = 0; t < 4; ++t) mx = fmaxf(mx, sc[g][s][t]);
       }
       if (__builtin_amdgcn_ballot_w64(mx > ref[g]) != 0) {  // (the maximum settles after the first tiles)
-        mx = exchange_max(mx);
+        mx = across_groups_max<16>(mx);
         const float ref_new = fmaxf(ref[g], mx);
         const float ref_safe = ref_new == -INFINITY ? 0.f : ref_new;
         const float alpha = __builtin_amdgcn_exp2f((ref[g] - ref_safe) * post);
@@ -657,8 +635,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
     if (__builtin_expect(w0 > 0, 0)) {
       // The lane's addresses are computed here and not ahead of the loop, where the compiler would move them: kept across the tiles they
       // cost registers that 32 tokens of 16-bit rows of 64 and of fp32 rows of 128 do not have (2 to 5 spilled, and with them the set-up
-      // of scratch memory for every wave; now none, in the plain grid of the former one, the thread's index, which is read after the
-      // loop).  us, with the spills -> without: 64 x 12 heads x 200..500 of 64, bf16, 32 tokens 22.1 -> 21.0, level ones of ~490, fp16 25.5 -> 23.6; 16 x 32 x
+      // of scratch memory for every wave; now none).  us, with the spills -> without: 64 x 12 heads x 200..500 of 64, bf16, 32 tokens 22.1 -> 21.0, level ones of ~490, fp16 25.5 -> 23.6; 16 x 32 x
       // 400..800, fp16, 20 tokens 20.6 -> 19.3; 8 x 32 x ~600 fp32 of 128, 24 tokens 44.2 -> 43.8.
       int ln = 16 * c4 + qi;
       asm volatile("" : "+v"(ln));
@@ -720,7 +697,7 @@ __attribute__((amdgpu_waves_per_eu(MatrixShape<Elt, D, G>::kWaves, MatrixShape<E
   const int qn = lane_here & 15, cn = lane_here >> 4;  // qi and c4
 #pragma unroll
   for (int g = 0; g < G; ++g) {  // the four lanes of a query hold the weights of disjoint rows
-    lsum[g] = exchange_sum(lsum[g]) * Elt::kWeightScale;
+    lsum[g] = across_groups_sum<16>(lsum[g]) * Elt::kWeightScale;
     if (cn == 0) s_ml[16 * g + qn][wave] = f32x2{ref[g], lsum[g]};
   }
   // Of 16 kAtOnce tokens a thread finishes `part`'s quads of columns of token `mine`: columns 4 (part + kPerToken i) .. + 3.
