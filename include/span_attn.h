@@ -129,7 +129,8 @@ typedef struct span_attn_desc {
  * pairwise-disjoint intervals.  On a list that would not validate the result is unspecified, yet
  * no row outside [0, max_len) of the sequence's own cache slab is read, and interval indices
  * outside [0, num_intervals) are never read.  A sequence with no attended position gets an
- * all-zero output row (never NaN).
+ * all-zero output row (never NaN).  An attended row whose score is NaN or +Inf makes its output row
+ * NaN, as the definition does, in every entry point and however the sequence is cut.
  */
 int span_decode_attn(const span_attn_desc_t* desc, const void* q, const void* k_cache, const void* v_cache,
                      const int32_t* span_offsets, const int32_t* span_starts, const int32_t* span_ends,
